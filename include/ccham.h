@@ -29,7 +29,9 @@
  * A pointer argument is a host pointer unless `flags & CCH_MEM_DEVICE`, in
  * which case it is a device pointer on the context's device. Device work is
  * ordered on the context's HIP stream; cch_sync() waits for it.
- * One context must not be used from two threads at once.
+ * One context must not be used from two threads at once. A context keeps the
+ * work space of its calls (at most 1/64 of the device's memory while idle;
+ * none under cch_plan_opts.max_device_bytes) until cch_destroy.
  */
 #ifndef CCHAM_H
 #define CCHAM_H
@@ -402,7 +404,7 @@ cch_status cch_target_hamiltonian(cch_ctx *ctx, int32_t sym_a, int32_t sym_b, do
  * context reads the lower triangle of H once per 16 vectors; a context
  * planned with CCH_PLAN_SPARSE_L2 reads its continuum panels and the CSR of
  * the L2 block. The sums run in a fixed order: equal inputs give equal bits.
- * Scratch (and, for host arrays, staging) is allocated per call.
+ * Scratch (and, for host arrays, staging) comes from the context's work space.
  * CCH_E_STATE before cch_build, CCH_E_INVALID_ARG for b < 0, a NULL array
  * with b > 0 or a leading dimension below D. Synchronous. */
 cch_status cch_apply(cch_ctx *ctx, const double *V, int64_t ldv, int32_t b, double *W, int64_t ldw,

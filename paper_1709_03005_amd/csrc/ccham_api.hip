@@ -225,6 +225,69 @@ struct LtPlan {
 
 }  // namespace
 
+// Work space of a context's calls (solver bases, mat-vec partials, staging of
+// host arrays), kept between calls: a hipFree waits for the whole device and
+// unmaps, and with several large contexts resident a product of 1 ms spent 11
+// ms on it (D = 24011; a solve at D = 8000 2.5 of its 14.5 ms). take() reuses
+// an idle block of at most twice the size, else allocates; give() keeps idle
+// blocks while they hold at most `keep` bytes in all and frees the largest
+// ones beyond that. The blocks belong to one context, whose calls run one at
+// a time and queue their kernels on one stream, so a reused block's earlier
+// work is ordered before its next.
+struct Scratch {
+    struct Block {
+        void *p;
+        size_t bytes;
+        bool used;
+    };
+    std::vector<Block> blocks;
+    size_t keep = 0;
+    void drop_idle(size_t most)
+    {
+        size_t idle = 0;
+        for (auto &b : blocks) idle += b.used ? 0 : b.bytes;
+        while (idle > most) {
+            size_t at = blocks.size();
+            for (size_t i = 0; i < blocks.size(); ++i)
+                if (!blocks[i].used && (at == blocks.size() || blocks[i].bytes > blocks[at].bytes)) at = i;
+            idle -= blocks[at].bytes;
+            (void)hipFree(blocks[at].p);
+            blocks.erase(blocks.begin() + (std::ptrdiff_t)at);
+        }
+    }
+    hipError_t take(void **p, size_t bytes)
+    {
+        bytes = (std::max<size_t>(bytes, 1) + 255) / 256 * 256;
+        Block *best = nullptr;
+        for (auto &b : blocks)
+            if (!b.used && b.bytes >= bytes && b.bytes / 2 <= bytes && (!best || b.bytes < best->bytes)) best = &b;
+        if (best) {
+            best->used = true;
+            *p = best->p;
+            return hipSuccess;
+        }
+        blocks.reserve(blocks.size() + 1);
+        void *q = nullptr;
+        hipError_t e = hipMalloc(&q, bytes);
+        if (e != hipSuccess) {   // the idle blocks may hold what is missing
+            drop_idle(0);
+            (void)hipGetLastError();
+            e = hipMalloc(&q, bytes);
+        }
+        if (e != hipSuccess) return e;
+        blocks.push_back({q, bytes, true});
+        *p = q;
+        return hipSuccess;
+    }
+    void give(void *p)
+    {
+        if (!p) return;
+        for (auto &b : blocks)
+            if (b.p == p) b.used = false;
+        drop_idle(keep);
+    }
+};
+
 constexpr int CCH_NAUX = 6;   // auxiliary streams of a build: 4 for the symmetry pairs, class 4, L2 block
 constexpr int CCH_NPAIRS_ST = 4;
 
@@ -234,6 +297,8 @@ struct cch_ctx {
     std::string err;
     std::vector<void *> allocs;
     int64_t bytes = 0;
+    Scratch scratch;            // work space of the calls
+    void *pinned = nullptr;     // the solver's pinned host block
     // orbitals
     bool have_orb = false;
     int n_o = 0, n_irrep = 1, total_irrep = 0, n_cont = 0, n_orb = 0, W = 0;
@@ -420,6 +485,11 @@ cch_status cch_create(cch_ctx **out, int32_t device, void *hip_stream)
                  hipEventCreateWithFlags(&c->join_ev[i], hipEventDisableTiming) == hipSuccess;
     for (int i = 0; i < 2 && aux_ok; ++i)
         aux_ok = hipEventCreate(&c->c4_ev[i]) == hipSuccess && hipEventCreate(&c->l2_ev[i]) == hipSuccess;
+    {
+        // idle work space kept by one context: 1/64 of the device (4.5 GB of 288)
+        size_t free_b = 0, total_b = 0;
+        if (hipMemGetInfo(&free_b, &total_b) == hipSuccess) c->scratch.keep = total_b / 64;
+    }
     c->have_aux = aux_ok;   // without them every phase runs on the context stream
     c->opts.precision = CCH_PREC_FP64;
     *out = c;
@@ -432,6 +502,8 @@ cch_status cch_destroy(cch_ctx *c)
     (void)hipSetDevice(c->device);
     (void)hipStreamSynchronize(c->stream);
     for (void *p : c->allocs) (void)hipFree(p);
+    for (auto &b : c->scratch.blocks) (void)hipFree(b.p);
+    if (c->pinned) (void)hipHostFree(c->pinned);
     if (!c->csr.planned) {
         (void)hipFree(c->csr.off);
         (void)hipFree(c->csr.col);
@@ -872,6 +944,10 @@ cch_status cch_plan(cch_ctx *c, const cch_plan_opts *opts)
         if (opts->max_device_bytes < 0) return fail(c, CCH_E_INVALID_ARG, "negative memory budget");
         if (opts->flags & ~CCH_PLAN_SPARSE_L2) return fail(c, CCH_E_INVALID_ARG, "unknown plan flags %d", opts->flags);
         c->opts = *opts;
+        if (opts->max_device_bytes > 0) {   // a caller who budgets memory gets it back after each call
+            c->scratch.keep = 0;
+            c->scratch.drop_idle(0);
+        }
     }
     HIPCK(c, hipSetDevice(c->device));
     // rows
@@ -1600,9 +1676,9 @@ cch_status cch_apply(cch_ctx *c, const double *V, int64_t ldv, int32_t b, double
     const int64_t lv = dev ? ldv : D, lw = dev ? ldw : D;
     const int64_t nscr = c->sparse ? l2csr_scratch((int)D, (int)c->Dc) : matvec_scratch_doubles((int)D);
     double *dV = dev ? const_cast<double *>(V) : nullptr, *dW = dev ? W : nullptr, *Wp = nullptr;
-    hipError_t e = hipMalloc((void **)&Wp, 8 * (size_t)std::max<int64_t>(nscr, 1));
-    if (e == hipSuccess && !dev) e = hipMalloc((void **)&dV, 8 * (size_t)(D * b));
-    if (e == hipSuccess && !dev) e = hipMalloc((void **)&dW, 8 * (size_t)(D * b));
+    hipError_t e = c->scratch.take((void **)&Wp, 8 * (size_t)std::max<int64_t>(nscr, 1));
+    if (e == hipSuccess && !dev) e = c->scratch.take((void **)&dV, 8 * (size_t)(D * b));
+    if (e == hipSuccess && !dev) e = c->scratch.take((void **)&dW, 8 * (size_t)(D * b));
     if (e == hipSuccess && !dev)
         e = hipMemcpy2DAsync(dV, 8 * D, V, 8 * ldv, 8 * D, b, hipMemcpyHostToDevice, c->stream);
     if (e == hipSuccess)
@@ -1612,10 +1688,10 @@ cch_status cch_apply(cch_ctx *c, const double *V, int64_t ldv, int32_t b, double
     if (e == hipSuccess && !dev)
         e = hipMemcpy2DAsync(W, 8 * ldw, dW, 8 * D, 8 * D, b, hipMemcpyDeviceToHost, c->stream);
     if (e == hipSuccess) e = hipStreamSynchronize(c->stream);
-    (void)hipFree(Wp);
+    c->scratch.give(Wp);
     if (!dev) {
-        (void)hipFree(dV);
-        (void)hipFree(dW);
+        c->scratch.give(dV);
+        c->scratch.give(dW);
     }
     if (e != hipSuccess) return fail(c, CCH_E_HIP, "cch_apply: %s", hipGetErrorString(e));
     return CCH_OK;
@@ -1770,11 +1846,11 @@ cch_status cch_subspace_eig(cch_ctx *c, const double *G, int32_t ldg, int32_t m,
     int32_t *dF = nullptr;
     auto cleanup = [&]() {
         if (!dev) {
-            (void)hipFree(dG);
-            (void)hipFree(dT);
-            (void)hipFree(dY);
+            c->scratch.give(dG);
+            c->scratch.give(dT);
+            c->scratch.give(dY);
         }
-        (void)hipFree(dF);
+        c->scratch.give(dF);
     };
 #define ECK(x)                                                                                  \
     do {                                                                                        \
@@ -1789,12 +1865,12 @@ cch_status cch_subspace_eig(cch_ctx *c, const double *G, int32_t ldg, int32_t m,
         dT = theta;
         dY = Y;
     } else {
-        ECK(hipMalloc((void **)&dG, 8 * (size_t)m * ldg));
-        ECK(hipMalloc((void **)&dT, 8 * (size_t)m));
-        ECK(hipMalloc((void **)&dY, 8 * (size_t)m * ldy));
+        ECK(c->scratch.take((void **)&dG, 8 * (size_t)m * ldg));
+        ECK(c->scratch.take((void **)&dT, 8 * (size_t)m));
+        ECK(c->scratch.take((void **)&dY, 8 * (size_t)m * ldy));
         ECK(hipMemcpyAsync(dG, G, 8 * (size_t)m * ldg, hipMemcpyHostToDevice, st));
     }
-    ECK(hipMalloc((void **)&dF, 4));
+    ECK(c->scratch.take((void **)&dF, 4));
     ECK(hipMemsetAsync(dF, 0, 4, st));
     if (method == CCH_EIG_JACOBI) ECK(launch_jacobi_eig(dG, ldg, m, dT, dY, ldy, st));
     else ECK(launch_rr_eig(dG, ldg, m, dT, dY, ldy, dF, st));
@@ -1831,9 +1907,9 @@ cch_status cch_eig_all(cch_ctx *c, const double *A, int64_t lda, int32_t n, doub
     const int64_t ld = ((int64_t)n + 31) / 32 * 32;
     const int NB = 128;   // reflectors per block of the back-transformation (at most 128: launch_larft)
     std::vector<void *> tmp;
-    auto cleanup = [&]() { for (void *p : tmp) (void)hipFree(p); };
+    auto cleanup = [&]() { for (void *p : tmp) c->scratch.give(p); };
     auto al = [&](void **p, size_t bytes) -> bool {
-        if (hipMalloc(p, bytes ? bytes : 8) != hipSuccess) return false;
+        if (c->scratch.take(p, bytes ? bytes : 8) != hipSuccess) return false;
         tmp.push_back(*p);
         return true;
     };
@@ -2836,14 +2912,9 @@ cch_status cch_davidson(cch_ctx *c, const cch_dav_opts *o, double *evals, double
     const int64_t ldv = ((int64_t)D + 31) / 32 * 32;
     const int BMAX = 32;                       // block columns (<= 2k <= 32)
     std::vector<void *> tmp;
-    void *tmp_host = nullptr;
-    auto cleanup = [&]() {
-        for (void *p : tmp) (void)hipFree(p);
-        if (tmp_host) (void)hipHostFree(tmp_host);
-        tmp_host = nullptr;
-    };
+    auto cleanup = [&]() { for (void *p : tmp) c->scratch.give(p); };
     auto A = [&](void **p, size_t bytes) -> bool {
-        if (hipMalloc(p, bytes ? bytes : 8) != hipSuccess) return false;
+        if (c->scratch.take(p, bytes ? bytes : 8) != hipSuccess) return false;
         tmp.push_back(*p);
         return true;
     };
@@ -2920,13 +2991,13 @@ cch_status cch_davidson(cch_ctx *c, const cch_dav_opts *o, double *evals, double
         // the projected block it gives
         double y[16 * 96], th[96], q[96 * 32], gx[16 * 16];
     };
-    HostIO *hio = nullptr;
     int32_t seqno = 0;
-    if (hipHostMalloc((void **)&hio, sizeof(HostIO), hipHostMallocCoherent) != hipSuccess) {
+    if (!c->pinned && hipHostMalloc(&c->pinned, sizeof(HostIO), hipHostMallocCoherent) != hipSuccess) {
+        c->pinned = nullptr;
         cleanup();
         return fail(c, CCH_E_OOM, "pinned host buffer");
     }
-    tmp_host = hio;
+    HostIO *hio = (HostIO *)c->pinned;
     __atomic_store_n(&hio->seq, 0, __ATOMIC_RELEASE);   // before any posted number
     double *hres = hio->res;
     DavSel sel{};
