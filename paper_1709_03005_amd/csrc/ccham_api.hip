@@ -32,12 +32,15 @@ hipError_t launch_bucket(PairList pl, int64_t n, const int32_t *pqidx, int n_o, 
                          int64_t *tmp, int64_t *d0, hipStream_t st);
 hipError_t launch_gamma(int W, PairList pl, const int64_t *start, const int64_t *count,
                         const int64_t *sorted, const int64_t *d0, int M0, const int32_t *slotP,
-                        const int32_t *slotQ, int n_slot, const uint64_t *da, const int8_t *spa, const int8_t *spb,
-                        const double *ca, int Sa, const double *cb, int Sb, int nrows, const int32_t *rn,
-                        const int32_t *rn2, double *At, hipStream_t st);
-hipError_t launch_relayout(const double *ttcc, const double *tctc, int n_o, int n_cont,
-                           const int32_t *slotP, const int32_t *slotQ, int n_slot, int ja0, int nca,
-                           int jb0, int ncb, double *B, hipStream_t st, const PackedCC *pk);
+                        const int32_t *slotQ, const GammaList &gl, const uint64_t *da, const int8_t *spa,
+                        const int8_t *spb, const double *ca, int Sa, const double *cb, int Sb, int nrows,
+                        const int32_t *rn, const int32_t *rn2, double *At, hipStream_t st);
+hipError_t launch_relayout(const double *ttcc, const double *tctc, int n_o, int n_cont, const int32_t *slotPJ,
+                           const int32_t *slotQJ, int nJ, const int32_t *slotPK, const int32_t *slotQK, int nK,
+                           int ja0, int nca, int jb0, int ncb, double *B, hipStream_t st, const PackedCC *pk);
+hipError_t launch_relayout_sq(const double *ttcc, const double *tctc, int n_o, int n_cont, const int32_t *fP,
+                              const int32_t *fQ, int nF, int n_off, int ja0, int nc, int j0, int j1, double *B,
+                              hipStream_t st, const PackedCC *pk);
 struct ExpandEpi {
     double *H;
     int64_t ld;
@@ -49,8 +52,15 @@ struct ExpandEpi {
     const double *h;
     int n_o, n_orb;
 };
-hipError_t launch_expand_f64(const double *At, const double *B, int nrows, int N, int K, const ExpandEpi &ep,
-                             hipStream_t st);
+struct ExpandOp {
+    const double *At, *B;
+    int nrows, KS, KA;
+    int sq, j0, j1;
+    int N;
+    ExpandEpi ep;
+};
+hipError_t launch_expand_f64(const ExpandOp &op, hipStream_t st);
+int expand_cols(const ExpandOp &op);
 hipError_t launch_to_f32(const double *x, float *y, int64_t n, hipStream_t st);
 hipError_t launch_expand_f32(const float *At, const float *B, int nrows, int N, int K, const ExpandEpi &ep,
                              hipStream_t st);
@@ -71,18 +81,14 @@ hipError_t launch_l2_block(int W, const L2Args &a, hipStream_t st);
 hipError_t launch_l2csf_gather(const double *Hd, int64_t ldd, int Dc, int ncsf, const int32_t *start,
                                const int32_t *det, const double *coef, double *H, int64_t ld, hipStream_t st);
 struct GemmTask {
-    const double *At;
-    const double *B;
-    int nrows, N, K;
+    ExpandOp op;
     int tiles_m, tiles_n;
     int64_t first;
-    ExpandEpi ep;
 };
 struct L2Task {
     L2Args a;
     int64_t first;
 };
-int expand_tiles(int nrows, int N, int bm);
 int64_t l2_tiles(int n_l2);
 hipError_t launch_expand_f64_batched(const GemmTask *tasks, int ntask, int64_t total, int bm, int grid,
                                      hipStream_t st);
@@ -205,6 +211,12 @@ struct PairPlan {
     DevPairs pr;
     int n_slot = 0, nrows = 0;
     int32_t *d_slotP = nullptr, *d_slotQ = nullptr, *d_pqidx = nullptr, *d_rn = nullptr, *d_rn2 = nullptr;
+    // FP64 expansion, each distinct integral once: nF pairs P >= Q of slots
+    // (n_off with P > Q first), as slot indices and as orbitals; rect pairs also
+    // list the exchange rows P Q, Q P alternating
+    GammaMode form = GAM_PLAIN;
+    int nF = 0, n_off = 0;
+    int32_t *d_k1 = nullptr, *d_k2 = nullptr, *d_fP = nullptr, *d_fQ = nullptr, *d_xP = nullptr, *d_xQ = nullptr;
     double *d_hv = nullptr, *d_Y = nullptr, *d_Yo = nullptr, *d_HT = nullptr, *d_O = nullptr, *d_At = nullptr;
     int32_t *d_key = nullptr;
     int64_t *d_count = nullptr, *d_start = nullptr, *d_cursor = nullptr, *d_sorted = nullptr, *d_tmp = nullptr,
@@ -217,6 +229,17 @@ struct PairPlan {
     __bf16 *d_SA = nullptr, *d_SB = nullptr;
     int ldk = 0;
 };
+
+// rows (k) and columns of a pair's integral layout
+int64_t b_rows(const PairPlan &p)
+{
+    if (p.form == GAM_SQUARE) return 2 * (int64_t)p.nF + p.n_off;
+    return p.form == GAM_RECT ? 3 * (int64_t)p.n_off : 2 * (int64_t)p.n_slot;
+}
+int64_t b_cols(const PairPlan &p, const SymInfo &sa, const SymInfo &sb)
+{
+    return p.form == GAM_SQUARE ? (int64_t)sa.nc * (sa.nc + 1) / 2 : (int64_t)sa.nc * sb.nc;
+}
 
 struct LtPlan {
     int sym = 0;
@@ -1006,6 +1029,35 @@ cch_status cch_plan(cch_ctx *c, const cch_plan_opts *opts)
                     rn2.push_back(n2);
                 }
             p.nrows = (int)rn.size();
+            if (c->opts.precision == CCH_PREC_FP64) {
+                p.form = sa.ja0 == sb.ja0 && sa.nc == sb.nc ? GAM_SQUARE : GAM_RECT;
+                std::vector<int32_t> k1, k2, fP, fQ, xP, xQ;
+                for (int diag = 0; diag < 2; ++diag)   // the pairs P = Q last
+                    for (int k = 0; k < p.n_slot; ++k) {
+                        if (sP[k] < sQ[k] || (sP[k] == sQ[k]) != (diag == 1)) continue;
+                        k1.push_back(k);
+                        k2.push_back(diag ? -1 : pq[(size_t)sQ[k] * c->n_o + sP[k]]);
+                        fP.push_back(sP[k]);
+                        fQ.push_back(sQ[k]);
+                        p.n_off += diag ? 0 : 1;
+                        if (!diag) {
+                            xP.insert(xP.end(), {sP[k], sQ[k]});
+                            xQ.insert(xQ.end(), {sQ[k], sP[k]});
+                        }
+                    }
+                p.nF = (int)k1.size();
+                // two symmetries of one irrep share their continuum range and have
+                // slots P = Q; a rect pair (different irreps) has none
+                if (p.form == GAM_RECT && p.nF != p.n_off) return fail(c, CCH_E_STATE, "symmetry pair (%d, %d)", a, b);
+                TRY(upload(c, &p.d_k1, k1));
+                TRY(upload(c, &p.d_k2, k2));
+                TRY(upload(c, &p.d_fP, fP));
+                TRY(upload(c, &p.d_fQ, fQ));
+                if (p.form == GAM_RECT) {
+                    TRY(upload(c, &p.d_xP, xP));
+                    TRY(upload(c, &p.d_xQ, xQ));
+                }
+            }
             TRY(upload(c, &p.d_slotP, sP));
             TRY(upload(c, &p.d_slotQ, sQ));
             TRY(upload(c, &p.d_pqidx, pq));
@@ -1016,7 +1068,7 @@ cch_status cch_plan(cch_ctx *c, const cch_plan_opts *opts)
             TRY(dalloc(c, &p.d_Yo, (size_t)sa.M * sb.S));
             TRY(dalloc(c, &p.d_HT, p.nrows));
             TRY(dalloc(c, &p.d_O, p.nrows));
-            TRY(dalloc(c, &p.d_At, (size_t)2 * p.n_slot * p.nrows));
+            TRY(dalloc(c, &p.d_At, (size_t)b_rows(p) * p.nrows));
             TRY(dalloc(c, &p.d_key, p.pr.n));
             TRY(dalloc(c, &p.d_count, p.n_slot + 1));
             TRY(dalloc(c, &p.d_start, p.n_slot + 1));
@@ -1029,7 +1081,7 @@ cch_status cch_plan(cch_ctx *c, const cch_plan_opts *opts)
             // operands are derived from a full copy
             if (c->opts.precision != CCH_PREC_FP64) TRY(dalloc(c, &p.d_B, (size_t)2 * p.n_slot * sa.nc * sb.nc));
             p.jj_chunk = sa.nc;
-            maxB += (int64_t)2 * p.n_slot * sa.nc * sb.nc;
+            maxB += b_rows(p) * b_cols(p, sa, sb);
             {
                 const size_t K = (size_t)2 * p.n_slot, N = (size_t)sa.nc * sb.nc;
                 if (c->opts.precision == CCH_PREC_FP32) {
@@ -1095,7 +1147,7 @@ cch_status cch_plan(cch_ctx *c, const cch_plan_opts *opts)
         const int64_t budget = c->opts.max_device_bytes;
         if (budget == 0 || c->bytes + 8 * maxB <= budget) {
             for (auto &p : c->pp)   // one pass: every pair keeps its integral rows
-                TRY(dalloc(c, &p.d_B, (size_t)2 * p.n_slot * c->syms[p.a].nc * c->syms[p.b].nc));
+                TRY(dalloc(c, &p.d_B, (size_t)(b_rows(p) * b_cols(p, c->syms[p.a], c->syms[p.b]))));
         } else {
             // the budget left after everything else holds one shared buffer; each pair
             // relays and multiplies as many continuum rows j per pass as fit
@@ -1104,7 +1156,7 @@ cch_status cch_plan(cch_ctx *c, const cch_plan_opts *opts)
             c->expansion_passes = 1;
             for (auto &p : c->pp) {
                 const SymInfo &sa = c->syms[p.a], &sb = c->syms[p.b];
-                const int64_t row = (int64_t)2 * p.n_slot * sb.nc;   // one j of B
+                const int64_t row = b_rows(p) * sb.nc;   // one j of B, at most
                 if (row == 0 || sa.nc == 0) continue;
                 const int64_t fit = std::min<int64_t>(sa.nc, left / row);
                 if (fit < 1)
@@ -1165,6 +1217,24 @@ static ExpandEpi expand_epi(cch_ctx *c, const PairPlan &p)
                      p.d_O, c->d_h, c->n_o, c->n_orb};
 }
 
+// the FP64 product of a pair for the continuum rows j0..j1-1 of its first
+// symmetry (all of them, or one pass of them)
+static ExpandOp expand_op(cch_ctx *c, const PairPlan &p, int j0, int j1)
+{
+    const SymInfo &sb = c->syms[p.b];
+    ExpandOp op{p.d_At, p.d_B, p.nrows, (int)b_rows(p), 0, p.form == GAM_SQUARE, j0, j1, (j1 - j0) * sb.nc,
+                expand_epi(c, p)};
+    if (op.sq) {
+        op.KS = 2 * p.nF;
+        op.KA = p.n_off;
+        op.N = (int)((int64_t)j1 * (j1 + 1) / 2 - (int64_t)j0 * (j0 + 1) / 2);
+    } else {
+        op.ep.row0a += j0;
+        op.ep.ja0 += j0;
+    }
+    return op;
+}
+
 // Independent launches of one phase spread round-robin over the auxiliary
 // streams: begin() makes them wait for what the stream has queued, end() makes
 // the stream wait for all of them. Off (batch capture, no streams): all on st.
@@ -1208,6 +1278,19 @@ static PackedCC packed_cc(const cch_ctx *c, const PairPlan &p, int j0)
     return pk;
 }
 
+// the integral rows of a pair's FP64 product for the continuum rows j0..j1-1
+static hipError_t relayout_f64(cch_ctx *c, const PairPlan &p, int j0, int j1, hipStream_t st)
+{
+    const SymInfo &sa = c->syms[p.a], &sb = c->syms[p.b];
+    const bool sq = p.form == GAM_SQUARE;
+    const PackedCC pk = packed_cc(c, p, sq ? 0 : j0);
+    if (sq)
+        return launch_relayout_sq(c->d_ttcc, c->d_tctc, c->n_o, c->n_cont, p.d_fP, p.d_fQ, p.nF, p.n_off, sa.ja0,
+                                  sa.nc, j0, j1, p.d_B, st, c->packed ? &pk : nullptr);
+    return launch_relayout(c->d_ttcc, c->d_tctc, c->n_o, c->n_cont, p.d_fP, p.d_fQ, p.nF, p.d_xP, p.d_xQ, 2 * p.n_off,
+                           sa.ja0 + j0, j1 - j0, sb.ja0, sb.nc, p.d_B, st, c->packed ? &pk : nullptr);
+}
+
 // phases 0-2: scans, target elements and densities, relayout; every symmetry
 // pair (and L2-target group) writes only its own buffers, so with `fan` they
 // run on the auxiliary streams side by side
@@ -1245,8 +1328,9 @@ static cch_status enqueue_pre(cch_ctx *c, hipStream_t st, bool ev, bool fan, boo
         HIPCK(c, launch_bucket(p.pr.pl, p.pr.n, p.d_pqidx, c->n_o, p.n_slot, sa.M, p.d_key, p.d_count, p.d_start,
                                p.d_cursor, p.d_sorted, p.d_tmp, p.d_d0, s));
         const int M0 = (sa.irrep == sb.irrep) ? sa.M : 0;
+        const GammaList gl{p.form, p.form == GAM_PLAIN ? p.n_slot : p.nF, p.d_k1, p.d_k2};
         HIPCK(c, launch_gamma(c->W, p.pr.pl, p.d_start, p.d_count, p.d_sorted, p.d_d0, M0, p.d_slotP, p.d_slotQ,
-                              p.n_slot, sa.d_dets, sa.d_cspin, sb.d_cspin, sa.d_ci, sa.S, sb.d_ci, sb.S, p.nrows,
+                              gl, sa.d_dets, sa.d_cspin, sb.d_cspin, sa.d_ci, sa.S, sb.d_ci, sb.S, p.nrows,
                               p.d_rn, p.d_rn2, p.d_At, s));
     }
     HIPCK(c, f.end());
@@ -1258,9 +1342,14 @@ static cch_status enqueue_pre(cch_ctx *c, hipStream_t st, bool ev, bool fan, boo
         if (sa.nc == 0 || sb.nc == 0) continue;
         if (c->b_shared) continue;   // one shared buffer: rows are laid out pass by pass in phase 3
         const hipStream_t s = f(w++);
+        if (p.form != GAM_PLAIN) {
+            HIPCK(c, relayout_f64(c, p, 0, sa.nc, s));
+            continue;
+        }
         const PackedCC pk = packed_cc(c, p, 0);
-        HIPCK(c, launch_relayout(c->d_ttcc, c->d_tctc, c->n_o, c->n_cont, p.d_slotP, p.d_slotQ, p.n_slot, sa.ja0,
-                                 sa.nc, sb.ja0, sb.nc, p.d_B, s, c->packed ? &pk : nullptr));
+        HIPCK(c, launch_relayout(c->d_ttcc, c->d_tctc, c->n_o, c->n_cont, p.d_slotP, p.d_slotQ, p.n_slot, p.d_slotP,
+                                 p.d_slotQ, p.n_slot, sa.ja0, sa.nc, sb.ja0, sb.nc, p.d_B, s,
+                                 c->packed ? &pk : nullptr));
         const int K = 2 * p.n_slot, N = sa.nc * sb.nc;
         if (c->opts.precision == CCH_PREC_FP32) {
             HIPCK(c, launch_to_f32(p.d_At, p.d_At32, (int64_t)K * p.nrows, s));
@@ -1295,19 +1384,14 @@ static cch_status enqueue_gemm(cch_ctx *c, hipStream_t st, bool fan)
             HIPCK(c, launch_expand_bf16split(p.d_SA, p.d_SB, p.d_sigA, p.d_sigB, c->opts.split_slices, p.nrows, N,
                                              p.ldk, ep, s));
         else if (!c->b_shared)
-            HIPCK(c, launch_expand_f64(p.d_At, p.d_B, p.nrows, N, K, ep, s));
+            HIPCK(c, launch_expand_f64(expand_op(c, p, 0, sa.nc), s));
         else {
             // passes over ranges of j: the rows j0..j0+nj-1 of the integral layout, then
             // the product's columns (j, j') of those rows; each output keeps its sum over K
             for (int j0 = 0; j0 < sa.nc; j0 += p.jj_chunk) {
-                const int nj = std::min(p.jj_chunk, sa.nc - j0);
-                const PackedCC pk = packed_cc(c, p, j0);
-                HIPCK(c, launch_relayout(c->d_ttcc, c->d_tctc, c->n_o, c->n_cont, p.d_slotP, p.d_slotQ, p.n_slot,
-                                         sa.ja0 + j0, nj, sb.ja0, sb.nc, p.d_B, st, c->packed ? &pk : nullptr));
-                ExpandEpi e2 = ep;
-                e2.row0a += j0;
-                e2.ja0 += j0;
-                HIPCK(c, launch_expand_f64(p.d_At, p.d_B, p.nrows, nj * sb.nc, K, e2, st));
+                const int j1 = std::min(j0 + p.jj_chunk, sa.nc);
+                HIPCK(c, relayout_f64(c, p, j0, j1, st));
+                HIPCK(c, launch_expand_f64(expand_op(c, p, j0, j1), st));
             }
         }
     }
@@ -1454,7 +1538,7 @@ cch_status cch_work_counts(const cch_ctx *c, double *out)
     double gemm = 0.0, tp = 0.0, ltp = 0.0, c4 = 0.0;
     for (auto &p : c->pp) {
         const SymInfo &sa = c->syms[p.a], &sb = c->syms[p.b];
-        gemm += 2.0 * p.nrows * (double)sa.nc * sb.nc * (2.0 * p.n_slot);
+        gemm += 2.0 * p.nrows * (double)b_cols(p, sa, sb) * (double)b_rows(p);
         tp += (double)p.pr.n;
     }
     for (auto &L : c->lt) ltp += (double)L.pr.n;
@@ -2607,9 +2691,9 @@ cch_status cch_batch_create(cch_batch **out, cch_ctx *const *ctxs, int32_t n, in
         for (auto &p : c->pp) {
             SymInfo &sa = c->syms[p.a], &sb = c->syms[p.b];
             if (sa.nc == 0 || sb.nc == 0 || p.nrows == 0) continue;
-            GemmTask g{p.d_At, p.d_B, p.nrows, sa.nc * sb.nc, 2 * p.n_slot, 0, 0, 0, expand_epi(c, p)};
+            GemmTask g{expand_op(c, p, 0, sa.nc), 0, 0, 0};
             g.tiles_m = (p.nrows + 31) / 32;
-            g.tiles_n = expand_tiles(1, g.N, 32);
+            g.tiles_n = expand_cols(g.op);
             g.first = t32;
             t32 += (int64_t)g.tiles_m * g.tiles_n;
             g32.push_back(g);

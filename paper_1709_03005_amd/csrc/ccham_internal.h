@@ -236,6 +236,14 @@ struct PackedCC {
     int jr0, nca_full;
 };
 
+// the slots (or pairs of slots) a density launch forms, and how it lays the
+// rows out for the expansion product (k_target.hip); k1 = nullptr: slot t
+enum GammaMode { GAM_PLAIN = 0, GAM_RECT = 1, GAM_SQUARE = 2 };
+struct GammaList {
+    int mode, n;
+    const int32_t *k1, *k2;
+};
+
 // work vectors of the Householder tridiagonalisation (length n each): wp =
 // the current column after the panel's corrections, p = tau_j A_j v_j; the
 // diagonal d, the off-diagonal e and the reflector scalars tau of T

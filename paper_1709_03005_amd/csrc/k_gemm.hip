@@ -6,9 +6,24 @@
 //   Ht[(n,n'), (j,j')] = sum_{PQ} Gamma_{nn',PQ} (PQ|jj')
 //                      - sum_{PQ} Gamma^alpha_{nn',PQ} (Pj'|jQ)
 //                      + delta_{jj'} (C^T H_T C')_{nn'} + (C^T O C')_{nn'} h_{jj'}
-// K0 lays the integral rows out as B[(PQ)][(j,j')]; K5 multiplies with FP64
-// MFMA (v_mfma_f64_16x16x4) and scatters each (n,n',j,j') to its row
+// K0 lays the integral rows out as B[k][(j,j')]; K5 multiplies with FP64
+// MFMA (v_mfma_f64_4x4x4) and scatters each (n,n',j,j') to its row
 // (i,n,j) / column (i',n',j') of the contracted matrix (lower triangle).
+//
+// The FP64 product multiplies each distinct integral once, by the
+// permutational symmetry of real orbitals, (PQ|jj') = (QP|jj') = (PQ|j'j) and
+// (Pj'|jQ) = (Qj|j'P):
+//   * the Coulomb rows hold one (P, Q) of each pair P >= Q, with
+//     Gamma_PQ + Gamma_QP;
+//   * between two symmetries coupled to one continuum range (the "square"
+//     form) the exchange sum over {PQ, QP} splits into a part symmetric in
+//     j, j' (the mean of the two densities times the sum of the two integrals)
+//     and an antisymmetric one (half the difference times the difference), so
+//     only j >= j' is multiplied: H(j,j') = S + A, H(j',j) = S - A.
+// The square form takes 3/4 of the rows and half the columns of the plain
+// product (0.38 of its flops; 2420 rows x 80200 columns instead of 3200 x
+// 160000 at 40 target and 400 continuum orbitals), the other pairs ("rect")
+// 3/4 of the rows. The reduced-precision forms keep the plain layout.
 #include <algorithm>
 
 #include "ccham_internal.h"
@@ -16,9 +31,11 @@
 namespace cch {
 
 // ---------------------------------------------------------------------------
-// K0: B[k][jj*ncb + jj'] for one symmetry pair.
-//   k <  n_slot: (P Q | J J')    = ttcc[P][Q][J][J']       (row copy)
-//   k >= n_slot: -(P J' | J Q)   = -tctc[P][J'][Q][J]     (tile transpose)
+// K0: B[k][jj*ncb + jj'] for one symmetry pair (plain and rect forms).
+//   k <  nJ: (P Q | J J')    = ttcc[P][Q][J][J']       (row copy)
+//   k >= nJ: -(P J' | J Q)   = -tctc[P][J'][Q][J]     (tile transpose)
+// over two lists of (P, Q): every slot in both (plain), or the pairs P > Q in
+// the first and P Q, Q P alternating in the second (rect).
 // ---------------------------------------------------------------------------
 // B[k][jj][jj'] = (P Q | ja0+jj, jb0+jj'): the slab of slot k is one contiguous
 // nca x ncb block of B, gathered from nca rows of ttcc; a workgroup copies
@@ -123,38 +140,122 @@ __global__ __launch_bounds__(256) void k_relayout_Kp(const double *__restrict__ 
     }
 }
 
-hipError_t launch_relayout(const double *ttcc, const double *tctc, int n_o, int n_cont,
-                           const int32_t *slotP, const int32_t *slotQ, int n_slot, int ja0, int nca,
-                           int jb0, int ncb, double *B, hipStream_t st, const PackedCC *pk)
+hipError_t launch_relayout(const double *ttcc, const double *tctc, int n_o, int n_cont, const int32_t *slotPJ,
+                           const int32_t *slotQJ, int nJ, const int32_t *slotPK, const int32_t *slotQK, int nK,
+                           int ja0, int nca, int jb0, int ncb, double *B, hipStream_t st, const PackedCC *pk)
 {
-    if (n_slot <= 0 || nca <= 0 || ncb <= 0) return hipSuccess;
+    if (nK <= 0 || nca <= 0 || ncb <= 0) return hipSuccess;
+    const dim3 gJ((int)(((int64_t)nca * ncb + RJ_PER - 1) / RJ_PER), nJ), gK((nca + 31) / 32, (ncb + 31) / 32, nK);
     if (pk) {
-        hipLaunchKernelGGL(k_relayout_Jp, dim3((int)(((int64_t)nca * ncb + RJ_PER - 1) / RJ_PER), n_slot), dim3(256),
-                           0, st, ttcc, *pk, n_o, slotP, slotQ, nca, ncb, B);
-        hipLaunchKernelGGL(k_relayout_Kp, dim3((nca + 31) / 32, (ncb + 31) / 32, n_slot), dim3(256), 0, st, tctc, *pk,
-                           n_o, slotP, slotQ, n_slot, nca, ncb, B);
+        hipLaunchKernelGGL(k_relayout_Jp, gJ, dim3(256), 0, st, ttcc, *pk, n_o, slotPJ, slotQJ, nca, ncb, B);
+        hipLaunchKernelGGL(k_relayout_Kp, gK, dim3(256), 0, st, tctc, *pk, n_o, slotPK, slotQK, nJ, nca, ncb, B);
         return hipGetLastError();
     }
-    hipLaunchKernelGGL(k_relayout_J, dim3((int)(((int64_t)nca * ncb + RJ_PER - 1) / RJ_PER), n_slot), dim3(256), 0, st,
-                       ttcc, n_o, n_cont, slotP, slotQ, ja0, nca, jb0, ncb, B);
-    hipLaunchKernelGGL(k_relayout_K, dim3((nca + 31) / 32, (ncb + 31) / 32, n_slot), dim3(256), 0, st, tctc,
-                       n_o, n_cont, slotP, slotQ, n_slot, ja0, nca, jb0, ncb, B);
+    hipLaunchKernelGGL(k_relayout_J, gJ, dim3(256), 0, st, ttcc, n_o, n_cont, slotPJ, slotQJ, ja0, nca, jb0, ncb, B);
+    hipLaunchKernelGGL(k_relayout_K, gK, dim3(256), 0, st, tctc, n_o, n_cont, slotPK, slotQK, nJ, ja0, nca, jb0, ncb,
+                       B);
+    return hipGetLastError();
+}
+
+// K0 of the square form: rows of the pairs P >= Q (the nF - n_off diagonal ones
+// last), columns j >= j' packed by rows j, j0 <= j < j1:
+//   B[t][tri(j) - tri(j0) + j']           = (P Q | j j')
+//   B[nF + t]                             = (P j'|Q j) + (P j|Q j')   (once for P = Q)
+//   B[2 nF + t], t < n_off                = (P j'|Q j) - (P j|Q j')
+// One launch: blockIdx.z < nF copies (tt|cc) rows, a wave per row j; the rest
+// read the pair of 32 x 32 tiles of (P x|Q y) that mirror each other. Bound by
+// HBM: every value of a pair P > Q is read once and 12 bytes move per plain
+// element instead of 32.
+__host__ __device__ __forceinline__ int64_t tri64(int64_t j) { return j * (j + 1) / 2; }
+
+template <bool PACKED>
+__global__ __launch_bounds__(256) void k_relayout_sq(const double *__restrict__ ttcc, const double *__restrict__ tctc,
+                                                     PackedCC pk, int n_o, int n_cont,
+                                                     const int32_t *__restrict__ fP, const int32_t *__restrict__ fQ,
+                                                     int nF, int n_off, int ja0, int nc, int j0, int j1,
+                                                     double *__restrict__ B)
+{
+    __shared__ double ta[32][33], tb[32][33];
+    const int64_t ldb = tri64(j1) - tri64(j0);
+    const int jt = j0 + blockIdx.x * 32, pt = blockIdx.y * 32;
+    if (pt > min(jt + 31, j1 - 1)) return;   // no j' <= j in this tile (the whole workgroup)
+    const bool coul = (int)blockIdx.z < nF;
+    const int t = coul ? blockIdx.z : blockIdx.z - nF;
+    const int P = fP[t], Q = fQ[t];
+    const int tx = threadIdx.x & 31, ty = threadIdx.x >> 5;    // 32 x 8
+    if (coul) {
+        const double *src = PACKED ? ttcc + pk.rec[(size_t)P * n_o + Q] + pk.boffJ
+                                   : ttcc + ((size_t)P * n_o + Q) * n_cont * n_cont + (size_t)ja0 * n_cont + ja0;
+        const int64_t ls = PACKED ? nc : n_cont;
+        double *dst = B + t * ldb - tri64(j0);
+        double v[4];
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+            const int j = jt + ty + 8 * u, jp = pt + tx;
+            v[u] = (j < j1 && jp <= j) ? src[j * ls + jp] : 0.0;
+        }
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+            const int j = jt + ty + 8 * u, jp = pt + tx;
+            if (j < j1 && jp <= j) dst[tri64(j) + jp] = v[u];
+        }
+        return;
+    }
+    // T[x][y] = (P x | Q y)
+    const double *src = PACKED ? tctc + pk.rec[(size_t)P * n_o + Q] + pk.boffK
+                               : tctc + (((size_t)P * n_cont + ja0) * n_o + Q) * n_cont + ja0;
+    const int64_t ls = PACKED ? nc : (int64_t)n_o * n_cont;
+    for (int r = ty; r < 32; r += 8) {
+        ta[r][tx] = (jt + r < j1 && pt + tx < nc) ? src[(jt + r) * ls + pt + tx] : 0.0;
+        tb[r][tx] = (pt + r < nc && jt + tx < j1) ? src[(pt + r) * ls + jt + tx] : 0.0;
+    }
+    __syncthreads();
+    double *dp = B + (nF + t) * ldb - tri64(j0), *dm = B + (2 * (int64_t)nF + t) * ldb - tri64(j0);
+    for (int r = ty; r < 32; r += 8) {
+        const int j = jt + r, jp = pt + tx;
+        if (j >= j1 || jp > j) continue;
+        const double x = tb[tx][r], y = ta[r][tx];   // T[j'][j], T[j][j']
+        if (t < n_off) {
+            dp[tri64(j) + jp] = x + y;
+            dm[tri64(j) + jp] = x - y;
+        } else {
+            dp[tri64(j) + jp] = x;
+        }
+    }
+}
+
+hipError_t launch_relayout_sq(const double *ttcc, const double *tctc, int n_o, int n_cont, const int32_t *fP,
+                              const int32_t *fQ, int nF, int n_off, int ja0, int nc, int j0, int j1, double *B,
+                              hipStream_t st, const PackedCC *pk)
+{
+    if (nF <= 0 || j1 <= j0) return hipSuccess;
+    const dim3 g((j1 - j0 + 31) / 32, (j1 + 31) / 32, 2 * nF);
+    if (pk)
+        hipLaunchKernelGGL(k_relayout_sq<true>, g, dim3(256), 0, st, ttcc, tctc, *pk, n_o, n_cont, fP, fQ, nF, n_off,
+                           ja0, nc, j0, j1, B);
+    else
+        hipLaunchKernelGGL(k_relayout_sq<false>, g, dim3(256), 0, st, ttcc, tctc, PackedCC{}, n_o, n_cont, fP, fQ, nF,
+                           n_off, ja0, nc, j0, j1, B);
     return hipGetLastError();
 }
 
 // ---------------------------------------------------------------------------
 // K5: C = A * B with A given K-major (At[k][r]), FP64 MFMA 4x4x4 (four
-// blocks). Workgroup tile 64 (r) x 128 (col), 4 waves in 2 x 2, each 32 x 64 =
-// 8 x 4 instructions of 4 rows x 16 columns. K staged through LDS in slices
-// of 16. Operand layout of the four-block 4x4x4 f64 MFMA (lane l = j + 4 blk +
-// 16 i, checked on gfx950): A[blk][i][k] at lane i + 4 blk + 16 k, B[blk][k][j]
-// at lane j + 4 blk + 16 k, D[blk][i][j] at lane j + 4 blk + 16 i. With the
-// same A slab in every block, an instruction multiplies 4 rows by 16 columns
-// (B's column 4 blk + j); on this chip it issues faster per flop than the
-// 16x16x4 form.
+// blocks). Workgroup tile BM (r) x 128 (col), 4 waves; each wave has up to 32
+// rows x (128 / waves along the columns) = 8 x NT instructions of 4 rows x 16
+// columns. K staged through LDS in slices of 16. Operand layout of the
+// four-block 4x4x4 f64 MFMA (lane l = j + 4 blk + 16 i, checked on gfx950):
+// A[blk][i][k] at lane i + 4 blk + 16 k, B[blk][k][j] at lane j + 4 blk + 16 k,
+// D[blk][i][j] at lane j + 4 blk + 16 i. With the same A slab in every block,
+// an instruction multiplies 4 rows by 16 columns (B's column 4 blk + j); on
+// this chip it issues faster per flop than the 16x16x4 form.
+//
+// Square form: a tile's 128 columns are 8 values of j x 16 of j' (so a wave's
+// 16 lanes write 128 contiguous bytes of a row, and the mirrored elements of
+// its values of j lie side by side in theirs); the rows of the symmetric part
+// (k < KS) and of the antisymmetric one (KS <= k < KS + KA) go to two sets of
+// accumulators.
 // ---------------------------------------------------------------------------
-typedef double dx4 __attribute__((ext_vector_type(4)));
-
 struct ExpandEpi {
     double *H;            // contracted matrix, row-major
     int64_t ld;
@@ -167,7 +268,17 @@ struct ExpandEpi {
     int n_o, n_orb;
 };
 
-constexpr int GBN = 128, GBK = 16;
+// one product: rect, N = (rows j of the pass) x ncb columns, KA = 0; or square,
+// columns j >= j' of j0 <= j < j1
+struct ExpandOp {
+    const double *At, *B;
+    int nrows, KS, KA;
+    int sq, j0, j1;
+    int N;                // columns of B (the leading dimension)
+    ExpandEpi ep;
+};
+
+constexpr int GBN = 128, GBK = 16, GBJ = 8;
 
 __device__ __forceinline__ int xcd_remap(int b, int nb)
 {
@@ -178,121 +289,197 @@ __device__ __forceinline__ int xcd_remap(int b, int nb)
     return (b % 8) * per + b / 8;
 }
 
-// One output tile (BM rows x 128 columns) of the expansion product; 4 waves,
-// BM/32 x (4/(BM/32)) of them, each 32 rows x (128 / waves_n) columns.
-template <int BM>
-__device__ __forceinline__ void expand_tile_f64(const double *__restrict__ At, const double *__restrict__ B,
-                                                int nrows, int N, int K, const ExpandEpi &ep, int tm, int tn,
-                                                double (*As)[BM], double (*Bs)[GBN])
+// square form: column tiles of the eight rows j from jt on (16 j' each)
+__host__ __device__ __forceinline__ int sq_tiles(int jt, int j1)
 {
-    constexpr int WAVES_M = BM / 32, WAVES_N = 4 / WAVES_M;
+    return ((jt + GBJ < j1 ? jt + GBJ : j1) - 1) / 16 + 1;
+}
+
+template <int BM, bool SQ>
+__device__ __forceinline__ void expand_tile_f64(const ExpandOp &op, int tm, int tn, double (*As)[BM],
+                                                double (*Bs)[GBN])
+{
+    constexpr int WAVES_M = BM >= 64 ? 2 : 1, WAVES_N = 4 / WAVES_M;
+    constexpr int MA = BM / WAVES_M / 4;                    // 4-row steps per wave
     constexpr int WCOLS = GBN / WAVES_N, NT = WCOLS / 16;   // MFMA tiles along N per wave
     constexpr int AQ = BM * GBK / 256, BQ = GBN * GBK / 256;
+    const double *__restrict__ At = op.At;
+    const int nrows = op.nrows;
+    const int64_t ldb = op.N;
+    const ExpandEpi &ep = op.ep;
     const int r0 = tm * BM, c0 = tn * GBN;
     const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
     const int wm = wv % WAVES_M, wn = wv / WAVES_M;
+    // the column of B that this thread stages
+    const int cc = threadIdx.x & (GBN - 1), kc = threadIdx.x / GBN;
+    int jt = 0, jp0 = 0;
+    bool cok;
+    int64_t coff;
+    if (SQ) {
+        jt = op.j0;
+        for (int left = tn;;) {
+            const int n = sq_tiles(jt, op.j1);
+            if (left < n) {
+                jp0 = 16 * left;
+                break;
+            }
+            left -= n;
+            jt += GBJ;
+        }
+        const int j = jt + (cc >> 4), jp = jp0 + (cc & 15);
+        cok = j < op.j1 && jp <= j;
+        coff = tri64(j) - tri64(op.j0) + jp;
+    } else {
+        cok = c0 + cc < op.N;
+        coff = c0 + cc;
+    }
+    const double *__restrict__ Bc = op.B + (cok ? coff : 0);
 
     // 4x4x4 FP64 MFMA (four blocks sharing the A slab): one instruction is 4
     // rows x 16 columns x 4 k; lane l holds row 4 m + (l >> 4), column 16 n +
-    // (l & 15) of the wave's 32 x WCOLS tile
-    double acc[8][NT];
-#pragma unroll
-    for (int a = 0; a < 8; ++a)
-#pragma unroll
-        for (int b = 0; b < NT; ++b) acc[a][b] = 0.0;
-
+    // (l & 15) of the wave's tile
+    double acc[MA][NT], acca[SQ ? MA : 1][SQ ? NT : 1];
     double ra[AQ], rb[BQ];
-    auto gload = [&](int k0) {
+    auto gload = [&](int k0, int ke) {
 #pragma unroll
         for (int q = 0; q < AQ; ++q) {
             const int e = threadIdx.x + 256 * q;
-            const int kk = e / BM, rr = e % BM;
-            const int k = k0 + kk, r = r0 + rr;
-            ra[q] = (k < K && r < nrows) ? At[(size_t)k * nrows + r] : 0.0;
+            const int k = k0 + e / BM, r = r0 + e % BM;
+            ra[q] = (k < ke && r < nrows) ? At[(size_t)k * nrows + r] : 0.0;
         }
 #pragma unroll
         for (int q = 0; q < BQ; ++q) {
-            const int e = threadIdx.x + 256 * q;
-            const int kk = e / GBN, cc = e % GBN;
-            const int k = k0 + kk, c = c0 + cc;
-            rb[q] = (k < K && c < N) ? B[(size_t)k * N + c] : 0.0;
+            const int k = k0 + kc + 2 * q;
+            rb[q] = (k < ke && cok) ? Bc[(int64_t)k * ldb] : 0.0;
         }
     };
-    gload(0);
-    for (int k0 = 0; k0 < K; k0 += GBK) {
-        __syncthreads();
+    auto product = [&](int kb, int ke, auto &ac) {
 #pragma unroll
-        for (int q = 0; q < AQ; ++q) {
-            const int e = threadIdx.x + 256 * q;
-            As[e / BM][e % BM] = ra[q];
-        }
+        for (int a = 0; a < MA; ++a)
 #pragma unroll
-        for (int q = 0; q < BQ; ++q) {
-            const int e = threadIdx.x + 256 * q;
-            Bs[e / GBN][e % GBN] = rb[q];
-        }
-        __syncthreads();
-        if (k0 + GBK < K) gload(k0 + GBK);
+            for (int b = 0; b < NT; ++b) ac[a][b] = 0.0;
+        if (kb >= ke) return;
+        gload(kb, ke);
+        for (int k0 = kb; k0 < ke; k0 += GBK) {
+            __syncthreads();
 #pragma unroll
-        for (int ks = 0; ks < GBK; ks += 4) {
-            const int kk = ks + (lane >> 4);
-            double bf[NT];
+            for (int q = 0; q < AQ; ++q) {
+                const int e = threadIdx.x + 256 * q;
+                As[e / BM][e % BM] = ra[q];
+            }
 #pragma unroll
-            for (int b = 0; b < NT; ++b) bf[b] = Bs[kk][wn * WCOLS + b * 16 + (lane & 15)];
+            for (int q = 0; q < BQ; ++q) Bs[kc + 2 * q][cc] = rb[q];
+            __syncthreads();
+            if (k0 + GBK < ke) gload(k0 + GBK, ke);
 #pragma unroll
-            for (int a = 0; a < 8; ++a) {
-                const double af = As[kk][wm * 32 + 4 * a + (lane & 3)];
+            for (int ks = 0; ks < GBK; ks += 4) {
+                const int kk = ks + (lane >> 4);
+                double bf[NT];
 #pragma unroll
-                for (int b = 0; b < NT; ++b)
-                    acc[a][b] = __builtin_amdgcn_mfma_f64_4x4x4f64(af, bf[b], acc[a][b], 0, 0, 0);
+                for (int b = 0; b < NT; ++b) bf[b] = Bs[kk][wn * WCOLS + b * 16 + (lane & 15)];
+#pragma unroll
+                for (int a = 0; a < MA; ++a) {
+                    const double af = As[kk][wm * 32 + 4 * a + (lane & 3)];
+#pragma unroll
+                    for (int b = 0; b < NT; ++b)
+                        ac[a][b] = __builtin_amdgcn_mfma_f64_4x4x4f64(af, bf[b], ac[a][b], 0, 0, 0);
+                }
             }
         }
-    }
+    };
+    product(0, op.KS, acc);
+    if constexpr (SQ) product(op.KS, op.KS + op.KA, acca);
     __syncthreads();   // the LDS tiles are reused by the next tile of a persistent loop
 
     // epilogue: scatter into the contracted matrix (lower triangle only)
 #pragma unroll
-    for (int a = 0; a < 8; ++a) {
-        {
-            const int r = r0 + wm * 32 + 4 * a + (lane >> 4);
-            if (r >= nrows) continue;
-            const int n = ep.rn[r], n2 = ep.rn2[r];
-            const double ht = ep.HT[r], ov = ep.O[r];
+    for (int a = 0; a < MA; ++a) {
+        const int r = r0 + wm * 32 + 4 * a + (lane >> 4);
+        if (r >= nrows) continue;
+        const int n = ep.rn[r], n2 = ep.rn2[r];
+        const double ht = ep.HT[r], ov = ep.O[r];
 #pragma unroll
-            for (int b = 0; b < NT; ++b) {
+        for (int b = 0; b < NT; ++b) {
+            int jj, jp;
+            if (SQ) {
+                jj = jt + wn * NT + b;
+                jp = jp0 + (lane & 15);
+                if (jj >= op.j1 || jp > jj) continue;
+            } else {
                 const int c = c0 + wn * WCOLS + b * 16 + (lane & 15);
-                if (c >= N) continue;
-                const int jj = c / ep.ncb, jp = c - jj * ep.ncb;
-                const int64_t R = ep.row0a + (int64_t)n * ep.nca + jj;
-                const int64_t C = ep.row0b + (int64_t)n2 * ep.ncb + jp;
-                if (R < C) continue;
-                const int J = ep.ja0 + jj, Jp = ep.jb0 + jp;
+                if (c >= op.N) continue;
+                jj = c / ep.ncb;
+                jp = c - jj * ep.ncb;
+            }
+            const int J = ep.ja0 + jj, Jp = ep.jb0 + jp;
+            const int64_t R = ep.row0a + (int64_t)n * ep.nca + jj;
+            const int64_t C = ep.row0b + (int64_t)n2 * ep.ncb + jp;
+            if (R >= C) {
                 double val = acc[a][b];
+                if constexpr (SQ) val += acca[a][b];
                 if (J == Jp) val += ht;
                 val += ov * ep.h[(size_t)(ep.n_o + J) * ep.n_orb + (ep.n_o + Jp)];
                 ep.H[R * ep.ld + C] = val;
+            }
+            if constexpr (SQ) {
+                const int64_t R2 = ep.row0a + (int64_t)n * ep.nca + jp;
+                const int64_t C2 = ep.row0b + (int64_t)n2 * ep.ncb + jj;
+                if (jp < jj && R2 >= C2) {
+                    double val = acc[a][b] - acca[a][b];
+                    val += ov * ep.h[(size_t)(ep.n_o + Jp) * ep.n_orb + (ep.n_o + J)];
+                    ep.H[R2 * ep.ld + C2] = val;
+                }
             }
         }
     }
 }
 
-__global__ __launch_bounds__(256) void k_expand_f64(const double *__restrict__ At, const double *__restrict__ B,
-                                                    int nrows, int N, int K, ExpandEpi ep)
+template <int BM, bool SQ>
+__global__ __launch_bounds__(256) void k_expand_f64(ExpandOp op, int tiles_m, int tiles)
 {
-    __shared__ double As[GBK][64];
+    __shared__ double As[GBK][BM];
     __shared__ double Bs[GBK][GBN];
-    const int tiles_m = (nrows + 63) / 64;
-    const int tiles_n = (N + GBN - 1) / GBN;
-    const int lb = xcd_remap(blockIdx.x, tiles_m * tiles_n);
-    expand_tile_f64<64>(At, B, nrows, N, K, ep, lb % tiles_m, lb / tiles_m, As, Bs);
+    const int lb = xcd_remap(blockIdx.x, tiles);
+    expand_tile_f64<BM, SQ>(op, lb % tiles_m, lb / tiles_m, As, Bs);
 }
 
-hipError_t launch_expand_f64(const double *At, const double *B, int nrows, int N, int K, const ExpandEpi &ep,
-                             hipStream_t st)
+// column tiles of a product
+int expand_cols(const ExpandOp &op)
 {
-    if (nrows <= 0 || N <= 0) return hipSuccess;
-    const int tiles = ((nrows + 63) / 64) * ((N + GBN - 1) / GBN);
-    hipLaunchKernelGGL(k_expand_f64, dim3(tiles), dim3(256), 0, st, At, B, nrows, N, K, ep);
+    if (!op.sq) return (op.N + GBN - 1) / GBN;
+    int n = 0;
+    for (int jt = op.j0; jt < op.j1; jt += GBJ) n += sq_tiles(jt, op.j1);
+    return n;
+}
+
+// tile height: 64 rows unless that pads the rows by a quarter more than lower
+// tiles would (15 rows of five states take a 16-row tile, 25 a 32-row one) or
+// leaves the 256 compute units without two workgroups each. Every height gives
+// the same bits (each element is one sum over k in order).
+static int expand_height(int nrows, int cols)
+{
+    if (nrows <= 16) return 16;
+    const int p64 = (nrows + 63) / 64 * 64, p32 = (nrows + 31) / 32 * 32;
+    return (4 * p64 > 5 * p32 || (p64 / 64) * cols < 512) ? 32 : 64;
+}
+
+template <int BM>
+static void expand_launch(const ExpandOp &op, int cols, hipStream_t st)
+{
+    const int tm = (op.nrows + BM - 1) / BM;
+    if (op.sq) hipLaunchKernelGGL((k_expand_f64<BM, true>), dim3(tm * cols), dim3(256), 0, st, op, tm, tm * cols);
+    else hipLaunchKernelGGL((k_expand_f64<BM, false>), dim3(tm * cols), dim3(256), 0, st, op, tm, tm * cols);
+}
+
+hipError_t launch_expand_f64(const ExpandOp &op, hipStream_t st)
+{
+    if (op.nrows <= 0 || op.N <= 0) return hipSuccess;
+    const int cols = expand_cols(op);
+    switch (expand_height(op.nrows, cols)) {
+    case 16: expand_launch<16>(op, cols, st); break;
+    case 32: expand_launch<32>(op, cols, st); break;
+    default: expand_launch<64>(op, cols, st); break;
+    }
     return hipGetLastError();
 }
 
@@ -302,12 +489,9 @@ hipError_t launch_expand_f64(const double *At, const double *B, int nrows, int N
 // tiles [first[d], first[d] + tiles_m * tiles_n).
 // ---------------------------------------------------------------------------
 struct GemmTask {
-    const double *At;
-    const double *B;
-    int nrows, N, K;
+    ExpandOp op;
     int tiles_m, tiles_n;
     int64_t first;
-    ExpandEpi ep;
 };
 
 template <int BM>
@@ -325,12 +509,11 @@ __global__ __launch_bounds__(256) void k_expand_f64_batched(const GemmTask *__re
         }
         const GemmTask &g = tasks[lo];
         const int64_t local = t - g.first;
-        expand_tile_f64<BM>(g.At, g.B, g.nrows, g.N, g.K, g.ep, (int)(local % g.tiles_m),
-                            (int)(local / g.tiles_m), As, Bs);
+        const int tm = (int)(local % g.tiles_m), tn = (int)(local / g.tiles_m);
+        if (g.op.sq) expand_tile_f64<BM, true>(g.op, tm, tn, As, Bs);
+        else expand_tile_f64<BM, false>(g.op, tm, tn, As, Bs);
     }
 }
-
-int expand_tiles(int nrows, int N, int bm) { return ((nrows + bm - 1) / bm) * ((N + GBN - 1) / GBN); }
 
 hipError_t launch_expand_f64_batched(const GemmTask *tasks, int ntask, int64_t total, int bm, int grid,
                                      hipStream_t st)

@@ -289,13 +289,19 @@ hipError_t launch_bucket(PairList pl, int64_t n, const int32_t *pqidx, int n_o, 
 }
 
 // ---------------------------------------------------------------------------
-// Gamma: one workgroup per label slot k = (P, Q).
+// Gamma: one workgroup per label slot (P, Q), or in the folded layouts per pair
+// of slots (P, Q), (Q, P). Per slot,
 //   J[r] = sum over degree-1 pairs with label (P,Q) of s c_a[m][n] c_b[m'][n']
 //          (+ for P == Q the degree-0 pairs weighted by the occupation of P)
 //   K[r] = the exchange weights: excitations from a hole of the bra's continuum
 //          spin to a particle of the ket's (alpha -> alpha when both continuum
 //          electrons are alpha) / occupation of P with the continuum spin.
-// Output Kt-major: At[k][r] = J, At[n_slot + k][r] = K.
+// Output At[k][r], by layout (J, K of slot k1, J', K' of slot k2):
+//   GAM_PLAIN  At[t] = J, At[nt + t] = K;
+//   GAM_RECT   At[t] = J + J', At[nt + 2t] = K, At[nt + 2t + 1] = K';
+//   GAM_SQUARE At[t] = J + J', At[nt + t] = -(K + K') / 2, and for t < n_off
+//              At[2 nt + t] = -(K - K') / 2; a single slot (k2 < 0):
+//              At[nt + t] = -K.
 // ---------------------------------------------------------------------------
 constexpr int GAM_BATCH = 16;
 constexpr int GAM_RPT = 8;      // rows per thread per pass
@@ -306,7 +312,7 @@ __global__ __launch_bounds__(256) void k_gamma(PairList pl, const int64_t *__res
                                                const int64_t *__restrict__ sorted,
                                                const int64_t *__restrict__ d0, int M0,
                                                const int32_t *__restrict__ slotP,
-                                               const int32_t *__restrict__ slotQ, int n_slot,
+                                               const int32_t *__restrict__ slotQ, GammaList gl,
                                                const uint64_t *__restrict__ da,
                                                const int8_t *__restrict__ spa,
                                                const int8_t *__restrict__ spb,
@@ -320,105 +326,122 @@ __global__ __launch_bounds__(256) void k_gamma(PairList pl, const int64_t *__res
     double *sa = sh;                            // [GAM_BATCH][Sa]
     double *sb = sh + GAM_BATCH * Sa;           // [GAM_BATCH][Sb]
     __shared__ double wj[GAM_BATCH], wk[GAM_BATCH];
-    const int k = blockIdx.x;
-    const int P = slotP[k], Q = slotQ[k];
-    const int64_t s1 = start[k], n1 = count[k];
-    const int64_t n0 = (P == Q) ? M0 : 0;
-    const int64_t ntot = n1 + n0;
+    const int t0 = blockIdx.x;
+    const int ks[2] = {gl.k1 ? gl.k1[t0] : t0, gl.k2 ? gl.k2[t0] : -1};
 
     for (int rbase = 0; rbase < nrows; rbase += 256 * GAM_RPT) {
-        double J[GAM_RPT], K[GAM_RPT];
+        double J[GAM_RPT], K[2][GAM_RPT];
 #pragma unroll
-        for (int q = 0; q < GAM_RPT; ++q) J[q] = K[q] = 0.0;
-        for (int64_t e0 = 0; e0 < ntot; e0 += GAM_BATCH) {
-            const int ne = (int)min<int64_t>(GAM_BATCH, ntot - e0);
-            __syncthreads();
-            // stage weights and CI rows of this batch
-            for (int t = threadIdx.x; t < ne; t += 256) {
-                const int64_t e = e0 + t;
-                const int64_t pidx = e < n1 ? sorted[s1 + e] : d0[e - n1];
-                double a = 0.0, b = 0.0;
-                if (pidx < 0) {
-                    // no identical ket for this bra row
-                } else if (e < n1) {
-                    // particle p (in the bra), hole q (in the ket); the Coulomb weight
-                    // needs equal continuum spins and a spin-conserving excitation, the
-                    // exchange weight a particle of the ket's continuum spin and a hole
-                    // of the bra's (the spin-flip pairs of doublet-coupled triplets)
-                    const int s = pl.phase[pidx];
-                    const uint64_t lab = pl.label[pidx];
-                    const int sp = lab_field(lab, 0) & 1, sq = lab_field(lab, 1) & 1;
-                    const int sx = spa ? spa[pl.x[pidx]] : 0, sy = spb ? spb[pl.y[pidx]] : 0;
-                    a = (sx == sy && sp == sq) ? (double)s : 0.0;
-                    b = (sp == sy && sq == sx) ? (double)s : 0.0;
-                } else {
-                    // occupation of spatial orbital P in the bra determinant (both spins;
-                    // the continuum spin's for the exchange weight)
-                    const uint64_t *d = da + (size_t)pl.x[pidx] * W;
-                    const int ka = 2 * P, kb = 2 * P + 1;
-                    const int oa = (int)((d[ka >> 6] >> (ka & 63)) & 1ull);
-                    const int ob = (int)((d[kb >> 6] >> (kb & 63)) & 1ull);
-                    const int sx = spa ? spa[pl.x[pidx]] : 0;
-                    a = (double)(oa + ob);
-                    b = (double)(sx ? ob : oa);
-                }
-                wj[t] = a;
-                wk[t] = b;
-            }
-            for (int t = threadIdx.x; t < ne * Sa; t += 256) {
-                const int ee = t / Sa, n = t % Sa;
-                const int64_t e = e0 + ee;
-                const int64_t pidx = e < n1 ? sorted[s1 + e] : d0[e - n1];
-                sa[ee * Sa + n] = pidx < 0 ? 0.0 : ca[(size_t)pl.x[pidx] * Sa + n];
-            }
-            for (int t = threadIdx.x; t < ne * Sb; t += 256) {
-                const int ee = t / Sb, n = t % Sb;
-                const int64_t e = e0 + ee;
-                const int64_t pidx = e < n1 ? sorted[s1 + e] : d0[e - n1];
-                sb[ee * Sb + n] = pidx < 0 ? 0.0 : cb[(size_t)pl.y[pidx] * Sb + n];
-            }
-            __syncthreads();
+        for (int q = 0; q < GAM_RPT; ++q) J[q] = K[0][q] = K[1][q] = 0.0;
 #pragma unroll
-            for (int q = 0; q < GAM_RPT; ++q) {
-                const int r = rbase + threadIdx.x + 256 * q;
-                if (r < nrows) {
-                    const int n = rn[r], n2 = rn2[r];
-                    double j = J[q], kk = K[q];
-                    for (int ee = 0; ee < ne; ++ee) {
-                        const double cc = sa[ee * Sa + n] * sb[ee * Sb + n2];
-                        j = fma(wj[ee], cc, j);
-                        kk = fma(wk[ee], cc, kk);
+        for (int half = 0; half < 2; ++half) {
+            const int k = ks[half];
+            if (k < 0) continue;
+            const int P = slotP[k], Q = slotQ[k];
+            const int64_t s1 = start[k], n1 = count[k];
+            const int64_t n0 = (P == Q) ? M0 : 0;
+            const int64_t ntot = n1 + n0;
+            for (int64_t e0 = 0; e0 < ntot; e0 += GAM_BATCH) {
+                const int ne = (int)min<int64_t>(GAM_BATCH, ntot - e0);
+                __syncthreads();
+                // stage weights and CI rows of this batch
+                for (int t = threadIdx.x; t < ne; t += 256) {
+                    const int64_t e = e0 + t;
+                    const int64_t pidx = e < n1 ? sorted[s1 + e] : d0[e - n1];
+                    double a = 0.0, b = 0.0;
+                    if (pidx < 0) {
+                        // no identical ket for this bra row
+                    } else if (e < n1) {
+                        // particle p (in the bra), hole q (in the ket); the Coulomb weight
+                        // needs equal continuum spins and a spin-conserving excitation, the
+                        // exchange weight a particle of the ket's continuum spin and a hole
+                        // of the bra's (the spin-flip pairs of doublet-coupled triplets)
+                        const int s = pl.phase[pidx];
+                        const uint64_t lab = pl.label[pidx];
+                        const int sp = lab_field(lab, 0) & 1, sq = lab_field(lab, 1) & 1;
+                        const int sx = spa ? spa[pl.x[pidx]] : 0, sy = spb ? spb[pl.y[pidx]] : 0;
+                        a = (sx == sy && sp == sq) ? (double)s : 0.0;
+                        b = (sp == sy && sq == sx) ? (double)s : 0.0;
+                    } else {
+                        // occupation of spatial orbital P in the bra determinant (both spins;
+                        // the continuum spin's for the exchange weight)
+                        const uint64_t *d = da + (size_t)pl.x[pidx] * W;
+                        const int ka = 2 * P, kb = 2 * P + 1;
+                        const int oa = (int)((d[ka >> 6] >> (ka & 63)) & 1ull);
+                        const int ob = (int)((d[kb >> 6] >> (kb & 63)) & 1ull);
+                        const int sx = spa ? spa[pl.x[pidx]] : 0;
+                        a = (double)(oa + ob);
+                        b = (double)(sx ? ob : oa);
                     }
-                    J[q] = j;
-                    K[q] = kk;
+                    wj[t] = a;
+                    wk[t] = b;
+                }
+                for (int t = threadIdx.x; t < ne * Sa; t += 256) {
+                    const int ee = t / Sa, n = t % Sa;
+                    const int64_t e = e0 + ee;
+                    const int64_t pidx = e < n1 ? sorted[s1 + e] : d0[e - n1];
+                    sa[ee * Sa + n] = pidx < 0 ? 0.0 : ca[(size_t)pl.x[pidx] * Sa + n];
+                }
+                for (int t = threadIdx.x; t < ne * Sb; t += 256) {
+                    const int ee = t / Sb, n = t % Sb;
+                    const int64_t e = e0 + ee;
+                    const int64_t pidx = e < n1 ? sorted[s1 + e] : d0[e - n1];
+                    sb[ee * Sb + n] = pidx < 0 ? 0.0 : cb[(size_t)pl.y[pidx] * Sb + n];
+                }
+                __syncthreads();
+#pragma unroll
+                for (int q = 0; q < GAM_RPT; ++q) {
+                    const int r = rbase + threadIdx.x + 256 * q;
+                    if (r < nrows) {
+                        const int n = rn[r], n2 = rn2[r];
+                        double j = J[q], kk = K[half][q];
+                        for (int ee = 0; ee < ne; ++ee) {
+                            const double cc = sa[ee * Sa + n] * sb[ee * Sb + n2];
+                            j = fma(wj[ee], cc, j);
+                            kk = fma(wk[ee], cc, kk);
+                        }
+                        J[q] = j;
+                        K[half][q] = kk;
+                    }
                 }
             }
         }
+        const size_t t = t0, nt = gl.n;
 #pragma unroll
         for (int q = 0; q < GAM_RPT; ++q) {
             const int r = rbase + threadIdx.x + 256 * q;
             if (r < nrows) {
-                At[(size_t)k * nrows + r] = J[q];
-                At[(size_t)(n_slot + k) * nrows + r] = K[q];
+                At[t * nrows + r] = J[q];
+                if (gl.mode == GAM_PLAIN) {
+                    At[(nt + t) * nrows + r] = K[0][q];
+                } else if (gl.mode == GAM_RECT) {
+                    At[(nt + 2 * t) * nrows + r] = K[0][q];
+                    At[(nt + 2 * t + 1) * nrows + r] = K[1][q];
+                } else if (ks[1] < 0) {
+                    At[(nt + t) * nrows + r] = -K[0][q];
+                } else {
+                    At[(nt + t) * nrows + r] = -0.5 * (K[0][q] + K[1][q]);
+                    At[(2 * nt + t) * nrows + r] = -0.5 * (K[0][q] - K[1][q]);
+                }
             }
         }
     }
 }
 
 hipError_t launch_gamma(int W, PairList pl, const int64_t *start, const int64_t *count,
-                        const int64_t *sorted, const int64_t *d0, int M0, const int32_t *slotP, const int32_t *slotQ, int n_slot,
-                        const uint64_t *da, const int8_t *spa, const int8_t *spb, const double *ca, int Sa,
-                        const double *cb, int Sb, int nrows, const int32_t *rn, const int32_t *rn2, double *At,
+                        const int64_t *sorted, const int64_t *d0, int M0, const int32_t *slotP, const int32_t *slotQ,
+                        const GammaList &gl, const uint64_t *da, const int8_t *spa, const int8_t *spb, const double *ca,
+                        int Sa, const double *cb, int Sb, int nrows, const int32_t *rn, const int32_t *rn2, double *At,
                         hipStream_t st)
 {
-    if (n_slot <= 0 || nrows <= 0) return hipSuccess;
+    if (gl.n <= 0 || nrows <= 0) return hipSuccess;
     const size_t shm = sizeof(double) * GAM_BATCH * (size_t)(Sa + Sb);
-    const dim3 g(n_slot), b(256);
+    const dim3 g(gl.n), b(256);
     switch (W) {
-    case 1: hipLaunchKernelGGL((k_gamma<1>), g, b, shm, st, pl, start, count, sorted, d0, M0, slotP, slotQ, n_slot, da, spa, spb, ca, Sa, cb, Sb, nrows, rn, rn2, At); break;
-    case 2: hipLaunchKernelGGL((k_gamma<2>), g, b, shm, st, pl, start, count, sorted, d0, M0, slotP, slotQ, n_slot, da, spa, spb, ca, Sa, cb, Sb, nrows, rn, rn2, At); break;
-    case 3: hipLaunchKernelGGL((k_gamma<3>), g, b, shm, st, pl, start, count, sorted, d0, M0, slotP, slotQ, n_slot, da, spa, spb, ca, Sa, cb, Sb, nrows, rn, rn2, At); break;
-    case 4: hipLaunchKernelGGL((k_gamma<4>), g, b, shm, st, pl, start, count, sorted, d0, M0, slotP, slotQ, n_slot, da, spa, spb, ca, Sa, cb, Sb, nrows, rn, rn2, At); break;
+    case 1: hipLaunchKernelGGL((k_gamma<1>), g, b, shm, st, pl, start, count, sorted, d0, M0, slotP, slotQ, gl, da, spa, spb, ca, Sa, cb, Sb, nrows, rn, rn2, At); break;
+    case 2: hipLaunchKernelGGL((k_gamma<2>), g, b, shm, st, pl, start, count, sorted, d0, M0, slotP, slotQ, gl, da, spa, spb, ca, Sa, cb, Sb, nrows, rn, rn2, At); break;
+    case 3: hipLaunchKernelGGL((k_gamma<3>), g, b, shm, st, pl, start, count, sorted, d0, M0, slotP, slotQ, gl, da, spa, spb, ca, Sa, cb, Sb, nrows, rn, rn2, At); break;
+    case 4: hipLaunchKernelGGL((k_gamma<4>), g, b, shm, st, pl, start, count, sorted, d0, M0, slotP, slotQ, gl, da, spa, spb, ca, Sa, cb, Sb, nrows, rn, rn2, At); break;
     default: return hipErrorInvalidValue;
     }
     return hipGetLastError();
