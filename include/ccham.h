@@ -522,7 +522,8 @@ cch_status cch_work_counts(const cch_ctx *ctx, double *out8);
  *        outer product of a CI row with an integral row over j);
  *   11   connected L2 x L2 pairs (degree <= 2), lower triangle with the
  *        diagonal: the structural non-zeros of classes 2 and 8;
- *   12   bytes of the mirror: 16 per element above the diagonal. */
+ *   12   bytes of the mirror: 16 per element above the diagonal that the L2
+ *        block kernel does not write itself (both triangles). */
 cch_status cch_work_detail(cch_ctx *ctx, double *out, int32_t n);
 
 /* Device memory held by the planned context (bytes) and the number of passes

@@ -76,6 +76,7 @@ struct L2Args {
     double *H;
     int64_t ld;
     int64_t row0;
+    int both;
 };
 hipError_t launch_l2_block(int W, const L2Args &a, hipStream_t st);
 hipError_t launch_l2csf_gather(const double *Hd, int64_t ldd, int Dc, int ncsf, const int32_t *start,
@@ -94,7 +95,7 @@ hipError_t launch_expand_f64_batched(const GemmTask *tasks, int ntask, int64_t t
                                      hipStream_t st);
 hipError_t launch_l2_batched(int W, const L2Task *tasks, int ntask, int64_t total, int grid, hipStream_t st);
 hipError_t launch_class4_batched(int W, const C4Task *tasks, int ntask, int64_t total, int grid, hipStream_t st);
-hipError_t launch_mirror(double *H, int64_t ld, int D, hipStream_t st);
+hipError_t launch_mirror(double *H, int64_t ld, int D, int C, hipStream_t st);
 hipError_t launch_scatter_pairs(const int32_t *px, const int32_t *py, const double *v, int64_t n, int transpose,
                                 double *out, int64_t ldo, hipStream_t st);
 hipError_t launch_pair_census(const int8_t *deg, const uint64_t *label, int64_t n, unsigned long long *out,
@@ -1419,7 +1420,7 @@ static cch_status enqueue_l2(cch_ctx *c, hipStream_t st)
             HIPCK(c, launch_l2s_values(c->W, c->d_l2, c->n_l2, I, c->csr.off, c->csr.col, c->csr.val,
                                        c->d_diag + c->Dc, st));
         } else {
-            L2Args a{c->d_l2, c->n_l2, I, c->d_Hb, c->ldb, c->Dc};
+            L2Args a{c->d_l2, c->n_l2, I, c->d_Hb, c->ldb, c->Dc, c->l2csf ? 0 : 1};
             HIPCK(c, launch_l2_block(c->W, a, st));
         }
     }
@@ -1430,7 +1431,7 @@ static cch_status enqueue_post(cch_ctx *c, hipStream_t st)
 {
     if (c->sparse) {
         // upper triangle of the continuum block, its diagonal, and the transpose of class 4
-        HIPCK(c, launch_mirror(c->d_H, c->ld, (int)c->Dc, st));
+        HIPCK(c, launch_mirror(c->d_H, c->ld, (int)c->Dc, (int)c->Dc, st));
         HIPCK(c, launch_diag(c->d_H, c->ld, (int)c->Dc, c->d_diag, st));
         HIPCK(c, launch_transpose_c4(c->d_H, c->ld, (int)c->Dc, c->n_l2, c->d_R, c->ldr, st));
         return CCH_OK;
@@ -1438,7 +1439,9 @@ static cch_status enqueue_post(cch_ctx *c, hipStream_t st)
     if (c->l2csf)   // the matrix over the CSFs (lower triangle) from the one over the determinants
         HIPCK(c, launch_l2csf_gather(c->d_Hd, c->ldd, (int)c->Dc, c->n_l2r, c->d_csf_start, c->d_csf_det,
                                      c->d_csf_coef, c->d_H, c->ld, st));
-    HIPCK(c, launch_mirror(c->d_H, c->ld, (int)c->D, st));
+    // the L2 block kernel writes both triangles (not over CSFs, whose gather
+    // writes the lower one)
+    HIPCK(c, launch_mirror(c->d_H, c->ld, (int)c->D, (int)(c->l2csf ? c->D : c->Dc), st));
     HIPCK(c, launch_diag(c->d_H, c->ld, (int)c->D, c->d_diag, st));
     return CCH_OK;
 }
@@ -1657,7 +1660,8 @@ cch_status cch_work_detail(cch_ctx *c, double *out, int32_t n)
     // mirror: 16 bytes per element above the diagonal of the dense parts (a
     // sparse L2 block also writes the transpose of class 4)
     v[12] = c->sparse ? 16.0 * (double)c->Dc * (double)(c->Dc - 1) / 2.0 + 16.0 * (double)c->Dc * c->n_l2
-                      : 16.0 * (double)c->D * (double)(c->D - 1) / 2.0;
+                      : c->l2csf ? 16.0 * (double)c->D * (double)(c->D - 1) / 2.0
+                                 : 16.0 * ((double)c->Dc * (double)(c->Dc - 1) / 2.0 + (double)c->Dc * c->n_l2);
     for (int i = 0; i < n && i < 16; ++i) out[i] = v[i];
     for (int i = 16; i < n; ++i) out[i] = 0.0;
     return CCH_OK;
@@ -2711,7 +2715,7 @@ cch_status cch_batch_create(cch_batch **out, cch_ctx *const *ctxs, int32_t n, in
         }
         if (c->n_l2 > 0) {
             const TgtInts I{c->d_h, c->d_tttt, c->n_o, c->n_orb, c->e_core};
-            L2Task t{L2Args{c->d_l2, c->n_l2, I, c->d_H, c->ld, c->Dc}, l2t[c->W]};
+            L2Task t{L2Args{c->d_l2, c->n_l2, I, c->d_H, c->ld, c->Dc, 1}, l2t[c->W]};
             l2t[c->W] += l2_tiles(c->n_l2);
             l2[c->W].push_back(t);
         }

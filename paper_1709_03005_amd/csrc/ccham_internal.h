@@ -162,9 +162,23 @@ __device__ __forceinline__ double g4(const TgtInts &I, int P, int Q, int R, int 
     return I.tttt[(((size_t)P * I.n_o + Q) * I.n_o + R) * I.n_o + S];
 }
 
+// the next four set bits of x (taken out of it); where fewer are left, `ok`
+// is false and the index 0
+__device__ __forceinline__ void next_four(uint64_t &x, int base, int *k, bool *ok)
+{
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+        ok[u] = x != 0;
+        k[u] = ok[u] ? base + (int)__builtin_ctzll(x) : 0;
+        x &= x - 1;
+    }
+}
+
 // <A|H|B> for target-only determinants connected by degree 0..2, from the
 // excitation (holes h, particles p, sign s). The degree-1 sum runs over all
-// of B: its k = h term cancels exactly.
+// of B: its k = h term cancels exactly. The sums over electrons take their
+// integrals four electrons at a time and add them in order (one load after
+// the other left a diagonal element of ten electrons at 45 dependent steps).
 template <int W>
 __device__ double sc_value(const TgtInts &I, const uint64_t *A, const uint64_t *B, int deg,
                            const int *h, const int *p, int s)
@@ -179,11 +193,27 @@ __device__ double sc_value(const TgtInts &I, const uint64_t *A, const uint64_t *
         for (int a = 0; a < n; ++a) {
             const int ka = occ[a], Pa = ka >> 1;
             e += I.h[(size_t)Pa * I.n_orb + Pa];
-            for (int b = 0; b < a; ++b) {
-                const int kb = occ[b], Pb = kb >> 1;
-                double v = g4(I, Pa, Pa, Pb, Pb);
-                if ((ka & 1) == (kb & 1)) v -= g4(I, Pa, Pb, Pb, Pa);
-                e2 += v;
+#pragma unroll
+            for (int w = 0; w < W; ++w) {
+                uint64_t x = A[w] & lowmask(ka - 64 * w);
+                while (x) {
+                    int k[4];
+                    bool ok[4];
+                    double gc[4], gx[4];
+                    next_four(x, 64 * w, k, ok);
+#pragma unroll
+                    for (int u = 0; u < 4; ++u) {
+                        const int Pb = k[u] >> 1;
+                        gc[u] = g4(I, Pa, Pa, Pb, Pb);
+                        gx[u] = g4(I, Pa, Pb, Pb, Pa);
+                    }
+#pragma unroll
+                    for (int u = 0; u < 4; ++u) {
+                        double v = gc[u];
+                        if ((ka & 1) == (k[u] & 1)) v -= gx[u];
+                        if (ok[u]) e2 += v;
+                    }
+                }
             }
         }
         return e + e2;
@@ -196,11 +226,21 @@ __device__ double sc_value(const TgtInts &I, const uint64_t *A, const uint64_t *
         for (int w = 0; w < W; ++w) {
             uint64_t x = B[w];
             while (x) {
-                const int k = 64 * w + (int)__builtin_ctzll(x);
-                x &= x - 1;
-                const int K = k >> 1;
-                v += g4(I, P, H, K, K);
-                if ((k & 1) == sp) v -= g4(I, P, K, K, H);
+                int k[4];
+                bool ok[4];
+                double gc[4], gx[4];
+                next_four(x, 64 * w, k, ok);
+#pragma unroll
+                for (int u = 0; u < 4; ++u) {
+                    const int K = k[u] >> 1;
+                    gc[u] = g4(I, P, H, K, K);
+                    gx[u] = (k[u] & 1) == sp ? g4(I, P, K, K, H) : 0.0;
+                }
+#pragma unroll
+                for (int u = 0; u < 4; ++u) {
+                    if (ok[u]) v += gc[u];
+                    if (ok[u] && (k[u] & 1) == sp) v -= gx[u];
+                }
             }
         }
         return s * v;

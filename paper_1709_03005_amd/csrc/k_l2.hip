@@ -1,9 +1,20 @@
 // Classes 2 and 8: the pure L2 block <chi_l | H | chi_l'> with no
 // contraction (Sec. 2.2), evaluated by Slater's rules on bitstrings for the
 // lower triangle (Sec. 3.1 collapses the triangular double loop into one
-// loop; here each workgroup takes one 64 x 64 tile of the flattened lower
-// triangle). The scan and the element evaluation are fused: every tile
-// element is written (zero when more than a double substitution apart).
+// loop; here each workgroup takes one tile of TR rows x 64 columns of the
+// flattened lower triangle).
+//
+// A tile is scanned first: every pair takes an XOR and a popcount per word,
+// and the few within a double substitution (1.3% of the pairs at 40000
+// functions) go to a list in LDS, single substitutions from one end and
+// double ones from the other. The list is then evaluated by full waves on
+// like work -- in one pass over the tile half of the waves had at least one
+// connected lane, and the other 63 waited for its integrals -- and the tile
+// is written from LDS to both triangles, so no later pass reads the L2 block
+// back. Bound by the HBM write of the two triangles, 16 B per pair: 40000
+// functions, both triangles in 7.6 ms beside class 4, where the one-pass form
+// took 6.9 ms for the lower one and the mirror 3.0 ms for the rest; 2997
+// functions 0.058 ms instead of 0.320 + 0.03.
 #include <algorithm>
 
 #include "ccham_internal.h"
@@ -17,68 +28,129 @@ struct L2Args {
     double *H;
     int64_t ld;
     int64_t row0;           // first L2 row / column of the matrix
+    int both;               // write the upper triangle as well
 };
 
+// tiles of TR rows x 64 columns (TR divides 64) in the rows before tile row i
+template <int TR>
+__host__ __device__ __forceinline__ int64_t l2_tiles_before(int64_t i)
+{
+    constexpr int64_t f = 64 / TR;   // tile rows per 64 rows: tile row i has i / f + 1 tiles
+    const int64_t m = i / f, r = i % f;
+    return f * (m * (m + 1) / 2) + r * (m + 1);
+}
+
+template <int TR>
 __device__ __forceinline__ void tri_decode(int64_t b, int64_t *ti, int64_t *tj)
 {
-    // flattened lower-triangular tile index -> (ti >= tj)
-    int64_t i = (int64_t)((sqrt(8.0 * (double)b + 1.0) - 1.0) * 0.5);
-    while (i * (i + 1) / 2 > b) --i;
-    while ((i + 1) * (i + 2) / 2 <= b) ++i;
+    int64_t i = (int64_t)((sqrt(8.0 * (double)b * (TR / 64.0) + 1.0) - 1.0) * 0.5 * (64 / TR));
+    while (l2_tiles_before<TR>(i) > b) --i;
+    while (l2_tiles_before<TR>(i + 1) <= b) ++i;
     *ti = i;
-    *tj = b - i * (i + 1) / 2;
+    *tj = b - l2_tiles_before<TR>(i);
 }
 
-template <int W>
-__device__ __forceinline__ void l2_tile(const L2Args &a, int64_t b, uint64_t (*bra)[W], uint64_t (*ket)[W])
+template <int W, int TR>
+struct L2Shared {
+    uint64_t bra[TR][W], ket[64][W];
+    double tile[TR][65];
+    uint16_t list[TR * 64];
+    int n1, n2;
+};
+
+template <int W, int TR>
+__device__ __forceinline__ void l2_tile(const L2Args &a, int64_t b, L2Shared<W, TR> &sh)
 {
     int64_t ti, tj;
-    tri_decode(b, &ti, &tj);
-    const int l0 = (int)(ti * 64), k0 = (int)(tj * 64);
-    __syncthreads();   // the LDS dets are reused by the next tile of a persistent loop
+    tri_decode<TR>(b, &ti, &tj);
+    const int l0 = (int)(ti * TR), k0 = (int)(tj * 64);
+    __syncthreads();   // the LDS of the previous tile of a persistent loop
     for (int t = threadIdx.x; t < 64 * W; t += 256) {
         const int r = t / W, w = t % W;
-        bra[r][w] = (l0 + r < a.n_l2) ? a.dets[(size_t)(l0 + r) * W + w] : 0ull;
-        ket[r][w] = (k0 + r < a.n_l2) ? a.dets[(size_t)(k0 + r) * W + w] : 0ull;
+        if (r < TR) sh.bra[r][w] = (l0 + r < a.n_l2) ? a.dets[(size_t)(l0 + r) * W + w] : 0ull;
+        sh.ket[r][w] = (k0 + r < a.n_l2) ? a.dets[(size_t)(k0 + r) * W + w] : 0ull;
+    }
+    if (threadIdx.x == 0) sh.n1 = sh.n2 = 0;
+    __syncthreads();
+    const int c = threadIdx.x & 63, lc = k0 + c;
+    {
+        uint64_t B[W];
+#pragma unroll
+        for (int w = 0; w < W; ++w) B[w] = sh.ket[c][w];
+#pragma unroll 4
+        for (int r = threadIdx.x >> 6; r < TR; r += 4) {
+            const int lr = l0 + r;
+            int x = 0;
+#pragma unroll
+            for (int w = 0; w < W; ++w) x += __popcll(sh.bra[r][w] ^ B[w]);
+            sh.tile[r][c] = 0.0;
+            if (x <= 4 && lc <= lr && lr < a.n_l2) {
+                const int at = x <= 2 ? atomicAdd(&sh.n1, 1) : TR * 64 - 1 - atomicAdd(&sh.n2, 1);
+                sh.list[at] = (uint16_t)(r * 64 + c);
+            }
+        }
     }
     __syncthreads();
-    const int c = threadIdx.x & 63;
-    const int lc = k0 + c;
-    uint64_t B[W];
+    const int n1 = sh.n1, n2 = sh.n2;
+    for (int t = threadIdx.x; t < n1 + n2; t += 256) {
+        const int rc = t < n1 ? sh.list[t] : sh.list[TR * 64 - 1 - (t - n1)];
+        uint64_t A[W], B[W];
 #pragma unroll
-    for (int w = 0; w < W; ++w) B[w] = ket[c][w];
-    for (int r = threadIdx.x >> 6; r < 64; r += 4) {
-        const int lr = l0 + r;
-        if (lr >= a.n_l2 || lc >= a.n_l2 || lc > lr) continue;
-        uint64_t A[W];
-#pragma unroll
-        for (int w = 0; w < W; ++w) A[w] = bra[r][w];
+        for (int w = 0; w < W; ++w) {
+            A[w] = sh.bra[rc >> 6][w];
+            B[w] = sh.ket[rc & 63][w];
+        }
         int h[2], p[2], s;
         const int deg = excite<W>(A, B, h, p, &s);
-        double v = 0.0;
-        if (deg <= 2) v = sc_value<W>(a.I, A, B, deg, h, p, s);
-        a.H[(a.row0 + lr) * a.ld + a.row0 + lc] = v;
+        sh.tile[rc >> 6][rc & 63] = sc_value<W>(a.I, A, B, deg, h, p, s);
+    }
+    __syncthreads();
+    double *H = a.H + a.row0 * a.ld + a.row0;
+    if (lc < a.n_l2) {
+#pragma unroll 4
+        for (int r = threadIdx.x >> 6; r < TR; r += 4) {
+            const int lr = l0 + r;
+            if (lr < a.n_l2 && lc <= lr) H[(int64_t)lr * a.ld + lc] = sh.tile[r][c];
+        }
+    }
+    if (!a.both) return;
+    // column by column: row k0 + cc of the upper triangle, TR elements
+    const int rr = threadIdx.x % TR;
+#pragma unroll 4
+    for (int cc = threadIdx.x / TR; cc < 64; cc += 256 / TR) {
+        const int lr = l0 + rr, lk = k0 + cc;
+        if (lr < a.n_l2 && lk < lr) H[(int64_t)lk * a.ld + lr] = sh.tile[rr][cc];
     }
 }
 
-template <int W>
+template <int W, int TR>
 __global__ __launch_bounds__(256) void k_l2_block(L2Args a)
 {
-    __shared__ uint64_t bra[64][W], ket[64][W];
-    l2_tile<W>(a, blockIdx.x, bra, ket);
+    __shared__ L2Shared<W, TR> sh;
+    l2_tile<W, TR>(a, blockIdx.x, sh);
+}
+
+template <int W>
+static void l2_launch(const L2Args &a, hipStream_t st)
+{
+    // 64 x 64 tiles write whole 512-byte runs of both triangles; below 1024 of
+    // them (2900 functions) the chip is not full and four times as many tiles of
+    // 16 rows finish sooner
+    const int64_t T = (a.n_l2 + 63) / 64, T16 = (a.n_l2 + 15) / 16;
+    if (T * (T + 1) / 2 >= 1024)
+        hipLaunchKernelGGL((k_l2_block<W, 64>), dim3((unsigned)l2_tiles_before<64>(T)), dim3(256), 0, st, a);
+    else
+        hipLaunchKernelGGL((k_l2_block<W, 16>), dim3((unsigned)l2_tiles_before<16>(T16)), dim3(256), 0, st, a);
 }
 
 hipError_t launch_l2_block(int W, const L2Args &a, hipStream_t st)
 {
     if (a.n_l2 <= 0) return hipSuccess;
-    const int64_t T = (a.n_l2 + 63) / 64;
-    const int64_t nb = T * (T + 1) / 2;
-    const dim3 g((unsigned)nb), bl(256);
     switch (W) {
-    case 1: hipLaunchKernelGGL((k_l2_block<1>), g, bl, 0, st, a); break;
-    case 2: hipLaunchKernelGGL((k_l2_block<2>), g, bl, 0, st, a); break;
-    case 3: hipLaunchKernelGGL((k_l2_block<3>), g, bl, 0, st, a); break;
-    case 4: hipLaunchKernelGGL((k_l2_block<4>), g, bl, 0, st, a); break;
+    case 1: l2_launch<1>(a, st); break;
+    case 2: l2_launch<2>(a, st); break;
+    case 3: l2_launch<3>(a, st); break;
+    case 4: l2_launch<4>(a, st); break;
     default: return hipErrorInvalidValue;
     }
     return hipGetLastError();
@@ -150,7 +222,7 @@ int64_t l2_tiles(int n_l2)
 template <int W>
 __global__ __launch_bounds__(256) void k_l2_batched(const L2Task *__restrict__ tasks, int ntask, int64_t total)
 {
-    __shared__ uint64_t bra[64][W], ket[64][W];
+    __shared__ L2Shared<W, 64> sh;
     for (int64_t t = blockIdx.x; t < total; t += gridDim.x) {
         int lo = 0, hi = ntask - 1;
         while (lo < hi) {
@@ -158,7 +230,7 @@ __global__ __launch_bounds__(256) void k_l2_batched(const L2Task *__restrict__ t
             if (tasks[mid].first <= t) lo = mid;
             else hi = mid - 1;
         }
-        l2_tile<W>(tasks[lo].a, t - tasks[lo].first, bra, ket);
+        l2_tile<W, 64>(tasks[lo].a, t - tasks[lo].first, sh);
     }
 }
 

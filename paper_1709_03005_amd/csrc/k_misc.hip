@@ -7,35 +7,47 @@
 
 namespace cch {
 
-// H[c][r] = H[r][c] for r > c, over 64 x 64 tiles of the lower triangle;
-// off-diagonal tiles go through LDS so both reads and writes are coalesced.
-__global__ __launch_bounds__(256) void k_mirror(double *__restrict__ H, int64_t ld, int D)
+// H[c][r] = H[r][c] for r > c and c < C, over the 64 x 64 tiles of the lower
+// triangle with a column before C; tiles go through LDS so both reads and
+// writes are coalesced. (The L2 block, behind the C continuum columns, is
+// written to both triangles by its own kernel.)
+__global__ __launch_bounds__(256) void k_mirror(double *__restrict__ H, int64_t ld, int D, int C)
 {
     __shared__ double tile[64][65];
-    const int64_t b = blockIdx.x;
-    int64_t ti = (int64_t)((sqrt(8.0 * (double)b + 1.0) - 1.0) * 0.5);
-    while (ti * (ti + 1) / 2 > b) --ti;
-    while ((ti + 1) * (ti + 2) / 2 <= b) ++ti;
-    const int64_t tj = b - ti * (ti + 1) / 2;
+    // tile columns 0 .. tc-1; rows of tiles first by their triangle, then full
+    const int64_t tc = (C + 63) / 64, b = blockIdx.x, ntri = tc * (tc + 1) / 2;
+    int64_t ti, tj;
+    if (b < ntri) {
+        ti = (int64_t)((sqrt(8.0 * (double)b + 1.0) - 1.0) * 0.5);
+        while (ti * (ti + 1) / 2 > b) --ti;
+        while ((ti + 1) * (ti + 2) / 2 <= b) ++ti;
+        tj = b - ti * (ti + 1) / 2;
+    } else {
+        ti = tc + (b - ntri) / tc;
+        tj = (b - ntri) % tc;
+    }
     const int r0 = (int)(ti * 64), c0 = (int)(tj * 64);
     const int tx = threadIdx.x & 63, ty = threadIdx.x >> 6;
+#pragma unroll 4
     for (int r = ty; r < 64; r += 4) {
-        const int R = r0 + r, C = c0 + tx;
-        tile[r][tx] = (R < D && C < D) ? H[(int64_t)R * ld + C] : 0.0;
+        const int R = r0 + r, Cc = c0 + tx;
+        tile[r][tx] = (R < D && Cc < C) ? H[(int64_t)R * ld + Cc] : 0.0;
     }
     __syncthreads();
+#pragma unroll 4
     for (int r = ty; r < 64; r += 4) {
         // destination row c0 + r, column r0 + tx  <-  source (r0 + tx, c0 + r)
-        const int R = c0 + r, C = r0 + tx;
-        if (R < D && C < D && C > R) H[(int64_t)R * ld + C] = tile[tx][r];
+        const int R = c0 + r, Cc = r0 + tx;
+        if (R < C && Cc < D && Cc > R) H[(int64_t)R * ld + Cc] = tile[tx][r];
     }
 }
 
-hipError_t launch_mirror(double *H, int64_t ld, int D, hipStream_t st)
+// C = D: the whole matrix
+hipError_t launch_mirror(double *H, int64_t ld, int D, int C, hipStream_t st)
 {
-    if (D <= 0) return hipSuccess;
-    const int64_t T = (D + 63) / 64;
-    hipLaunchKernelGGL(k_mirror, dim3((unsigned)(T * (T + 1) / 2)), dim3(256), 0, st, H, ld, D);
+    if (D <= 0 || C <= 0) return hipSuccess;
+    const int64_t T = (D + 63) / 64, tc = (C + 63) / 64;
+    hipLaunchKernelGGL(k_mirror, dim3((unsigned)(tc * (tc + 1) / 2 + (T - tc) * tc)), dim3(256), 0, st, H, ld, D, C);
     return hipGetLastError();
 }
 
