@@ -536,9 +536,9 @@ def main():
 
     # roofline figures per kernel family (algorithmic work / measured device time)
     D = inst.dim()
-    # dense H from D = 16384 on: the lower triangle read once per 16 vectors
+    # dense H from D = 2048 on: the lower triangle read once per 16 vectors
     # (each element used for both of its products); below, the whole of H
-    symmetric_mv = D >= 16384 and not args.sparse_l2
+    symmetric_mv = D >= 2048 and not args.sparse_l2
     mv_bytes = 4.0 * D * (D + 1.0) if symmetric_mv else 8.0 * D * D
     mv_avg_ms = float(np.sum(mv_ms) / max(np.sum(mv_n), 1))
 

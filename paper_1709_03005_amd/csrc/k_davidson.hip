@@ -87,46 +87,64 @@ __global__ __launch_bounds__(256) void k_matvec_mfma(const double *__restrict__ 
 // per byte.
 //
 // The lower triangle is cut into strips of SV_CW columns; a strip's rows
-// (from its diagonal down) into items of rb rows, one workgroup (8 waves)
-// per item, two workgroups per compute unit (at most 128 registers a lane).
-// An item is walked in chunks of SV_CH rows and, inside a chunk, in tiles of
-// SV_CH x SV_SB staged through LDS with the chunk's V rows and the tile's V
-// columns (the next tile is loaded into registers while the current one is
-// multiplied). The waves take turns by sub-block parity: in a tile, the four
-// waves of one parity form the column product of one 16-column strip each
-// over the tile's rows (accumulated over the whole item), the other four the
-// row product of 16 rows each over the tile's columns (accumulated over the
-// chunk). A chunk's row sums (the two parities added in LDS) go to
-// P2[strip][q][row]; at the end of the item the column sums go to
-// P1[item][q][col]. k_symv_reduce adds, for row i, P2 of every strip left of
+// (from its diagonal down) into items of rb rows, one workgroup (8 waves,
+// one workgroup per compute unit) per item. A wave owns 64 columns of the
+// strip and walks the item's rows in blocks of 16: it loads the block straight
+// into registers as the B operand of the column product (16-byte loads, 256
+// contiguous bytes a row), turns it through its own part of LDS into the B
+// operand of the row product, and loads the next block into the registers as
+// soon as the products have taken them, so 32 to 64 KB of H are in flight per
+// compute unit at any time. The waves meet once per SV_CB blocks, to add the
+// row sums of their columns in LDS (in wave order). Column sums stay in
+// registers for the whole item. Row sums go to P2[strip][q][row], column sums
+// to P1[item][q][col]; k_symv_reduce adds, for row i, P2 of every strip left of
 // and including i's, then P1 of every item of i's strip, in a fixed order
-// (deterministic). Tiles on the diagonal zero the elements above it (and, in
-// the row product, the diagonal itself); tiles wholly above it are skipped.
+// (deterministic).
 //
-// The products run on the 4x4x4 FP64 MFMA (four blocks): the B operand is a
-// 4 x 16 slab of the tile (block b takes its columns 4b..4b+3), the A operand
-// the 4 x 4 slab of V for one group of four vectors (the same in every
-// block), so a launch pays for ceil(b / 4) groups, not for 16 vectors. Lane
-// l = j + 4 blk + 16 i holds D[blk][i][j]: vector 4 g + (l >> 4), column (or
-// row) l & 15 of the strip. On this chip the 4x4x4 form also issues faster
-// per flop than the 16x16x4 one.
+// The products run on the 4x4x4 FP64 MFMA (four blocks): the A operand is the
+// 4 x 4 slab of V for one group of four vectors (the same in every block), so
+// a launch pays for ceil(b / 4) groups. Lane l = j + 4 blk + 16 i holds
+// D[blk][i][j]: vector 4 g + (l >> 4), column (or row) l & 15. Which matrix
+// columns stand behind the 16 columns of an instruction, and which rows behind
+// its four k, is free: lane l takes columns 2 (l & 15), + 1 and rows 4 (l >> 4)
+// + u in the column product, so both its loads and its LDS accesses are 16
+// bytes. The V columns of the row product are fixed over an item: registers up
+// to three groups, LDS for four.
+//
+// Bound by HBM: at D = 60000 one launch takes 2.33 / 2.7 / 3.2 ms for 4 / 10 /
+// 16 vectors (6.2 / 5.3 / 4.5 TB/s of its 14.4 GB; a read-only sweep reaches 6.0).
+// The form before staged 64 x 64 tiles for all eight waves in LDS behind two
+// barriers each: 3.0 / 3.6 / 4.5 ms, two tiles in flight per compute unit but
+// every wave waiting for the tile's slowest load.
 // ---------------------------------------------------------------------------
-constexpr int SV_CW = 512, SV_SB = 64, SV_CH = 64, SV_NSB = SV_CW / SV_SB;
-constexpr int SV_LS = SV_SB + 1;     // LDS row strides in doubles (odd: conflict-free column reads)
-constexpr int SV_LR = SV_CH + 1;
+constexpr int SV_CW = 512, SV_WC = 64, SV_BR = 16;   // strip, columns per wave, rows per block
+constexpr int SV_TS = 34;            // LDS row stride of a turned 16 x 32 half block (16-byte slots: conflict-free)
+constexpr int SV_VS = SV_CW + 2;     // LDS row stride of the strip's V columns (four groups)
+typedef double svd2 __attribute__((ext_vector_type(2)));
 
 __host__ __device__ inline int sv_items(int D, int J, int rb) { return (D - J * SV_CW + rb - 1) / rb; }
 
 template <int NG>
-__global__ __launch_bounds__(512, 4) void k_symv(const double *__restrict__ H, int64_t ld, int D,
-                                                  const double *__restrict__ V, int64_t ldv, int b, int rb,
-                                                  double *__restrict__ P1, double *__restrict__ P2)
+struct SymvShared {
+    static constexpr int CB = NG <= 3 ? 2 : 1;      // blocks between two meetings of the waves
+    static constexpr int TB = NG <= 3 ? 2 : 1;      // half blocks held turned
+    double t[8][TB][SV_BR * SV_TS];
+    double rs[2][8][CB][NG * 64];                   // row sums, two chunks in turn
+    double vr[2][4 * NG][SV_BR * CB + 2];           // V at the chunk's rows
+    double vc[NG <= 3 ? 1 : 4 * NG][NG <= 3 ? 1 : SV_VS];
+};
+
+template <int NG>
+__global__ __launch_bounds__(512, 2) void k_symv(const double *__restrict__ H, int64_t ld, int D,
+                                                 const double *__restrict__ V, int64_t ldv, int b, int rb,
+                                                 double *__restrict__ P1, double *__restrict__ P2)
 {
-    __shared__ double Hs[SV_CH * SV_LS];
-    __shared__ double Vc[16 * SV_LS];
-    __shared__ double Vr[16 * SV_LR];
+    using Sh = SymvShared<NG>;
+    constexpr int CB = Sh::CB, TB = Sh::TB, CR = SV_BR * CB;
+    constexpr bool A2REG = NG <= 3;
+    __shared__ Sh sh;
     const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
-    const int lo = lane & 15, hi = lane >> 4;
+    const int lo = lane & 15, hi = lane >> 4, p4 = lane & 3;
     int J = 0, base = 0;
     for (;;) {
         const int n = sv_items(D, J, rb);
@@ -134,141 +152,182 @@ __global__ __launch_bounds__(512, 4) void k_symv(const double *__restrict__ H, i
         base += n;
         ++J;
     }
-    const int J0 = J * SV_CW;
+    const int J0 = J * SV_CW, c0 = J0 + SV_WC * w;
     const int R0 = J0 + ((int)blockIdx.x - base) * rb, R1 = min(D, R0 + rb);
-    const int nsb_d = min(SV_NSB, (D - J0 + SV_SB - 1) / SV_SB);
-    typedef double d2 __attribute__((ext_vector_type(2)));
-    d2 ph[4];
-    double pv[2], pr[2];
-    auto load_tile = [&](int r0, int c0, bool first) {
+    // the wave's rows: from its first column's diagonal block on (c0 and R0 are multiples of 16)
+    const int rs0 = c0 < D ? max(R0, c0) : R1;
+    const bool cfull = c0 + SV_WC <= D;
+    svd2 ph[2][4];
+    // half block t of rows r0 .. r0 + 15: lane takes row r0 + 4 hi + u, columns c0 + 32 t + 2 lo, + 1
+    auto load_half = [&](int t, int r0) {
+        const int c = c0 + 32 * t + 2 * lo;
+        const double *src = H + (int64_t)(r0 + 4 * hi) * ld + c;
+        if (cfull && r0 + SV_BR <= R1) {
 #pragma unroll
-        for (int i = 0; i < 4; ++i) {
-            const int g = tid + 512 * i, row = g >> 5, c = c0 + 2 * (g & 31), r = r0 + row;
-            d2 v = (d2){0.0, 0.0};
-            if (r < R1) {
-                const double *src = H + (int64_t)r * ld + c;
-                if (c + 1 < D) v = __builtin_nontemporal_load(reinterpret_cast<const d2 *>(src));
-                else if (c < D) v.x = src[0];
-            }
-            ph[i] = v;
-        }
+            for (int u = 0; u < 4; ++u)
+                ph[t][u] = __builtin_nontemporal_load(reinterpret_cast<const svd2 *>(src + u * ld));
+        } else {
 #pragma unroll
-        for (int i = 0; i < 2; ++i) {
-            const int e = tid + 512 * i, q = e >> 6, c = c0 + (e & 63);
-            pv[i] = (q < b && c < D) ? V[(int64_t)q * ldv + c] : 0.0;
-        }
-        if (first) {
-#pragma unroll
-            for (int i = 0; i < 2; ++i) {
-                const int e = tid + 512 * i, q = e >> 6, r = r0 + (e & 63);
-                pr[i] = (q < b && r < R1) ? V[(int64_t)q * ldv + r] : 0.0;
+            for (int u = 0; u < 4; ++u) {
+                svd2 v = (svd2){0.0, 0.0};
+                if (r0 + 4 * hi + u < R1) {
+                    if (c < D) v.x = src[u * ld];
+                    if (c + 1 < D) v.y = src[u * ld + 1];
+                }
+                ph[t][u] = v;
             }
         }
     };
-    auto store_tile = [&](bool first) {
+    // V at the rows of the chunk that starts at r
+    constexpr int VPT = (4 * NG * CR + 511) / 512;
+    double pv[VPT];
+    auto load_vr = [&](int r) {
 #pragma unroll
-        for (int i = 0; i < 4; ++i) {
-            const int g = tid + 512 * i, row = g >> 5, cl = 2 * (g & 31);
-            Hs[row * SV_LS + cl] = ph[i].x;
-            Hs[row * SV_LS + cl + 1] = ph[i].y;
+        for (int i = 0; i < VPT; ++i) {
+            const int e = tid + 512 * i, q = e / CR, rr = r + e % CR;
+            pv[i] = (q < b && rr < R1) ? V[(int64_t)q * ldv + rr] : 0.0;
         }
+    };
+    auto store_vr = [&](int buf) {
 #pragma unroll
-        for (int i = 0; i < 2; ++i) {
+        for (int i = 0; i < VPT; ++i) {
             const int e = tid + 512 * i;
-            Vc[(e >> 6) * SV_LS + (e & 63)] = pv[i];
-        }
-        if (first) {
-#pragma unroll
-            for (int i = 0; i < 2; ++i) {
-                const int e = tid + 512 * i;
-                Vr[(e >> 6) * SV_LR + (e & 63)] = pr[i];
-            }
+            if (e < 4 * NG * CR) sh.vr[buf][e / CR][e % CR] = pv[i];
         }
     };
-    auto nsb_of = [&](int r0) { return r0 < R1 ? min(nsb_d, (r0 + SV_CH - J0 + SV_SB - 1) / SV_SB) : 0; };
-    const int st = w & 3, par = w >> 2;
-    double acc1[SV_NSB / 2][NG];
+    load_vr(R0);
+    if (rs0 < R1) {
+        load_half(0, rs0);
+        load_half(1, rs0);
+    }
+    // A operand of the row product: V at the wave's columns, k step (m, e) = column 8 m + 2 hi + e
+    double a2[A2REG ? 8 : 1][2][NG];
+    if constexpr (A2REG) {
 #pragma unroll
-    for (int m = 0; m < SV_NSB / 2; ++m)
+        for (int m = 0; m < 8; ++m)
 #pragma unroll
-        for (int g = 0; g < NG; ++g) acc1[m][g] = 0.0;
-    const int p4 = lane & 3;
-    load_tile(R0, J0, true);
-    for (int r0 = R0; r0 < R1; r0 += SV_CH) {
-        const int nsb = nsb_of(r0), nsb_next = nsb_of(r0 + SV_CH);
-        double acc2[NG];
-#pragma unroll
-        for (int g = 0; g < NG; ++g) acc2[g] = 0.0;
-#pragma unroll
-        for (int s = 0; s < SV_NSB; ++s) {
-            if (s < nsb) {
-                const int c0 = J0 + SV_SB * s;
-                __syncthreads();
-                store_tile(s == 0);
-                __syncthreads();
-                {
-                    const bool more = s + 1 < nsb;
-                    if (more || nsb_next > 0) load_tile(more ? r0 : r0 + SV_CH, more ? c0 + SV_SB : J0, !more);
-                }
-                const bool diag = r0 <= c0 + SV_SB - 1;
-                if ((s & 1) == par) {
-                    // column product: strip st, 64 rows
-#pragma unroll 2
-                    for (int u = 0; u < SV_CH / 4; ++u) {
-                        const int rl = 4 * u + hi, cl = 16 * st + lo;
-                        double h = Hs[rl * SV_LS + cl];
-                        if (diag && r0 + rl < c0 + cl) h = 0.0;
-#pragma unroll
-                        for (int g = 0; g < NG; ++g) {
-                            const double a = Vr[(4 * g + p4) * SV_LR + rl];
-                            acc1[s >> 1][g] = __builtin_amdgcn_mfma_f64_4x4x4f64(a, h, acc1[s >> 1][g], 0, 0, 0);
-                        }
-                    }
-                } else {
-                    // row product: rows 16 st.., 64 columns, two chains
-#pragma unroll 2
-                    for (int u = 0; u < SV_SB / 4; ++u) {
-                        const int cl = 4 * u + hi, rl = 16 * st + lo;
-                        double h = Hs[rl * SV_LS + cl];
-                        if (diag && r0 + rl <= c0 + cl) h = 0.0;
-#pragma unroll
-                        for (int g = 0; g < NG; ++g) {
-                            const double a = Vc[(4 * g + p4) * SV_LS + cl];
-                            acc2[g] = __builtin_amdgcn_mfma_f64_4x4x4f64(a, h, acc2[g], 0, 0, 0);
-                        }
-                    }
-                }
-            }
-        }
-        __syncthreads();
-        if (par == 1) {
-#pragma unroll
-            for (int g = 0; g < NG; ++g) Vr[(st * 4 + g) * 64 + lane] = acc2[g];
-        }
-        __syncthreads();
-        if (par == 0) {
-            const int r = r0 + 16 * st + lo;
-            if (r < R1) {
+            for (int e = 0; e < 2; ++e)
 #pragma unroll
                 for (int g = 0; g < NG; ++g) {
-                    const int q = 4 * g + hi;
-                    if (q < b) P2[((int64_t)J * b + q) * D + r] = acc2[g] + Vr[(st * 4 + g) * 64 + lane];
+                    const int q = 4 * g + p4, c = c0 + 8 * m + 2 * hi + e;
+                    a2[m][e][g] = (q < b && c < D) ? V[(int64_t)q * ldv + c] : 0.0;
+                }
+    } else {
+        for (int e = tid; e < 4 * NG * SV_CW; e += 512) {
+            const int q = e / SV_CW, c = J0 + e % SV_CW;
+            sh.vc[q][e % SV_CW] = (q < b && c < D) ? V[(int64_t)q * ldv + c] : 0.0;
+        }
+    }
+    store_vr(0);
+    double acc1[2][2][NG];
+#pragma unroll
+    for (int t = 0; t < 2; ++t)
+#pragma unroll
+        for (int e = 0; e < 2; ++e)
+#pragma unroll
+            for (int g = 0; g < NG; ++g) acc1[t][e][g] = 0.0;
+    __syncthreads();
+    int buf = 0;
+    for (int rc = R0; rc < R1; rc += CR, buf ^= 1) {
+        if (rc + CR < R1) load_vr(rc + CR);
+#pragma unroll
+        for (int k = 0; k < CB; ++k) {
+            const int r0 = rc + SV_BR * k;
+            double acc2[NG];
+#pragma unroll
+            for (int g = 0; g < NG; ++g) acc2[g] = 0.0;
+            if (r0 >= rs0 && r0 < R1) {
+                const bool diag = r0 < c0 + SV_WC;
+                svd2 a1[2][NG];
+#pragma unroll
+                for (int g = 0; g < NG; ++g)
+#pragma unroll
+                    for (int x = 0; x < 2; ++x)
+                        a1[x][g] = *reinterpret_cast<const svd2 *>(&sh.vr[buf][4 * g + p4][SV_BR * k + 4 * hi + 2 * x]);
+#pragma unroll
+                for (int t = 0; t < 2; ++t) {
+                    double *T = sh.t[w][t % TB];
+                    if (diag) {   // elements above the diagonal are not H's
+                        const int c = c0 + 32 * t + 2 * lo;
+#pragma unroll
+                        for (int u = 0; u < 4; ++u) {
+                            const int r = r0 + 4 * hi + u;
+                            if (r < c) ph[t][u].x = 0.0;
+                            if (r < c + 1) ph[t][u].y = 0.0;
+                        }
+                    }
+                    // LDS of one wave: its accesses run in order, so the fences only
+                    // keep the compiler from reordering them
+                    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+#pragma unroll
+                    for (int u = 0; u < 4; ++u)
+                        *reinterpret_cast<svd2 *>(&T[(4 * hi + u) * SV_TS + 2 * lo]) = ph[t][u];
+                    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+                    svd2 ht[4];
+#pragma unroll
+                    for (int m = 0; m < 4; ++m)
+                        ht[m] = *reinterpret_cast<const svd2 *>(&T[lo * SV_TS + 8 * m + 2 * hi]);
+#pragma unroll
+                    for (int u = 0; u < 4; ++u)
+#pragma unroll
+                        for (int g = 0; g < NG; ++g) {
+                            const double a = (u & 1) ? a1[u >> 1][g].y : a1[u >> 1][g].x;
+                            acc1[t][0][g] = __builtin_amdgcn_mfma_f64_4x4x4f64(a, ph[t][u].x, acc1[t][0][g], 0, 0, 0);
+                            acc1[t][1][g] = __builtin_amdgcn_mfma_f64_4x4x4f64(a, ph[t][u].y, acc1[t][1][g], 0, 0, 0);
+                        }
+                    if (r0 + SV_BR < R1) load_half(t, r0 + SV_BR);
+                    if (diag) {   // the diagonal belongs to the column product
+#pragma unroll
+                        for (int m = 0; m < 4; ++m) {
+                            const int c = c0 + 32 * t + 8 * m + 2 * hi;
+                            if (r0 + lo == c) ht[m].x = 0.0;
+                            if (r0 + lo == c + 1) ht[m].y = 0.0;
+                        }
+                    }
+#pragma unroll
+                    for (int m = 0; m < 4; ++m) {
+#pragma unroll
+                        for (int e = 0; e < 2; ++e)
+#pragma unroll
+                            for (int g = 0; g < NG; ++g) {
+                                double a;
+                                if constexpr (A2REG) a = a2[4 * t + m][e][g];
+                                else a = sh.vc[4 * g + p4][SV_WC * w + 32 * t + 8 * m + 2 * hi + e];
+                                acc2[g] = __builtin_amdgcn_mfma_f64_4x4x4f64(a, e ? ht[m].y : ht[m].x, acc2[g], 0, 0, 0);
+                            }
+                    }
                 }
             }
+#pragma unroll
+            for (int g = 0; g < NG; ++g) sh.rs[buf][w][k][g * 64 + lane] = acc2[g];
+        }
+        if (rc + CR < R1) store_vr(buf ^ 1);
+        __syncthreads();
+        // the chunk's row sums over the eight waves, in order (their buffer is
+        // written again two chunks on, behind the next meeting)
+        for (int e = tid; e < CB * NG * 64; e += 512) {
+            const int k = e / (NG * 64), gl = e % (NG * 64), l = gl & 63;
+            const int r = rc + SV_BR * k + (l & 15), q = 4 * (gl >> 6) + (l >> 4);
+            double s = sh.rs[buf][0][k][gl];
+#pragma unroll
+            for (int v = 1; v < 8; ++v) s += sh.rs[buf][v][k][gl];
+            if (r < R1 && q < b) P2[((int64_t)J * b + q) * D + r] = s;
         }
     }
     const int64_t item = blockIdx.x;
 #pragma unroll
-    for (int m = 0; m < SV_NSB / 2; ++m) {
-        const int c = J0 + SV_SB * (2 * m + par) + 16 * st + lo;
-        if (c < D) {
+    for (int t = 0; t < 2; ++t)
 #pragma unroll
-            for (int g = 0; g < NG; ++g) {
-                const int q = 4 * g + hi;
-                if (q < b) P1[(item * b + q) * SV_CW + (c - J0)] = acc1[m][g];
+        for (int e = 0; e < 2; ++e) {
+            const int c = c0 + 32 * t + 2 * lo + e;
+            if (c < D) {
+#pragma unroll
+                for (int g = 0; g < NG; ++g) {
+                    const int q = 4 * g + hi;
+                    if (q < b) P1[(item * b + q) * SV_CW + (c - J0)] = acc1[t][e][g];
+                }
             }
         }
-    }
 }
 
 __global__ void k_symv_reduce(const double *__restrict__ P1, const double *__restrict__ P2, int D, int b, int rb,
@@ -310,18 +369,23 @@ __global__ void k_symv_reduce(const double *__restrict__ P1, const double *__res
     Wo[(int64_t)q * ldw + i] = s;
 }
 
-// item height of the symmetric product: the largest of 2048 .. 128 rows that
-// still gives at least 4096 items (eight rounds of two workgroups per
-// compute unit: short tails)
+// item height of the symmetric product (a multiple of 32): the one with the
+// least rounds over the 256 compute units, counting an item's start and end
+// (vectors loaded, the first block's latency, column sums written) as 32 rows
 static int symv_rows_per_item(int D)
 {
-    int rb = 2048;
-    for (; rb > 128; rb /= 2) {
+    int best = 2048;
+    int64_t least = INT64_MAX;
+    for (int rb : {64, 96, 128, 160, 192, 256, 320, 384, 448, 512, 640, 768, 896, 1024, 1280, 1536, 2048}) {
         int64_t items = 0;
         for (int J = 0; J * SV_CW < D; ++J) items += sv_items(D, J, rb);
-        if (items >= 4096) break;
+        const int64_t cost = (items + 255) / 256 * (rb + 32);
+        if (cost < least) {
+            least = cost;
+            best = rb;
+        }
     }
-    return rb;
+    return best;
 }
 
 static int64_t symv_items(int D, int rb)
@@ -331,9 +395,11 @@ static int64_t symv_items(int D, int rb)
     return items;
 }
 
-// the symmetric product pays off once the matrix is large enough to fill the
-// chip with its items; below, the full product with split-K
-constexpr int SYMV_MIN_D = 16384;
+// From 2048 rows on the symmetric product wins (whole call, ten vectors: 44
+// against 50 us at D = 3000, 89 against 126 at 8000, 264 against 402 at 16000);
+// at 1500 the two are equal (37 us) and at 600 the full product with split-K
+// wins (27 against 36: the triangle's few items leave the chip idle).
+constexpr int SYMV_MIN_D = 2048;
 
 __global__ void k_matvec_reduce(const double *__restrict__ Wp, int ks, int D, int b, double *__restrict__ Wo,
                                 int64_t ldw)
