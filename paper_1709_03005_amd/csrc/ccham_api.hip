@@ -109,9 +109,9 @@ hipError_t launch_get_block(const double *H, int64_t ldh, int64_t row0, int nrow
 hipError_t launch_l2_csr_count(const double *H, int64_t ld, int Dc, int nl2, int64_t *cnt, hipStream_t st);
 hipError_t launch_l2_csr_fill(const double *H, int64_t ld, int Dc, int nl2, const int64_t *off, int32_t *col,
                               double *val, hipStream_t st);
-hipError_t launch_matvec_l2csr(const double *P, int64_t ldp, const double *R, int64_t ldr, int rc0, int D, int Dc,
-                               const int64_t *off, const int32_t *col, const double *val, const double *V,
-                               int64_t ldv, int b, double *W, int64_t ldw, double *Wp, hipStream_t st);
+hipError_t launch_matvec_l2csr(const double *P, int64_t ldp, int D, int Dc, const int64_t *off, const int32_t *col,
+                               const double *val, const double *V, int64_t ldv, int b, double *W, int64_t ldw,
+                               double *Wp, hipStream_t st);
 // sparse L2 block (classes 2 and 8 as CSR)
 hipError_t launch_l2s_struct(int W, const uint64_t *dets, int n, const int64_t *off, int64_t *cnt, int32_t *col,
                              hipStream_t st);
@@ -1770,8 +1770,8 @@ cch_status cch_apply(cch_ctx *c, const double *V, int64_t ldv, int32_t b, double
     if (e == hipSuccess && !dev)
         e = hipMemcpy2DAsync(dV, 8 * D, V, 8 * ldv, 8 * D, b, hipMemcpyHostToDevice, c->stream);
     if (e == hipSuccess)
-        e = c->sparse ? launch_matvec_l2csr(c->d_H, c->ld, c->d_R, c->ldr, (int)c->Dc, (int)D, (int)c->Dc, c->csr.off,
-                                            c->csr.col, c->csr.val, dV, lv, b, dW, lw, Wp, c->stream)
+        e = c->sparse ? launch_matvec_l2csr(c->d_H, c->ld, (int)D, (int)c->Dc, c->csr.off, c->csr.col, c->csr.val, dV,
+                                            lv, b, dW, lw, Wp, c->stream)
                       : launch_matvec(c->d_H, c->ld, (int)D, dV, lv, b, dW, lw, Wp, c->stream);
     if (e == hipSuccess && !dev)
         e = hipMemcpy2DAsync(W, 8 * ldw, dW, 8 * D, 8 * D, b, hipMemcpyDeviceToHost, c->stream);
@@ -3138,8 +3138,7 @@ cch_status cch_davidson(cch_ctx *c, const cch_dav_opts *o, double *evals, double
         const int m0 = m;
         DCK(hipEventRecord(c->mv0, st));
         if (sparse)
-            DCK(launch_matvec_l2csr(c->d_H, c->ld, c->sparse ? c->d_R : c->d_H, c->sparse ? c->ldr : c->ld,
-                                    c->sparse ? (int)c->Dc : 0, D, (int)c->Dc, c->csr.off, c->csr.col, c->csr.val,
+            DCK(launch_matvec_l2csr(c->d_H, c->ld, D, (int)c->Dc, c->csr.off, c->csr.col, c->csr.val,
                                     b.V + (int64_t)m * ldv, ldv, nb, b.Wv + (int64_t)m * ldv, ldv, b.Wp, st));
         else
             DCK(launch_matvec(c->d_H, c->ld, D, b.V + (int64_t)m * ldv, ldv, nb, b.Wv + (int64_t)m * ldv, ldv, b.Wp,

@@ -384,6 +384,9 @@ hipError_t launch_scan(int mode, int W, const uint64_t *A, int nA, const uint64_
                        hipStream_t st);
 hipError_t launch_exclusive_scan(const int64_t *in, int64_t *out, int n, int64_t *total,
                                  hipStream_t st);
+hipError_t launch_symv(const double *H, int64_t ld, int D, int C, const double *V, int64_t ldv, int b, double *W,
+                       int64_t ldw, double *Wp, hipStream_t st);
+int64_t symv_scratch_doubles(int D, int C);
 hipError_t launch_fill_i64(int64_t *p, int64_t v, int64_t n, hipStream_t st);
 hipError_t launch_fill_f64(double *p, double v, int64_t n, hipStream_t st);
 }  // namespace cch

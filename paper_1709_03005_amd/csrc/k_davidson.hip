@@ -99,7 +99,8 @@ __global__ __launch_bounds__(256) void k_matvec_mfma(const double *__restrict__ 
 // registers for the whole item. Row sums go to P2[strip][q][row], column sums
 // to P1[item][q][col]; k_symv_reduce adds, for row i, P2 of every strip left of
 // and including i's, then P1 of every item of i's strip, in a fixed order
-// (deterministic).
+// (deterministic). With C < D only the columns c < C are multiplied (strips up
+// to C): the continuum part of a matrix whose L2 block is held as CSR.
 //
 // The products run on the 4x4x4 FP64 MFMA (four blocks): the A operand is the
 // 4 x 4 slab of V for one group of four vectors (the same in every block), so
@@ -135,7 +136,7 @@ struct SymvShared {
 };
 
 template <int NG>
-__global__ __launch_bounds__(512, 2) void k_symv(const double *__restrict__ H, int64_t ld, int D,
+__global__ __launch_bounds__(512, 2) void k_symv(const double *__restrict__ H, int64_t ld, int D, int C,
                                                  const double *__restrict__ V, int64_t ldv, int b, int rb,
                                                  double *__restrict__ P1, double *__restrict__ P2)
 {
@@ -155,8 +156,8 @@ __global__ __launch_bounds__(512, 2) void k_symv(const double *__restrict__ H, i
     const int J0 = J * SV_CW, c0 = J0 + SV_WC * w;
     const int R0 = J0 + ((int)blockIdx.x - base) * rb, R1 = min(D, R0 + rb);
     // the wave's rows: from its first column's diagonal block on (c0 and R0 are multiples of 16)
-    const int rs0 = c0 < D ? max(R0, c0) : R1;
-    const bool cfull = c0 + SV_WC <= D;
+    const int rs0 = c0 < C ? max(R0, c0) : R1;
+    const bool cfull = c0 + SV_WC <= C;
     svd2 ph[2][4];
     // half block t of rows r0 .. r0 + 15: lane takes row r0 + 4 hi + u, columns c0 + 32 t + 2 lo, + 1
     auto load_half = [&](int t, int r0) {
@@ -171,8 +172,8 @@ __global__ __launch_bounds__(512, 2) void k_symv(const double *__restrict__ H, i
             for (int u = 0; u < 4; ++u) {
                 svd2 v = (svd2){0.0, 0.0};
                 if (r0 + 4 * hi + u < R1) {
-                    if (c < D) v.x = src[u * ld];
-                    if (c + 1 < D) v.y = src[u * ld + 1];
+                    if (c < C) v.x = src[u * ld];
+                    if (c + 1 < C) v.y = src[u * ld + 1];
                 }
                 ph[t][u] = v;
             }
@@ -210,12 +211,12 @@ __global__ __launch_bounds__(512, 2) void k_symv(const double *__restrict__ H, i
 #pragma unroll
                 for (int g = 0; g < NG; ++g) {
                     const int q = 4 * g + p4, c = c0 + 8 * m + 2 * hi + e;
-                    a2[m][e][g] = (q < b && c < D) ? V[(int64_t)q * ldv + c] : 0.0;
+                    a2[m][e][g] = (q < b && c < C) ? V[(int64_t)q * ldv + c] : 0.0;
                 }
     } else {
         for (int e = tid; e < 4 * NG * SV_CW; e += 512) {
             const int q = e / SV_CW, c = J0 + e % SV_CW;
-            sh.vc[q][e % SV_CW] = (q < b && c < D) ? V[(int64_t)q * ldv + c] : 0.0;
+            sh.vc[q][e % SV_CW] = (q < b && c < C) ? V[(int64_t)q * ldv + c] : 0.0;
         }
     }
     store_vr(0);
@@ -320,7 +321,7 @@ __global__ __launch_bounds__(512, 2) void k_symv(const double *__restrict__ H, i
 #pragma unroll
         for (int e = 0; e < 2; ++e) {
             const int c = c0 + 32 * t + 2 * lo + e;
-            if (c < D) {
+            if (c < C) {
 #pragma unroll
                 for (int g = 0; g < NG; ++g) {
                     const int q = 4 * g + hi;
@@ -330,13 +331,13 @@ __global__ __launch_bounds__(512, 2) void k_symv(const double *__restrict__ H, i
         }
 }
 
-__global__ void k_symv_reduce(const double *__restrict__ P1, const double *__restrict__ P2, int D, int b, int rb,
-                              double *__restrict__ Wo, int64_t ldw)
+__global__ void k_symv_reduce(const double *__restrict__ P1, const double *__restrict__ P2, int D, int C, int b,
+                              int rb, double *__restrict__ Wo, int64_t ldw)
 {
     const int i = blockIdx.x * blockDim.x + threadIdx.x;
     const int q = blockIdx.y;
     if (i >= D || q >= b) return;
-    const int J = i / SV_CW;
+    const int J = min(i, C - 1) / SV_CW;
     int base = 0;
     for (int j = 0; j < J; ++j) base += sv_items(D, j, rb);
     const int n = sv_items(D, J, rb);
@@ -354,6 +355,10 @@ __global__ void k_symv_reduce(const double *__restrict__ P1, const double *__res
         for (int k = 0; k < 8; ++k) s += u[k];
     }
     for (; j <= J; ++j) s += P2[((int64_t)j * b + q) * D + i];
+    if (i >= C) {   // no column of its own
+        Wo[(int64_t)q * ldw + i] = s;
+        return;
+    }
     const double *p1 = P1 + ((int64_t)base * b + q) * SV_CW + (i - J * SV_CW);
     const int64_t st1 = (int64_t)b * SV_CW;
     int t = 0;
@@ -372,14 +377,19 @@ __global__ void k_symv_reduce(const double *__restrict__ P1, const double *__res
 // item height of the symmetric product (a multiple of 32): the one with the
 // least rounds over the 256 compute units, counting an item's start and end
 // (vectors loaded, the first block's latency, column sums written) as 32 rows
-static int symv_rows_per_item(int D)
+static int64_t symv_items(int D, int C, int rb)
+{
+    int64_t items = 0;
+    for (int J = 0; J * SV_CW < C; ++J) items += sv_items(D, J, rb);
+    return items;
+}
+
+static int symv_rows_per_item(int D, int C)
 {
     int best = 2048;
     int64_t least = INT64_MAX;
     for (int rb : {64, 96, 128, 160, 192, 256, 320, 384, 448, 512, 640, 768, 896, 1024, 1280, 1536, 2048}) {
-        int64_t items = 0;
-        for (int J = 0; J * SV_CW < D; ++J) items += sv_items(D, J, rb);
-        const int64_t cost = (items + 255) / 256 * (rb + 32);
+        const int64_t cost = (symv_items(D, C, rb) + 255) / 256 * (rb + 32);
         if (cost < least) {
             least = cost;
             best = rb;
@@ -388,11 +398,36 @@ static int symv_rows_per_item(int D)
     return best;
 }
 
-static int64_t symv_items(int D, int rb)
+// doubles of scratch of launch_symv: column sums per item, row sums per strip
+// (rounded up to whole 128-byte lines)
+int64_t symv_scratch_doubles(int D, int C)
 {
-    int64_t items = 0;
-    for (int J = 0; J * SV_CW < D; ++J) items += sv_items(D, J, rb);
-    return items;
+    if (C <= 0) return 0;
+    const int64_t nstrip = (C + SV_CW - 1) / SV_CW;
+    return (symv_items(D, C, symv_rows_per_item(D, C)) * SV_CW + nstrip * D) * 16;
+}
+
+// W = (the lower triangle's columns c < C, mirrored) V; C = D: W = H V
+hipError_t launch_symv(const double *H, int64_t ld, int D, int C, const double *V, int64_t ldv, int b, double *W,
+                       int64_t ldw, double *Wp, hipStream_t st)
+{
+    const int rb = symv_rows_per_item(D, C);
+    const int64_t items = symv_items(D, C, rb);
+    double *P1 = Wp, *P2 = Wp + items * 16 * SV_CW;
+    const dim3 g((unsigned)items), bl(512);
+    for (int q0 = 0; q0 < b; q0 += 16) {
+        const int bb = std::min(16, b - q0);
+        const double *Vq = V + (int64_t)q0 * ldv;
+        switch ((bb + 3) / 4) {   // groups of four vectors on the 4x4x4 FP64 MFMA
+        case 1: hipLaunchKernelGGL(k_symv<1>, g, bl, 0, st, H, ld, D, C, Vq, ldv, bb, rb, P1, P2); break;
+        case 2: hipLaunchKernelGGL(k_symv<2>, g, bl, 0, st, H, ld, D, C, Vq, ldv, bb, rb, P1, P2); break;
+        case 3: hipLaunchKernelGGL(k_symv<3>, g, bl, 0, st, H, ld, D, C, Vq, ldv, bb, rb, P1, P2); break;
+        default: hipLaunchKernelGGL(k_symv<4>, g, bl, 0, st, H, ld, D, C, Vq, ldv, bb, rb, P1, P2); break;
+        }
+        hipLaunchKernelGGL(k_symv_reduce, dim3((D + 255) / 256, bb), dim3(256), 0, st, P1, P2, D, C, bb, rb,
+                           W + (int64_t)q0 * ldw, ldw);
+    }
+    return hipGetLastError();
 }
 
 // From 2048 rows on the symmetric product wins (whole call, ten vectors: 44
@@ -425,26 +460,7 @@ hipError_t launch_matvec(const double *H, int64_t ld, int D, const double *V, in
                          int64_t ldw, double *Wp, hipStream_t st)
 {
     if (D <= 0 || b <= 0) return hipSuccess;
-    if (D >= SYMV_MIN_D) {
-        const int rb = symv_rows_per_item(D);
-        const int64_t items = symv_items(D, rb);
-        const int nstrip = (D + SV_CW - 1) / SV_CW;
-        double *P1 = Wp, *P2 = Wp + items * 16 * SV_CW;
-        (void)nstrip;
-        for (int q0 = 0; q0 < b; q0 += 16) {
-            const int bb = std::min(16, b - q0);
-            const double *Vq = V + (int64_t)q0 * ldv;
-            switch ((bb + 3) / 4) {   // groups of four vectors on the 4x4x4 FP64 MFMA
-            case 1: hipLaunchKernelGGL(k_symv<1>, dim3((unsigned)items), dim3(512), 0, st, H, ld, D, Vq, ldv, bb, rb, P1, P2); break;
-            case 2: hipLaunchKernelGGL(k_symv<2>, dim3((unsigned)items), dim3(512), 0, st, H, ld, D, Vq, ldv, bb, rb, P1, P2); break;
-            case 3: hipLaunchKernelGGL(k_symv<3>, dim3((unsigned)items), dim3(512), 0, st, H, ld, D, Vq, ldv, bb, rb, P1, P2); break;
-            default: hipLaunchKernelGGL(k_symv<4>, dim3((unsigned)items), dim3(512), 0, st, H, ld, D, Vq, ldv, bb, rb, P1, P2); break;
-            }
-            hipLaunchKernelGGL(k_symv_reduce, dim3((D + 255) / 256, bb), dim3(256), 0, st, P1, P2, D, bb, rb,
-                               W + (int64_t)q0 * ldw, ldw);
-        }
-        return hipGetLastError();
-    }
+    if (D >= SYMV_MIN_D) return launch_symv(H, ld, D, D, V, ldv, b, W, ldw, Wp, st);
     const int ks = matvec_splits(D);
     int rps = (D + ks - 1) / ks;
     rps = (rps + 4 * MVM_UNROLL - 1) / (4 * MVM_UNROLL) * (4 * MVM_UNROLL);
@@ -464,9 +480,7 @@ int64_t matvec_scratch_doubles(int D)
 {
     const int64_t full = (int64_t)16 * D * (matvec_splits(D) + 1);
     if (D < SYMV_MIN_D) return full;
-    const int rb = symv_rows_per_item(D);
-    const int64_t nstrip = (D + SV_CW - 1) / SV_CW;
-    return std::max(full, symv_items(D, rb) * 16 * SV_CW + nstrip * 16 * (int64_t)D);
+    return std::max(full, symv_scratch_doubles(D, D));
 }
 
 // ---------------------------------------------------------------------------

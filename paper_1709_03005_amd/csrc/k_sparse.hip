@@ -1,12 +1,11 @@
 // A mat-vec for L2-heavy matrices (Sec. 2.2: the off-diagonal pure-L2 class
 // is the sparse one): W = H V with H split at Dc, the first L2 row, into
-//   [ Hcc  Hcl ]   dense continuum rows and columns, read from the dense
-//   [ Hlc  Hll ]   matrix; Hll (classes 2 and 8) as CSR,
-// so that a block of b <= 16 vectors costs the continuum panels plus the
-// non-zeros of the L2 block instead of the whole dense matrix.
-//   W[:, c <  Dc] = sum over all rows of H[row][c] V[row]       (panel A)
-//   W[:, c >= Dc] = sum over rows < Dc of H[row][c] V[row]      (panel B)
-//                 + sum over the non-zeros of L2 row c - Dc     (CSR part)
+//   [ Hcc  Hcl ]   dense continuum rows and columns: the lower-triangle product
+//   [ Hlc  Hll ]   of k_davidson.hip over the columns < Dc, which reads Hcc's
+//                  lower triangle and Hlc once for both of their products;
+//                  Hll (classes 2 and 8) as CSR,
+// so that a block of b <= 16 vectors costs one read of the continuum columns
+// plus the non-zeros of the L2 block instead of the whole dense matrix.
 // Every sum has a fixed order, so the result does not depend on timing.
 #include <algorithm>
 
@@ -79,184 +78,133 @@ hipError_t launch_l2_csr_fill(const double *H, int64_t ld, int Dc, int nl2, cons
     return hipGetLastError();
 }
 
-// ---------------------------------------------------------------------------
-// Panel mat-vec on FP64 MFMA 16x16x4: Wp[split][q][c - c0] = sum over the
-// rows of the split (inside [r0, r1)) of H[row][c] V[q][row], c in [c0, c1).
-// One wave owns 64 columns (four 16-column strips sharing the V fragment);
-// the B operand is 4 rows x 16 columns of H, the A operand 16 vectors x the
-// same 4 rows (zero rows for q >= b).
-// ---------------------------------------------------------------------------
-typedef double px4 __attribute__((ext_vector_type(4)));
-constexpr int PN_U = 8;   // 4-row MFMA steps per register block
-
-__global__ __launch_bounds__(256) void k_panel_mfma(const double *__restrict__ H, int64_t ld, int hc0, int r0, int r1,
-                                                    int c0, int c1, const double *__restrict__ V, int64_t ldv, int b,
-                                                    int rps, double *__restrict__ Wp)
-{
-    const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
-    const int cb0 = c0 + (blockIdx.x * 4 + wv) * 64;
-    const int q = lane & 15, kq = lane >> 4;
-    const int rb = r0 + blockIdx.y * rps, re = min(r1, rb + rps);
-    const bool qok = q < b;
-    const double *vrow = V + (int64_t)(qok ? q : 0) * ldv;
-    const double *hcol[4];
-    bool colok[4];
-#pragma unroll
-    for (int t = 0; t < 4; ++t) {
-        const int c = cb0 + 16 * t + q;
-        colok[t] = c < c1;
-        hcol[t] = H + (colok[t] ? c - hc0 : 0);   // column c of the matrix is column c - hc0 of H
-    }
-    px4 acc[4];
-#pragma unroll
-    for (int t = 0; t < 4; ++t) acc[t] = (px4){0.0, 0.0, 0.0, 0.0};
-    for (int k0 = rb; k0 < re; k0 += 4 * PN_U) {
-        double bv[PN_U][4], av[PN_U];
-#pragma unroll
-        for (int u = 0; u < PN_U; ++u) {
-            const int row = k0 + 4 * u + kq;
-            const bool ok = row < re;
-            av[u] = (ok && qok) ? vrow[row] : 0.0;
-#pragma unroll
-            for (int t = 0; t < 4; ++t)
-                bv[u][t] = (ok && colok[t]) ? __builtin_nontemporal_load(hcol[t] + (int64_t)row * ld) : 0.0;
-        }
-#pragma unroll
-        for (int u = 0; u < PN_U; ++u)
-#pragma unroll
-            for (int t = 0; t < 4; ++t)
-                acc[t] = __builtin_amdgcn_mfma_f64_16x16x4f64(av[u], bv[u][t], acc[t], 0, 0, 0);
-    }
-    // item v of lane l: vector l/16 + 4 v, column l % 16 of the strip
-    const int nc = c1 - c0;
-#pragma unroll
-    for (int t = 0; t < 4; ++t) {
-        const int c = cb0 + 16 * t + q;
-        if (colok[t]) {
-#pragma unroll
-            for (int v = 0; v < 4; ++v) {
-                const int qq = kq + 4 * v;
-                if (qq < b) Wp[((int64_t)blockIdx.y * 16 + qq) * nc + (c - c0)] = acc[t][v];
-            }
-        }
-    }
-}
-
-// W[q][c] = sum of the splits in order, c in [c0, c1)
-__global__ void k_panel_reduce(const double *__restrict__ Wp, int ns, int c0, int c1, int b, double *__restrict__ W,
-                               int64_t ldw)
-{
-    const int i = blockIdx.x * blockDim.x + threadIdx.x, qq = blockIdx.y;
-    const int nc = c1 - c0;
-    if (i >= nc || qq >= b) return;
-    double s = 0.0;
-    for (int k = 0; k < ns; ++k) s += Wp[((int64_t)k * 16 + qq) * nc + i];
-    W[(int64_t)qq * ldw + c0 + i] = s;
-}
-
-// VT[i][q] = V[q][i] (0 for q >= b), i < D: the vectors of one row in one
-// aligned 128-byte line for the gathers of the sparse product
-__global__ void k_vt16(const double *__restrict__ V, int64_t ldv, int D, int b, double *__restrict__ VT)
+// VT[i][q] = V[q][i] (0 for q >= b), i < n, q < 2 LPR: the vectors of one row
+// side by side for the gathers of the sparse product
+template <int LPR>
+__global__ __launch_bounds__(256) void k_vt(const double *__restrict__ V, int64_t ldv, int n, int b,
+                                            double *__restrict__ VT)
 {
     const int i = blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= D) return;
+    if (i >= n) return;
 #pragma unroll
-    for (int q = 0; q < 16; ++q) VT[(int64_t)i * 16 + q] = q < b ? V[(int64_t)q * ldv + i] : 0.0;
+    for (int q = 0; q < 2 * LPR; ++q) VT[(int64_t)i * (2 * LPR) + q] = q < b ? V[(int64_t)q * ldv + i] : 0.0;
 }
 
-// W[q][Dc + r] (+)= sum over the non-zeros (j, v) of L2 row r of v VT[Dc + j][q]
-// (added to panel B's sums when there are continuum rows, else assigned):
-// one wave per row, lanes over the non-zeros, a fixed-order tree across lanes
+// W[q][Dc + r] (+)= sum over the non-zeros (j, v) of L2 row r of v VT[j][q]
+// (added to the continuum part's sums when there are continuum rows, else
+// assigned): one wave per row. LPR lanes take one non-zero, two vectors (16
+// bytes) each, so an instruction gathers 64 / LPR records of 16 LPR bytes that
+// lie in one cache line each; the wave's next 64 columns and values are loaded
+// side by side and handed to the groups by lane permutes. The groups' sums are
+// added across lanes in a fixed order. Bound by the gathers' requests to L2, one
+// 128-byte line per non-zero whatever the record's length: 88 million non-zeros
+// (50000 functions) take 1.04 / 0.89 / 0.87 ms for records of 128 / 64 / 32
+// bytes. A lane per non-zero, with the 16 vectors in its registers, took 1.95
+// ms: each of its eight loads touched 64 different lines.
+typedef double px2 __attribute__((ext_vector_type(2)));
+
+template <int LPR>
 __global__ __launch_bounds__(256) void k_l2_spmm(const int64_t *__restrict__ off, const int32_t *__restrict__ col,
                                                  const double *__restrict__ val, int Dc, int nl2,
                                                  const double *__restrict__ VT, int b, double *__restrict__ W,
                                                  int64_t ldw, int accumulate)
 {
-    const int lane = threadIdx.x & 63;
+    constexpr int NPS = 64 / LPR;   // non-zeros per instruction
+    const int lane = threadIdx.x & 63, g = lane / LPR, q2 = lane % LPR;
     const int r = blockIdx.x * 4 + (threadIdx.x >> 6);
     if (r >= nl2) return;   // the whole wave
-    double acc[16];
+    const px2 *vl = reinterpret_cast<const px2 *>(VT) + q2;
+    const int64_t e1 = off[r + 1];
+    px2 acc = (px2){0.0, 0.0};
+    int64_t e0 = off[r];
+    int cn = 0;
+    double vn = 0.0;
+    if (e0 + lane < e1) {
+        cn = col[e0 + lane];
+        vn = val[e0 + lane];
+    }
+    for (; e0 < e1; e0 += 64) {
+        const int c = cn;
+        const double v = vn;
+        cn = 0;
+        vn = 0.0;
+        if (e0 + 64 + lane < e1) {
+            cn = col[e0 + 64 + lane];
+            vn = val[e0 + 64 + lane];
+        }
+        const int left = (int)min<int64_t>(64, e1 - e0);
+        constexpr int U = LPR < 8 ? LPR : 8;   // gathers in flight
 #pragma unroll
-    for (int q = 0; q < 16; ++q) acc[q] = 0.0;
-    const px4 *vl = reinterpret_cast<const px4 *>(VT + (int64_t)Dc * 16);
-    for (int64_t e = off[r] + lane; e < off[r + 1]; e += 64) {
-        const double v = val[e];
-        const px4 *x = vl + (int64_t)col[e] * 4;
+        for (int s0 = 0; s0 < LPR; s0 += U) {
+            if (s0 * NPS < left) {   // past the end of the row: column 0 with the value 0
+                px2 x[U];
+                double a[U];
 #pragma unroll
-        for (int u = 0; u < 4; ++u) {
-            const px4 y = x[u];
+                for (int u = 0; u < U; ++u) {
+                    const int from = (s0 + u) * NPS + g;
+                    x[u] = vl[(int64_t)__shfl(c, from, 64) * LPR];
+                    a[u] = __shfl(v, from, 64);
+                }
 #pragma unroll
-            for (int t = 0; t < 4; ++t) acc[4 * u + t] = fma(v, y[t], acc[4 * u + t]);
+                for (int u = 0; u < U; ++u) {
+                    acc.x = fma(a[u], x[u].x, acc.x);
+                    acc.y = fma(a[u], x[u].y, acc.y);
+                }
+            }
         }
     }
 #pragma unroll
-    for (int q = 0; q < 16; ++q) {
-        double s = acc[q];
-        for (int o = 32; o > 0; o >>= 1) s += __shfl_xor(s, o, 64);
-        acc[q] = s;
+    for (int o = 32; o >= LPR; o >>= 1) {
+        acc.x += __shfl_xor(acc.x, o, 64);
+        acc.y += __shfl_xor(acc.y, o, 64);
     }
-    if (lane == 0)
+    if (lane < LPR) {
 #pragma unroll
-        for (int q = 0; q < 16; ++q)
-            if (q < b) W[(int64_t)q * ldw + Dc + r] = accumulate ? W[(int64_t)q * ldw + Dc + r] + acc[q] : acc[q];
+        for (int t = 0; t < 2; ++t) {
+            const int q = 2 * q2 + t;
+            const double s = t ? acc.y : acc.x;
+            if (q < b) W[(int64_t)q * ldw + Dc + r] = accumulate ? W[(int64_t)q * ldw + Dc + r] + s : s;
+        }
+    }
 }
 
-// splits of a panel: enough waves to cover HBM latency (about 4096), at most 64
-static int panel_splits(int rows, int cols)
+template <int LPR>
+static void spmm_launch(const int64_t *off, const int32_t *col, const double *val, int Dc, int nl2, const double *V,
+                        int64_t ldv, int b, double *W, int64_t ldw, double *VT, hipStream_t st)
 {
-    const int waves = std::max(1, (cols + 63) / 64);
-    int ks = (4096 + waves - 1) / waves;
-    ks = std::max(1, std::min(ks, 64));
-    return std::min(ks, std::max(1, (rows + 4 * PN_U - 1) / (4 * PN_U)));
+    hipLaunchKernelGGL((k_vt<LPR>), dim3((nl2 + 255) / 256), dim3(256), 0, st, V + Dc, ldv, nl2, b, VT);
+    hipLaunchKernelGGL((k_l2_spmm<LPR>), dim3((nl2 + 3) / 4), dim3(256), 0, st, off, col, val, Dc, nl2, VT, b, W, ldw,
+                       Dc > 0 ? 1 : 0);
 }
 
 // doubles of scratch that launch_matvec_l2csr needs
 int64_t l2csr_scratch(int D, int Dc)
 {
-    const int64_t a = (int64_t)panel_splits(D, Dc) * 16 * std::max(Dc, 1);
-    const int64_t b = (int64_t)panel_splits(Dc, D - Dc) * 16 * std::max(D - Dc, 1);
-    return a + b + (int64_t)16 * D;   // panel partials, then the transposed block
+    // the continuum part's sums (a multiple of 16 doubles), then the transposed block
+    return symv_scratch_doubles(D, Dc) + (int64_t)16 * D;
 }
 
-static hipError_t panel(const double *H, int64_t ld, int hc0, int r0, int r1, int c0, int c1, const double *V,
-                        int64_t ldv, int b, double *W, int64_t ldw, double *Wp, hipStream_t st)
-{
-    if (r1 <= r0 || c1 <= c0) return hipSuccess;
-    const int ns = panel_splits(r1 - r0, c1 - c0);
-    int rps = (r1 - r0 + ns - 1) / ns;
-    rps = (rps + 4 * PN_U - 1) / (4 * PN_U) * (4 * PN_U);
-    const int nsu = (r1 - r0 + rps - 1) / rps;
-    hipLaunchKernelGGL(k_panel_mfma, dim3((c1 - c0 + 255) / 256, nsu), dim3(256), 0, st, H, ld, hc0, r0, r1, c0, c1, V,
-                       ldv, b, rps, Wp);
-    hipLaunchKernelGGL(k_panel_reduce, dim3((c1 - c0 + 255) / 256, b), dim3(256), 0, st, Wp, nsu, c0, c1, b, W, ldw);
-    return hipGetLastError();
-}
-
-// P: rows 0..D-1, columns < Dc (leading dimension ldp); R: rows < Dc, the
-// matrix's column c >= Dc at R column c - rc0 (leading dimension ldr). The
-// dense matrix passes itself for both (rc0 = 0); a sparse-L2 matrix its two
-// panels (rc0 = Dc).
-hipError_t launch_matvec_l2csr(const double *P, int64_t ldp, const double *R, int64_t ldr, int rc0, int D, int Dc,
-                               const int64_t *off, const int32_t *col, const double *val, const double *V,
-                               int64_t ldv, int b, double *W, int64_t ldw, double *Wp, hipStream_t st)
+// P: rows 0..D-1, columns < Dc (leading dimension ldp)
+hipError_t launch_matvec_l2csr(const double *P, int64_t ldp, int D, int Dc, const int64_t *off, const int32_t *col,
+                               const double *val, const double *V, int64_t ldv, int b, double *W, int64_t ldw,
+                               double *Wp, hipStream_t st)
 {
     if (D <= 0 || b <= 0) return hipSuccess;
     if (Dc < 0 || Dc > D) return hipErrorInvalidValue;
     const int nl2 = D - Dc;
-    double *WpA = Wp, *WpB = Wp + (int64_t)panel_splits(D, Dc) * 16 * std::max(Dc, 1);
-    double *VT = WpB + (int64_t)panel_splits(Dc, D - Dc) * 16 * std::max(D - Dc, 1);   // 128-byte aligned
-    for (int q0 = 0; q0 < b; q0 += 16) {
+    double *VT = Wp + symv_scratch_doubles(D, Dc);   // 128-byte aligned
+    if (Dc > 0) {
+        const hipError_t e = launch_symv(P, ldp, D, Dc, V, ldv, b, W, ldw, Wp, st);
+        if (e != hipSuccess) return e;
+    }
+    for (int q0 = 0; q0 < b && nl2 > 0; q0 += 16) {
         const int bb = std::min(16, b - q0);
         const double *Vq = V + (int64_t)q0 * ldv;
         double *Wq = W + (int64_t)q0 * ldw;
-        hipError_t e = panel(P, ldp, 0, 0, D, 0, Dc, Vq, ldv, bb, Wq, ldw, WpA, st);   // columns < Dc, all rows
-        if (e == hipSuccess) e = panel(R, ldr, rc0, 0, Dc, Dc, D, Vq, ldv, bb, Wq, ldw, WpB, st);   // rows < Dc
-        if (e != hipSuccess) return e;
-        if (nl2 > 0) {
-            hipLaunchKernelGGL(k_vt16, dim3((D + 255) / 256), dim3(256), 0, st, Vq, ldv, D, bb, VT);
-            hipLaunchKernelGGL(k_l2_spmm, dim3((nl2 + 3) / 4), dim3(256), 0, st, off, col, val, Dc, nl2, VT, bb, Wq,
-                               ldw, Dc > 0 ? 1 : 0);
-        }
+        // the shortest record that holds the vectors: 32, 64 or 128 bytes
+        if (bb <= 4) spmm_launch<2>(off, col, val, Dc, nl2, Vq, ldv, bb, Wq, ldw, VT, st);
+        else if (bb <= 8) spmm_launch<4>(off, col, val, Dc, nl2, Vq, ldv, bb, Wq, ldw, VT, st);
+        else spmm_launch<8>(off, col, val, Dc, nl2, Vq, ldv, bb, Wq, ldw, VT, st);
     }
     return hipGetLastError();
 }
