@@ -140,7 +140,7 @@ hipError_t launch_cluster_mgs(double *Z, int64_t ldz, const int32_t *desc, int n
                               const double *e, const double *w, double *S, int64_t lds, double piv, hipStream_t st);
 hipError_t launch_copy_reflectors(const double *A, int64_t lda, int n, int j0, int nb, double *Vb, hipStream_t st);
 hipError_t launch_larft(const double *G, const double *tau, int nb, double *T, double *X, hipStream_t st);
-hipError_t launch_symmetrize(double *W, int64_t ld, int n, hipStream_t st);
+hipError_t launch_symmetrize(double *W, int64_t ld, int n, unsigned long long *amax, hipStream_t st);
 hipError_t launch_transpose_sq(const double *Z, int64_t ldz, int n, double *out, int64_t ldo, hipStream_t st);
 int64_t l2csr_scratch(int D, int Dc);
 hipError_t launch_matvec(const double *H, int64_t ld, int D, const double *V, int64_t ldv, int b, double *W,
@@ -2006,9 +2006,10 @@ cch_status cch_eig_all(cch_ctx *c, const double *A, int64_t lda, int32_t n, doub
     // split-K partials of the back-transformation's long products
     const int64_t p_cap = std::max<int64_t>((int64_t)16 * NB * n, (int64_t)64 * NB * NB);
     const bool want_v = V != nullptr;
-    double *pan = nullptr;   // the reduction's panel buffers PV, PW and the products z
+    double *pan = nullptr;   // the reduction's panel buffers
+    TrdPanel tp{};
     bool ok = al((void **)&W, 8 * (size_t)n * ld) && al((void **)&vec, 8 * (size_t)10 * n + 64) &&
-              al((void **)&w_d, 8 * (size_t)n) && al((void **)&pan, 8 * trd_panel_doubles(n, ld));
+              al((void **)&w_d, 8 * (size_t)n) && al((void **)&pan, 8 * trd_panel_layout(n, ld, nullptr, &tp));
     if (ok && want_v)
         // S: the twisted-factorisation scratch, then two NB x n products of the back-transformation
         ok = al((void **)&Z, 8 * (size_t)n * ld) &&
@@ -2044,20 +2045,14 @@ cch_status cch_eig_all(cch_ctx *c, const double *A, int64_t lda, int32_t n, doub
     else
         EGK(hipMemcpy2DAsync(W, 8 * ld, A, 8 * lda, 8 * (size_t)n, n,
                              dev ? hipMemcpyDeviceToDevice : hipMemcpyHostToDevice, st));
-    EGK(launch_symmetrize(W, ld, n, st));
+    // vec: x, y, d, e, tau, the second x (from an even offset), two free lengths,
+    // e2 and the eigenvalues; the word behind them
+    TrdVec tv{vec, vec + (5 * (int64_t)n + 1) / 2 * 2, vec + n, vec + 2 * (int64_t)n, vec + 3 * (int64_t)n,
+              vec + 4 * (int64_t)n, (unsigned long long *)(vec + 10 * (int64_t)n)};
+    EGK(launch_symmetrize(W, ld, n, tv.amax, st));
     EGK(hipEventRecord(e0, st));
-    TrdVec tv{vec, vec + n, vec + 2 * (int64_t)n, vec + 3 * (int64_t)n, vec + 4 * (int64_t)n};
     double *e2v = vec + 8 * (int64_t)n;
-    TrdPanel tp;
-    tp.PVt = pan;
-    tp.PV = pan + (int64_t)2 * TRD_NB * n;
-    tp.PW = tp.PV + (int64_t)2 * TRD_NB * ld;
-    tp.ldp = ld;
-    tp.part1 = tp.PV + (int64_t)4 * TRD_NB * ld;
-    tp.part2 = tp.part1 + (int64_t)((n + TRD_CR - 1) / TRD_CR) * TRD_PS;
-    tp.rowp = tp.part2 + (n + 3) / 4;
-    tp.colp = tp.rowp + (int64_t)trd_tiles(n) * n;
-    tp.z = tp.colp + (int64_t)trd_tiles(n) * n;
+    (void)trd_panel_layout(n, ld, pan, &tp);
     for (int j0 = 0; j0 < n; j0 += TRD_NB) EGK(launch_trd_panel(W, ld, n, j0, std::min(TRD_NB, n - j0), tv, tp, st));
     EGK(hipEventRecord(e1, st));
     // Gershgorin interval, pivot floor and the split of T into unreduced

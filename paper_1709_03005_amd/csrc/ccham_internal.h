@@ -148,6 +148,71 @@ __device__ __forceinline__ int excite_cont_l2(const uint64_t *D, const uint64_t 
 }
 
 // ---------------------------------------------------------------------------
+// short scalar chains and wave reductions
+// ---------------------------------------------------------------------------
+// 1/q from the hardware estimate and two Newton-Raphson corrections
+// r <- r + r (1 - q r), each squaring the relative error: a short dependent
+// chain for the recurrences below, within about one ulp of the quotient
+__device__ __forceinline__ double rr_recip(double q)
+{
+    double r = __builtin_amdgcn_rcp(q);
+    double e = fma(-q, r, 1.0);
+    r = fma(r, e, r);
+    e = fma(-q, r, 1.0);
+    return fma(r, e, r);
+}
+
+// 1/sqrt(x), x > 0, from the hardware estimate and two Newton-Raphson
+// corrections r <- r + r (1 - x r^2) / 2
+__device__ __forceinline__ double rr_rsqrt(double x)
+{
+    double r = __builtin_amdgcn_rsq(x);
+    double e = fma(-x * r, r, 1.0);
+    r = fma(0.5 * r, e, r);
+    e = fma(-x * r, r, 1.0);
+    return fma(0.5 * r, e, r);
+}
+
+// Cross-lane helpers on doubles as two 32-bit halves: DPP moves (row shifts
+// and row broadcasts) and readlane with a wave-uniform lane index.
+struct RrI2 {
+    int x, y;
+};
+
+template <int CTRL, int ROW_MASK, int BANK_MASK>
+__device__ __forceinline__ double rr_dpp(double v)
+{
+    RrI2 a = __builtin_bit_cast(RrI2, v);
+    a.x = __builtin_amdgcn_update_dpp(0, a.x, CTRL, ROW_MASK, BANK_MASK, true);
+    a.y = __builtin_amdgcn_update_dpp(0, a.y, CTRL, ROW_MASK, BANK_MASK, true);
+    return __builtin_bit_cast(double, a);
+}
+
+__device__ __forceinline__ double rr_rl(double v, int lane)
+{
+    RrI2 a = __builtin_bit_cast(RrI2, v);
+    a.x = __builtin_amdgcn_readlane(a.x, lane);
+    a.y = __builtin_amdgcn_readlane(a.y, lane);
+    return __builtin_bit_cast(double, a);
+}
+
+// sum over the 64 lanes, returned to every lane: partial sums of 4 within
+// each row of 16 (row_shr 1..3), of 8 and 16 (row_shr 4, 8 on the upper
+// banks), then rows 0+1 and 2+3 (row_bcast15) and all four (row_bcast31)
+// collect in lane 63. Fixed order, so every wave gets the same bits.
+__device__ __forceinline__ double rr_wsum(double v)
+{
+    double s = v + rr_dpp<0x111, 0xf, 0xf>(v);
+    s += rr_dpp<0x112, 0xf, 0xf>(v);
+    s += rr_dpp<0x113, 0xf, 0xf>(v);
+    s += rr_dpp<0x114, 0xf, 0xe>(s);
+    s += rr_dpp<0x118, 0xf, 0xc>(s);
+    s += rr_dpp<0x142, 0xa, 0xf>(s);
+    s += rr_dpp<0x143, 0xc, 0xf>(s);
+    return rr_rl(s, 63);
+}
+
+// ---------------------------------------------------------------------------
 // integrals over target orbitals
 // ---------------------------------------------------------------------------
 struct TgtInts {
@@ -284,43 +349,64 @@ struct GammaList {
     const int32_t *k1, *k2;
 };
 
-// work vectors of the Householder tridiagonalisation (length n each): wp =
-// the current column after the panel's corrections, p = tau_j A_j v_j; the
-// diagonal d, the off-diagonal e and the reflector scalars tau of T
+// work vectors of the Householder tridiagonalisation (length n each): x = the
+// current column after the panel's corrections times a power of two (two
+// buffers, by column parity), y = A_0 x as the row pass leaves it; the diagonal
+// d, the off-diagonal e and the reflector scalars tau of T; amax: the largest
+// |entry| of the matrix (its bits), whose exponent is that power of two's.
+// x0, x1: 16-byte aligned
 struct TrdVec {
-    double *wp, *p;
+    double *x0, *x1, *y;
     double *d, *e, *tau;
+    unsigned long long *amax;
 };
 
 // columns per panel of the blocked tridiagonalisation
 constexpr int TRD_NB = 32;
 // rows per workgroup of the column kernel, and the stride of its partial sums
-constexpr int TRD_CR = 256, TRD_PS = 2 * TRD_NB + 8;
+constexpr int TRD_CR = 128, TRD_PS = 2 * TRD_NB + 8;
 constexpr int TRD_PT = 2 * TRD_NB;   // doubles per row of PVt
 // trailing blocks of at least TRD_TILE_MIN rows are multiplied from their
 // lower triangle in TRD_TT x TRD_TT tiles (below that the row pass reads
 // whole rows)
 constexpr int TRD_TT = 128, TRD_TILE_MIN = 3072;
-constexpr int TRD_SR = 32;   // rows per workgroup of the tiled pass's row sums
 struct TrdPanel {
     double *PV, *PW;   // 2 TRD_NB rows each, ldp doubles a row (the panel update's operands)
     int64_t ldp;
     double *PVt;       // PV by matrix row: PVt[r][d] = PV[d][r], 2 TRD_NB doubles a row
-    double *part1;     // column kernel: TRD_PS partial sums per workgroup
-    double *part2;     // row pass: one partial sum per workgroup
-    double *rowp, *colp;   // tiled pass: [tile column][n] row sums, [tile row][n] column sums
-    double *z;             // tiled pass: z[d] of its reflector (2 TRD_NB)
+    double *part1;     // column kernel: TRD_PS partial sums per workgroup (two buffers, by column parity)
+    int64_t part1_len; // doubles of one of them
+    double *part2;     // product: one partial sum of x . A_0 x per workgroup
+    double *rowp, *colp;   // tiled product: [tile column][n] row sums, [tile row][n] column sums
 };
 
-// tiles per side of the tiled pass over m trailing rows
+// first row of the tiles of the trailing block that starts at row r
+__host__ __device__ inline int trd_base(int r) { return r & ~15; }
+// tiles per side over m rows
 __host__ __device__ inline int trd_tiles(int m) { return (m + TRD_TT - 1) / TRD_TT; }
 
-// doubles of the panel buffers for dimension n with rows of ldp doubles
-inline size_t trd_panel_doubles(int n, int64_t ldp)
+// the panel buffers for dimension n with rows of ldp doubles, carved from one
+// allocation (base = nullptr: only the size in doubles is wanted)
+inline size_t trd_panel_layout(int n, int64_t ldp, double *base, TrdPanel *P)
 {
     const size_t T = (size_t)trd_tiles(n);
-    return (size_t)2 * TRD_NB * n + (size_t)4 * TRD_NB * ldp + (size_t)((n + TRD_CR - 1) / TRD_CR) * TRD_PS +
-           (size_t)(n + 3) / 4 + 2 * T * (size_t)n + 2 * TRD_NB;
+    size_t at = 0;
+    auto take = [&](size_t len) {
+        double *p = base ? base + at : nullptr;
+        at += (len + 3) / 4 * 4;
+        return p;
+    };
+    P->ldp = ldp;
+    P->PVt = take((size_t)TRD_PT * n);
+    P->PV = take((size_t)2 * TRD_NB * ldp);
+    P->PW = take((size_t)2 * TRD_NB * ldp);
+    P->part1_len = (int64_t)((n + TRD_CR - 1) / TRD_CR) * TRD_PS;
+    P->part1 = take(2 * (size_t)P->part1_len);
+    const size_t tiles = T * (T + 1) / 2, rows = (size_t)(n + 3) / 4;
+    P->part2 = take(tiles > rows ? tiles : rows);
+    P->rowp = take(T * (size_t)n);
+    P->colp = take(T * (size_t)n);
+    return at;
 }
 
 // a matrix whose L2 block (classes 2 and 8) is held as CSR: P[r][c] for

@@ -3,12 +3,11 @@
 // diagonaliser is used then):
 //   1. Householder tridiagonalisation Q^T A Q = T, one reflector per column,
 //      blocked in panels of TRD_NB columns with lazy updates: per column
-//      the corrected column with its partial sums, then the product of the
-//      trailing block with the reflector (the HBM-bound part: from the lower
-//      triangle in tiles, plus a kernel that adds the tiles' partial sums,
-//      while the block has at least TRD_TILE_MIN rows; by whole rows below
-//      that), and one rank-2 TRD_NB FP64 MFMA update of the trailing block
-//      per panel.
+//      one kernel for the reflector, its w and the next corrected column, and
+//      the product of the trailing block with that column (the HBM-bound part:
+//      from the lower triangle in tiles while the block has at least
+//      TRD_TILE_MIN rows, by whole rows below that), and one rank-2 TRD_NB
+//      FP64 MFMA update of the trailing block per panel.
 //   2. Eigenvalues of T by multisection on Sturm counts, 8 lanes each.
 //   3. Eigenvectors of T by twisted factorisations, one thread each, with
 //      modified Gram-Schmidt (and inverse iteration for vectors that
@@ -184,16 +183,22 @@ hipError_t launch_eig_gemm(int M, int N, int K, double alpha, const double *A, i
 //    w_k (v_k . v_j)); one rank-2 TRD_NB product (FP64 MFMA) updates the
 //    trailing block at the end of the panel. w_j = p - (tau_j / 2)(p . v_j) v_j
 //    with p = tau_j A_j v_j.
-// Per column a column kernel and a pass, each spread over the rows; a
-// workgroup never waits for another one. The column kernel adds the pass's
-// partial sums of p . v (the scalar of the previous w), finishes that w,
-// corrects column j and stores, per workgroup, the partial sums of sigma =
-// |x|^2 over the part to annihilate and of the panel's vectors times it.
-// Every workgroup of the pass adds those partial sums in workgroup order (so
-// all get the same reflector) and forms v_j = x / (alpha - beta) as it reads
-// it; the pass leaves p and the partial sums of p . v_j. For trailing blocks
-// of at least TRD_TILE_MIN rows the pass reads only the lower triangle, in
-// tiles, and a second kernel adds each row's tile sums.
+// Two launches per column, each spread over the rows; a workgroup never waits
+// for another one. The product of column j is taken with the corrected column
+// x itself, before its reflector is known: with v_j = scale x below row j + 1
+// and v_j[j + 1] = 1, A_0 v_j = A_0[:, j + 1] + scale A_0[:, j + 2:] x, so the
+// product kernels read nothing but A_0 and x and also leave partial sums of
+// x . A_0 x. The column kernel of column j + 1 then has everything: from the
+// partial sums of its predecessor (sigma = |x|^2 over the part to annihilate,
+// and the panel's vectors times x) every workgroup forms the reflector j and z
+// alike, p . v = tau (v . A_0 v - 2 sum_k (v_k . v)(w_k . v)) follows without a
+// further pass over the rows (x . A_0 x is cubic in the matrix: x is stored
+// times the power of two that brings the largest entry to [1, 2), which leaves v
+// and tau as they are, so that the range of the entries stays that of their
+// squares), and the workgroup finishes v_j, p and w_j for its
+// rows, corrects column j + 1 and stores the partial sums for the next one.
+// For trailing blocks of at least TRD_TILE_MIN rows the product reads only the
+// lower triangle, in tiles, whose row and column sums the column kernel adds.
 // panel buffers (ldp doubles a row): PV rows 2k, 2k + 1 = v_k, w_k; PW rows
 // 2k, 2k + 1 = w_k, v_k (the update is A -= PV^T PW over 2 nb rows); PVt the
 // same values by matrix row (PVt[r][d] = PV[d][r]: a row's panel entries are
@@ -202,350 +207,362 @@ hipError_t launch_eig_gemm(int M, int N, int K, double alpha, const double *A, i
 // read.
 // ---------------------------------------------------------------------------
 
+// sum over the 64 lanes of a whole wave (DPP: a chain of a shuffle per step
+// through LDS took a third of a microsecond)
+__device__ __forceinline__ double wave_sum(double x) { return rr_wsum(x); }
+
 __device__ __forceinline__ double blk_sum(double x, double *red)
 {
-    // sum over the 256 threads of a workgroup (red: 256 doubles of LDS)
-    for (int o = 32; o > 0; o >>= 1) x += __shfl_xor(x, o, 64);
+    // sum over the 256 threads of a workgroup (red: 4 doubles of LDS)
+    x = wave_sum(x);
     __syncthreads();
     if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = x;
     __syncthreads();
     return red[0] + red[1] + red[2] + red[3];
 }
 
-// x[b stride] summed for b = b0, b0 + step, ... < b1 in that order; the
-// loads go out in batches of 8
-__device__ __forceinline__ double ordered_sum(const double *__restrict__ x, int64_t stride, int b0, int b1, int step)
+__device__ __forceinline__ double quad_sum(double x)   // over lanes 4 a .. 4 a + 3, to each of them
 {
-    double y = 0.0;
-    for (int b = b0; b < b1; b += 8 * step) {
-        double v[8];
-#pragma unroll
-        for (int u = 0; u < 8; ++u) {
-            const int c = b + u * step;
-            v[u] = c < b1 ? x[(int64_t)c * stride] : 0.0;
-        }
-#pragma unroll
-        for (int u = 0; u < 8; ++u) y += v[u];
-    }
-    return y;
+    x += rr_dpp<0xb1, 0xf, 0xf>(x);          // lanes 1, 0, 3, 2
+    return x + rr_dpp<0x4e, 0xf, 0xf>(x);    // lanes 2, 3, 0, 1
 }
 
-// rows j + TRD_CR blockIdx.x + threadIdx.x. With i > 0, w of the panel's
-// reflector i - 1 (column j - 1) into PV row 2i - 1 and PW row 2i - 2 for
-// rows >= j. With col: column j of the current matrix into wp, d[j], and the
-// partial sums [sigma, PV[0] . x, ..., PV[2i - 1] . x] of this workgroup's
-// rows >= j + 2 into part1.
-__global__ __launch_bounds__(256) void k_trd_col(const double *__restrict__ A, int64_t lda, int n, int j, int i,
-                                                 int col, TrdVec V, TrdPanel P)
+// The column kernel of column c, panel index i (so many reflectors of the panel
+// before it), rows c + TRD_CR blockIdx.x + (0 .. TRD_CR - 1), four threads a
+// row. fin: finish reflector j = c - 1 (panel index i - 1): v_j, w_j into the
+// panel buffers and column j of A, e[j], tau[j]. col: column c of the current
+// matrix into x, d[c], and this workgroup's partial sums [sigma, PV[0] . x, ...,
+// PV[2i - 1] . x] over its rows >= c + 2 into part1. TILED: the product left the
+// sums of T tile rows (counted from row trd_base(c)) instead of y; rowc: column
+// c may be read as row c. g2: partial sums in part2.
+// Bound by latency: one level of loads (the row's panel pairs, 16 bytes each,
+// eight per thread; its tile sums; the partial sums), four barriers, and the
+// fetch of its own code, which every launch pays anew (unrolled further, with
+// a branch around each load, it was 10.7 KB long and half a microsecond
+// slower; the tiled form, with more to add up, gains from the longer batches).
+// Measured: 5.8 us at n = 301, 8.5 us with tiles (n from 8000 to 3072), where
+// three launches a column took 8.0 and 9.1 us for this part, and 4.8 us more
+// for the tile sums; a column with its product 8.7 instead of 12.3 us at
+// n = 301 and 30 instead of 42 at n = 8000 to 3072
+constexpr int TRD_CT = 4 * TRD_CR;         // threads of the column kernel
+constexpr int TRD_CW = TRD_CT / 64;
+constexpr int TRD_LS = 2 * TRD_NB + 8;     // LDS row stride of the panel rows (two rows apart: other banks)
+static_assert(TRD_CR * 64 / TRD_CT == 16, "rows per wave");
+
+template <bool TILED>
+__global__ __launch_bounds__(TRD_CT) void k_trd_col(double *__restrict__ A, int64_t lda, int n, int c, int i, int fin,
+                                                    int col, int T, int rowc, int g2, TrdVec V, TrdPanel P)
 {
-    __shared__ double vw[2 * TRD_NB];   // v_k[j], w_k[j], k < i
-    __shared__ double xs[TRD_CR], ws[TRD_CR];
-    __shared__ double red[256];
-    const int t = threadIdx.x;
-    const int r0 = j + (int)blockIdx.x * TRD_CR, r = r0 + t;
+    typedef double d2 __attribute__((ext_vector_type(2)));
+    __shared__ double S[TRD_CR * TRD_LS];      // the workgroup's panel rows
+    __shared__ double red[TRD_CW][2 * TRD_NB + 1];
+    __shared__ double p1[4][128];              // partial sums of sigma, PV[q] . x_j (four groups)
+    __shared__ double pv1[2 * TRD_NB], zs[2 * TRD_NB];   // PV at row c; z
+    __shared__ double xs[TRD_CR];
+    __shared__ double r2[TRD_CW], sc;
+    const int t = threadIdx.x, lane = t & 63, wv = t >> 6;
+    const int rl = t >> 2, qd = t & 3;
+    const int r = c + (int)blockIdx.x * TRD_CR + rl, rr = min(r, n - 1);
     const bool in = r < n;
-    double wr = 0.0;
-    if (i > 0) {
-        // p of reflector j - 1 (rows >= j) and the scalar -(tau / 2)(p . v) of its w
-        const double *vq = P.PVt + (2 * i - 2);   // v of reflector i - 1, stride 2 TRD_NB
-        // (the row pass leaves one partial sum of p . v per 4 rows, the sum
-        // kernel of the tiled pass one per TRD_SR rows)
-        const int g2 = n - j < TRD_TILE_MIN ? (n - j + 3) / 4 : (n - j + TRD_SR - 1) / TRD_SR;
-        const double al = -0.5 * V.tau[j - 1] * blk_sum(ordered_sum(P.part2, 1, t, g2, 256), red);
-        const double pr = in ? V.p[r] : 0.0, pj = t == 0 ? V.p[j] : 0.0;
+    const int j = c - 1, np = fin ? i - 1 : i;   // pairs of the panel already stored
+    // the power of two that x is stored with, and its reciprocal (normal numbers both)
+    const uint64_t ex = min(max((uint64_t)(*V.amax >> 52), (uint64_t)1), (uint64_t)2045);
+    const double fx = __builtin_bit_cast(double, (2046 - ex) << 52), fxi = __builtin_bit_cast(double, ex << 52);
+    const double *xj = (j & 1) ? V.x1 : V.x0;
+    // item b <= rt of a row's tile sums is rowp[b][r], item b > rt colp[b - 1][r]
+    auto tile_sum = [&](int b, int rt, int row) -> double {
+        const double *p = b <= rt ? P.rowp : P.colp - n;
+        return p[(int64_t)b * n + row];
+    };
+    // ---- this row ----
+    d2 pr[TRD_NB / 4];
+#pragma unroll
+    for (int u = 0; u < TRD_NB / 4; ++u) {
+        pr[u] = (d2){0.0, 0.0};
+        if (!TILED || 4 * u < np) pr[u] = *reinterpret_cast<const d2 *>(P.PVt + (int64_t)rr * TRD_PT + 2 * (qd + 4 * u));
+    }
+    const double a1 = rowc ? A[(int64_t)c * lda + rr] : A[(int64_t)rr * lda + c];
+    double x = a1, vr = 0.0, wr = 0.0;
+    if (fin) {
+        // ---- the reflector, alike in every workgroup ----
+        const double alpha = xj[c], a1c = A[(int64_t)c * lda + c], xr = xj[rr];
+        double yr = TILED || c + 1 >= n ? 0.0 : V.y[rr], yj = TILED || c + 1 >= n ? 0.0 : V.y[c];
+        const double pvr = t < 2 * TRD_NB ? P.PVt[(int64_t)c * TRD_PT + t] : 0.0;
+        double s1 = 0.0, s2 = 0.0;
+        const int g1 = (n - j + TRD_CR - 1) / TRD_CR, rt = (rr - trd_base(c)) / TRD_TT;
+        constexpr int B1 = TILED ? 16 : 8;   // 64 (32) workgroups a batch
+        if (!TILED || (t & 127) < 2 * np + 1) {   // what lies past them is not used
+            const double *pin = P.part1 + (j & 1) * P.part1_len + min(t & 127, TRD_PS - 1);
+            for (int b = t >> 7; b < g1; b += 4 * B1) {
+                double u[B1];
+#pragma unroll
+                for (int k = 0; k < B1; ++k) u[k] = pin[(int64_t)min(b + 4 * k, g1 - 1) * TRD_PS];
+#pragma unroll
+                for (int k = 0; k < B1; ++k) s1 += b + 4 * k < g1 ? u[k] : 0.0;
+            }
+        }
+        for (int b = t; b < g2; b += 4 * TRD_CT) {
+            double u[4];
+#pragma unroll
+            for (int k = 0; k < 4; ++k) u[k] = P.part2[min(b + k * TRD_CT, g2 - 1)];
+#pragma unroll
+            for (int k = 0; k < 4; ++k) s2 += b + k * TRD_CT < g2 ? u[k] : 0.0;
+        }
+        if (TILED) {
+            for (int b0 = qd; b0 <= T; b0 += 64) {
+                double u[16];
+#pragma unroll
+                for (int k = 0; k < 16; ++k) u[k] = b0 + 4 * k <= T ? tile_sum(b0 + 4 * k, rt, rr) : 0.0;
+#pragma unroll
+                for (int k = 0; k < 16; ++k) yr += u[k];
+            }
+            if (wv == TRD_CW - 1) {   // the wave that adds row c's tile sums
+                for (int b = lane; b <= T; b += 64) yj += tile_sum(b, 0, c);
+                yj = wave_sum(yj);
+                if (lane == 0) sc = yj;
+            }
+        }
+        p1[t >> 7][t & 127] = s1;
+        s2 = wave_sum(s2);
+        if (lane == 0) r2[wv] = s2;
+        if (t < 2 * TRD_NB) pv1[t] = t < 2 * np ? pvr : 0.0;
+        __syncthreads();
+        if (TILED) yj = sc;
+        auto sum1 = [&](int q) { return (p1[0][q] + p1[1][q]) + (p1[2][q] + p1[3][q]); };
+        const double sig = sum1(0);
+        double xax = 0.0;
+#pragma unroll
+        for (int k = 0; k < TRD_CW; ++k) xax += r2[k];
+        // (the root and the two quotients to about one ulp: short chains)
+        double tau = 0.0, beta = alpha, scale = 0.0;
+        if (sig > 0.0) {
+            const double h = fma(alpha, alpha, sig);
+            beta = -copysign(h * rr_rsqrt(h), alpha);
+            tau = fma(-alpha, rr_recip(beta), 1.0);   // (beta - alpha) / beta
+            scale = rr_recip(alpha - beta);
+        }
+        if (t < 2 * TRD_NB) zs[t] = t < 2 * np ? pvr + scale * sum1(t + 1) : 0.0;
+        if (blockIdx.x == 0 && t == 0) {
+            V.e[j] = beta * fxi;
+            V.tau[j] = tau;
+        }
+        __syncthreads();
+        // sum_k z_v z_w and the correction of p at row c, in every wave alike (lane = pair k)
+        const int kl = lane & (TRD_NB - 1);
+        const double zv = lane < TRD_NB ? zs[2 * kl] : 0.0, zw = zs[2 * kl + 1];
+        const double zz = wave_sum(zv * zw);
+        const double cj = wave_sum(lane < TRD_NB ? pv1[2 * kl] * zw + pv1[2 * kl + 1] * zv : 0.0);
+        const double vav = a1c + scale * (2.0 * yj + scale * xax);
+        const double al = -0.5 * tau * (tau * (vav - 2.0 * zz));   // -(tau / 2) (p . v)
+        const double wc = tau * (a1c + scale * yj - cj) + al;      // w_j at row c, where v_j = 1
+        double cr = 0.0, cx = 0.0;
+#pragma unroll
+        for (int u = 0; u < TRD_NB / 4; ++u) {
+            const int k = qd + 4 * u;
+            if (k >= np) pr[u] = (d2){0.0, 0.0};
+            cr += pr[u].x * zs[2 * k + 1] + pr[u].y * zs[2 * k];
+            cx += pr[u].x * pv1[2 * k + 1] + pr[u].y * pv1[2 * k];
+        }
+        cr = quad_sum(cr);
+        cx = quad_sum(cx);
+        if (TILED) yr = quad_sum(yr);
+        vr = r == c ? 1.0 : scale * xr;
+        wr = tau * (a1 + scale * yr - cr) + al * vr;
+        x = a1 - cx - (vr * wc + wr);
         if (in) {
-            wr = pr + al * vq[(int64_t)r * TRD_PT];
-            P.PV[(int64_t)(2 * i - 1) * P.ldp + r] = wr;
-            P.PW[(int64_t)(2 * i - 2) * P.ldp + r] = wr;
-            P.PVt[(int64_t)r * TRD_PT + 2 * i - 1] = wr;
+            // PV rows v, w; PW rows w, v: lane qd of the row writes one each
+            double *o = ((qd & 2) ? P.PW : P.PV) + (int64_t)(2 * np + (qd & 1)) * P.ldp;
+            o[r] = qd == 0 || qd == 3 ? vr : wr;
+            if (qd == 0) *reinterpret_cast<d2 *>(P.PVt + (int64_t)r * TRD_PT + 2 * np) = (d2){vr, wr};
+            if (qd == 1) A[(int64_t)r * lda + j] = vr;   // kept for the back-transformation
         }
-        if (col && t == 0) {
-            vw[2 * i - 2] = vq[(int64_t)j * TRD_PT];
-            vw[2 * i - 1] = pj + al * vq[(int64_t)j * TRD_PT];
-        }
+        if (qd == 0) *reinterpret_cast<d2 *>(&S[rl * TRD_LS + 2 * np]) = (d2){vr, wr};
     }
     if (!col) return;
-    for (int e = t; e < 2 * i - 2; e += 256) vw[e] = P.PVt[(int64_t)j * TRD_PT + e];
-    __syncthreads();
-    double x = 0.0;
-    if (in) {
-        x = A[(int64_t)r * lda + j];
-#pragma unroll 4
-        for (int k = 0; k < i - 1; ++k)
-            x -= P.PVt[(int64_t)r * TRD_PT + 2 * k] * vw[2 * k + 1] + P.PVt[(int64_t)r * TRD_PT + 2 * k + 1] * vw[2 * k];
-        if (i > 0) x -= P.PVt[(int64_t)r * TRD_PT + 2 * i - 2] * vw[2 * i - 1] + wr * vw[2 * i - 2];
-        V.wp[r] = x;
-        if (r == j) V.d[j] = x;
+    if (in && qd == 0) {
+        ((c & 1) ? V.x1 : V.x0)[r] = x * fx;
+        if (r == c) V.d[c] = x;
     }
-    if (j >= n - 1) return;   // the last column has no reflector (one workgroup)
-    const bool below = in && r >= j + 2;
-    xs[t] = below ? x : 0.0;
-    ws[t] = below ? wr : 0.0;
-    const double sig = blk_sum(below ? x * x : 0.0, red);   // (its barriers publish xs, ws)
-    // PV[q] . x over this workgroup's rows: thread (q = t mod 64, g = t / 64)
-    // over the 64 rows 64 g .. 64 g + 63, then the four groups in order
-    const int q = t & 63, g = t >> 6;
-    double y = 0.0;
-    if (q < 2 * i - 1) {
-        // (the 64 lanes read 64 consecutive entries of one row of PVt)
-        const double *pr = P.PVt + (int64_t)(r0 + 64 * g) * TRD_PT + q;
-        const int lo = max(0, j + 2 - r0 - 64 * g), hi = min(64, n - r0 - 64 * g);
-#pragma unroll 16
-        for (int k = lo; k < hi; ++k) y += pr[(int64_t)k * TRD_PT] * xs[64 * g + k];
-    } else if (q == 2 * i - 1) {   // w_{i-1}, kept in ws
-#pragma unroll 16
-        for (int k = 0; k < 64; ++k) y += ws[64 * g + k] * xs[64 * g + k];
+    if (c >= n - 1) return;   // the last column has no reflector (one workgroup)
+    // ---- partial sums over this workgroup's rows >= c + 2 ----
+    const double xb = in && r >= c + 2 ? x * fx : 0.0;
+#pragma unroll
+    for (int u = 0; u < TRD_NB / 4; ++u)
+        if (qd + 4 * u < np) *reinterpret_cast<d2 *>(&S[rl * TRD_LS + 2 * (qd + 4 * u)]) = pr[u];
+    if (qd == 0) xs[rl] = xb;
+    const double sg = wave_sum(qd == 0 ? xb * xb : 0.0);
+    __syncthreads();
+    double y = 0.0;   // PV[lane] . x over the 16 rows of this wave's share
+    if (lane < 2 * i)
+#pragma unroll 8
+        for (int k = 16 * wv; k < 16 * wv + 16; ++k) y += S[k * TRD_LS + lane] * xs[k];
+    red[wv][1 + lane] = y;
+    if (lane == 0) red[wv][0] = sg;
+    __syncthreads();
+    if (t < 2 * i + 1) {
+        double s = 0.0;
+#pragma unroll
+        for (int k = 0; k < TRD_CW; ++k) s += red[k][t];
+        P.part1[(c & 1) * P.part1_len + (int64_t)blockIdx.x * TRD_PS + t] = s;
     }
-    __syncthreads();
-    red[t] = y;
-    __syncthreads();
-    double *out = P.part1 + (int64_t)blockIdx.x * TRD_PS;
-    if (t == 0) out[0] = sig;
-    if (t < 2 * i) out[1 + t] = red[t] + red[64 + t] + red[128 + t] + red[192 + t];
 }
 
-// rows r of the trailing block (j, n), one wave per row, lanes over the
-// columns, fixed-order reductions: v_j[r] into column j of A and the panel
-// buffers, p[r] = tau_j (A_0[r][j+1:] . v_j - sum_k (v_k[r] (w_k . v_j) +
-// w_k[r] (v_k . v_j))), and this workgroup's partial sum of p . v_j into
-// part2. The row is streamed first as A_0[r][j+1] + scale (A_0[r][j+2:] . x)
-// (v_j = 1 at row j + 1 and scale x below), while every workgroup forms the
-// reflector of column j from the column kernel's partial sums (workgroup 0
-// stores e[j] and tau[j]) and z.
-__global__ __launch_bounds__(256) void k_trd_pass(double *__restrict__ A, int64_t lda, int n, int j, int i, TrdVec V,
+// y[r] = A_0[r][j + 2:] . x for the rows r >= j + 1, one wave per row, lanes
+// over the columns, fixed-order reduction; this workgroup's partial sum of
+// x . y over its rows >= j + 2 into part2
+__global__ __launch_bounds__(256) void k_trd_pass(const double *__restrict__ A, int64_t lda, int n, int j, TrdVec V,
                                                   TrdPanel P)
 {
-    __shared__ double red[TRD_PS];
-    __shared__ double zs[2 * TRD_NB];
-    __shared__ double sc[2];
+    __shared__ double red[4];
     const int t = threadIdx.x, lane = t & 63, wv = t >> 6;
-    const int g1 = (n - j + TRD_CR - 1) / TRD_CR;
     const int r = j + 1 + (int)blockIdx.x * 4 + wv;
-    const bool in = r < n;
-    // loads first: the partial sums, z's panel entries at row j + 1, alpha,
-    // this row's panel entries and x at this row
-    double ps = 0.0;
-    if (t < 2 * i + 1) {
-        double u[32];
-#pragma unroll
-        for (int b = 0; b < 32; ++b) u[b] = b < g1 ? P.part1[(int64_t)b * TRD_PS + t] : 0.0;
-#pragma unroll
-        for (int b = 0; b < 32; ++b) ps += u[b];
-        for (int b = 32; b < g1; ++b) ps += P.part1[(int64_t)b * TRD_PS + t];
-    }
-    const double pz = t < 2 * i ? P.PVt[(int64_t)(j + 1) * TRD_PT + t] : 0.0;
-    const double alpha = t == 0 ? V.wp[j + 1] : 0.0;
-    double k0 = 0.0, k1 = 0.0, xr = 0.0;
-    if (in && lane < i) {
-        k0 = P.PVt[(int64_t)r * TRD_PT + 2 * lane];
-        k1 = P.PVt[(int64_t)r * TRD_PT + 2 * lane + 1];
-    }
-    if (in) xr = V.wp[r];
-    // the row: A_0[r][j+1] and A_0[r][j+2:] . x
-    double s1 = 0.0, s2 = 0.0;
-    if (in) {
+    const double *x = (j & 1) ? V.x1 : V.x0;
+    double s = 0.0, xr = 0.0;
+    if (r < n) {
+        // whole lines: columns from the 16-aligned one at or before j + 2 on,
+        // two per lane (the rows are padded to 32 columns)
+        typedef double d2 __attribute__((ext_vector_type(2)));
         const double *row = A + (int64_t)r * lda;
-        if (lane == 0) s1 = row[j + 1];
-#pragma unroll 8
-        for (int c = j + 2 + lane; c < n; c += 64) s2 += row[c] * V.wp[c];
-        for (int o = 32; o > 0; o >>= 1) s2 += __shfl_xor(s2, o, 64);
-    }
-    if (t < 2 * i + 1) red[t] = ps;
-    __syncthreads();
-    if (t == 0) {
-        const double sig = red[0];
-        double tau = 0.0, beta = alpha, scale = 0.0;
-        if (sig > 0.0) {
-            beta = -copysign(sqrt(alpha * alpha + sig), alpha);
-            tau = (beta - alpha) / beta;
-            scale = 1.0 / (alpha - beta);
+        if (r >= j + 2) xr = x[r];
+        for (int c0 = ((j + 2) & ~15) + 2 * lane; c0 < n; c0 += 8 * 128) {
+            d2 a[8], b[8];
+#pragma unroll
+            for (int u = 0; u < 8; ++u) {
+                const int c = c0 + 128 * u;
+                a[u] = b[u] = (d2){0.0, 0.0};
+                if (c < n) {
+                    a[u] = *reinterpret_cast<const d2 *>(row + c);
+                    b[u] = *reinterpret_cast<const d2 *>(x + c);
+                }
+            }
+#pragma unroll
+            for (int u = 0; u < 8; ++u) {
+                const int c = c0 + 128 * u;
+                s += c >= j + 2 && c < n ? a[u].x * b[u].x : 0.0;
+                s += c + 1 >= j + 2 && c + 1 < n ? a[u].y * b[u].y : 0.0;
+            }
         }
-        sc[0] = scale;
-        sc[1] = tau;
-        if (blockIdx.x == 0) {
-            V.e[j] = beta;
-            V.tau[j] = tau;
-        }
+        s = wave_sum(s);
+        if (lane == 0) V.y[r] = s;
     }
+    if (lane == 0) red[wv] = xr * s;
     __syncthreads();
-    const double scale = sc[0], tau = sc[1];
-    // z[d] = PV[d] . v_j with v_j[j + 1] = 1 and v_j = scale x below
-    if (t < 2 * i) zs[t] = pz + scale * red[t + 1];
-    __syncthreads();
-    double pv = 0.0;
-    if (in) {
-        double q = lane < i ? k0 * zs[2 * lane + 1] + k1 * zs[2 * lane] : 0.0;
-        for (int o = 32; o > 0; o >>= 1) q += __shfl_xor(q, o, 64);
-        const double sr = __shfl(s1, 0, 64) + scale * s2;
-        const double vr = r == j + 1 ? 1.0 : xr * scale;
-        const double p = tau * (sr - q);
-        if (lane == 0) {
-            V.p[r] = p;
-            A[(int64_t)r * lda + j] = vr;   // kept for the back-transformation
-            P.PV[(int64_t)(2 * i) * P.ldp + r] = vr;
-            P.PW[(int64_t)(2 * i + 1) * P.ldp + r] = vr;
-            P.PVt[(int64_t)r * TRD_PT + 2 * i] = vr;
-        }
-        pv = p * vr;
-    }
-    __syncthreads();
-    if (lane == 0) red[wv] = pv;
-    __syncthreads();
-    if (t == 0) P.part2[blockIdx.x] = red[0] + red[1] + red[2] + red[3];
+    if (t == 0) P.part2[blockIdx.x] = (red[0] + red[1]) + (red[2] + red[3]);
 }
 
-// the product of the trailing block (j, n) with v_j from its lower triangle
-// only, for trailing blocks of at least TRD_TILE_MIN rows: one workgroup per
-// TRD_TT x TRD_TT tile (rt, ct), ct <= rt, of the block (tile rows and columns
-// counted from row j + 1). A tile stores the row sums of its rows (columns up
-// to the diagonal) into rowp[ct], the column sums of its columns (rows below
-// the diagonal) into colp[rt]; k_trd_tile_sum adds them per row in a fixed
-// order. As in the row
-// pass every workgroup first forms the reflector of column j; workgroup 0
-// stores e[j], tau[j] and z, and the tiles of column 0 store v_j for
-// their rows.
-__global__ __launch_bounds__(256, 4) void k_trd_tiles(double *__restrict__ A, int64_t lda, int n, int j, int i, TrdVec V,
-                                                   TrdPanel P)
+// the product of the trailing block (j, n) with x (its entry j + 1 taken as 0)
+// from its lower triangle only, for trailing blocks of at least TRD_TILE_MIN
+// rows: one workgroup per TRD_TT x TRD_TT tile (rt, ct), ct <= rt, tile rows and
+// columns counted from row trd_base(j + 1), the last multiple of 16 before the
+// block (so that every row of a tile is eight whole cache lines; what it holds
+// before column j + 1 meets zeros of x). A tile stores the row sums of its rows
+// (columns up to the diagonal) into rowp[ct], the column sums of its columns
+// (rows below the diagonal) into colp[rt], and its share of x . A_0 x into
+// part2; the column kernel adds them in a fixed order. Bound by memory: 22 us on
+// average from 8000 to 3072 trailing rows (6.0 TB/s, what a plain read of that
+// size reaches), 27.6 us with 8-byte loads of rows that began anywhere in a
+// line. One group of loads in flight a wave: a second one spills at four waves a
+// SIMD.
+struct TrdTileShared {
+    double vr[TRD_TT], vc[TRD_TT], rsum[TRD_TT];
+    double cs[4][TRD_TT];
+    double red[2];
+};
+
+template <bool DIAG>
+__device__ __forceinline__ void trd_tile(const double *__restrict__ A, int64_t lda, int n, int R0, int C0, double ve,
+                                         TrdTileShared &sh)
 {
-    __shared__ double red[TRD_PS];
-    __shared__ double sc[2];
-    __shared__ double vr[TRD_TT], vc[TRD_TT], rsum[TRD_TT];
-    __shared__ double cs[4][TRD_TT];
-    const int t = threadIdx.x, lane = t & 63, wv = t >> 6;
-    const int b = blockIdx.x;
-    int rt = (int)((sqrt(8.0 * b + 1.0) - 1.0) * 0.5);
-    while ((rt + 1) * (rt + 2) / 2 <= b) ++rt;
-    while (rt * (rt + 1) / 2 > b) --rt;
-    const int ct = b - rt * (rt + 1) / 2;
-    const int R0 = j + 1 + TRD_TT * rt, C0 = j + 1 + TRD_TT * ct;
-    // the reflector of column j (as in the row pass)
-    const int g1 = (n - j + TRD_CR - 1) / TRD_CR;
-    const double ps = t < 2 * i + 1 ? ordered_sum(P.part1 + t, TRD_PS, 0, g1, 1) : 0.0;
-    const double pz = t < 2 * i ? P.PVt[(int64_t)(j + 1) * TRD_PT + t] : 0.0;
-    const double alpha = t == 0 ? V.wp[j + 1] : 0.0;
-    const int e = t < TRD_TT ? R0 + t : C0 + t - TRD_TT;   // this thread's row (t < TT) or column of x
-    const double xe = e < n ? V.wp[e] : 0.0;
-    if (t < 2 * i + 1) red[t] = ps;
+    typedef double d2 __attribute__((ext_vector_type(2)));
+    const int t = threadIdx.x, lane = t & 63;
+    const int wv = __builtin_amdgcn_readfirstlane(t >> 6);   // scalar: row addresses stay in scalar registers
+    // wave wv: tile rows 32 wv .. 32 wv + 31 in four groups of 8, two columns a
+    // lane; row sums per lane, then over the lanes. The first group goes out
+    // before x is in LDS, the next one as soon as a group is multiplied. Rows
+    // past n are read from the last row and pairs past column n from the last
+    // pair or the zero pad (the rows are padded to 32 columns): they meet zeros
+    // of x.
+    d2 a[8];
+    const int pc = min(C0 + 2 * lane, (n - 1) & ~1) >> 1;
+    auto load = [&](int g) {
+        const int rg = R0 + 32 * wv + 8 * g;
+#pragma unroll
+        for (int u = 0; u < 8; ++u) a[u] = reinterpret_cast<const d2 *>(A + (int64_t)min(rg + u, n - 1) * lda)[pc];
+    };
+    load(0);
+    if (t < TRD_TT) sh.vr[t] = ve;
+    else sh.vc[t - TRD_TT] = ve;
     __syncthreads();
-    if (t == 0) {
-        const double sig = red[0];
-        double tau = 0.0, beta = alpha, scale = 0.0;
-        if (sig > 0.0) {
-            beta = -copysign(sqrt(alpha * alpha + sig), alpha);
-            tau = (beta - alpha) / beta;
-            scale = 1.0 / (alpha - beta);
-        }
-        sc[0] = scale;
-        if (b == 0) {
-            V.e[j] = beta;
-            V.tau[j] = tau;
-        }
-    }
-    __syncthreads();
-    const double scale = sc[0];
-    const double ve = e < n ? (e == j + 1 ? 1.0 : xe * scale) : 0.0;
-    if (t < TRD_TT) vr[t] = ve;
-    else vc[t - TRD_TT] = ve;
-    if (b == 0 && t < 2 * i) P.z[t] = pz + scale * red[t + 1];
-    if (ct == 0 && t < TRD_TT && e < n) {
-        A[(int64_t)e * lda + j] = ve;   // kept for the back-transformation
-        P.PV[(int64_t)(2 * i) * P.ldp + e] = ve;
-        P.PW[(int64_t)(2 * i + 1) * P.ldp + e] = ve;
-        P.PVt[(int64_t)e * TRD_PT + 2 * i] = ve;
-    }
-    __syncthreads();
-    // wave wv: tile rows 32 wv .. 32 wv + 31 in four groups of 8, lanes over
-    // 64 columns at a time; row sums per lane, then over the lanes
-    const bool diag = ct == rt;
-    double colacc[2] = {0.0, 0.0};
+    const d2 vcl = (d2){sh.vc[2 * lane], sh.vc[2 * lane + 1]};
+    d2 colacc = (d2){0.0, 0.0};
 #pragma unroll 1
     for (int g = 0; g < 4; ++g) {
         const int rl0 = 32 * wv + 8 * g;
         double racc[8];
 #pragma unroll
-        for (int u = 0; u < 8; ++u) racc[u] = 0.0;
-#pragma unroll
-        for (int ch = 0; ch < 2; ++ch) {
-            const int cl = 64 * ch + lane, c = C0 + cl;
-            const double vcl = vc[cl];
-            double a[8];
-#pragma unroll
-            for (int u = 0; u < 8; ++u) {
-                const int r = R0 + rl0 + u;
-                a[u] = (r < n && c < n && (!diag || cl <= rl0 + u)) ? A[(int64_t)r * lda + c] : 0.0;
+        for (int u = 0; u < 8; ++u) {
+            d2 v = a[u];
+            if (DIAG) {
+                if (2 * lane > rl0 + u) v.x = 0.0;
+                if (2 * lane + 1 > rl0 + u) v.y = 0.0;
             }
-            __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-            for (int u = 0; u < 8; ++u) {
-                racc[u] += a[u] * vcl;   // row part: c <= r
-                colacc[ch] += ((!diag || cl < rl0 + u) ? a[u] : 0.0) * vr[rl0 + u];   // column part: r > c
+            racc[u] = v.x * vcl.x + v.y * vcl.y;   // row part: c <= r
+            if (DIAG) {
+                if (2 * lane == rl0 + u) v.x = 0.0;
+                if (2 * lane + 1 == rl0 + u) v.y = 0.0;
             }
+            const double w = sh.vr[rl0 + u];
+            colacc.x += v.x * w;                   // column part: r > c
+            colacc.y += v.y * w;
         }
+        if (g < 3) load(g + 1);
         // the 8 row sums over the 64 lanes (halving exchanges in a fixed pattern)
-        const bool b5 = lane & 32, b4 = lane & 16, b3 = lane & 8;
+        const bool b5 = lane & 32, b4 = lane & 16;
         double h4[4], h2[2];
 #pragma unroll
         for (int k = 0; k < 4; ++k)
             h4[k] = (b5 ? racc[4 + k] : racc[k]) + __shfl_xor(b5 ? racc[k] : racc[4 + k], 32, 64);
 #pragma unroll
-        for (int k = 0; k < 2; ++k) h2[k] = (b4 ? h4[2 + k] : h4[k]) + __shfl_xor(b4 ? h4[k] : h4[2 + k], 16, 64);
-        double h1 = (b3 ? h2[1] : h2[0]) + __shfl_xor(b3 ? h2[0] : h2[1], 8, 64);
-        h1 += __shfl_xor(h1, 4, 64);
-        h1 += __shfl_xor(h1, 2, 64);
-        h1 += __shfl_xor(h1, 1, 64);
-        if ((lane & 7) == 0) rsum[rl0 + 4 * b5 + 2 * b4 + (b3 ? 1 : 0)] = h1;
+        for (int k = 0; k < 2; ++k) {
+            h2[k] = (b4 ? h4[2 + k] : h4[k]) + __shfl_xor(b4 ? h4[k] : h4[2 + k], 16, 64);
+            // over the 16 lanes of a row
+            h2[k] += rr_dpp<0x128, 0xf, 0xf>(h2[k]);   // row_ror 8, 4, 2, 1
+            h2[k] += rr_dpp<0x124, 0xf, 0xf>(h2[k]);
+            h2[k] += rr_dpp<0x122, 0xf, 0xf>(h2[k]);
+            h2[k] += rr_dpp<0x121, 0xf, 0xf>(h2[k]);
+        }
+        if ((lane & 15) < 2) sh.rsum[rl0 + 4 * b5 + 2 * b4 + (lane & 1)] = (lane & 1) ? h2[1] : h2[0];
     }
-    cs[wv][lane] = colacc[0];
-    cs[wv][64 + lane] = colacc[1];
+    sh.cs[wv][2 * lane] = colacc.x;
+    sh.cs[wv][2 * lane + 1] = colacc.y;
     __syncthreads();
-    if (t < TRD_TT) {
-        const int r = R0 + t, c = C0 + t;
-        if (r < n) P.rowp[(int64_t)ct * n + r] = rsum[t];
-        if (c < n) P.colp[(int64_t)rt * n + c] = cs[0][t] + cs[1][t] + cs[2][t] + cs[3][t];
-    }
 }
 
-// p[r] = tau_j (A_0 v_j - sum_k (v_k (w_k . v_j) + w_k (v_k . v_j)))[r] for the
-// rows r of the tiled pass of column j: eight lanes per row add its row sums
-// (tile columns up to its own) and column sums (tile rows from its own down),
-// lane l taking items l, l + 8, ..., then the eight lanes in a fixed pattern;
-// p into V.p and this workgroup's partial sum of p . v_j into part2 (as the
-// row pass leaves them)
-__global__ __launch_bounds__(256) void k_trd_tile_sum(int n, int j, int i, TrdVec V, TrdPanel P)
+__global__ __launch_bounds__(256, 4) void k_trd_tiles(const double *__restrict__ A, int64_t lda, int n, int j, TrdVec V,
+                                                      TrdPanel P)
 {
-    __shared__ double red[256];
-    const int t = threadIdx.x, l = t & 7;
-    const int r = j + 1 + (int)blockIdx.x * TRD_SR + (t >> 3);
-    const int T = trd_tiles(n - j - 1);
-    double s = 0.0, q = 0.0;
-    if (r < n) {
-        const int rt = (r - j - 1) / TRD_TT;
-        // item b <= rt: rowp[b][r]; item b > rt: colp[b - 1][r]
-        for (int b0 = l; b0 <= T; b0 += 32) {
-            double u[4];
-#pragma unroll
-            for (int k = 0; k < 4; ++k) {
-                const int b = b0 + 8 * k;
-                u[k] = b > T ? 0.0 : (b <= rt ? P.rowp[(int64_t)b * n + r] : P.colp[(int64_t)(b - 1) * n + r]);
-            }
-#pragma unroll
-            for (int k = 0; k < 4; ++k) s += u[k];
-        }
-        for (int k = l; k < i; k += 8)
-            q += P.PVt[(int64_t)r * TRD_PT + 2 * k] * P.z[2 * k + 1] + P.PVt[(int64_t)r * TRD_PT + 2 * k + 1] * P.z[2 * k];
+    __shared__ TrdTileShared sh;
+    const int t = threadIdx.x, b = blockIdx.x;
+    int rt = (int)((sqrt(8.0 * b + 1.0) - 1.0) * 0.5);
+    while ((rt + 1) * (rt + 2) / 2 <= b) ++rt;
+    while (rt * (rt + 1) / 2 > b) --rt;
+    const int ct = b - rt * (rt + 1) / 2;
+    const int B0 = trd_base(j + 1), R0 = B0 + TRD_TT * rt, C0 = B0 + TRD_TT * ct;
+    const double *x = (j & 1) ? V.x1 : V.x0;
+    const int e = t < TRD_TT ? R0 + t : C0 + t - TRD_TT;   // this thread's row (t < TT) or column of x
+    const double ve = e < n && e > j + 1 ? x[e] : 0.0;
+    if (rt == ct) trd_tile<true>(A, lda, n, R0, C0, ve, sh);
+    else trd_tile<false>(A, lda, n, R0, C0, ve, sh);
+    if (t < TRD_TT) {
+        const int r = R0 + t, c = C0 + t;
+        const double rs = sh.rsum[t], cl = sh.cs[0][t] + sh.cs[1][t] + sh.cs[2][t] + sh.cs[3][t];
+        if (r < n) P.rowp[(int64_t)ct * n + r] = rs;
+        if (c < n) P.colp[(int64_t)rt * n + c] = cl;
+        const double s = wave_sum(sh.vr[t] * rs + sh.vc[t] * cl);   // (past n: 0)
+        if ((t & 63) == 0) sh.red[t >> 6] = s;
     }
-    for (int o = 4; o > 0; o >>= 1) {
-        s += __shfl_xor(s, o, 8);
-        q += __shfl_xor(q, o, 8);
-    }
-    double pv = 0.0;
-    if (r < n && l == 0) {
-        const double p = V.tau[j] * (s - q);
-        V.p[r] = p;
-        pv = p * P.PVt[(int64_t)r * TRD_PT + 2 * i];
-    }
-    pv = blk_sum(pv, red);   // (rows in order of their first lane; the others add 0)
-    if (t == 0) P.part2[blockIdx.x] = pv;
+    __syncthreads();
+    if (t == 0) P.part2[b] = sh.red[0] + sh.red[1];
 }
 
 // columns j0 .. j0 + nbp - 1 of the reduction, then the update of the
@@ -553,26 +570,32 @@ __global__ __launch_bounds__(256) void k_trd_tile_sum(int n, int j, int i, TrdVe
 hipError_t launch_trd_panel(double *A, int64_t lda, int n, int j0, int nbp, const TrdVec &V, const TrdPanel &P,
                             hipStream_t st)
 {
+    // the column kernel of column c, after i reflectors of the panel
+    auto column = [&](int c, int i, int fin, int col) {
+        const int m = n - c;   // rows from c on = rows of the product of column c - 1
+        const int T = trd_tiles(n - trd_base(c)), tiled = m >= TRD_TILE_MIN;
+        const int g2 = m < 2 ? 0 : (tiled ? T * (T + 1) / 2 : (m + 3) / 4);
+        // the last TRD_TILE_MIN rows are updated as a whole square
+        const dim3 g((m + TRD_CR - 1) / TRD_CR), b(TRD_CT);
+        const int rowc = m <= TRD_TILE_MIN;
+        if (tiled) hipLaunchKernelGGL(k_trd_col<true>, g, b, 0, st, A, lda, n, c, i, fin, col, T, rowc, g2, V, P);
+        else hipLaunchKernelGGL(k_trd_col<false>, g, b, 0, st, A, lda, n, c, i, fin, col, 0, rowc, g2, V, P);
+    };
     for (int i = 0; i < nbp; ++i) {
-        const int j = j0 + i;
-        hipLaunchKernelGGL(k_trd_col, dim3((n - j + TRD_CR - 1) / TRD_CR), dim3(256), 0, st, A, lda, n, j, i, 1, V,
-                           P);
-        if (j < n - 1) {
-            const int m = n - j - 1;
-            if (m >= TRD_TILE_MIN) {
-                const int T = trd_tiles(m);
-                hipLaunchKernelGGL(k_trd_tiles, dim3(T * (T + 1) / 2), dim3(256), 0, st, A, lda, n, j, i, V, P);
-                hipLaunchKernelGGL(k_trd_tile_sum, dim3((m + TRD_SR - 1) / TRD_SR), dim3(256), 0, st, n, j, i, V, P);
-            } else {
-                hipLaunchKernelGGL(k_trd_pass, dim3((m + 3) / 4), dim3(256), 0, st, A, lda, n, j, i, V, P);
-            }
+        const int j = j0 + i, m = n - j - 1;
+        column(j, i, i > 0, 1);
+        if (m < 2) continue;   // no column right of j + 1: nothing to multiply
+        if (m >= TRD_TILE_MIN) {
+            const int T = trd_tiles(n - trd_base(j + 1));
+            hipLaunchKernelGGL(k_trd_tiles, dim3(T * (T + 1) / 2), dim3(256), 0, st, A, lda, n, j, V, P);
+        } else {
+            hipLaunchKernelGGL(k_trd_pass, dim3((m + 3) / 4), dim3(256), 0, st, A, lda, n, j, V, P);
         }
     }
     const int t = j0 + nbp;
     if (t < n) {
-        // w of the panel's last reflector, then A -= PV^T PW on the trailing block
-        hipLaunchKernelGGL(k_trd_col, dim3((n - t + TRD_CR - 1) / TRD_CR), dim3(256), 0, st, A, lda, n, t, nbp, 0, V,
-                           P);
+        // v and w of the panel's last reflector, then A -= PV^T PW on the trailing block
+        column(t, nbp, 1, 0);
         hipError_t e = hipGetLastError();
         if (e != hipSuccess) return e;
         // while the trailing block has TRD_TILE_MIN rows or more it is read
@@ -586,20 +609,52 @@ hipError_t launch_trd_panel(double *A, int64_t lda, int n, int j0, int nbp, cons
     return hipGetLastError();
 }
 
-// W = (W + W^T) / 2 in place (the operation is defined on a symmetric matrix)
-__global__ void k_symmetrize(double *__restrict__ W, int64_t ld, int n)
+// W = (W + W^T) / 2 in place (the operation is defined on a symmetric matrix);
+// the rows' pad columns n .. ld - 1 become 0; amax: the largest |entry| as bits
+// (zeroed by k_word_zero). A workgroup takes the 32 x 32 tiles (rt, ct) and
+// (ct, rt), ct <= rt, through LDS, so that both are read and written by rows:
+// bound by memory (one pass over W each way), 0.19 ms at n = 8000 (5.3 TB/s)
+// against 0.84 with the upper triangle read and written by columns.
+constexpr int SYM_T = 32;
+__global__ __launch_bounds__(256) void k_symmetrize(double *__restrict__ W, int64_t ld, int n,
+                                                    unsigned long long *__restrict__ amax)
 {
-    const int64_t i = blockIdx.y, j = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (j >= i) return;
-    const double a = 0.5 * (W[i * ld + j] + W[j * ld + i]);
-    W[i * ld + j] = a;
-    W[j * ld + i] = a;
+    __shared__ double L[SYM_T][SYM_T + 1], U[SYM_T][SYM_T + 1];
+    const int t = threadIdx.x, cl = t & 31, r0 = t >> 5;
+    const int R0 = (int)blockIdx.y * SYM_T, C0 = (int)blockIdx.x * SYM_T;
+    if (C0 > R0) return;
+    if (C0 == 0 && n + cl < ld)
+        for (int r = r0; r < SYM_T && R0 + r < n; r += 8) W[(int64_t)(R0 + r) * ld + n + cl] = 0.0;
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+        const int r = r0 + 8 * u;
+        L[r][cl] = R0 + r < n && C0 + cl < n ? W[(int64_t)(R0 + r) * ld + C0 + cl] : 0.0;
+        U[r][cl] = C0 + r < n && R0 + cl < n ? W[(int64_t)(C0 + r) * ld + R0 + cl] : 0.0;
+    }
+    __syncthreads();
+    unsigned long long m = 0;
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+        const int r = r0 + 8 * u;
+        const double lo = R0 + r == C0 + cl ? L[r][cl] : 0.5 * (L[r][cl] + U[cl][r]);
+        const double up = C0 + r == R0 + cl ? U[r][cl] : 0.5 * (L[cl][r] + U[r][cl]);
+        m = max(m, __builtin_bit_cast(unsigned long long, fabs(lo)));
+        if (R0 + r < n && C0 + cl < n) W[(int64_t)(R0 + r) * ld + C0 + cl] = lo;
+        if (C0 < R0 && C0 + r < n && R0 + cl < n) W[(int64_t)(C0 + r) * ld + R0 + cl] = up;
+    }
+    for (int o = 32; o > 0; o >>= 1) m = max(m, __shfl_xor(m, o));
+    // (few waves find a larger entry than those before them)
+    if ((t & 63) == 0 && m > __hip_atomic_load(amax, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) atomicMax(amax, m);
 }
 
-hipError_t launch_symmetrize(double *W, int64_t ld, int n, hipStream_t st)
+__global__ void k_word_zero(unsigned long long *__restrict__ w) { *w = 0; }
+
+hipError_t launch_symmetrize(double *W, int64_t ld, int n, unsigned long long *amax, hipStream_t st)
 {
-    if (n <= 1) return hipSuccess;
-    hipLaunchKernelGGL(k_symmetrize, dim3((n + 255) / 256, n), dim3(256), 0, st, W, ld, n);
+    if (n < 1) return hipSuccess;
+    const unsigned T = (unsigned)((n + SYM_T - 1) / SYM_T);
+    hipLaunchKernelGGL(k_word_zero, dim3(1), dim3(1), 0, st, amax);
+    hipLaunchKernelGGL(k_symmetrize, dim3(T, T), dim3(256), 0, st, W, ld, n, amax);
     return hipGetLastError();
 }
 
@@ -608,7 +663,10 @@ hipError_t launch_symmetrize(double *W, int64_t ld, int n, hipStream_t st)
 // 2. eigenvalues of the tridiagonal T (diagonal d[0..n), off-diagonal e[0..n-1))
 // ---------------------------------------------------------------------------
 // number of eigenvalues below x of the unreduced block d[0..m), e2[0..m-1)
-// (Sturm sequence of the LDL^T pivots)
+// (Sturm sequence of the LDL^T pivots; the chain's quotient e2 / q as e2 times
+// the refined hardware reciprocal, about one ulp off, which is a relative
+// change of e2 by as much: at |q| >= pivmin neither it nor the product
+// overflows)
 __device__ __forceinline__ int sturm_count(const double *__restrict__ d, const double *__restrict__ e2, int m,
                                            double x, double pivmin)
 {
@@ -627,13 +685,13 @@ __device__ __forceinline__ int sturm_count(const double *__restrict__ d, const d
         __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
         for (int u = 0; u < 8; ++u) {
-            q = dv[u] - x - ev[u] / q;
+            q = dv[u] - x - ev[u] * rr_recip(q);
             if (fabs(q) < pivmin) q = -pivmin;
             c += q < 0.0;
         }
     }
     for (; i < m; ++i) {
-        q = d[i] - x - e2[i - 1] / q;
+        q = d[i] - x - e2[i - 1] * rr_recip(q);
         if (fabs(q) < pivmin) q = -pivmin;
         c += q < 0.0;
     }
@@ -646,10 +704,12 @@ __device__ __forceinline__ int sturm_count(const double *__restrict__ d, const d
 // between the last point with count <= k and the first with count > k, until
 // no representable point lies strictly inside. With monotone counts this ends
 // on the same pair of adjacent doubles as bisection, in about a third of the
-// dependent steps. (8 lanes: 12.7 ms for the 8000 eigenvalues of the D =
-// 8000 matrix; 16 lanes 13.6 ms, 32 lanes 19.0 ms, 64 lanes 29.5 ms: the
-// counts are bound by issue, not by the length of the chain.)
-constexpr int TRI_G = 8;
+// dependent steps. Bound by the chain of dependent quotients, so a small n, which
+// leaves the chip empty, takes more points a step: with 64 lanes 0.18 ms at
+// n = 301 (8 lanes and the division: 0.42), with 8 lanes 9.4 ms at n = 8000
+// (12.6 with the division); 16 lanes are the better ones between 1024 and 3072,
+// where the chip is filled by them
+template <int TRI_G>
 __global__ __launch_bounds__(256) void k_tri_bisect(const double *__restrict__ d, const double *__restrict__ e2, int n,
                                                     const int32_t *__restrict__ bs, const int32_t *__restrict__ bm,
                                                     const int32_t *__restrict__ bk, double lo0, double hi0,
@@ -692,8 +752,12 @@ hipError_t launch_tri_eigenvalues(const double *d, const double *e, double *e2, 
 {
     if (n <= 0) return hipSuccess;
     if (n > 1) hipLaunchKernelGGL(k_tri_prep, dim3((n + 255) / 256), dim3(256), 0, st, e, n, e2);
-    hipLaunchKernelGGL(k_tri_bisect, dim3((unsigned)(((int64_t)n * TRI_G + 255) / 256)), dim3(256), 0, st, d, e2, n,
-                       bs, bm, bk, lo, hi, pivmin, w);
+    // lanes per eigenvalue: as many as the chip has room for
+    const int G = n <= 1024 ? 64 : (n <= 3072 ? 16 : 8);
+    const dim3 g((unsigned)(((int64_t)n * G + 255) / 256)), b(256);
+    if (G == 64) hipLaunchKernelGGL(k_tri_bisect<64>, g, b, 0, st, d, e2, n, bs, bm, bk, lo, hi, pivmin, w);
+    else if (G == 16) hipLaunchKernelGGL(k_tri_bisect<16>, g, b, 0, st, d, e2, n, bs, bm, bk, lo, hi, pivmin, w);
+    else hipLaunchKernelGGL(k_tri_bisect<8>, g, b, 0, st, d, e2, n, bs, bm, bk, lo, hi, pivmin, w);
     return hipGetLastError();
 }
 
@@ -724,8 +788,8 @@ __global__ void k_tri_vectors(const double *__restrict__ dg, const double *__res
         return;
     }
     // Every loop below is a dependent chain over the rows; the loads of
-    // TV_B steps go out before the chain runs through them (same arithmetic
-    // in the same order).
+    // TV_B steps go out before the chain runs through them, and the quotients
+    // are products with the refined hardware reciprocal (about one ulp).
     constexpr int TV_B = 8;
     // forward: dp_i into S, l_i into Z (both column k)
     double dp = d[0] - lam;
@@ -742,7 +806,7 @@ __global__ void k_tri_vectors(const double *__restrict__ dg, const double *__res
         __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
         for (int u = 0; u < TV_B; ++u) {
-            const double l = ev[u] / dp;
+            const double l = ev[u] * rr_recip(dp);
             Z[(int64_t)(i + u) * ldz + k] = l;
             dp = dv[u] - lam - l * ev[u];
             if (fabs(dp) < pivmin) dp = -pivmin;
@@ -750,7 +814,7 @@ __global__ void k_tri_vectors(const double *__restrict__ dg, const double *__res
         }
     }
     for (; i < m - 1; ++i) {
-        const double l = e[i] / dp;
+        const double l = e[i] * rr_recip(dp);
         Z[(int64_t)i * ldz + k] = l;
         dp = d[i + 1] - lam - l * e[i];
         if (fabs(dp) < pivmin) dp = -pivmin;
@@ -773,7 +837,7 @@ __global__ void k_tri_vectors(const double *__restrict__ dg, const double *__res
         __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
         for (int u = 0; u < TV_B; ++u) {
-            const double uu = ev[u] / dm;
+            const double uu = ev[u] * rr_recip(dm);
             dm = dv[u] - lam - uu * ev[u];
             if (fabs(dm) < pivmin) dm = -pivmin;
             const double g = fabs(sv[u] + dm - (dv[u] - lam));
@@ -784,7 +848,7 @@ __global__ void k_tri_vectors(const double *__restrict__ dg, const double *__res
         }
     }
     for (; i >= 0; --i) {
-        const double u = e[i] / dm;
+        const double u = e[i] * rr_recip(dm);
         dm = d[i] - lam - u * e[i];
         if (fabs(dm) < pivmin) dm = -pivmin;
         const double g = fabs(S[(int64_t)i * lds + k] + dm - (d[i] - lam));
@@ -807,14 +871,14 @@ __global__ void k_tri_vectors(const double *__restrict__ dg, const double *__res
         __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
         for (int u = 0; u < TV_B; ++u) {
-            const double uu = ev[u] / dm;
+            const double uu = ev[u] * rr_recip(dm);
             S[(int64_t)(i - u) * lds + k] = uu;
             dm = dv[u] - lam - uu * ev[u];
             if (fabs(dm) < pivmin) dm = -pivmin;
         }
     }
     for (; i >= r; --i) {
-        const double u = e[i] / dm;
+        const double u = e[i] * rr_recip(dm);
         S[(int64_t)i * lds + k] = u;
         dm = d[i] - lam - u * e[i];
         if (fabs(dm) < pivmin) dm = -pivmin;
@@ -994,21 +1058,19 @@ hipError_t launch_cluster_mgs(double *Z, int64_t ldz, const int32_t *desc, int n
 __global__ void k_copy_reflectors(const double *__restrict__ A, int64_t lda, int n, int j0, int nb,
                                   double *__restrict__ Vb)
 {
-    const int r = blockIdx.x * blockDim.x + threadIdx.x;
-    const int m = n - j0 - 1;
-    if (r >= m) return;
-    const int row = j0 + 1 + r;
-    for (int i = 0; i < nb; ++i) {
-        const int j = j0 + i;   // reflector j starts at row j + 1
-        Vb[(int64_t)r * nb + i] = (row >= j + 1) ? A[(int64_t)row * lda + j] : 0.0;
-    }
+    // consecutive threads: consecutive reflectors of one row (both sides contiguous)
+    const int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    const int r = (int)(e / nb), i = (int)(e % nb);
+    if (r >= n - j0 - 1) return;
+    Vb[e] = r >= i ? A[(int64_t)(j0 + 1 + r) * lda + j0 + i] : 0.0;   // reflector j starts at row j + 1
 }
 
 hipError_t launch_copy_reflectors(const double *A, int64_t lda, int n, int j0, int nb, double *Vb, hipStream_t st)
 {
     const int m = n - j0 - 1;
-    if (m <= 0) return hipSuccess;
-    hipLaunchKernelGGL(k_copy_reflectors, dim3((m + 255) / 256), dim3(256), 0, st, A, lda, n, j0, nb, Vb);
+    if (m <= 0 || nb <= 0) return hipSuccess;
+    hipLaunchKernelGGL(k_copy_reflectors, dim3((unsigned)(((int64_t)m * nb + 255) / 256)), dim3(256), 0, st, A, lda, n,
+                       j0, nb, Vb);
     return hipGetLastError();
 }
 
@@ -1018,19 +1080,30 @@ hipError_t launch_copy_reflectors(const double *A, int64_t lda, int n, int j0, i
 // four diagonal blocks of 16 by that column recurrence side by side (one
 // wave each; thread r forms entry r, its sum in order), then neighbouring
 // blocks joined, 16 -> 32 -> 64, by T12 = -T11 G12 T22 (the same T: the
-// product of the first reflectors times that of the next ones)
+// product of the first reflectors times that of the next ones). The sums run
+// over whole blocks (T is zero below its diagonal), unrolled, so that their LDS
+// reads overlap. Workgroup h of two forms the diagonal block of reflectors
+// [64 h, 64 h + 64) of nb_all and zeroes the block left of it.
 constexpr int LARFT_MAX = 64;
-__global__ __launch_bounds__(256) void k_larft(const double *__restrict__ G, int ldg, const double *__restrict__ tau,
-                                               int nb, double *__restrict__ T, int ldt)
+__global__ __launch_bounds__(256) void k_larft(const double *__restrict__ G_all, int ldg,
+                                               const double *__restrict__ tau_all, int nb_all,
+                                               double *__restrict__ T_all, int ldt)
 {
+    const int off = LARFT_MAX * blockIdx.x, nb = min(LARFT_MAX, nb_all - off);
+    const double *G = G_all + (int64_t)off * ldg + off, *tau = tau_all + off;
+    double *T = T_all + (int64_t)off * ldt + off;
+    for (int e = threadIdx.x; e < nb * off; e += 256) T_all[(int64_t)(off + e / off) * ldt + e % off] = 0.0;
     __shared__ double Ts[LARFT_MAX][LARFT_MAX + 1];
     __shared__ double Gs[LARFT_MAX][LARFT_MAX + 1];
     __shared__ double Ws[LARFT_MAX / 2][LARFT_MAX / 2 + 1];
     __shared__ double ts[LARFT_MAX];
     const int t = threadIdx.x, lane = t & 63, wv = t >> 6;
-    for (int e = t; e < LARFT_MAX * LARFT_MAX; e += 256) Ts[e / LARFT_MAX][e % LARFT_MAX] = 0.0;
 #pragma unroll 4
-    for (int e = t; e < nb * nb; e += 256) Gs[e / nb][e % nb] = G[(int64_t)(e / nb) * ldg + e % nb];
+    for (int e = t; e < LARFT_MAX * LARFT_MAX; e += 256) {
+        const int r = e / LARFT_MAX, c = e % LARFT_MAX;
+        Ts[r][c] = 0.0;
+        Gs[r][c] = r < nb && c < nb ? G[(int64_t)r * ldg + c] : 0.0;
+    }
     if (t < nb) ts[t] = tau[t];
     __syncthreads();
     // the diagonal blocks [16 wv, 16 wv + 16)
@@ -1040,7 +1113,8 @@ __global__ __launch_bounds__(256) void k_larft(const double *__restrict__ G, int
             const int c = b0 + i;
             if (lane < i) {
                 double acc = 0.0;
-                for (int q = lane; q < i; ++q) acc += Ts[b0 + lane][b0 + q] * Gs[b0 + q][c];
+#pragma unroll
+                for (int q = 0; q < 16; ++q) acc += Ts[b0 + lane][b0 + q] * Gs[b0 + q][c];   // (columns from i on: 0)
                 Ts[b0 + lane][c] = -ts[c] * acc;
             } else if (lane == i) {
                 Ts[c][c] = ts[c];
@@ -1059,7 +1133,8 @@ __global__ __launch_bounds__(256) void k_larft(const double *__restrict__ G, int
             for (int e = t; e < h * h2; e += 256) {
                 const int r = e / h2, cc = e % h2;
                 double acc = 0.0;
-                for (int q = 0; q <= cc; ++q) acc += Gs[a0 + r][c0 + q] * Ts[c0 + q][c0 + cc];
+#pragma unroll 16
+                for (int q = 0; q < h2; ++q) acc += Gs[a0 + r][c0 + q] * Ts[c0 + q][c0 + cc];
                 Ws[r][cc] = acc;
             }
             __syncthreads();
@@ -1067,7 +1142,8 @@ __global__ __launch_bounds__(256) void k_larft(const double *__restrict__ G, int
             for (int e = t; e < h * h2; e += 256) {
                 const int r = e / h2, cc = e % h2;
                 double acc = 0.0;
-                for (int q = r; q < h; ++q) acc += Ts[a0 + r][a0 + q] * Ws[q][cc];
+#pragma unroll 16
+                for (int q = 0; q < h; ++q) acc += Ts[a0 + r][a0 + q] * Ws[q][cc];
                 Ts[a0 + r][c0 + cc] = -acc;
             }
             __syncthreads();
@@ -1083,17 +1159,10 @@ __global__ __launch_bounds__(256) void k_larft(const double *__restrict__ G, int
 hipError_t launch_larft(const double *G, const double *tau, int nb, double *T, double *X, hipStream_t st)
 {
     if (nb > 2 * LARFT_MAX) return hipErrorInvalidValue;
-    if (nb <= LARFT_MAX) {
-        hipLaunchKernelGGL(k_larft, dim3(1), dim3(256), 0, st, G, nb, tau, nb, T, nb);
-        return hipGetLastError();
-    }
+    hipLaunchKernelGGL(k_larft, dim3((nb + LARFT_MAX - 1) / LARFT_MAX), dim3(256), 0, st, G, nb, tau, nb, T, nb);
+    hipError_t e = hipGetLastError();
+    if (nb <= LARFT_MAX || e != hipSuccess) return e;
     const int h = LARFT_MAX, n2 = nb - h;
-    hipError_t e = launch_fill_f64(T, 0.0, (int64_t)nb * nb, st);
-    if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(k_larft, dim3(1), dim3(256), 0, st, G, nb, tau, h, T, nb);
-    hipLaunchKernelGGL(k_larft, dim3(1), dim3(256), 0, st, G + (int64_t)h * nb + h, nb, tau + h, n2,
-                       T + (int64_t)h * nb + h, nb);
-    if ((e = hipGetLastError()) != hipSuccess) return e;
     // X = G12 T2, then T12 = -T1 X
     if ((e = launch_eig_gemm(h, n2, n2, 1.0, G + h, nb, 1, T + (int64_t)h * nb + h, nb, 1, 0.0, X, n2, st, nullptr,
                              0, -1)) != hipSuccess)

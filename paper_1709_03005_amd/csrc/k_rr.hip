@@ -81,45 +81,6 @@ __device__ __forceinline__ double rr_block_max(double v, double *red)
     return s;
 }
 
-// Cross-lane helpers on doubles as two 32-bit halves: DPP moves (row shifts
-// and row broadcasts) and readlane with a wave-uniform lane index.
-struct RrI2 {
-    int x, y;
-};
-
-template <int CTRL, int ROW_MASK, int BANK_MASK>
-__device__ __forceinline__ double rr_dpp(double v)
-{
-    RrI2 a = __builtin_bit_cast(RrI2, v);
-    a.x = __builtin_amdgcn_update_dpp(0, a.x, CTRL, ROW_MASK, BANK_MASK, true);
-    a.y = __builtin_amdgcn_update_dpp(0, a.y, CTRL, ROW_MASK, BANK_MASK, true);
-    return __builtin_bit_cast(double, a);
-}
-
-__device__ __forceinline__ double rr_rl(double v, int lane)
-{
-    RrI2 a = __builtin_bit_cast(RrI2, v);
-    a.x = __builtin_amdgcn_readlane(a.x, lane);
-    a.y = __builtin_amdgcn_readlane(a.y, lane);
-    return __builtin_bit_cast(double, a);
-}
-
-// sum over the 64 lanes, returned to every lane: partial sums of 4 within
-// each row of 16 (row_shr 1..3), of 8 and 16 (row_shr 4, 8 on the upper
-// banks), then rows 0+1 and 2+3 (row_bcast15) and all four (row_bcast31)
-// collect in lane 63. Fixed order, so every wave gets the same bits.
-__device__ __forceinline__ double rr_wsum(double v)
-{
-    double s = v + rr_dpp<0x111, 0xf, 0xf>(v);
-    s += rr_dpp<0x112, 0xf, 0xf>(v);
-    s += rr_dpp<0x113, 0xf, 0xf>(v);
-    s += rr_dpp<0x114, 0xf, 0xe>(s);
-    s += rr_dpp<0x118, 0xf, 0xc>(s);
-    s += rr_dpp<0x142, 0xa, 0xf>(s);
-    s += rr_dpp<0x143, 0xc, 0xf>(s);
-    return rr_rl(s, 63);
-}
-
 // element i (wave-uniform, < 128) of a vector held as lo = x[lane], hi = x[lane + 64]
 __device__ __forceinline__ double rr_get(double lo, double hi, int i)
 {
@@ -131,29 +92,6 @@ __device__ __forceinline__ double rr_get(double lo, double hi, int i)
 // rotations per round, m-1 rounds per sweep; a rotation is skipped when
 // |a_pq| <= 1e-16 sqrt(|a_pp a_qq|), and the sweeps stop after one with no
 // rotation. Reads G itself (unscaled) and writes theta and Y.
-// 1/q from the hardware estimate and two Newton-Raphson corrections
-// r <- r + r (1 - q r), each squaring the relative error: a short dependent
-// chain for the recurrences below, within about one ulp of the quotient
-__device__ __forceinline__ double rr_recip(double q)
-{
-    double r = __builtin_amdgcn_rcp(q);
-    double e = fma(-q, r, 1.0);
-    r = fma(r, e, r);
-    e = fma(-q, r, 1.0);
-    return fma(r, e, r);
-}
-
-// 1/sqrt(x), x > 0, from the hardware estimate and two Newton-Raphson
-// corrections r <- r + r (1 - x r^2) / 2
-__device__ __forceinline__ double rr_rsqrt(double x)
-{
-    double r = __builtin_amdgcn_rsq(x);
-    double e = fma(-x * r, r, 1.0);
-    r = fma(0.5 * r, e, r);
-    e = fma(-x * r, r, 1.0);
-    return fma(0.5 * r, e, r);
-}
-
 // a value every lane holds alike (read from LDS), as a wave-uniform scalar
 __device__ __forceinline__ double rr_uni(double v)
 {
