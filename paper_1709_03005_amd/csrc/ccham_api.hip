@@ -31,10 +31,9 @@ hipError_t launch_bucket(PairList pl, int64_t n, const int32_t *pqidx, int n_o, 
                          int32_t *key, int64_t *count, int64_t *start, int64_t *cursor, int64_t *sorted,
                          int64_t *tmp, int64_t *d0, hipStream_t st);
 hipError_t launch_gamma(int W, PairList pl, const int64_t *start, const int64_t *count,
-                        const int64_t *sorted, const int64_t *d0, int M0, const int32_t *slotP,
-                        const int32_t *slotQ, const GammaList &gl, const uint64_t *da, const int8_t *spa,
-                        const int8_t *spb, const double *ca, int Sa, const double *cb, int Sb, int nrows,
-                        const int32_t *rn, const int32_t *rn2, double *At, hipStream_t st);
+                        const int64_t *sorted, const int64_t *d0, int M0, const int32_t *slotP, const int32_t *slotQ,
+                        const GammaList &gl, const uint64_t *da, const int8_t *spa, const int8_t *spb, const double *ca,
+                        int Sa, const double *cb, int Sb, bool tri, double *At, hipStream_t st);
 hipError_t launch_relayout(const double *ttcc, const double *tctc, int n_o, int n_cont, const int32_t *slotPJ,
                            const int32_t *slotQJ, int nJ, const int32_t *slotPK, const int32_t *slotQK, int nK,
                            int ja0, int nca, int jb0, int ncb, double *B, hipStream_t st, const PackedCC *pk);
@@ -1331,8 +1330,8 @@ static cch_status enqueue_pre(cch_ctx *c, hipStream_t st, bool ev, bool fan, boo
         const int M0 = (sa.irrep == sb.irrep) ? sa.M : 0;
         const GammaList gl{p.form, p.form == GAM_PLAIN ? p.n_slot : p.nF, p.d_k1, p.d_k2};
         HIPCK(c, launch_gamma(c->W, p.pr.pl, p.d_start, p.d_count, p.d_sorted, p.d_d0, M0, p.d_slotP, p.d_slotQ,
-                              gl, sa.d_dets, sa.d_cspin, sb.d_cspin, sa.d_ci, sa.S, sb.d_ci, sb.S, p.nrows,
-                              p.d_rn, p.d_rn2, p.d_At, s));
+                              gl, sa.d_dets, sa.d_cspin, sb.d_cspin, sa.d_ci, sa.S, sb.d_ci, sb.S, p.a == p.b,
+                              p.d_At, s));
     }
     HIPCK(c, f.end());
     EVREC(2);

@@ -54,43 +54,82 @@ hipError_t launch_pair_values(int W, TgtInts I, const uint64_t *da, const uint64
 }
 
 // ---------------------------------------------------------------------------
-// Y[m][n'] = sum_{pairs (m, m')} H_T[m,m'] c'[m'][n'],  Yo = same over
-// degree-0 pairs with weight 1. One wave per bra row, pairs in order.
-// ---------------------------------------------------------------------------
 // Y[m][n] = sum over the connected pairs p of row m of hv[p] cb[y_p][n]
-// (Yo likewise with weight 1 on degree-0 pairs): one wave per row m, its lanes
-// split into G pair groups x (64 / G) states; the G partial sums of a state
-// are combined by xor-shuffles over the group bits (fixed order).
-__global__ __launch_bounds__(256) void k_spmm_rows(int M, const int64_t *__restrict__ row_off,
+// (Yo likewise with weight 1 on degree-0 pairs): one workgroup per row m, each
+// of its waves taking every SP_W-th batch of 64 pairs, its lanes split into G
+// pair groups x (64 / G) states; the G partial sums of a state are combined by
+// xor-shuffles over the group bits and the waves' in order. The pairs' indices
+// and values come one pair a lane (the next batch while this one is added) and
+// go to the lanes by shuffles, and the CI entries of SP_B steps are on their way
+// together. Bound by the longest rows: the low substitutions connect to every
+// determinant, the mean row is a tenth of that (3.4 M pairs of 8000
+// determinants with 40 states: 1.79 ms with a wave a row that waits for two
+// loads a step, 0.77 with the batches, 0.16 with both).
+// ---------------------------------------------------------------------------
+constexpr int SP_B = 8, SP_W = 8;
+
+__global__ __launch_bounds__(64 * SP_W) void k_spmm_rows(int M, const int64_t *__restrict__ row_off,
                                                    const int64_t *__restrict__ row_cnt, PairList pl,
                                                    const double *__restrict__ hv,
                                                    const double *__restrict__ cb, int Sb, int lg_states,
                                                    double *__restrict__ Y, double *__restrict__ Yo)
 {
-    const int m = blockIdx.x * 4 + (threadIdx.x >> 6);
-    const int lane = threadIdx.x & 63;
-    if (m >= M) return;   // whole waves
+    __shared__ double red[2][SP_W][64];
+    const int m = blockIdx.x;
+    const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
     const int ns = 1 << lg_states;              // state lanes (power of two, <= 64)
-    const int ng = 64 >> lg_states;             // pair groups
+    const int lg_g = 6 - lg_states;             // pair groups: 1 << lg_g
     const int nl = lane & (ns - 1), g = lane >> lg_states;
-    const int64_t p0 = row_off[m], p1 = p0 + row_cnt[m];
+    const int64_t p0 = row_off[m], np = row_cnt[m];
+    // (the flag of a degree-0 pair in the sign bit of its row; a lane past the
+    // row's end holds the row's first pair with value 0)
+    auto pair = [&](int64_t q, int32_t &y, double &h) {
+        const int64_t p = p0 + (q < np ? q : 0);
+        y = pl.y[p] | (q < np && pl.deg[p] == 0 ? INT32_MIN : 0);
+        h = q < np ? hv[p] : 0.0;
+    };
     for (int n0 = 0; n0 < Sb; n0 += ns) {
-        const int n = n0 + nl;
+        const int n = n0 + nl, nc = min(n, Sb - 1);
         double acc = 0.0, acco = 0.0;
-        if (n < Sb) {
-            for (int64_t p = p0 + g; p < p1; p += ng) {
-                const double c = cb[(size_t)pl.y[p] * Sb + n];
-                acc = fma(hv[p], c, acc);
-                if (pl.deg[p] == 0) acco += c;
+        int32_t y = 0;
+        double h = 0.0;
+        if (64 * wv < np) pair(64 * wv + lane, y, h);
+        for (int64_t q0 = 64 * wv; q0 < np; q0 += 64 * SP_W) {
+            const int32_t yq = y;
+            const double hq = h;
+            if (q0 + 64 * SP_W < np) pair(q0 + 64 * SP_W + lane, y, h);
+            const int steps = (int)((min<int64_t>(64, np - q0) + (1 << lg_g) - 1) >> lg_g);
+            for (int k0 = 0; k0 < steps; k0 += SP_B) {
+                double c[SP_B], hh[SP_B];
+                int32_t yy[SP_B];
+#pragma unroll
+                for (int u = 0; u < SP_B; ++u) {
+                    const int src = (g + ((k0 + u) << lg_g)) & 63;
+                    yy[u] = __shfl(yq, src);
+                    hh[u] = __shfl(hq, src);
+                    c[u] = cb[(size_t)(yy[u] & INT32_MAX) * Sb + nc];
+                }
+#pragma unroll
+                for (int u = 0; u < SP_B; ++u)
+                    if (q0 + g + ((k0 + u) << lg_g) < np && k0 + u < steps) {
+                        acc = fma(hh[u], c[u], acc);
+                        if (yy[u] < 0) acco += c[u];
+                    }
             }
         }
         for (int o = ns; o < 64; o <<= 1) {
             acc += __shfl_xor(acc, o, 64);
             acco += __shfl_xor(acco, o, 64);
         }
-        if (g == 0 && n < Sb) {
-            Y[(size_t)m * Sb + n] = acc;
-            Yo[(size_t)m * Sb + n] = acco;
+        __syncthreads();   // the sums of the previous states have been read
+        red[0][wv][lane] = acc;
+        red[1][wv][lane] = acco;
+        __syncthreads();
+        if (wv < 2 && g == 0 && n < Sb) {   // wave 0 adds up Y, wave 1 Yo
+            double s = 0.0;
+#pragma unroll
+            for (int z = 0; z < SP_W; ++z) s += red[wv][z][lane];
+            (wv ? Yo : Y)[(size_t)m * Sb + n] = s;
         }
     }
 }
@@ -155,7 +194,7 @@ hipError_t launch_projection(int M, const int64_t *row_off, const int64_t *row_c
     if (M > 0) {
         int lg = 0;   // state lanes: the power of two >= Sb, at most 64
         while ((1 << lg) < Sb && lg < 6) ++lg;
-        hipLaunchKernelGGL(k_spmm_rows, dim3((M + 3) / 4), dim3(256), 0, st, M, row_off, row_cnt, pl,
+        hipLaunchKernelGGL(k_spmm_rows, dim3(M), dim3(64 * SP_W), 0, st, M, row_off, row_cnt, pl,
                            hv, cb, Sb, lg, Y, Yo);
     }
     hipLaunchKernelGGL(k_project, dim3(nrows), dim3(256), 0, st, M, ca, Sa, Y, Yo, Sb, rn, rn2, HT, O);
@@ -303,147 +342,202 @@ hipError_t launch_bucket(PairList pl, int64_t n, const int32_t *pqidx, int n_o, 
 //              At[2 nt + t] = -(K - K') / 2; a single slot (k2 < 0):
 //              At[nt + t] = -K.
 // ---------------------------------------------------------------------------
-constexpr int GAM_BATCH = 16;
-constexpr int GAM_RPT = 8;      // rows per thread per pass
+// The two weights make J and K products of the CI rows' columns, ca[x]^T w
+// cb[y] over the entries of the slot: on the FP64 matrix cores (16x16x4: four
+// entries an instruction), a workgroup per slot, 16 states of the bra and NB x
+// 16 of the ket. Each of its eight waves takes every eighth batch of 64 entries
+// with no barrier: one entry a lane is looked up (the next batch while this one
+// is multiplied) and handed out by shuffles, and the CI rows of GAM_U
+// instructions are on their way together (NB > 2 leaves two waves a SIMD and
+// spills). The waves' sums are added in order.
+// Bound by the longest slots: those with P = Q hold every target determinant
+// (they are launched first), the others some hundred pairs. 0.20 ms for 8000
+// determinants with 40 states and 40 orbitals (3.69 with one batch of 16 entries
+// at a time through LDS), 9 us for 500 with 5 states (95).
+// ---------------------------------------------------------------------------
+constexpr int GAM_W = 8;        // waves
+constexpr int GAM_U = 4;        // instructions' operands loaded together
 
-template <int W>
-__global__ __launch_bounds__(256) void k_gamma(PairList pl, const int64_t *__restrict__ start,
-                                               const int64_t *__restrict__ count,
-                                               const int64_t *__restrict__ sorted,
-                                               const int64_t *__restrict__ d0, int M0,
-                                               const int32_t *__restrict__ slotP,
-                                               const int32_t *__restrict__ slotQ, GammaList gl,
-                                               const uint64_t *__restrict__ da,
-                                               const int8_t *__restrict__ spa,
-                                               const int8_t *__restrict__ spb,
-                                               const double *__restrict__ ca, int Sa,
-                                               const double *__restrict__ cb, int Sb, int nrows,
-                                               const int32_t *__restrict__ rn,
-                                               const int32_t *__restrict__ rn2,
-                                               double *__restrict__ At)
+typedef double gam4 __attribute__((ext_vector_type(4)));
+
+template <int W, int NB>
+__global__ __launch_bounds__(64 * GAM_W) void k_gamma(PairList pl, const int64_t *__restrict__ start,
+                                                      const int64_t *__restrict__ count,
+                                                      const int64_t *__restrict__ sorted,
+                                                      const int64_t *__restrict__ d0, int M0,
+                                                      const int32_t *__restrict__ slotP,
+                                                      const int32_t *__restrict__ slotQ, GammaList gl,
+                                                      const uint64_t *__restrict__ da,
+                                                      const int8_t *__restrict__ spa,
+                                                      const int8_t *__restrict__ spb,
+                                                      const double *__restrict__ ca, int Sa,
+                                                      const double *__restrict__ cb, int Sb, int tri, int nrows,
+                                                      double *__restrict__ At)
 {
-    extern __shared__ double sh[];
-    double *sa = sh;                            // [GAM_BATCH][Sa]
-    double *sb = sh + GAM_BATCH * Sa;           // [GAM_BATCH][Sb]
-    __shared__ double wj[GAM_BATCH], wk[GAM_BATCH];
-    const int t0 = blockIdx.x;
+    __shared__ double red[GAM_W][NB * 256];
+    const int t0 = gl.n - 1 - (int)blockIdx.x;
+    const int na0 = (int)blockIdx.y * 16, nb0 = (int)blockIdx.z * 16 * NB;
+    if (tri && nb0 > na0 + 15) return;   // rows n >= n' only
+    const int nbt = min(NB, (min(Sb, tri ? na0 + 16 : Sb) - nb0 + 15) / 16);   // ket tiles with an output
+    const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
+    const int lo = lane & 15, hi = lane >> 4;
     const int ks[2] = {gl.k1 ? gl.k1[t0] : t0, gl.k2 ? gl.k2[t0] : -1};
-
-    for (int rbase = 0; rbase < nrows; rbase += 256 * GAM_RPT) {
-        double J[GAM_RPT], K[2][GAM_RPT];
+    const double *ca_l = ca + min(na0 + lo, Sa - 1);
+    const double *cb_l[NB];
 #pragma unroll
-        for (int q = 0; q < GAM_RPT; ++q) J[q] = K[0][q] = K[1][q] = 0.0;
+    for (int b = 0; b < NB; ++b) cb_l[b] = cb + min(nb0 + 16 * b + lo, Sb - 1);
+    gam4 J[NB], K[2][NB];
 #pragma unroll
-        for (int half = 0; half < 2; ++half) {
-            const int k = ks[half];
-            if (k < 0) continue;
-            const int P = slotP[k], Q = slotQ[k];
-            const int64_t s1 = start[k], n1 = count[k];
-            const int64_t n0 = (P == Q) ? M0 : 0;
-            const int64_t ntot = n1 + n0;
-            for (int64_t e0 = 0; e0 < ntot; e0 += GAM_BATCH) {
-                const int ne = (int)min<int64_t>(GAM_BATCH, ntot - e0);
-                __syncthreads();
-                // stage weights and CI rows of this batch
-                for (int t = threadIdx.x; t < ne; t += 256) {
-                    const int64_t e = e0 + t;
-                    const int64_t pidx = e < n1 ? sorted[s1 + e] : d0[e - n1];
-                    double a = 0.0, b = 0.0;
-                    if (pidx < 0) {
-                        // no identical ket for this bra row
-                    } else if (e < n1) {
-                        // particle p (in the bra), hole q (in the ket); the Coulomb weight
-                        // needs equal continuum spins and a spin-conserving excitation, the
-                        // exchange weight a particle of the ket's continuum spin and a hole
-                        // of the bra's (the spin-flip pairs of doublet-coupled triplets)
-                        const int s = pl.phase[pidx];
-                        const uint64_t lab = pl.label[pidx];
-                        const int sp = lab_field(lab, 0) & 1, sq = lab_field(lab, 1) & 1;
-                        const int sx = spa ? spa[pl.x[pidx]] : 0, sy = spb ? spb[pl.y[pidx]] : 0;
-                        a = (sx == sy && sp == sq) ? (double)s : 0.0;
-                        b = (sp == sy && sq == sx) ? (double)s : 0.0;
-                    } else {
-                        // occupation of spatial orbital P in the bra determinant (both spins;
-                        // the continuum spin's for the exchange weight)
-                        const uint64_t *d = da + (size_t)pl.x[pidx] * W;
-                        const int ka = 2 * P, kb = 2 * P + 1;
-                        const int oa = (int)((d[ka >> 6] >> (ka & 63)) & 1ull);
-                        const int ob = (int)((d[kb >> 6] >> (kb & 63)) & 1ull);
-                        const int sx = spa ? spa[pl.x[pidx]] : 0;
-                        a = (double)(oa + ob);
-                        b = (double)(sx ? ob : oa);
-                    }
-                    wj[t] = a;
-                    wk[t] = b;
-                }
-                for (int t = threadIdx.x; t < ne * Sa; t += 256) {
-                    const int ee = t / Sa, n = t % Sa;
-                    const int64_t e = e0 + ee;
-                    const int64_t pidx = e < n1 ? sorted[s1 + e] : d0[e - n1];
-                    sa[ee * Sa + n] = pidx < 0 ? 0.0 : ca[(size_t)pl.x[pidx] * Sa + n];
-                }
-                for (int t = threadIdx.x; t < ne * Sb; t += 256) {
-                    const int ee = t / Sb, n = t % Sb;
-                    const int64_t e = e0 + ee;
-                    const int64_t pidx = e < n1 ? sorted[s1 + e] : d0[e - n1];
-                    sb[ee * Sb + n] = pidx < 0 ? 0.0 : cb[(size_t)pl.y[pidx] * Sb + n];
-                }
-                __syncthreads();
+    for (int b = 0; b < NB; ++b) J[b] = K[0][b] = K[1][b] = (gam4){0.0, 0.0, 0.0, 0.0};
+    int waves = 1;   // that had entries
 #pragma unroll
-                for (int q = 0; q < GAM_RPT; ++q) {
-                    const int r = rbase + threadIdx.x + 256 * q;
-                    if (r < nrows) {
-                        const int n = rn[r], n2 = rn2[r];
-                        double j = J[q], kk = K[half][q];
-                        for (int ee = 0; ee < ne; ++ee) {
-                            const double cc = sa[ee * Sa + n] * sb[ee * Sb + n2];
-                            j = fma(wj[ee], cc, j);
-                            kk = fma(wk[ee], cc, kk);
+    for (int half = 0; half < 2; ++half) {
+        const int k = ks[half];
+        if (k < 0) continue;
+        const int P = slotP[k], Q = slotQ[k];
+        const int64_t s1 = start[k], n1 = count[k];
+        const int64_t ntot = n1 + (P == Q ? M0 : 0);
+        waves = max(waves, (int)min<int64_t>(GAM_W, (ntot + 63) / 64));
+        // entry e: its CI rows and weights (whole numbers from -1 to 2, two apart
+        // from 0 in four bits each); past the end the last entry with weights 0
+        auto entry = [&](int64_t e, int32_t &x, int32_t &y, int32_t &w) {
+            const bool in = e < ntot;
+            e = min(e, ntot - 1);
+            const int64_t pidx = e < n1 ? sorted[s1 + e] : d0[e - n1];
+            int a = 0, b = 0;
+            x = y = 0;
+            if (pidx >= 0) {   // else no identical ket for this bra row
+                x = pl.x[pidx];
+                y = pl.y[pidx];
+                if (e < n1) {
+                    // particle p (in the bra), hole q (in the ket); the Coulomb weight
+                    // needs equal continuum spins and a spin-conserving excitation, the
+                    // exchange weight a particle of the ket's continuum spin and a hole
+                    // of the bra's (the spin-flip pairs of doublet-coupled triplets)
+                    const int s = pl.phase[pidx];
+                    const uint64_t lab = pl.label[pidx];
+                    const int sp = lab_field(lab, 0) & 1, sq = lab_field(lab, 1) & 1;
+                    const int sx = spa ? spa[x] : 0, sy = spb ? spb[y] : 0;
+                    a = (sx == sy && sp == sq) ? s : 0;
+                    b = (sp == sy && sq == sx) ? s : 0;
+                } else {
+                    // occupation of spatial orbital P in the bra determinant (both spins;
+                    // the continuum spin's for the exchange weight)
+                    const uint64_t *d = da + (size_t)x * W;
+                    const int ka = 2 * P, kb = 2 * P + 1;
+                    const int oa = (int)((d[ka >> 6] >> (ka & 63)) & 1ull);
+                    const int ob = (int)((d[kb >> 6] >> (kb & 63)) & 1ull);
+                    const int sx = spa ? spa[x] : 0;
+                    a = oa + ob;
+                    b = sx ? ob : oa;
+                }
+            }
+            w = in ? (a + 2) | ((b + 2) << 4) : 0x22;
+        };
+        int32_t xn = 0, yn = 0, wn = 0;
+        if (64 * wv < ntot) entry(64 * wv + lane, xn, yn, wn);
+        for (int64_t e0 = 64 * wv; e0 < ntot; e0 += 64 * GAM_W) {
+            const int32_t x = xn, y = yn, w = wn;
+            if (e0 + 64 * GAM_W < ntot) entry(e0 + 64 * GAM_W + lane, xn, yn, wn);
+            const int steps = (int)((min<int64_t>(64, ntot - e0) + 3) / 4);
+            for (int u0 = 0; u0 < steps; u0 += GAM_U) {   // (entries past the end: weights 0)
+                double av[GAM_U], bv[GAM_U][NB];
+                int32_t ww[GAM_U];
+#pragma unroll
+                for (int u = 0; u < GAM_U; ++u) {
+                    const int src = 4 * (u0 + u) + hi;
+                    const size_t xx = (size_t)__shfl(x, src) * Sa, yy = (size_t)__shfl(y, src) * Sb;
+                    ww[u] = __shfl(w, src);
+                    av[u] = ca_l[xx];
+#pragma unroll
+                    for (int b = 0; b < NB; ++b)
+                        if (b < nbt) bv[u][b] = cb_l[b][yy];
+                }
+#pragma unroll
+                for (int u = 0; u < GAM_U; ++u) {
+                    const double aj = av[u] * (double)((ww[u] & 15) - 2), ak = av[u] * (double)((ww[u] >> 4) - 2);
+#pragma unroll
+                    for (int b = 0; b < NB; ++b)
+                        if (b < nbt) {
+                            J[b] = __builtin_amdgcn_mfma_f64_16x16x4f64(aj, bv[u][b], J[b], 0, 0, 0);
+                            K[half][b] = __builtin_amdgcn_mfma_f64_16x16x4f64(ak, bv[u][b], K[half][b], 0, 0, 0);
                         }
-                        J[q] = j;
-                        K[half][q] = kk;
-                    }
                 }
             }
         }
-        const size_t t = t0, nt = gl.n;
+    }
+    // the waves' sums, in order; a lane holds states na0 + hi + 4 v of the bra
+    // and nb0 + 16 b + lo of the ket
+    constexpr int NO = (NB * 256 + 64 * GAM_W - 1) / (64 * GAM_W);   // outputs a thread
+    double out[3][NO];
 #pragma unroll
-        for (int q = 0; q < GAM_RPT; ++q) {
-            const int r = rbase + threadIdx.x + 256 * q;
-            if (r < nrows) {
-                At[t * nrows + r] = J[q];
-                if (gl.mode == GAM_PLAIN) {
-                    At[(nt + t) * nrows + r] = K[0][q];
-                } else if (gl.mode == GAM_RECT) {
-                    At[(nt + 2 * t) * nrows + r] = K[0][q];
-                    At[(nt + 2 * t + 1) * nrows + r] = K[1][q];
-                } else if (ks[1] < 0) {
-                    At[(nt + t) * nrows + r] = -K[0][q];
-                } else {
-                    At[(nt + t) * nrows + r] = -0.5 * (K[0][q] + K[1][q]);
-                    At[(2 * nt + t) * nrows + r] = -0.5 * (K[0][q] - K[1][q]);
-                }
-            }
+    for (int q = 0; q < 3; ++q) {
+        if (q == 2 && ks[1] < 0) break;
+        __syncthreads();
+        if (wv < waves)
+#pragma unroll
+            for (int b = 0; b < NB; ++b)
+#pragma unroll
+                for (int v = 0; v < 4; ++v)
+                    red[wv][256 * b + 16 * (hi + 4 * v) + lo] = q == 0 ? J[b][v] : K[q - 1][b][v];
+        __syncthreads();
+#pragma unroll
+        for (int o = 0; o < NO; ++o) {
+            const int e = (int)threadIdx.x + 64 * GAM_W * o;
+            double s = 0.0;
+            if (e < 256 * nbt)
+                for (int z = 0; z < waves; ++z) s += red[z][e];
+            out[q][o] = s;
+        }
+    }
+    const size_t t = t0, nt = gl.n;
+#pragma unroll
+    for (int o = 0; o < NO; ++o) {
+        const int e = (int)threadIdx.x + 64 * GAM_W * o;
+        const int n = na0 + ((e >> 4) & 15), n2 = nb0 + 16 * (e >> 8) + (e & 15);
+        if (e >= 256 * nbt || n >= Sa || n2 >= Sb || (tri && n2 > n)) continue;
+        const size_t r = tri ? (size_t)n * (n + 1) / 2 + n2 : (size_t)n * Sb + n2;
+        At[t * nrows + r] = out[0][o];
+        if (gl.mode == GAM_PLAIN) {
+            At[(nt + t) * nrows + r] = out[1][o];
+        } else if (gl.mode == GAM_RECT) {
+            At[(nt + 2 * t) * nrows + r] = out[1][o];
+            At[(nt + 2 * t + 1) * nrows + r] = out[2][o];
+        } else if (ks[1] < 0) {
+            At[(nt + t) * nrows + r] = -out[1][o];
+        } else {
+            At[(nt + t) * nrows + r] = -0.5 * (out[1][o] + out[2][o]);
+            At[(2 * nt + t) * nrows + r] = -0.5 * (out[1][o] - out[2][o]);
         }
     }
 }
 
+// rows r = (n, n'): every pair of states, or with tri (a symmetry with itself)
+// those with n' <= n; n' runs fastest
 hipError_t launch_gamma(int W, PairList pl, const int64_t *start, const int64_t *count,
                         const int64_t *sorted, const int64_t *d0, int M0, const int32_t *slotP, const int32_t *slotQ,
                         const GammaList &gl, const uint64_t *da, const int8_t *spa, const int8_t *spb, const double *ca,
-                        int Sa, const double *cb, int Sb, int nrows, const int32_t *rn, const int32_t *rn2, double *At,
-                        hipStream_t st)
+                        int Sa, const double *cb, int Sb, bool tri, double *At, hipStream_t st)
 {
+    const int nrows = tri ? Sa * (Sa + 1) / 2 : Sa * Sb;
     if (gl.n <= 0 || nrows <= 0) return hipSuccess;
-    const size_t shm = sizeof(double) * GAM_BATCH * (size_t)(Sa + Sb);
-    const dim3 g(gl.n), b(256);
-    switch (W) {
-    case 1: hipLaunchKernelGGL((k_gamma<1>), g, b, shm, st, pl, start, count, sorted, d0, M0, slotP, slotQ, gl, da, spa, spb, ca, Sa, cb, Sb, nrows, rn, rn2, At); break;
-    case 2: hipLaunchKernelGGL((k_gamma<2>), g, b, shm, st, pl, start, count, sorted, d0, M0, slotP, slotQ, gl, da, spa, spb, ca, Sa, cb, Sb, nrows, rn, rn2, At); break;
-    case 3: hipLaunchKernelGGL((k_gamma<3>), g, b, shm, st, pl, start, count, sorted, d0, M0, slotP, slotQ, gl, da, spa, spb, ca, Sa, cb, Sb, nrows, rn, rn2, At); break;
-    case 4: hipLaunchKernelGGL((k_gamma<4>), g, b, shm, st, pl, start, count, sorted, d0, M0, slotP, slotQ, gl, da, spa, spb, ca, Sa, cb, Sb, nrows, rn, rn2, At); break;
+    const int NB = Sb > 16 ? 2 : 1, groups = (Sb + 16 * NB - 1) / (16 * NB);
+    const dim3 g(gl.n, (Sa + 15) / 16, groups), b(64 * GAM_W);
+#define GAMMA(W_, NB_)                                                                                              \
+    case 8 * W_ + NB_:                                                                                              \
+        hipLaunchKernelGGL((k_gamma<W_, NB_>), g, b, 0, st, pl, start, count, sorted, d0, M0, slotP, slotQ, gl, da, \
+                           spa, spb, ca, Sa, cb, Sb, (int)tri, nrows, At);                                          \
+        break;
+#define GAMMA_W(W_) GAMMA(W_, 1) GAMMA(W_, 2)
+    switch (8 * W + NB) {
+        GAMMA_W(1)
+        GAMMA_W(2)
+        GAMMA_W(3)
+        GAMMA_W(4)
     default: return hipErrorInvalidValue;
     }
+#undef GAMMA_W
+#undef GAMMA
     return hipGetLastError();
 }
 
