@@ -67,7 +67,8 @@ hipError_t launch_slices(const double *At, int nrows, const double *B, int K, in
                          double *sigA, __bf16 *SA, double *sigB, __bf16 *SB, hipStream_t st);
 hipError_t launch_expand_bf16split(const __bf16 *SA, const __bf16 *SB, const double *sigA, const double *sigB,
                                    int s, int nrows, int N, int ldk, const ExpandEpi &ep, hipStream_t st);
-hipError_t launch_class4(int W, const Class4Args &a, int n_l2, hipStream_t st);
+hipError_t launch_class4(const Class4Args &a, int n_l2, hipStream_t st);
+int c4_items(int S, int nc, int n_l2);
 struct L2Args {
     const uint64_t *dets;
     int n_l2;
@@ -93,7 +94,7 @@ int64_t l2_tiles(int n_l2);
 hipError_t launch_expand_f64_batched(const GemmTask *tasks, int ntask, int64_t total, int bm, int grid,
                                      hipStream_t st);
 hipError_t launch_l2_batched(int W, const L2Task *tasks, int ntask, int64_t total, int grid, hipStream_t st);
-hipError_t launch_class4_batched(int W, const C4Task *tasks, int ntask, int64_t total, int grid, hipStream_t st);
+hipError_t launch_class4_batched(const C4Task *tasks, int ntask, int64_t total, int grid, hipStream_t st);
 hipError_t launch_mirror(double *H, int64_t ld, int D, int C, hipStream_t st);
 hipError_t launch_scatter_pairs(const int32_t *px, const int32_t *py, const double *v, int64_t n, int transpose,
                                 double *out, int64_t ldo, hipStream_t st);
@@ -1206,7 +1207,7 @@ static Class4Args class4_args(cch_ctx *c, const LtPlan &L)
     a.ld = c->ldb;
     a.row_l2 = c->Dc;
     a.col0 = s.row0;
-    a.pairs_per_chunk = std::max(1, std::min(64, 1024 / (1 + 2 * c->n_elec)));
+    a.W = c->W;
     return a;
 }
 
@@ -1404,7 +1405,7 @@ static cch_status enqueue_class4(cch_ctx *c, hipStream_t st, bool fan)
     const Fan f{c, st, fan && c->have_aux};
     HIPCK(c, f.begin());
     int w = 0;
-    for (auto &L : c->lt) HIPCK(c, launch_class4(c->W, class4_args(c, L), c->n_l2, f(w++)));
+    for (auto &L : c->lt) HIPCK(c, launch_class4(class4_args(c, L), c->n_l2, f(w++)));
     HIPCK(c, f.end());
     return CCH_OK;
 }
@@ -2617,7 +2618,7 @@ static cch_status batch_gemm(cch_batch *b, int bm, int grid)
 
 static cch_status batch_c4(cch_batch *b, int grid)
 {
-    for (auto &g : b->c4g) BCK(b, launch_class4_batched(g.W, (const C4Task *)g.d_tasks, g.n, g.total, grid, b->st));
+    for (auto &g : b->c4g) BCK(b, launch_class4_batched((const C4Task *)g.d_tasks, g.n, g.total, grid, b->st));
     return CCH_OK;
 }
 
@@ -2683,8 +2684,9 @@ cch_status cch_batch_create(cch_batch **out, cch_ctx *const *ctxs, int32_t n, in
     std::vector<GemmTask> g32, g64;
     int64_t t32 = 0, t64 = 0;
     std::map<int, std::vector<L2Task>> l2;
-    std::map<int, std::vector<C4Task>> c4;
-    std::map<int, int64_t> l2t, c4t;
+    std::vector<C4Task> c4;
+    std::map<int, int64_t> l2t;
+    int64_t c4t = 0;
     for (cch_ctx *c : b->cs) {
         for (auto &p : c->pp) {
             SymInfo &sa = c->syms[p.a], &sb = c->syms[p.b];
@@ -2703,9 +2705,9 @@ cch_status cch_batch_create(cch_batch **out, cch_ctx *const *ctxs, int32_t n, in
         for (auto &L : c->lt) {
             const SymInfo &s = c->syms[L.sym];
             if (s.nc == 0 || c->n_l2 == 0) continue;
-            C4Task k{class4_args(c, L), c->n_l2, (s.nc + C4_JB - 1) / C4_JB, c4t[c->W]};
-            c4t[c->W] += (int64_t)k.n_l2 * k.jtiles;
-            c4[c->W].push_back(k);
+            C4Task k{class4_args(c, L), c->n_l2, c4t};
+            c4t += c4_items(s.S, s.nc, c->n_l2);
+            c4.push_back(k);
         }
         if (c->n_l2 > 0) {
             const TgtInts I{c->d_h, c->d_tttt, c->n_o, c->n_orb, c->e_core};
@@ -2725,10 +2727,10 @@ cch_status cch_batch_create(cch_batch **out, cch_ctx *const *ctxs, int32_t n, in
         if ((rc = bupload(b, &d, kv.second)) != CCH_OK) return cleanup_fail(rc);
         b->l2g.push_back({kv.first, d, (int)kv.second.size(), l2t[kv.first]});
     }
-    for (auto &kv : c4) {
+    if (!c4.empty()) {
         C4Task *d = nullptr;
-        if ((rc = bupload(b, &d, kv.second)) != CCH_OK) return cleanup_fail(rc);
-        b->c4g.push_back({kv.first, d, (int)kv.second.size(), c4t[kv.first]});
+        if ((rc = bupload(b, &d, c4)) != CCH_OK) return cleanup_fail(rc);
+        b->c4g.push_back({0, d, (int)c4.size(), c4t});
     }
     int cus = 256;
     {

@@ -428,18 +428,23 @@ struct Class4Args {
     int64_t ld;
     int64_t row_l2;          // first L2 row of the matrix
     int64_t col0;            // first column of the symmetry block
-    int pairs_per_chunk;
+    int W;                   // words per determinant
+};
+
+constexpr int CCH_MAX_WORDS = 4;   // words per determinant at most
+
+// passes over the states of nq quads each, blocks of bt tiles of 16 orbitals,
+// lpw L2 functions a workgroup
+struct C4Split {
+    int passes, nq, blocks, bt, lpw;
 };
 
 // one (instance, symmetry) block of the persistent class-4 launch
 struct C4Task {
     Class4Args a;
-    int n_l2, jtiles;
+    int n_l2;
     int64_t first;   // first global work item of this block
 };
-
-// continuum orbitals per class-4 workgroup (the j block of one L2 row)
-constexpr int C4_JB = 512;
 
 struct SparseMat {
     const double *P;

@@ -14,232 +14,332 @@
 //   double (chi_l = D_m - p + h1 + h2), sign s:
 //       s [ (P H1|H2 j) d(sp,sh1) d(sigma_m,sh2) - (P H2|H1 j) d(sp,sh2) d(sigma_m,sh1) ]
 // (sigma_m the continuum spin given with D_m, alpha unless stated).
-// The product runs on the FP64 matrix cores: for a block of 64 terms the
-// A operand is (coef_t c_{m_t n}) (terms x states, staged in LDS from the CI
-// rows) and the B operand the gathered integral rows X_t[j] (terms x j),
-// read straight from memory, 16 states x 16 continuum orbitals per MFMA
-// tile. One workgroup per (l, block of 512 j); each of its four waves takes
-// pairs of j tiles and every state tile, so each integral value is read once
-// per workgroup. Pairs are turned into terms in order and the term blocks are
-// added in order, so the accumulation order is fixed.
+// The product runs on the FP64 matrix cores in the 4x4x4 form (a quad of states
+// by 16 continuum orbitals by 4 terms): its rows come in fours, so 4 or 5 states
+// are not padded to 16, and it issues faster per flop than 16x16x4. A workgroup
+// takes a few L2 functions, up to 16 quads of states and up to four tiles of 32
+// orbitals, a wave each, two neighbouring orbitals a lane (16-byte loads and
+// stores: the rows begin anywhere in a line, and shorter pieces touch more of
+// them); the sums stay in registers over all terms. Each function's terms are
+// listed in LDS by one wave, a pair a lane; blocks of c4_tb of them are
+// multiplied, (coef_t c_{m_t n}) staged in LDS for all waves and the integral
+// rows read straight from memory, both for the next block (of the next function
+// too) while this one is multiplied: two buffers, one barrier a block. Pairs are
+// turned into terms in order and terms are added in order, so the accumulation
+// order is fixed.
+// Bound by the chain of an item (pairs, determinants, terms, then rows block by
+// block) against the items that a CU holds, and by the stores: with the products
+// left out it takes three quarters of its time, with the blocks left out a third.
+// Measured alone at 40 states, 300 orbitals, 28000 functions of 35 pairs: 1.69 ms
+// (0.8 of it matrix-core time, 2.7 GB written); 5.01 with blocks of 64 terms of
+// one function on 16x16x4, staged and multiplied in turn. At 5 states, 150
+// orbitals, 5000 functions of 5 pairs: 30 us (115).
 #include <algorithm>
 
 #include "ccham_internal.h"
 
 namespace cch {
 
+constexpr int C4_TERMS = 400;      // terms listed at a time (>= the most that a pair gives)
+constexpr int C4_W = 4;            // waves of a workgroup (more: fewer of them fit a CU, and they wait for each other)
+constexpr int C4_LPW = C4_W;       // L2 functions of a workgroup at most: a wave lists each one's terms
+// terms per block: the registers of 16 leave one workgroup a CU with many states
+constexpr int c4_tb(int nq) { return nq <= 4 ? 16 : 8; }
+static_assert(C4_TERMS >= 96 * CCH_MAX_WORDS, "terms of a single substitution: one, the electrons, those of a spin");
 
-constexpr int C4_TERMS = 1024;
-constexpr int C4_TB = 64;          // terms per MFMA block (16 k-steps)
+// LDS row stride of the staged operand: 4 doubles past a multiple of 16 or the
+// like, so that the four terms of an instruction lie in different banks
+constexpr int c4_stride(int nq) { return 4 * nq + (nq % 2 ? 0 : 4); }
 
-constexpr int C4_LA = 64 + 1;      // LDS row stride of the staged A operand
-
-struct C4Shared {
+struct C4List {
     const double *trow[C4_TERMS];
-    double tcoef[C4_TERMS];
-    int32_t tm[C4_TERMS];
-    int32_t poff[65];
-    double A[C4_TB * C4_LA];       // coef_t c[m_t][n], a block of terms x 64 states
+    int32_t tm[C4_TERMS];          // target determinant, the sign of the term in the top bit
+    int32_t nt, left;              // terms; pairs of the function not yet turned into terms
 };
 
-typedef double c4x4 __attribute__((ext_vector_type(4)));
-
-// one L2 row l and one block of C4_JB continuum orbitals
-template <int W>
-__device__ __forceinline__ void class4_row(const Class4Args &a, int l, int jblk, C4Shared &sh)
+// one wave lists the terms of the pairs p0 + (0 .. n - 1) behind the first nt,
+// as many pairs as fit (at most 64): the terms then, and the pairs taken
+__device__ __forceinline__ int c4_pairs(const Class4Args &a, int64_t p0, int64_t n, int lane, int &nt, C4List &sh)
 {
-    const double **trow = sh.trow;
-    double *tcoef = sh.tcoef;
-    int32_t *tm = sh.tm;
-    int32_t *poff = sh.poff;
-    const int j0 = jblk * C4_JB, jn = min(C4_JB, a.nc - j0);
-    __syncthreads();   // the LDS term lists are reused by the next row of a persistent loop
-    const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
+    const bool in = lane < n;
+    const int64_t pi = p0 + (in ? lane : 0);
+    const int deg = a.pl.deg[pi], m = a.pl.y[pi];
+    const uint64_t lab = a.pl.label[pi];
+    const int neg = a.pl.phase[pi] < 0;
+    const int sg = a.cspin ? a.cspin[m] : 0;   // continuum spin
+    const int pt = lab_field(lab, 0), h1 = lab_field(lab, 1), h2 = lab_field(lab, 2);
+    const size_t n_o = a.n_o;
+    // (deg 1: the hole is h1)
+    const bool one = in && deg == 1 && (h1 & 1) == sg;
+    const bool ta = in && deg != 1 && (pt & 1) == (h1 & 1) && (h2 & 1) == sg;
+    const bool tb = in && deg != 1 && (pt & 1) == (h2 & 1) && (h1 & 1) == sg;
+    int cnt = (int)ta + (int)tb;
+    if (one) {
+        const uint64_t mask = sg ? 0xAAAAAAAAAAAAAAAAull : 0x5555555555555555ull;
+        cnt = 1;
+        for (int w = 0; w < a.W; ++w) {
+            const uint64_t d = a.tdets[(size_t)m * a.W + w];
+            cnt += __popcll(d) + __popcll(d & mask);
+        }
+    }
+    int incl = cnt + (lane == 0 ? nt : 0);
+#pragma unroll
+    for (int o = 1; o < 64; o <<= 1) {
+        const int y = __shfl_up(incl, o, 64);
+        if (lane >= o) incl += y;
+    }
+    const int taken = __popcll(__ballot(in && incl <= C4_TERMS));   // (incl ascends)
+    if (taken > 0) nt = __shfl(incl, taken - 1);
+    int o = incl - cnt;
+    if (lane < taken) {
+        const size_t P = pt >> 1, H1 = h1 >> 1, H2 = h2 >> 1;
+        if (ta) {
+            sh.trow[o] = a.tttc + ((P * n_o + H1) * n_o + H2) * a.n_cont + a.ja0;
+            sh.tm[o++] = m | (neg ? INT32_MIN : 0);
+        }
+        if (tb) {
+            sh.trow[o] = a.tttc + ((P * n_o + H2) * n_o + H1) * a.n_cont + a.ja0;
+            sh.tm[o] = m | (neg ? 0 : INT32_MIN);
+        }
+    }
+    // single substitutions, one after another: a spin-orbital of D_m a lane
+    for (uint64_t todo = __ballot(one && lane < taken); todo; todo &= todo - 1) {
+        const int src = (int)__builtin_ctzll(todo);
+        const int mm = __shfl(m, src), sgn = __shfl(neg, src), sp = __shfl(sg, src);
+        const size_t H = (size_t)(__shfl(h1, src) >> 1);
+        int at = __shfl(incl - cnt, src);
+        const int32_t plus = mm | (sgn ? INT32_MIN : 0), minus = mm | (sgn ? 0 : INT32_MIN);
+        const uint64_t mask = sp ? 0xAAAAAAAAAAAAAAAAull : 0x5555555555555555ull;
+        if (lane == 0) {
+            sh.trow[at] = a.h + H * a.n_orb + a.n_o + a.ja0;
+            sh.tm[at] = plus;
+        }
+        ++at;
+        for (int w = 0; w < a.W; ++w) {
+            const uint64_t d = a.tdets[(size_t)mm * a.W + w], below = d & ((1ull << lane) - 1);
+            if ((d >> lane) & 1) {
+                const size_t K = (size_t)(64 * w + lane) >> 1;
+                const int q = at + __popcll(below) + __popcll(below & mask);
+                sh.trow[q] = a.tttc + ((K * n_o + K) * n_o + H) * a.n_cont + a.ja0;
+                sh.tm[q] = plus;
+                if ((lane & 1) == sp) {
+                    sh.trow[q + 1] = a.tttc + ((K * n_o + H) * n_o + K) * a.n_cont + a.ja0;
+                    sh.tm[q + 1] = minus;
+                }
+            }
+            at += __popcll(d) + __popcll(d & mask);
+        }
+    }
+    return taken;
+}
+
+// one wave lists the next terms of a function whose last `left` pairs end at p1
+__device__ __forceinline__ void c4_list(const Class4Args &a, int64_t p1, int left, int lane, C4List &sh)
+{
+    int nt = 0;
+    while (left > 0) {
+        const int k = c4_pairs(a, p1 - left, left, lane, nt, sh);
+        if (k == 0) break;
+        left -= k;
+    }
+    if (lane == 0) {
+        sh.nt = nt;
+        sh.left = left;
+    }
+}
+
+typedef double c4d2 __attribute__((ext_vector_type(2), aligned(8)));
+
+// the states s0 + (0 .. 4 NQ - 1) and the tiles t0 + (0 .. tiles - 1) of 32
+// orbitals, one a wave, of the L2 rows l0 .. l0 + nl - 1, nl <= C4_LPW
+template <int NQ, bool PAIR>
+__device__ __forceinline__ void class4_item(const Class4Args &a, int l0, int nl, int s0, int t0, int tiles,
+                                            C4List *__restrict__ lists, double *__restrict__ stage)
+{
+    constexpr int C4_TB = c4_tb(NQ), LA = c4_stride(NQ), NE = (C4_TB * 4 * NQ + 64 * C4_W - 1) / (64 * C4_W);
+    const int lane = threadIdx.x & 63, wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int lo = lane & 15, hi = lane >> 4;
-    const int64_t p0 = a.row_off[l], np = a.row_cnt[l];
-    const int jtiles = (jn + 15) / 16;
-    double *out = a.H + (a.row_l2 + l) * a.ld + a.col0 + j0;
-    bool have = false;   // some term block has written the outputs
+    const bool mine = wv < tiles;   // this wave has a tile
+    // this lane's two orbitals; past the end the last two again, which then are
+    // computed and stored twice alike
+    const int jo = PAIR ? min(32 * (t0 + wv) + 2 * lo, a.nc - 2) : 0;
+    double *out0 = a.H + a.row_l2 * a.ld + a.col0 + jo;
 
-    for (int64_t c0 = 0; c0 < np; c0 += a.pairs_per_chunk) {
-        const int nc_pairs = (int)min<int64_t>(a.pairs_per_chunk, np - c0);
-        __syncthreads();
-        // count the terms of each pair; offsets by a scan across wave 0
-        if (threadIdx.x < 64) {
-            int cnt = 0;
-            if (threadIdx.x < nc_pairs) {
-                const int64_t pi = p0 + c0 + threadIdx.x;
-                const int deg = a.pl.deg[pi];
-                const uint64_t lab = a.pl.label[pi];
-                const int sg = a.cspin ? a.cspin[a.pl.y[pi]] : 0;   // continuum spin
-                if (deg == 1) {
-                    const int h = lab_field(lab, 1);
-                    if ((h & 1) == sg) {
-                        const uint64_t *d = a.tdets + (size_t)a.pl.y[pi] * W;
-                        const uint64_t mask = sg ? 0xAAAAAAAAAAAAAAAAull : 0x5555555555555555ull;
-                        int ne = 0, ns = 0;
+    double acc[2][NQ], st[NE];
+    int32_t sg[NE];   // sign of st (applied when it is used, not to wait for it before the products), 0: no term
+    c4d2 b[C4_TB / 4];
+    auto clear = [&]() {
 #pragma unroll
-                        for (int w = 0; w < W; ++w) {
-                            ne += __popcll(d[w]);
-                            ns += __popcll(d[w] & mask);
-                        }
-                        cnt = 1 + ne + ns;
-                    }
-                } else {
-                    const int pt = lab_field(lab, 0), h1 = lab_field(lab, 1), h2 = lab_field(lab, 2);
-                    cnt = ((pt & 1) == (h1 & 1) && (h2 & 1) == sg) + ((pt & 1) == (h2 & 1) && (h1 & 1) == sg);
-                }
-            }
-            int incl = cnt;
+        for (int q = 0; q < NQ; ++q) acc[0][q] = acc[1][q] = 0.0;
+    };
+    // the block of terms tb .. of function il: this thread's part of the staged
+    // operand and this wave's rows (past the end the last term again, times 0)
+    auto load = [&](int il, int tb) {
+        const C4List &sh = lists[il];
+        const int tn = min(C4_TB, sh.nt - tb);
 #pragma unroll
-            for (int o = 1; o < 64; o <<= 1) {
-                const int y = __shfl_up(incl, o, 64);
-                if ((int)threadIdx.x >= o) incl += y;
-            }
-            if ((int)threadIdx.x < nc_pairs) poff[threadIdx.x] = incl - cnt;
-            if ((int)threadIdx.x == nc_pairs - 1) poff[nc_pairs] = incl;
+        for (int u = 0; u < NE; ++u) {
+            const int e = (int)threadIdx.x + 64 * C4_W * u, t = e / (4 * NQ), s = e % (4 * NQ);
+            const int32_t tm = sh.tm[tb + min(t, tn - 1)];
+            st[u] = a.ci[(size_t)(tm & INT32_MAX) * a.S + min(s0 + s, a.S - 1)];
+            sg[u] = t < tn ? (tm | 1) : 0;
         }
-        __syncthreads();
-        // generate the terms of each pair at its offset
-        if (threadIdx.x < nc_pairs) {
-            const int64_t pi = p0 + c0 + threadIdx.x;
-            const int deg = a.pl.deg[pi];
-            const uint64_t lab = a.pl.label[pi];
-            const double s = (double)a.pl.phase[pi];
-            const int m = a.pl.y[pi];
-            const int sg = a.cspin ? a.cspin[m] : 0;
-            int o = poff[threadIdx.x];
-            const size_t n_o = a.n_o;
-            if (deg == 1) {
-                const int h = lab_field(lab, 1);
-                if ((h & 1) == sg) {
-                    const int H = h >> 1;
-                    trow[o] = a.h + (size_t)H * a.n_orb + a.n_o + a.ja0;
-                    tcoef[o] = s;
-                    tm[o++] = m;
-                    const uint64_t *d = a.tdets + (size_t)m * W;
+        if (mine)
 #pragma unroll
-                    for (int w = 0; w < W; ++w) {
-                        uint64_t x = d[w];
-                        while (x) {
-                            const int k = 64 * w + (int)__builtin_ctzll(x);
-                            x &= x - 1;
-                            const size_t K = k >> 1;
-                            trow[o] = a.tttc + ((K * n_o + K) * n_o + H) * a.n_cont + a.ja0;
-                            tcoef[o] = s;
-                            tm[o++] = m;
-                            if ((k & 1) == sg) {
-                                trow[o] = a.tttc + ((K * n_o + H) * n_o + K) * a.n_cont + a.ja0;
-                                tcoef[o] = -s;
-                                tm[o++] = m;
-                            }
-                        }
-                    }
-                }
-            } else {
-                const int pt = lab_field(lab, 0), h1 = lab_field(lab, 1), h2 = lab_field(lab, 2);
-                const size_t P = pt >> 1, H1 = h1 >> 1, H2 = h2 >> 1;
-                if ((pt & 1) == (h1 & 1) && (h2 & 1) == sg) {
-                    trow[o] = a.tttc + ((P * n_o + H1) * n_o + H2) * a.n_cont + a.ja0;
-                    tcoef[o] = s;
-                    tm[o++] = m;
-                }
-                if ((pt & 1) == (h2 & 1) && (h1 & 1) == sg) {
-                    trow[o] = a.tttc + ((P * n_o + H2) * n_o + H1) * a.n_cont + a.ja0;
-                    tcoef[o] = -s;
-                    tm[o++] = m;
-                }
+            for (int u = 0; u < C4_TB / 4; ++u) {
+                const double *row = sh.trow[tb + min(4 * u + hi, tn - 1)] + jo;
+                if (PAIR) b[u] = *reinterpret_cast<const c4d2 *>(row);
+                else b[u] = (c4d2){row[0], 0.0};
             }
+    };
+    auto multiply = [&](const double *A, const c4d2 (&c)[C4_TB / 4], int u0, int u1) {
+#pragma unroll
+        for (int u = u0; u < u1; ++u) {
+            const double *Au = A + (4 * u + hi) * LA + (lane & 3);
+#pragma unroll
+            for (int q = 0; q < NQ; ++q) {
+                const double av = Au[4 * q];
+                acc[0][q] = __builtin_amdgcn_mfma_f64_4x4x4f64(av, c[u].x, acc[0][q], 0, 0, 0);
+                if (PAIR) acc[1][q] = __builtin_amdgcn_mfma_f64_4x4x4f64(av, c[u].y, acc[1][q], 0, 0, 0);
+            }
+            __builtin_amdgcn_sched_barrier(0);   // (the operands of every step at once would spill)
         }
-        __syncthreads();
-        const int nt = poff[nc_pairs];
-        // out[n][j] (+)= sum_t (coef_t c[m_t][n]) X_t[j], blocks of C4_TB terms:
-        // the A operand (coef_t c[m_t][n]) of a block and 64 states is staged in
-        // LDS; each wave takes pairs of 16-orbital j tiles and all state tiles of
-        // the pass, so an integral value is loaded once per workgroup
-        for (int tb = 0; tb < nt; tb += C4_TB) {
-            const int tn = min(C4_TB, nt - tb);
-            for (int nb = 0; nb < a.S; nb += 64) {
-                __syncthreads();   // the previous block's A is no longer read
-                for (int e = threadIdx.x; e < C4_TB * 64; e += blockDim.x) {
-                    const int t = e >> 6, n = nb + (e & 63);
-                    sh.A[t * C4_LA + (e & 63)] =
-                        (t < tn && n < a.S) ? tcoef[tb + t] * a.ci[(size_t)tm[tb + t] * a.S + n] : 0.0;
+    };
+    // lane holds state 4 q + hi of its orbitals
+    auto store = [&](int il) {
+        if (!mine) return;
+        int nc = a.nc, S = a.S;
+        asm volatile("" : "+s"(nc), "+s"(S));   // (the offsets of every quad kept over the functions would spill)
+        double *o = out0 + (int64_t)(l0 + il) * a.ld + (int64_t)(s0 + hi) * nc;
+#pragma unroll
+        for (int q = 0; q < NQ; ++q) {
+            if (s0 + 4 * q + hi < S) {
+                if (PAIR) *reinterpret_cast<c4d2 *>(o) = (c4d2){acc[0][q], acc[1][q]};
+                else if (lo == 0) *o = acc[0][q];
+            }
+            o += 4 * (int64_t)nc;
+        }
+    };
+
+    __syncthreads();   // the lists of the item before are no longer read
+    if (wv < nl) c4_list(a, a.row_off[l0 + wv] + a.row_cnt[l0 + wv], (int)a.row_cnt[l0 + wv], lane, lists[wv]);
+    __syncthreads();
+    clear();
+    for (int il = 0; il < nl; ++il)   // no terms: the row of the block is zero
+        if (lists[il].nt == 0) store(il);
+    int il = 0, buf = 0;
+    auto next = [&](int i) {   // the next function with terms
+        do ++i;
+        while (i < nl && lists[i].nt == 0);
+        return i;
+    };
+    il = next(-1);
+    if (il < nl) load(il, 0);
+    while (il < nl) {
+        clear();
+        const int ni = next(il);
+        for (;;) {
+            const int nt = lists[il].nt, left = lists[il].left;
+            for (int tb = 0; tb < nt; tb += C4_TB) {
+                double *A = stage + buf * C4_TB * LA;
+                buf ^= 1;   // (its last readers are behind the barrier of the block between)
+#pragma unroll
+                for (int u = 0; u < NE; ++u) {
+                    const int e = (int)threadIdx.x + 64 * C4_W * u;
+                    if (e < C4_TB * 4 * NQ)
+                        A[e / (4 * NQ) * LA + e % (4 * NQ)] = sg[u] > 0 ? st[u] : (sg[u] < 0 ? -st[u] : 0.0);
                 }
+                c4d2 c[C4_TB / 4];
+#pragma unroll
+                for (int u = 0; u < C4_TB / 4; ++u) c[u] = b[u];
                 __syncthreads();
-                const int nts = min(4, (a.S - nb + 15) / 16);
-                for (int jt = 2 * wv; jt < jtiles; jt += 8) {
-                    const int ja = 16 * jt + lo, jb = ja + 16;
-                    c4x4 acc[4][2];
-#pragma unroll
-                    for (int q = 0; q < 4; ++q) acc[q][0] = acc[q][1] = (c4x4){0.0, 0.0, 0.0, 0.0};
-#pragma unroll 4
-                    for (int u = 0; u < C4_TB / 4; ++u) {
-                        if (4 * u < tn) {
-                            const int t = 4 * u + hi;
-                            const double *tr = t < tn ? trow[tb + t] : nullptr;
-                            const double b0 = (tr && ja < jn) ? tr[j0 + ja] : 0.0;
-                            const double b1 = (tr && jb < jn) ? tr[j0 + jb] : 0.0;
-#pragma unroll
-                            for (int q = 0; q < 4; ++q) {
-                                if (q < nts) {
-                                    const double av = sh.A[t * C4_LA + 16 * q + lo];
-                                    acc[q][0] = __builtin_amdgcn_mfma_f64_16x16x4f64(av, b0, acc[q][0], 0, 0, 0);
-                                    acc[q][1] = __builtin_amdgcn_mfma_f64_16x16x4f64(av, b1, acc[q][1], 0, 0, 0);
-                                }
-                            }
-                        }
-                    }
-                    // lane holds state nb + 16 q + hi + 4 v of orbitals ja and jb
-#pragma unroll
-                    for (int q = 0; q < 4; ++q)
-#pragma unroll
-                        for (int v = 0; v < 4; ++v) {
-                            const int nn = nb + 16 * q + hi + 4 * v;
-                            if (q < nts && nn < a.S) {
-                                double *o = out + (size_t)nn * a.nc;
-                                if (ja < jn) o[ja] = have ? o[ja] + acc[q][0][v] : acc[q][0][v];
-                                if (jb < jn) o[jb] = have ? o[jb] + acc[q][1][v] : acc[q][1][v];
-                            }
-                        }
+                // the next block, unless its terms are yet to be listed
+                const bool more = tb + C4_TB < nt;
+                if (more || (left == 0 && ni < nl)) load(more ? il : ni, more ? tb + C4_TB : 0);
+                if (mine) {
+                    multiply(A, c, 0, C4_TB / 8);
+                    if (nt - tb > C4_TB / 2) multiply(A, c, C4_TB / 8, C4_TB / 4);
                 }
             }
-            have = true;
+            if (left == 0) break;
+            __syncthreads();   // the list has been read
+            if (wv == 0) c4_list(a, a.row_off[l0 + il] + a.row_cnt[l0 + il], left, lane, lists[il]);
+            __syncthreads();
+            // (the last pairs may give no terms)
+            if (lists[il].nt > 0) load(il, 0);
+            else if (ni < nl) load(ni, 0);
         }
-    }
-    if (!have) {
-        // no terms: the row of the block is zero
-        for (int e = threadIdx.x; e < a.S * jn; e += blockDim.x) out[(size_t)(e / jn) * a.nc + e % jn] = 0.0;
+        store(il);
+        il = ni;
     }
 }
 
-template <int W>
-__global__ __launch_bounds__(256) void k_class4(Class4Args a, int n_l2)
+// how the states and orbitals of a block are split: passes of at most 16 quads
+// of states, blocks of at most C4_W tiles of 32 orbitals. Functions go four to a
+// workgroup once that leaves 1024 of them
+__host__ __device__ inline C4Split c4_split(int S, int nc, int n_l2)
 {
-    __shared__ C4Shared sh;
-    if ((int)blockIdx.x >= n_l2) return;
-    class4_row<W>(a, blockIdx.x, blockIdx.y, sh);
+    C4Split p;
+    const int quads = (S + 3) / 4, tiles = (nc + 31) / 32;
+    p.passes = (quads + 15) / 16;
+    p.nq = (quads + p.passes - 1) / p.passes;
+    p.blocks = (tiles + C4_W - 1) / C4_W;
+    p.bt = (tiles + p.blocks - 1) / p.blocks;
+    p.blocks = (tiles + p.bt - 1) / p.bt;
+    p.lpw = (int64_t)n_l2 * p.passes * p.blocks >= 4096 ? C4_LPW : 1;
+    return p;
 }
 
-hipError_t launch_class4(int W, const Class4Args &a, int n_l2, hipStream_t st)
+int c4_items(int S, int nc, int n_l2)   // work items of a block
+{
+    const C4Split p = c4_split(S, nc, n_l2);
+    return p.passes * p.blocks * ((n_l2 + p.lpw - 1) / p.lpw);
+}
+
+template <int NQ, bool PAIR>
+__device__ __forceinline__ void class4_at(const Class4Args &a, const C4Split &p, int n_l2, int g, int part,
+                                          C4List *lists, double *stage)
+{
+    const int t0 = part % p.blocks * p.bt, s0 = part / p.blocks * 4 * p.nq, l0 = g * p.lpw;
+    class4_item<NQ, PAIR>(a, l0, min(p.lpw, n_l2 - l0), s0, t0, min(p.bt, (a.nc + 31) / 32 - t0), lists, stage);
+}
+
+template <int NQ, bool PAIR>
+__global__ __launch_bounds__(64 * C4_W, NQ <= 13 ? 4 : 3) void k_class4(Class4Args a, C4Split p, int n_l2)
+{
+    __shared__ C4List lists[C4_LPW];
+    __shared__ double stage[2 * c4_tb(NQ) * c4_stride(NQ)];
+    class4_at<NQ, PAIR>(a, p, n_l2, blockIdx.x, blockIdx.y, lists, stage);
+}
+
+// the smallest instance that holds p.nq quads; a single continuum orbital is no
+// pair to load
+#define C4_INSTANCES(X)                                                                             \
+    X(a.nc > 1, 1, true) X(a.nc > 1, 2, true) X(a.nc > 1, 3, true) X(a.nc > 1, 4, true)             \
+    X(a.nc > 1, 6, true) X(a.nc > 1, 8, true) X(a.nc > 1, 10, true) X(a.nc > 1, 13, true)           \
+    X(a.nc > 1, 16, true) X(true, 4, false) X(true, 16, false)
+
+hipError_t launch_class4(const Class4Args &a, int n_l2, hipStream_t st)
 {
     if (n_l2 <= 0 || a.nc <= 0 || a.S <= 0) return hipSuccess;
-    const dim3 g(n_l2, (a.nc + C4_JB - 1) / C4_JB), b(256);
-    switch (W) {
-    case 1: hipLaunchKernelGGL((k_class4<1>), g, b, 0, st, a, n_l2); break;
-    case 2: hipLaunchKernelGGL((k_class4<2>), g, b, 0, st, a, n_l2); break;
-    case 3: hipLaunchKernelGGL((k_class4<3>), g, b, 0, st, a, n_l2); break;
-    case 4: hipLaunchKernelGGL((k_class4<4>), g, b, 0, st, a, n_l2); break;
-    default: return hipErrorInvalidValue;
+    if (a.W < 1 || a.W > CCH_MAX_WORDS) return hipErrorInvalidValue;
+    const C4Split p = c4_split(a.S, a.nc, n_l2);
+    const dim3 g((n_l2 + p.lpw - 1) / p.lpw, p.passes * p.blocks), b(64 * C4_W);
+#define C4_RUN(COND, NQ, PAIR)                                              \
+    if ((COND) && p.nq <= NQ) {                                                 \
+        hipLaunchKernelGGL((k_class4<NQ, PAIR>), g, b, 0, st, a, p, n_l2);        \
+        return hipGetLastError();                                               \
     }
-    return hipGetLastError();
+    C4_INSTANCES(C4_RUN)
+#undef C4_RUN
+    return hipErrorInvalidValue;
 }
 
-// persistent form over many (instance, symmetry) blocks with the same word count
-template <int W>
-__global__ __launch_bounds__(256) void k_class4_batched(const C4Task *__restrict__ tasks, int ntask, int64_t total)
+// persistent form over many (instance, symmetry) blocks
+__global__ __launch_bounds__(64 * C4_W, 2) void k_class4_batched(const C4Task *__restrict__ tasks, int ntask, int64_t total)
 {
-    __shared__ C4Shared sh;
+    __shared__ C4List lists[C4_LPW];
+    __shared__ double stage[2 * c4_tb(16) * c4_stride(16)];
     for (int64_t t = blockIdx.x; t < total; t += gridDim.x) {
         int lo = 0, hi = ntask - 1;
         while (lo < hi) {
@@ -249,21 +349,24 @@ __global__ __launch_bounds__(256) void k_class4_batched(const C4Task *__restrict
         }
         const C4Task &k = tasks[lo];
         const int64_t local = t - k.first;
-        class4_row<W>(k.a, (int)(local / k.jtiles), (int)(local % k.jtiles), sh);
+        const Class4Args &a = k.a;
+        const C4Split p = c4_split(a.S, a.nc, k.n_l2);
+        const int parts = p.passes * p.blocks, g = (int)(local / parts), part = (int)(local % parts);
+#define C4_RUN(COND, NQ, PAIR)                  \
+    if ((COND) && p.nq <= NQ) {                     \
+        class4_at<NQ, PAIR>(a, p, k.n_l2, g, part, lists, stage); \
+        continue;                                   \
+    }
+        C4_INSTANCES(C4_RUN)
+#undef C4_RUN
     }
 }
 
-hipError_t launch_class4_batched(int W, const C4Task *tasks, int ntask, int64_t total, int grid, hipStream_t st)
+hipError_t launch_class4_batched(const C4Task *tasks, int ntask, int64_t total, int grid, hipStream_t st)
 {
     if (total <= 0) return hipSuccess;
-    const dim3 g((unsigned)std::min<int64_t>(total, grid)), bl(256);
-    switch (W) {
-    case 1: hipLaunchKernelGGL((k_class4_batched<1>), g, bl, 0, st, tasks, ntask, total); break;
-    case 2: hipLaunchKernelGGL((k_class4_batched<2>), g, bl, 0, st, tasks, ntask, total); break;
-    case 3: hipLaunchKernelGGL((k_class4_batched<3>), g, bl, 0, st, tasks, ntask, total); break;
-    case 4: hipLaunchKernelGGL((k_class4_batched<4>), g, bl, 0, st, tasks, ntask, total); break;
-    default: return hipErrorInvalidValue;
-    }
+    const dim3 g((unsigned)std::min<int64_t>(total, grid)), bl(64 * C4_W);
+    hipLaunchKernelGGL(k_class4_batched, g, bl, 0, st, tasks, ntask, total);
     return hipGetLastError();
 }
 
