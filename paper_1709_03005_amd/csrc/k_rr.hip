@@ -6,9 +6,10 @@
 // k_rr_eig, the main path:
 //   1. G is scaled by a power of two and reduced to tridiagonal form
 //      T = Q^T G Q by Householder reflectors (kept below the subdiagonal);
-//   2. every eigenvalue of T by multisection: Sturm counts from the
+//   2. every eigenvalue of T: isolated by Sturm counts from the
 //      leading-minor recurrence (rescaled by powers of two) at many shifts
-//      at once, one thread per shift;
+//      at once, one thread per shift, then Laguerre's method, and
+//      multisection for what it leaves;
 //   3. one eigenvector of T per thread from the twisted factorisation of
 //      T - lambda I at the twist index of smallest |gamma|;
 //   4. modified Gram-Schmidt (two passes) inside clusters of eigenvalues
@@ -37,6 +38,7 @@ struct RRShared {
     double Z[RR_MAX][RR_LD];
     double d[RR_MAX], e[RR_MAX], lam[RR_MAX], tau[RR_MAX], hinv[RR_MAX];
     double sc[6][RR_MAX];        // per-phase scratch vectors
+    alignas(16) double de[RR_MAX][2];   // d_i and e_{i-1}^2 (at least 2^-120), for the counts
     double red[2][32];           // alternating reduction buffers
     union {
         int cnt[RR_NT];                  // Sturm counts; Jacobi pairing tables
@@ -79,12 +81,6 @@ __device__ __forceinline__ double rr_block_max(double v, double *red)
     double s = red[0];
     for (int w = 1; w < (int)(blockDim.x >> 6); ++w) s = fmax(s, red[w]);
     return s;
-}
-
-// element i (wave-uniform, < 128) of a vector held as lo = x[lane], hi = x[lane + 64]
-__device__ __forceinline__ double rr_get(double lo, double hi, int i)
-{
-    return i < 64 ? rr_rl(lo, i) : rr_rl(hi, i - 64);
 }
 
 // ---------------------------------------------------------------------------
@@ -206,38 +202,223 @@ __global__ __launch_bounds__(RR_NT) void k_jacobi_eig(const double *__restrict__
     rr_jacobi(sh, G, ldg, m, theta, Y, ldy, max_sweeps);
 }
 
-// Sturm count: eigenvalues of T below x, from the signs of the leading
-// principal minors of T - xI (p_{i+1} = (d_i - x) p_i - e_{i-1}^2 p_{i-1});
-// an exact zero minor counts as negative. d and e^2 come from registers
-// (d_i in lane i of dl0 / dl1, e_i^2 in lane i of ql0 / ql1). The pair
-// (p_i, p_{i-1}) is rescaled by 2^-+500 every fourth step: T is scaled to
-// entries below 2 and couplings below eps (|d_i| + |d_{i+1}|) are zeroed,
-// so four steps can neither overflow nor underflow from [2^-500, 2^500].
-__device__ __forceinline__ int rr_sturm(double dl0, double dl1, double ql0, double ql1, int n, double x)
+// Householder reduction of A (n x n, in LDS) to T: d, e, and the reflectors
+// H_k = I - tau v v^T with v_{k+1} = 1 and v_r = x_r hinv[k] below, x = row k of
+// the trailing matrix, which row k of A keeps. One workgroup of 8 waves: waves
+// 1-7 hold the matrix in registers, thread (ty, tx) of 14 x 32 the rows
+// ty + 14 i and columns tx + 32 j, and wave 0 does what is done once per step,
+// an entry or two a lane. The rows' products with x are taken before its
+// reflector is known (v = e_{k+1} + hinv x below), so a step is one pass over the
+// rows, update and product together, during which wave 0 forms the next sigma,
+// tau and hinv, and then wave 0's sums, p, w and next x between two barriers.
+// Bound by that chain (the vector units issue an instruction of a wave in four
+// cycles: what every wave does alike costs as much as the rows themselves).
+// Measured: 87 us at n = 80 and 31 at n = 40, where the matrix in LDS, the
+// vector work in every wave and two barriers a step took 143 and 48.
+constexpr int RR_TY = 14, RR_TX = 32;
+constexpr int RR_RI = (RR_MAX + RR_TY - 1) / RR_TY, RR_CJ = RR_MAX / RR_TX;
+static_assert(RR_TY * RR_TX == RR_NT - 64, "waves 1-7");
+
+struct RRVec {   // entries of v, w and the next x below its second
+    double v, w, x, pad;
+};
+
+// element i (wave-uniform, < 128) of a vector over the lanes, without a branch
+__device__ __forceinline__ double rr_pick(double lo, double hi, int i)
 {
-    double pp = 1.0, p = rr_rl(dl0, 0) - x;
-    p = (p == 0.0) ? -DBL_MIN : p;
-    int c = p < 0.0;
-    auto step = [&](int i, double di, double qi) {
-        double q = fma(di - x, p, -(qi * pp));
-        q = (q == 0.0) ? (p > 0.0 ? -DBL_MIN : DBL_MIN) : q;
-        c += (q < 0.0) != (p < 0.0);
-        pp = p;
-        p = q;
-        if ((i & 3) == 0) {
-            const double mx = fmax(fabs(p), fabs(pp));
-            const double f = mx > 0x1p+500 ? 0x1p-500 : (mx < 0x1p-500 ? 0x1p+500 : 1.0);
-            p *= f;
-            pp *= f;
+    const double a = rr_rl(lo, i & 63), b = rr_rl(hi, i & 63);
+    return i < 64 ? a : b;
+}
+
+// v + its value 32 lanes away, in every lane
+__device__ __forceinline__ double rr_halves(double v)
+{
+    const RrI2 a = __builtin_bit_cast(RrI2, v);
+    const auto x = __builtin_amdgcn_permlane32_swap(a.x, a.x, false, false);
+    const auto y = __builtin_amdgcn_permlane32_swap(a.y, a.y, false, false);
+    return __builtin_bit_cast(double, RrI2{(int)x[0], (int)y[0]}) + __builtin_bit_cast(double, RrI2{(int)x[1], (int)y[1]});
+}
+
+// NI, CJ: row and column groups with entries (n <= RR_TY NI, n <= RR_TX CJ)
+template <int NI, int CJ>
+__device__ __forceinline__ void rr_house(RRShared &sh, int n, int tid, int wv)
+{
+    double(*A)[RR_LD] = sh.A;
+    double(*P)[RR_LD] = sh.Z;                                    // the waves' partial sums, then row k + 1
+    RRVec *vec = reinterpret_cast<RRVec *>(&sh.Z[RR_NW + 2][0]);   // 128 entries (an even row: 16-byte aligned)
+    const int lane = tid & 63;
+    const bool two = lane + 64 < RR_MAX;   // lanes with a second entry
+    const int c1 = two ? lane + 64 : RR_MAX;   // (column RR_MAX is padding)
+    double x0 = 0.0, x1 = 0.0;
+    if (wv == 0) {
+        x0 = lane >= 1 ? A[0][lane] : 0.0;
+        x1 = two ? A[0][c1] : 0.0;
+        if (lane == 0) sh.d[0] = A[0][0];
+        vec[lane] = RRVec{0.0, 0.0, lane >= 2 ? x0 : 0.0, 0.0};
+        vec[lane + 64] = RRVec{0.0, 0.0, x1, 0.0};
+        for (int k = 0; k + 2 < n; ++k) {
+            __syncthreads();
+            // sigma, beta, tau, hinv of x = row k right of the diagonal: sqrt and the
+            // two quotients from the refined hardware estimates (about one ulp each)
+            const double m0 = lane >= k + 2 ? x0 : 0.0, m1 = lane + 64 >= k + 2 ? x1 : 0.0;
+            const double sig = rr_uni(rr_wsum(m0 * m0 + m1 * m1));
+            const double alpha = rr_pick(x0, x1, k + 1);
+            const double h = fma(alpha, alpha, sig);
+            const double bt = -copysign(h * rr_rsqrt(h), alpha);
+            const double tau = sig == 0.0 ? 0.0 : fma(-alpha, rr_recip(bt), 1.0);   // (beta - alpha) / beta
+            const double inv = sig == 0.0 ? 0.0 : rr_recip(alpha - bt);
+            if (lane == 0) {
+                sh.tau[k] = tau;
+                sh.e[k] = sig == 0.0 ? alpha : bt;
+                sh.hinv[k] = inv;
+            }
+            A[k][lane] = x0;
+            A[k][c1] = x1;
+            const double v0 = lane == k + 1 ? 1.0 : m0 * inv, v1 = lane + 64 == k + 1 ? 1.0 : m1 * inv;
+            const double t0 = lane >= k + 1 ? tau : 0.0, t1 = two && lane + 64 >= k + 1 ? tau : 0.0;
+            __syncthreads();
+            double q0 = 0.0, q1 = 0.0;
+#pragma unroll
+            for (int q = 0; q < RR_NW - 1; ++q) {
+                q0 += P[q][lane];
+                if (CJ > 2) q1 += P[q][c1];
+            }
+            const double y0 = P[RR_NW - 1][lane], y1 = CJ > 2 ? P[RR_NW - 1][c1] : 0.0;
+            const double p0 = t0 * fma(inv, q0, y0);
+            const double p1 = CJ > 2 && two ? t1 * fma(inv, q1, y1) : 0.0;
+            const double K = 0.5 * tau * rr_wsum(CJ > 2 ? p0 * v0 + p1 * v1 : p0 * v0);
+            const double w0 = p0 - K * v0, w1 = p1 - K * v1;
+            // row k + 1 of the next matrix
+            const double wk = CJ > 2 ? rr_pick(w0, w1, k + 1) : rr_rl(w0, k + 1);
+            x0 = y0 - (w0 + wk * v0);
+            x1 = CJ > 2 && two ? y1 - (w1 + wk * v1) : 0.0;
+            vec[lane] = RRVec{v0, w0, lane >= k + 3 ? x0 : 0.0, 0.0};
+            vec[lane + 64] = RRVec{v1, w1, lane + 64 >= k + 3 ? x1 : 0.0, 0.0};
+            if (lane == ((k + 1) & 63)) sh.d[k + 1] = k + 1 < 64 ? x0 : x1;
+            x0 = lane >= k + 2 ? x0 : 0.0;
+            x1 = lane + 64 >= k + 2 ? x1 : 0.0;
         }
-    };
-    const int n0 = n < 64 ? n : 64;
-    int i = 1;
-    for (; i < n0; ++i) step(i, rr_rl(dl0, i), rr_rl(ql0, i - 1));
-    if (i < n) {
-        step(i, rr_rl(dl1, 0), rr_rl(ql0, 63));
-        for (++i; i < n; ++i) step(i, rr_rl(dl1, i - 64), rr_rl(ql1, i - 65));
+        __syncthreads();
+        __syncthreads();
+        // x is row n - 2; the last row's diagonal
+        if (n >= 2 && lane == ((n - 1) & 63)) {
+            sh.e[n - 2] = n - 1 < 64 ? x0 : x1;
+            sh.d[n - 1] = P[RR_NW - 1][n - 1];
+        }
+    } else {
+        const int ty = (tid - 64) / RR_TX, tx = tid % RR_TX;
+        double a[NI][CJ];
+#pragma unroll
+        for (int i = 0; i < NI; ++i) {
+            const int r = min(ty + RR_TY * i, RR_MAX - 1);
+#pragma unroll
+            for (int j = 0; j < CJ; ++j) a[i][j] = ty + RR_TY * i < RR_MAX ? A[r][tx + RR_TX * j] : 0.0;
+        }
+        for (int k = 0; k + 1 < max(n, 2); ++k) {
+            __syncthreads();
+            // the rows' update, their products with x = row k; row k + 1 to wave 0
+            double vc[CJ], wc[CJ], s[CJ];
+#pragma unroll
+            for (int j = 0; j < CJ; ++j) {
+                vc[j] = vec[tx + RR_TX * j].v;
+                wc[j] = vec[tx + RR_TX * j].w;
+                s[j] = 0.0;
+            }
+            const int g = (k + 1) / RR_TY;   // the group of row k + 1; those before it are done
+#pragma unroll
+            for (int i = 0; i < NI; ++i) {
+                if (i < g) continue;
+                const RRVec u = vec[ty + RR_TY * i];
+#pragma unroll
+                for (int j = 0; j < CJ; ++j) {
+                    a[i][j] -= u.v * wc[j] + u.w * vc[j];
+                    s[j] = fma(a[i][j], u.x, s[j]);
+                }
+                if (__builtin_expect(i == g, 0) && ty + RR_TY * i == k + 1)
+#pragma unroll
+                    for (int j = 0; j < CJ; ++j) P[RR_NW - 1][tx + RR_TX * j] = a[i][j];
+            }
+#pragma unroll
+            for (int j = 0; j < CJ; ++j) s[j] = rr_halves(s[j]);
+            if ((tid & 63) < RR_TX)
+#pragma unroll
+                for (int j = 0; j < CJ; ++j) P[wv - 1][tx + RR_TX * j] = s[j];
+            __syncthreads();
+        }
     }
+    __syncthreads();
+}
+
+// Sturm count: eigenvalues of T below x, from the signs of the leading
+// principal minors of T - xI (p_{i+1} = (d_i - x) p_i - e_{i-1}^2 p_{i-1}); an
+// exact zero minor counts as a sign change, and with e^2 > 0 the next one is
+// not zero and no change. One multiply-add per step on the chain; the signs are
+// beside it. d and e^2 come by broadcast reads of LDS, which run ahead (by lane
+// reads of a register, 20 cycles each on the chain of a step, the counts took
+// five times as long). The pair (p_i, p_{i-1}) is rescaled by 2^-+500 every
+// fourth step: T is scaled to entries below 2 and e^2 >= 2^-120, so four steps
+// can neither overflow nor underflow from [2^-500, 2^500].
+__device__ __forceinline__ double rr_range(double mx)   // the factor of a rescaling
+{
+    return mx > 0x1p+500 ? 0x1p-500 : (mx < 0x1p-500 ? 0x1p+500 : 1.0);
+}
+
+// calls f(d_i, e_{i-1}^2) for i = 1 .. n - 1 and g() after every four
+template <class F, class G>
+__device__ __forceinline__ void rr_chain(const double (*de)[2], int n, F f, G g)
+{
+    typedef double d2 __attribute__((ext_vector_type(2)));
+    int i = 1;
+    for (; i + 4 <= n; i += 4) {
+        d2 u[4];
+#pragma unroll
+        for (int k = 0; k < 4; ++k) u[k] = *reinterpret_cast<const d2 *>(de[i + k]);
+#pragma unroll
+        for (int k = 0; k < 4; ++k) f(u[k].x, u[k].y);
+        g();
+    }
+    for (; i < n; ++i) f(de[i][0], de[i][1]);
+    g();
+}
+
+// step(i, load(i)) for i from i0 to i1 (excluded) by dir, eight loads ahead of
+// their steps (the steps store to LDS, which holds later loads back)
+struct RRTrip {
+    double a, b, c;
+};
+template <class L, class S>
+__device__ __forceinline__ void rr_ahead(int i0, int i1, int dir, L load, S step)
+{
+    int i = i0;
+    for (; (i1 - i) * dir >= 8; i += 8 * dir) {
+        RRTrip t[8];
+#pragma unroll
+        for (int u = 0; u < 8; ++u) t[u] = load(i + u * dir);
+#pragma unroll
+        for (int u = 0; u < 8; ++u) step(i + u * dir, t[u]);
+    }
+    for (; (i1 - i) * dir > 0; i += dir) step(i, load(i));
+}
+
+__device__ __forceinline__ int rr_sturm(const double (*de)[2], int n, double x)
+{
+    double pp = 1.0, p = de[0][0] - x;
+    bool neg = !(p > 0.0);
+    int c = neg;
+    rr_chain(de, n,
+             [&](double di, double qi) {
+                 const double q = fma(di - x, p, -(qi * pp));
+                 const bool ng = q < 0.0 || (q == 0.0 && !neg);
+                 c += ng != neg;
+                 neg = ng;
+                 pp = p;
+                 p = q;
+             },
+             [&]() {
+                 const double f = rr_range(fmax(fabs(p), fabs(pp)));
+                 p *= f;
+                 pp *= f;
+             });
     return c;
 }
 
@@ -287,123 +468,23 @@ __global__ __launch_bounds__(RR_NT) void k_rr_eig(const double *__restrict__ G, 
 
     if (!bad) {
         // ---- Householder reduction to tridiagonal form ------------------------
-        // Step k: x = row k of the trailing matrix, H_k = I - tau v v^T with
-        // v_{k+1} = 1 and v_r = x_r * hinv[k] below; row k keeps x afterwards.
-        // Thread (wave w, lane l) owns column c = l + 64 (w & 1) over the rows
-        // k+1+s, k+1+s+RR_SL, ... of slice s = w >> 1. Broadcast operands (x_r,
-        // v_r, w_r) are LDS reads at one address per wave, not lane reads; wave 0
-        // alone forms sigma, beta, tau and hinv, which the others read after the
-        // barrier; each wave keeps its own copy of v and w (rows of Z, free here),
-        // so no barrier separates writing them from reading them. A lane whose
-        // column is not updated stores into the padding column RR_MAX. Up to 64
-        // columns the 8 waves are 8 row slices over one column half.
-        {
-            const int nsl = n <= 64 ? 2 * RR_SL : RR_SL;
-            const int half = n <= 64 ? 0 : wv & 1, slice = n <= 64 ? wv : wv >> 1;
-            const int col = lane + 64 * half;
-            const int cc = col < RR_MAX ? col : RR_MAX - 1;   // in-bounds column for loads
-            double *vw = &Z[2 * RR_SL + 2 * wv][0];             // this wave's v (then w at +RR_LD)
-            for (int k = 0; k + 2 < n; ++k) {
-                const double x0 = lane < n ? A[k][lane] : 0.0;
-                const double x1 = lane + 64 < n ? A[k][lane + 64] : 0.0;
-                // row k+1 before the barrier: other waves update it afterwards
-                const double y0 = lane < n ? A[k + 1][lane] : 0.0;
-                const double y1 = lane + 64 < n ? A[k + 1][lane + 64] : 0.0;
-                const bool act = col < n && col >= k + 1;
-                const int cst = act ? col : RR_MAX;   // store column
-                // partial S_c = sum over this slice's rows r >= k+2 of A[r][c] x_r
-                {
-                    double s0 = 0.0, s1 = 0.0;
-                    int r = k + 2 + slice;
-                    for (; r + nsl < n; r += 2 * nsl) {
-                        s0 = fma(A[r][cc], A[k][r], s0);
-                        s1 = fma(A[r + nsl][cc], A[k][r + nsl], s1);
-                    }
-                    if (r < n) s0 = fma(A[r][cc], A[k][r], s0);
-                    Z[slice][col < RR_MAX ? col : RR_MAX] = act ? s0 + s1 : 0.0;
-                }
-                if (wv == 0) {
-                    const double sig =
-                        rr_wsum((lane >= k + 2 ? x0 * x0 : 0.0) + (lane + 64 >= k + 2 ? x1 * x1 : 0.0));
-                    const double alpha = rr_get(x0, x1, k + 1);
-                    if (lane == 0) {
-                        if (sig == 0.0) {
-                            sh.tau[k] = 0.0;
-                            sh.e[k] = alpha;
-                            sh.hinv[k] = 0.0;
-                        } else {
-                            // short dependent chain: sqrt and the two quotients from the
-                            // refined hardware estimates (about one ulp each)
-                            const double s2 = fma(alpha, alpha, sig);
-                            const double beta = -copysign(s2 * rr_rsqrt(s2), alpha);
-                            sh.tau[k] = fma(-alpha, rr_recip(beta), 1.0);   // (beta - alpha) / beta
-                            sh.e[k] = beta;
-                            sh.hinv[k] = rr_recip(alpha - beta);
-                        }
-                    }
-                }
-                __syncthreads();
-                const double t = rr_uni(sh.tau[k]);
-                if (t == 0.0) {   // no reflection: row k+1 stays; nothing read Z
-                    continue;
-                }
-                const double inv = rr_uni(sh.hinv[k]);
-                const double v0 = lane == k + 1 ? 1.0 : (lane >= k + 2 ? x0 * inv : 0.0);
-                const double v1 = lane + 64 == k + 1 ? 1.0 : (lane + 64 >= k + 2 ? x1 * inv : 0.0);
-                // p_c = t (A[k+1][c] + inv S_c): v_{k+1} = 1, v_r = x_r inv below
-                double p0 = 0.0, p1 = 0.0;
-                for (int q = 0; q < nsl; ++q) {
-                    p0 += Z[q][lane];
-                    p1 += Z[q][lane + 64 < RR_MAX ? lane + 64 : RR_MAX];
-                }
-                p0 = lane < n ? t * fma(inv, p0, y0) : 0.0;
-                p1 = lane + 64 < n ? t * fma(inv, p1, y1) : 0.0;
-                const double K = 0.5 * t * rr_wsum(p0 * v0 + p1 * v1);
-                const double w0 = p0 - K * v0, w1 = p1 - K * v1;
-                vw[lane] = v0;
-                vw[RR_LD + lane] = w0;
-                if (lane + 64 < RR_MAX) {
-                    vw[lane + 64] = v1;
-                    vw[RR_LD + lane + 64] = w1;
-                }
-                // A' -= v w^T + w v^T on this thread's column and slice; loads and
-                // stores through one column index (idle lanes: the padding column),
-                // four rows loaded before any is stored
-                {
-                    const double vc = half ? v1 : v0, wc = half ? w1 : w0;
-                    int r = k + 1 + slice;
-                    for (; r + 3 * nsl < n; r += 4 * nsl) {
-                        double a[4], vr[4], wr[4];
-#pragma unroll
-                        for (int u = 0; u < 4; ++u) {
-                            a[u] = A[r + u * nsl][cst];
-                            vr[u] = vw[r + u * nsl];
-                            wr[u] = vw[RR_LD + r + u * nsl];
-                        }
-#pragma unroll
-                        for (int u = 0; u < 4; ++u) A[r + u * nsl][cst] = a[u] - (vr[u] * wc + wr[u] * vc);
-                    }
-                    for (; r < n; r += nsl) A[r][cst] = A[r][cst] - (vw[r] * wc + vw[RR_LD + r] * vc);
-                }
-                __syncthreads();
-            }
-        }
-        for (int i = tid; i < n; i += RR_NT) sh.d[i] = A[i][i];
-        if (tid == 0 && n >= 2) sh.e[n - 2] = A[n - 2][n - 1];
-        __syncthreads();
+        if (n <= 2 * RR_TX) rr_house<5, 2>(sh, n, tid, wv);
+        else rr_house<RR_RI, RR_CJ>(sh, n, tid, wv);
         for (int t = tid; t < RR_MAX * RR_MAX; t += RR_NT) Z[t / RR_MAX][t % RR_MAX] = 0.0;
-        // negligible couplings split T into independent blocks
+        // negligible couplings split T into independent blocks (a count takes them
+        // as 2^-60, far below the rounding of a T with a largest entry near 1)
         double *e2 = sh.sc[2];
         for (int i = tid; i + 1 < n; i += RR_NT) {
             double ei = sh.e[i];
             if (fabs(ei) <= DBL_EPSILON * (fabs(sh.d[i]) + fabs(sh.d[i + 1]))) ei = 0.0;
             sh.e[i] = ei;
-            e2[i] = ei * ei;
+            e2[i] = ei * ei;   // (twisted factorisations)
         }
         __syncthreads();
-        // d and e^2 in registers of every wave (element i in lane i / i - 64)
-        const double dl0 = lane < n ? sh.d[lane] : 0.0, dl1 = lane + 64 < n ? sh.d[lane + 64] : 0.0;
-        const double ql0 = lane + 1 < n ? e2[lane] : 0.0, ql1 = lane + 65 < n ? e2[lane + 64] : 0.0;
+        for (int i = tid; i < n; i += RR_NT) {
+            sh.de[i][0] = sh.d[i];
+            sh.de[i][1] = i > 0 ? fmax(e2[i - 1], 0x1p-120) : 0.0;
+        }
 
         // ---- eigenvalues by multisection ---------------------------------------
         double glo = INFINITY, ghi = -INFINITY;
@@ -422,7 +503,7 @@ __global__ __launch_bounds__(RR_NT) void k_rr_eig(const double *__restrict__ G, 
         int *cnt = sh.u.cnt;
         if (tid < RR_G) {   // RR_G shifts over the Gershgorin interval (whole waves)
             const double fr = (double)(tid + 1) / (double)(RR_G + 1);
-            cnt[tid] = rr_sturm(dl0, dl1, ql0, ql1, n, fma(gu - gl, fr, gl));
+            cnt[tid] = rr_sturm(sh.de, n, fma(gu - gl, fr, gl));
         }
         __syncthreads();
         if (tid < n) {
@@ -445,10 +526,12 @@ __global__ __launch_bounds__(RR_NT) void k_rr_eig(const double *__restrict__ G, 
             sh.sc[3][tid] = (tid - cl + 0.5) / (double)max(ch - cl, 1);
         }
         __syncthreads();
-        // Laguerre's method on det(T - xI) from the middle of each isolating
-        // interval (waves 0-1, one eigenvalue per lane): G = P'/P and
-        // H = G^2 - P''/P from the pivot recurrences q_i = d_i - x - e_{i-1}^2 / q_{i-1}
-        // and their first two derivatives; cubic convergence at simple roots.
+        // Laguerre's method on P(x) = det(T - xI) from the middle of each isolating
+        // interval (waves 0-1, one eigenvalue per lane): P, P' and P'' from the
+        // recurrence of the leading minors and its derivatives, rescaled together
+        // (three independent multiply-adds a step where the pivots' quotients were
+        // a chain of eight); cubic convergence at simple roots. The step is
+        // n P / (P' +- sqrt((n - 1) ((n - 1) P'^2 - n P P''))), the larger divisor.
         // A step leaving the interval, a non-finite value or no convergence in
         // 16 steps, or a result whose Sturm counts do not bracket index j,
         // leaves the interval to the multisection below.
@@ -459,32 +542,40 @@ __global__ __launch_bounds__(RR_NT) void k_rr_eig(const double *__restrict__ G, 
             bool conv = j >= n, ok = false;
             for (int it = 0; it < 16; ++it) {
                 if (__all(conv)) break;
-                double q = rr_rl(dl0, 0) - x;
-                q = (q == 0.0) ? -DBL_MIN : q;
-                double qp = -1.0, qpp = 0.0, rq = rr_recip(q);
-                double Gs = qp * rq, Hs = Gs * Gs;
-                auto lag = [&](double di, double e2p) {
-                    const double qn = (di - x) - e2p * rq;
-                    const double qpn = -1.0 + e2p * qp * rq * rq;
-                    const double qppn = e2p * (qpp - 2.0 * qp * qp * rq) * rq * rq;
-                    q = (qn == 0.0) ? -DBL_MIN : qn;
-                    qp = qpn;
-                    qpp = qppn;
-                    rq = rr_recip(q);
-                    const double t = qp * rq;
-                    Gs += t;
-                    Hs += t * t - qpp * rq;
-                };
-                {
-                    int i = 1;
-                    for (; i < n && i < 64; ++i) lag(rr_rl(dl0, i), rr_rl(ql0, i - 1));
-                    if (i < n) lag(rr_rl(dl1, 0), rr_rl(ql0, 63));
-                    for (++i; i < n; ++i) lag(rr_rl(dl1, i - 64), rr_rl(ql1, i - 65));
-                }
+                double p = sh.de[0][0] - x, pp = 1.0, p1 = -1.0, pp1 = 0.0, p2 = 0.0, pp2 = 0.0;
+                rr_chain(sh.de, n,
+                         [&](double di, double qi) {
+                             const double t = di - x;
+                             const double q = fma(t, p, -(qi * pp));
+                             const double q1 = fma(t, p1, -fma(qi, pp1, p));
+                             const double q2 = fma(t, p2, -fma(qi, pp2, 2.0 * p1));
+                             pp = p;
+                             pp1 = p1;
+                             pp2 = p2;
+                             p = q;
+                             p1 = q1;
+                             p2 = q2;
+                         },
+                         [&]() {
+                             const double f = rr_range(fmax(fmax(fmax(fabs(p), fabs(pp)), fmax(fabs(p1), fabs(pp1))),
+                                                            fmax(fabs(p2), fabs(pp2))));
+                             p *= f;
+                             pp *= f;
+                             p1 *= f;
+                             pp1 *= f;
+                             p2 *= f;
+                             pp2 *= f;
+                         });
                 if (!conv) {
-                    const double sq = sqrt(fmax((nd - 1.0) * (nd * Hs - Gs * Gs), 0.0));
-                    const double den = fabs(Gs + sq) >= fabs(Gs - sq) ? Gs + sq : Gs - sq;
-                    const double a = nd / den;
+                    // brought near 1: the squares are in range
+                    const int ex = -ilogb(fmax(fmax(fabs(p), fabs(p1)), fabs(p2)));
+                    p = ldexp(p, ex);
+                    p1 = ldexp(p1, ex);
+                    p2 = ldexp(p2, ex);
+                    const double g = (nd - 1.0) * p1;
+                    const double sq = sqrt(fmax(g * g - (nd - 1.0) * nd * (p * p2), 0.0));
+                    const double den = p1 >= 0.0 ? p1 + sq : p1 - sq;
+                    const double a = nd * p / den;
                     const double xn = x - a;
                     if (!(den != 0.0) || !isfinite(xn) || !(xn >= l0 && xn <= h0)) {
                         conv = true;
@@ -498,11 +589,27 @@ __global__ __launch_bounds__(RR_NT) void k_rr_eig(const double *__restrict__ G, 
                 }
             }
             const double dl = 4.0 * DBL_EPSILON * tnorm;
-            const int c1 = rr_sturm(dl0, dl1, ql0, ql1, n, x - dl);
-            const int c2 = rr_sturm(dl0, dl1, ql0, ql1, n, x + dl);
-            if (j < n && ok && c1 <= j && j < c2) {
+            const int c1 = rr_sturm(sh.de, n, x - dl);
+            const int c2 = rr_sturm(sh.de, n, x + dl);
+            ok = ok && c1 <= j && j < c2;
+            if (j < n && ok) {
                 lo[j] = x;
                 hi[j] = x;
+            }
+            // a start near it for the others: a wider bracket of the last iterate
+            if (__any(j < n && !ok)) {
+                const double l1 = fmax(l0, x - 0x1p-42 * tnorm), h1 = fmin(h0, x + 0x1p-42 * tnorm);
+                const int c3 = rr_sturm(sh.de, n, l1), c4 = rr_sturm(sh.de, n, h1);
+                if (j < n && !ok && l1 < h1) {
+                    if (c3 <= j) lo[j] = l1;
+                    else hi[j] = l1;
+                    if (j < c4) hi[j] = fmin(hi[j], h1);
+                    else lo[j] = h1;
+                    if (!(lo[j] < hi[j])) {   // (counts out of order)
+                        lo[j] = l0;
+                        hi[j] = h0;
+                    }
+                }
             }
         }
         // multisection for what Laguerre left: the open eigenvalues (ballot of
@@ -520,95 +627,113 @@ __global__ __launch_bounds__(RR_NT) void k_rr_eig(const double *__restrict__ G, 
             const unsigned long long m0 = sh.open_mask[0], m1 = sh.open_mask[1];
             const int c0 = __popcll(m0), na = c0 + __popcll(m1);
             if (na == 0) break;
-            const int per = max(2, min(64, RR_G / na));
-            const int slot = tid / per, sft = tid % per;
+            // a power of two of shifts each, in one wave: the counts meet in a ballot
+            int per = 64;
+            while (per * na > RR_G) per >>= 1;
+            const int slot = tid / per, sft = tid & (per - 1);
+            int j = 0, cnt_j = 0;
+            double l0 = 0.0, h0 = 0.0, x = 0.0;
             if (slot < na) {
                 // eigenvalue of this slot: the slot-th set bit of (m0, m1)
                 unsigned long long mk = slot < c0 ? m0 : m1;
                 for (int q = slot < c0 ? slot : slot - c0; q > 0; --q) mk &= mk - 1;
-                const int j = __builtin_ctzll(mk) + (slot < c0 ? 0 : 64);
-                const double fr = (double)(sft + 1) / (double)(per + 1);
-                cnt[tid] = rr_sturm(dl0, dl1, ql0, ql1, n, fma(hi[j] - lo[j], fr, lo[j]));
+                j = __builtin_ctzll(mk) + (slot < c0 ? 0 : 64);
+                l0 = lo[j];
+                h0 = hi[j];
+                x = fma(h0 - l0, (double)(sft + 1) / (double)(per + 1), l0);
+                cnt_j = rr_sturm(sh.de, n, x);
             }
-            __syncthreads();
-            if (tid < n && ((tid < 64 ? m0 >> tid : m1 >> (tid - 64)) & 1ull)) {
-                const int myslot = tid < 64 ? __popcll(m0 & ((1ull << tid) - 1ull))
-                                            : c0 + __popcll(m1 & ((1ull << (tid - 64)) - 1ull));
-                const double l0 = lo[tid], h0 = hi[tid];
-                double l = l0, h = h0;
-                for (int q = 0; q < per; ++q) {
-                    const double x = fma(h0 - l0, (double)(q + 1) / (double)(per + 1), l0);
-                    if (cnt[myslot * per + q] <= tid) l = fmax(l, x);
-                    else h = fmin(h, x);
-                }
-                lo[tid] = l;
-                hi[tid] = h;
+            const unsigned long long le = __ballot(slot < na && cnt_j <= j);
+            const unsigned long long all = per == 64 ? ~0ull : (1ull << per) - 1;
+            const unsigned long long mine = (le >> (lane & ~(per - 1))) & all;
+            if (slot < na && sft == 0) {   // the last shift with a count <= j, the first with one > j
+                auto at = [&](int q) { return fma(h0 - l0, (double)(q + 1) / (double)(per + 1), l0); };
+                if (mine) lo[j] = fmax(l0, at(63 - __builtin_clzll(mine)));
+                if (mine != all) hi[j] = fmin(h0, at(__builtin_ctzll(~mine)));
             }
         }
         if (tid < n) sh.lam[tid] = 0.5 * (lo[tid] + hi[tid]);
         __syncthreads();
 
         // ---- eigenvectors of T: twisted factorisations, one per thread ------
-        if (wv < 2) {   // d, e, e^2 by readlane: the loops below are wave-uniform
-            const int j = tid, jc = j < n ? j : 0;   // jc: in-bounds column for idle lanes
-            const double lj = sh.lam[jc];
+        double *vinv = sh.sc[0];   // reciprocal norms
+        if (wv < 2) {   // d, e, e^2 by broadcast reads: the loops below are wave-uniform
+            const int j = tid, jc = j < n ? j : RR_MAX;   // idle lanes: the padding column
+            const double lj = sh.lam[j < n ? j : 0];
             // top-down pivots delta+ kept in column j
-            double dp = rr_rl(dl0, 0) - lj;
+            double dp = sh.d[0] - lj;
             if (dp == 0.0) dp = -DBL_MIN;
-            if (j < n) Z[0][j] = dp;
-            auto fwd = [&](int i, double di, double qi) {
-                double x = (di - lj) - qi * rr_recip(dp);
-                if (x == 0.0) x = -DBL_MIN;
-                dp = x;
-                if (j < n) Z[i][j] = x;
-            };
-            {
-                int i = 1;
-                for (; i < n && i < 64; ++i) fwd(i, rr_rl(dl0, i), rr_rl(ql0, i - 1));
-                if (i < n) fwd(i, rr_rl(dl1, 0), rr_rl(ql0, 63));
-                for (++i; i < n; ++i) fwd(i, rr_rl(dl1, i - 64), rr_rl(ql1, i - 65));
-            }
+            Z[0][jc] = dp;
+            rr_ahead(1, n, 1, [&](int i) { return RRTrip{sh.d[i], e2[i - 1], 0.0}; },
+                     [&](int i, const RRTrip &t) {
+                         dp = (t.a - lj) - t.b * rr_recip(dp);
+                         if (dp == 0.0) dp = -DBL_MIN;
+                         Z[i][jc] = dp;
+                     });
             // bottom-up pivots delta-, twist index of smallest |gamma|
-            double dm = rr_get(dl0, dl1, n - 1) - lj;
+            double dm = sh.d[n - 1] - lj;
             if (dm == 0.0) dm = -DBL_MIN;
             double best = fabs(Z[n - 1][jc]);
             int r = n - 1;
-            auto bwd = [&](int i, double dv, double qi) {
-                const double di = dv - lj;
-                dm = di - qi * rr_recip(dm);
-                if (dm == 0.0) dm = -DBL_MIN;
-                const double g = fabs(Z[i][jc] + dm - di);
-                if (g < best) {
-                    best = g;
-                    r = i;
-                }
-            };
-            {
-                int i = n - 2;
-                for (; i >= 64; --i) bwd(i, rr_rl(dl1, i - 64), rr_rl(ql1, i - 64));
-                for (; i >= 0; --i) bwd(i, rr_rl(dl0, i), rr_rl(ql0, i));
+            rr_ahead(n - 2, -1, -1, [&](int i) { return RRTrip{sh.d[i], e2[i], Z[i][jc]}; },
+                     [&](int i, const RRTrip &t) {
+                         const double di = t.a - lj;
+                         dm = di - t.b * rr_recip(dm);
+                         if (dm == 0.0) dm = -DBL_MIN;
+                         const double g = fabs(t.c + dm - di);
+                         if (g < best) {
+                             best = g;
+                             r = i;
+                         }
+                     });
+            // (the two ends of this wave's twist indices bound the loops)
+            int rlo = j < n ? r : n - 1, rhi = j < n ? r : 0;
+            for (int o = 32; o > 0; o >>= 1) {
+                rlo = min(rlo, __shfl_xor(rlo, o));
+                rhi = max(rhi, __shfl_xor(rhi, o));
             }
+            rlo = __builtin_amdgcn_readfirstlane(rlo);
+            rhi = __builtin_amdgcn_readfirstlane(rhi);
+            // ratios below the twist: z_{i+1} / z_i = -e_i / delta-_{i+1}
+            dm = sh.d[n - 1] - lj;
+            if (dm == 0.0) dm = -DBL_MIN;
+            rr_ahead(n - 2, rlo - 1, -1, [&](int i) { return RRTrip{sh.d[i], sh.e[i], 0.0}; },
+                     [&](int i, const RRTrip &t) {
+                         const double rho = -t.b * rr_recip(dm);
+                         if (i >= r) Z[i + 1][jc] = rho;
+                         dm = (t.a - lj) + t.b * rho;
+                         if (dm == 0.0) dm = -DBL_MIN;
+                     });
+            double nn = 1.0, z = 1.0;
+            rr_ahead(rlo, n - 1, 1, [&](int i) { return RRTrip{Z[i + 1][jc], 0.0, 0.0}; },
+                     [&](int i, const RRTrip &t) {
+                         if (i >= r) {
+                             z *= t.a;
+                             nn = fma(z, z, nn);
+                             Z[i + 1][jc] = z;
+                         }
+                     });
+            // above the twist: z_i = -(e_i / delta+_i) z_{i+1}
+            z = 1.0;
+            rr_ahead(rhi - 1, -1, -1, [&](int i) { return RRTrip{-(sh.e[i] * rr_recip(Z[i][jc])), 0.0, 0.0}; },
+                     [&](int i, const RRTrip &t) {
+                         if (i < r) {
+                             z *= t.a;
+                             nn = fma(z, z, nn);
+                             Z[i][jc] = z;
+                         }
+                     });
+            Z[r][jc] = 1.0;
+            const double inv = 1.0 / sqrt(nn);
             if (j < n) {
-                // ratios below the twist: z_{i+1} / z_i = -e_i / delta-_{i+1}
-                dm = rr_get(dl0, dl1, n - 1) - lj;
-                if (dm == 0.0) dm = -DBL_MIN;
-                for (int i = n - 2; i >= r; --i) {
-                    const double ei = sh.e[i];
-                    const double rho = -ei * rr_recip(dm);
-                    Z[i + 1][j] = rho;
-                    dm = (sh.d[i] - lj) + ei * rho;
-                    if (dm == 0.0) dm = -DBL_MIN;
-                }
-                Z[r][j] = 1.0;
-                for (int i = r; i + 1 < n; ++i) Z[i + 1][j] *= Z[i][j];
-                // above the twist: z_i = -(e_i / delta+_i) z_{i+1}
-                for (int i = r - 1; i >= 0; --i) Z[i][j] = -(sh.e[i] * rr_recip(Z[i][j])) * Z[i + 1][j];
-                double nn = 0.0;
-                for (int i = 0; i < n; ++i) nn += Z[i][j] * Z[i][j];
-                const double inv = 1.0 / sqrt(nn);
-                for (int i = 0; i < n; ++i) Z[i][j] *= inv;
+                vinv[j] = inv;
                 if (!(nn > 0.0) || !isfinite(nn) || !(best * inv <= 1e-10 * tnorm)) sh.flag = 1;
             }
+        }
+        __syncthreads();
+        for (int t = tid; t < n * RR_MAX; t += RR_NT) {
+            const int c = t % RR_MAX;
+            if (c < n) Z[t / RR_MAX][c] *= vinv[c];
         }
         {
             // ---- clusters: modified Gram-Schmidt, two passes (one wave) ------
