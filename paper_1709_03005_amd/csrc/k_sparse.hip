@@ -94,14 +94,31 @@ __global__ __launch_bounds__(256) void k_vt(const double *__restrict__ V, int64_
 // (added to the continuum part's sums when there are continuum rows, else
 // assigned): one wave per row. LPR lanes take one non-zero, two vectors (16
 // bytes) each, so an instruction gathers 64 / LPR records of 16 LPR bytes that
-// lie in one cache line each; the wave's next 64 columns and values are loaded
-// side by side and handed to the groups by lane permutes. The groups' sums are
-// added across lanes in a fixed order. Bound by the gathers' requests to L2, one
-// 128-byte line per non-zero whatever the record's length: 88 million non-zeros
-// (50000 functions) take 1.04 / 0.89 / 0.87 ms for records of 128 / 64 / 32
-// bytes. A lane per non-zero, with the 16 vectors in its registers, took 1.95
-// ms: each of its eight loads touched 64 different lines.
+// lie in one cache line each. The columns and values of a batch of eight
+// gathers go to the lanes through LDS, those of the batch after it are on their
+// way, and the gathers of the next batch are issued before the sums of this one:
+// with each batch's gathers waited for, the wave was idle most of the time. The
+// groups' sums are added across lanes in a fixed order. 88 million non-zeros
+// (50000 functions) take 0.90 / 0.64 / 0.56 ms for records of 128 / 64 / 32
+// bytes (1.07 / 0.89 / 0.88 before): bound by the records' lines from L2 and,
+// for the longest, which do not fit it (6.4 MB), from the last-level cache; the
+// three waves a SIMD that the registers leave keep more of them there than four
+// do (1.00). A lane per non-zero, with the 16 vectors in its registers, took
+// 1.95 ms: each of its eight loads touched 64 different lines.
 typedef double px2 __attribute__((ext_vector_type(2)));
+
+struct alignas(16) SpEntry {
+    double v;
+    int32_t c, pad;
+};
+
+// the wave's LDS accesses before this one are done before those after it (a wave's
+// LDS instructions run in order: no instruction is needed, only their order kept)
+__device__ __forceinline__ void wave_order()
+{
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+}
 
 template <int LPR>
 __global__ __launch_bounds__(256) void k_l2_spmm(const int64_t *__restrict__ off, const int32_t *__restrict__ col,
@@ -110,48 +127,62 @@ __global__ __launch_bounds__(256) void k_l2_spmm(const int64_t *__restrict__ off
                                                  int64_t ldw, int accumulate)
 {
     constexpr int NPS = 64 / LPR;   // non-zeros per instruction
+    constexpr int U = 8, C = U / LPR, CH = 64 * C;   // gathers and non-zeros of a batch
     const int lane = threadIdx.x & 63, g = lane / LPR, q2 = lane % LPR;
     const int r = blockIdx.x * 4 + (threadIdx.x >> 6);
     if (r >= nl2) return;   // the whole wave
     const px2 *vl = reinterpret_cast<const px2 *>(VT) + q2;
     const int64_t e1 = off[r + 1];
     px2 acc = (px2){0.0, 0.0};
-    int64_t e0 = off[r];
-    int cn = 0;
-    double vn = 0.0;
-    if (e0 + lane < e1) {
-        cn = col[e0 + lane];
-        vn = val[e0 + lane];
-    }
-    for (; e0 < e1; e0 += 64) {
-        const int c = cn;
-        const double v = vn;
-        cn = 0;
-        vn = 0.0;
-        if (e0 + 64 + lane < e1) {
-            cn = col[e0 + 64 + lane];
-            vn = val[e0 + 64 + lane];
+    int c1[C];
+    double v1[C];
+    px2 xa[U], xb[U];
+    double aa[U], ab[U];
+    __shared__ SpEntry ring[4][CH];
+    SpEntry *mine = ring[threadIdx.x >> 6];   // this wave's batch
+    auto load = [&](int64_t e) {   // past the end: column 0 with the value 0
+#pragma unroll
+        for (int k = 0; k < C; ++k) {
+            const bool in = e + 64 * k + lane < e1;
+            c1[k] = in ? col[e + 64 * k + lane] : 0;
+            v1[k] = in ? val[e + 64 * k + lane] : 0.0;
         }
-        const int left = (int)min<int64_t>(64, e1 - e0);
-        constexpr int U = LPR < 8 ? LPR : 8;   // gathers in flight
+    };
+    auto gather = [&](px2 (&x)[U], double (&a)[U]) {
 #pragma unroll
-        for (int s0 = 0; s0 < LPR; s0 += U) {
-            if (s0 * NPS < left) {   // past the end of the row: column 0 with the value 0
-                px2 x[U];
-                double a[U];
+        for (int k = 0; k < C; ++k) mine[64 * k + lane] = SpEntry{v1[k], c1[k], 0};
+        wave_order();
 #pragma unroll
-                for (int u = 0; u < U; ++u) {
-                    const int from = (s0 + u) * NPS + g;
-                    x[u] = vl[(int64_t)__shfl(c, from, 64) * LPR];
-                    a[u] = __shfl(v, from, 64);
-                }
-#pragma unroll
-                for (int u = 0; u < U; ++u) {
-                    acc.x = fma(a[u], x[u].x, acc.x);
-                    acc.y = fma(a[u], x[u].y, acc.y);
-                }
-            }
+        for (int s = 0; s < U; ++s) {
+            const SpEntry t = mine[s * NPS + g];
+            a[s] = t.v;
+            x[s] = vl[(int64_t)t.c * LPR];
         }
+        wave_order();
+    };
+    auto add = [&](const px2 (&x)[U], const double (&a)[U]) {
+#pragma unroll
+        for (int s = 0; s < U; ++s) {
+            acc.x = fma(a[s], x[s].x, acc.x);
+            acc.y = fma(a[s], x[s].y, acc.y);
+        }
+    };
+    int64_t e = off[r];
+    load(e);
+    gather(xa, aa);
+    load(e + CH);
+    // a batch: the gathers of the next one, the columns and values of the one
+    // after that, then the sums of this one
+    auto batch = [&](const px2 (&x)[U], const double (&a)[U], px2 (&xn)[U], double (&an)[U]) {
+        if (e + CH < e1) gather(xn, an);
+        load(e + 2 * CH);
+        add(x, a);
+        e += CH;
+    };
+    while (e < e1) {
+        batch(xa, aa, xb, ab);
+        if (e >= e1) break;
+        batch(xb, ab, xa, aa);
     }
 #pragma unroll
     for (int o = 32; o >= LPR; o >>= 1) {
