@@ -150,6 +150,14 @@ __device__ __forceinline__ int excite_cont_l2(const uint64_t *D, const uint64_t 
 // ---------------------------------------------------------------------------
 // short scalar chains and wave reductions
 // ---------------------------------------------------------------------------
+// the wave's LDS accesses before this one are done before those after it (a wave's
+// LDS instructions run in order: no instruction is needed, only their order kept)
+__device__ __forceinline__ void wave_order()
+{
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+}
+
 // 1/q from the hardware estimate and two Newton-Raphson corrections
 // r <- r + r (1 - q r), each squaring the relative error: a short dependent
 // chain for the recurrences below, within about one ulp of the quotient

@@ -112,14 +112,6 @@ struct alignas(16) SpEntry {
     int32_t c, pad;
 };
 
-// the wave's LDS accesses before this one are done before those after it (a wave's
-// LDS instructions run in order: no instruction is needed, only their order kept)
-__device__ __forceinline__ void wave_order()
-{
-    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-    __builtin_amdgcn_wave_barrier();
-}
-
 template <int LPR>
 __global__ __launch_bounds__(256) void k_l2_spmm(const int64_t *__restrict__ off, const int32_t *__restrict__ col,
                                                  const double *__restrict__ val, int Dc, int nl2,
