@@ -2,13 +2,21 @@
 // bitstrings): every ket of a row is XORed with the row's bra and popcounted;
 // pairs within a double substitution are compacted, in ket order, with their
 // holes/particles packed into four 16-bit fields and the sign from masks.
-// One workgroup per bra row; a count pass sizes the lists at plan time, the
-// emit pass (same scan) writes them during the build. Integer work, bit-exact.
+// A count pass sizes the lists at plan time, the emit pass (same scan) writes them
+// during the build. Integer work, bit-exact.
+// One wave per bra row, 64 kets a step. The connected kets, some hundred of some
+// thousand, are listed in LDS as their population counts show them and worked out
+// 64 at a time, which also writes the row's pairs side by side: with the labels
+// and signs worked out where the pairs were found, nearly every step went through
+// all of that for a few lanes, between two barriers of a workgroup per row.
+// Bound by the population counts and the reading of the kets from the caches:
+// 8000 x 8000 determinants in 0.12 ms, 28000 L2 functions x 8000 in 0.19 (0.40
+// and 0.46).
 #include "ccham_internal.h"
 
 namespace cch {
 
-constexpr int SCAN_THREADS = 256;
+constexpr int SCAN_THREADS = 256, SCAN_WAVES = SCAN_THREADS / 64;
 
 template <int W, int MODE, bool EMIT>
 __global__ __launch_bounds__(SCAN_THREADS) void k_scan(const uint64_t *__restrict__ A, int nA,
@@ -16,73 +24,82 @@ __global__ __launch_bounds__(SCAN_THREADS) void k_scan(const uint64_t *__restric
                                                        int top, const int64_t *__restrict__ row_off,
                                                        int64_t *__restrict__ row_cnt, PairList out)
 {
-    const int x = blockIdx.x;
-    if (x >= nA) return;
+    __shared__ int32_t found[SCAN_WAVES][128];   // connected kets: fewer than 64 and one step's
+    const int lane = threadIdx.x & 63, wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int x = blockIdx.x * SCAN_WAVES + wv;
+    if (x >= nA) return;   // the whole wave
+    int32_t *list = found[wv];
     uint64_t a[W];
 #pragma unroll
     for (int w = 0; w < W; ++w) a[w] = A[(size_t)x * W + w];
     const int ylim = (MODE == SCAN_LL) ? x + 1 : nB;
-    __shared__ int wave_tot[SCAN_THREADS / 64];
-    __shared__ int64_t base_sh;
-    const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
-    int64_t base = EMIT ? row_off[x] : 0;
-    int64_t cnt = 0;
-    for (int y0 = 0; y0 < ylim; y0 += SCAN_THREADS) {
-        const int y = y0 + threadIdx.x;
-        int deg = 3, h[2] = {-1, -1}, p[2] = {-1, -1}, s = 1, pt = -1;
-        if (y < ylim) {
-            uint64_t b[W];
+    int64_t at = EMIT ? row_off[x] : 0;
+    int n = 0;   // listed
+    // kets are read two steps ahead
+    uint64_t b0[W], b1[W];
+    auto load = [&](int y0, uint64_t (&b)[W]) {
 #pragma unroll
-            for (int w = 0; w < W; ++w) b[w] = B[(size_t)y * W + w];
-            if (MODE == SCAN_LT)
-                deg = excite_cont_l2<W>(b, a, top, h, &pt, &s);   // bra = det y + continuum, ket = L2 x
-            else
-                deg = excite<W>(a, b, h, p, &s);
+        for (int w = 0; w < W; ++w) b[w] = B[(size_t)min(y0 + lane, ylim - 1) * W + w];
+    };
+    if (ylim > 0) {
+        load(0, b0);
+        load(64, b1);
+    }
+    for (int y0 = 0; y0 < ylim; y0 += 64) {
+        uint64_t b[W];
+#pragma unroll
+        for (int w = 0; w < W; ++w) {
+            b[w] = b0[w];
+            b0[w] = b1[w];
         }
-        const bool conn = deg <= 2;
+        if (y0 + 128 < ylim) load(y0 + 128, b1);
+        int d = 0;
+#pragma unroll
+        for (int w = 0; w < W; ++w) d += __popcll(a[w] ^ b[w]);
+        // L2 x target: one electron more on one side (the continuum one)
+        const bool conn = y0 + lane < ylim && (MODE == SCAN_LT ? d <= 3 && (d & 1) : d <= 4);
+        const uint64_t bal = __ballot(conn);
         if (!EMIT) {
-            cnt += conn;
+            at += __popcll(bal);
             continue;
         }
-        const uint64_t bal = __ballot(conn);
-        const int before = __popcll(bal & ((1ull << lane) - 1ull));
-        if (lane == 0) wave_tot[wv] = __popcll(bal);
-        __syncthreads();
-        int woff = 0, tot = 0;
+        if (conn) list[n + __popcll(bal & ((1ull << lane) - 1ull))] = y0 + lane;
+        n += __popcll(bal);
+        wave_order();
+        const bool last = y0 + 64 >= ylim;
+        while (n >= 64 || (last && n > 0)) {
+            const int m = min(n, 64);
+            if (lane < m) {
+                const int y = list[lane];
 #pragma unroll
-        for (int k = 0; k < SCAN_THREADS / 64; ++k) {
-            woff += (k < wv) ? wave_tot[k] : 0;
-            tot += wave_tot[k];
+                for (int w = 0; w < W; ++w) b[w] = B[(size_t)y * W + w];
+                int deg, h[2] = {-1, -1}, p[2] = {-1, -1}, s = 1, pt = -1;
+                if (MODE == SCAN_LT)
+                    deg = excite_cont_l2<W>(b, a, top, h, &pt, &s);   // bra = det y + continuum, ket = L2 x
+                else
+                    deg = excite<W>(a, b, h, p, &s);
+                const int64_t pos = at + lane;
+                out.x[pos] = x;
+                out.y[pos] = y;
+                out.deg[pos] = (int8_t)deg;
+                out.phase[pos] = (int8_t)s;
+                uint64_t lab;
+                if (MODE == SCAN_LT)
+                    lab = pack_label(deg == 2 ? pt : CCH_NOLAB, h[0], deg == 2 ? h[1] : CCH_NOLAB, CCH_NOLAB);
+                else
+                    lab = pack_label(deg >= 1 ? p[0] : CCH_NOLAB, deg >= 1 ? h[0] : CCH_NOLAB,
+                                     deg >= 2 ? p[1] : CCH_NOLAB, deg >= 2 ? h[1] : CCH_NOLAB);
+                out.label[pos] = lab;
+            }
+            at += m;
+            n -= m;
+            const int k = lane < n ? list[64 + lane] : 0;
+            wave_order();
+            if (lane < n) list[lane] = k;
+            wave_order();
         }
-        if (conn) {
-            const int64_t pos = base + woff + before;
-            out.x[pos] = x;
-            out.y[pos] = y;
-            out.deg[pos] = (int8_t)deg;
-            out.phase[pos] = (int8_t)s;
-            uint64_t lab;
-            if (MODE == SCAN_LT)
-                lab = pack_label(deg == 2 ? pt : CCH_NOLAB, h[0], deg == 2 ? h[1] : CCH_NOLAB, CCH_NOLAB);
-            else
-                lab = pack_label(deg >= 1 ? p[0] : CCH_NOLAB, deg >= 1 ? h[0] : CCH_NOLAB,
-                                 deg >= 2 ? p[1] : CCH_NOLAB, deg >= 2 ? h[1] : CCH_NOLAB);
-            out.label[pos] = lab;
-        }
-        base += tot;
-        __syncthreads();
     }
-    if (!EMIT) {
-        // block reduction of the per-thread counts
-        __shared__ int64_t red[SCAN_THREADS];
-        red[threadIdx.x] = cnt;
-        __syncthreads();
-        for (int o = SCAN_THREADS / 2; o > 0; o >>= 1) {
-            if (threadIdx.x < o) red[threadIdx.x] += red[threadIdx.x + o];
-            __syncthreads();
-        }
-        if (threadIdx.x == 0) row_cnt[x] = red[0];
-    }
-    (void)base_sh;
+    if (!EMIT && lane == 0) row_cnt[x] = at;
 }
 
 template <int W, int MODE>
@@ -90,11 +107,12 @@ static hipError_t scan_w(const uint64_t *A, int nA, const uint64_t *B, int nB, i
                          const int64_t *row_off, int64_t *row_cnt, PairList out, hipStream_t st)
 {
     if (nA <= 0) return hipSuccess;
+    const dim3 g((nA + SCAN_WAVES - 1) / SCAN_WAVES);
     if (row_off)
-        hipLaunchKernelGGL((k_scan<W, MODE, true>), dim3(nA), dim3(SCAN_THREADS), 0, st, A, nA, B,
+        hipLaunchKernelGGL((k_scan<W, MODE, true>), g, dim3(SCAN_THREADS), 0, st, A, nA, B,
                            nB, top, row_off, row_cnt, out);
     else
-        hipLaunchKernelGGL((k_scan<W, MODE, false>), dim3(nA), dim3(SCAN_THREADS), 0, st, A, nA, B,
+        hipLaunchKernelGGL((k_scan<W, MODE, false>), g, dim3(SCAN_THREADS), 0, st, A, nA, B,
                            nB, top, row_off, row_cnt, out);
     return hipGetLastError();
 }
