@@ -19,21 +19,10 @@
 
 namespace cch {
 // launchers defined in the kernel files
-hipError_t launch_pair_values(int W, TgtInts I, const uint64_t *da, const uint64_t *db, PairList pl,
-                              int64_t n, double *hv, hipStream_t st);
 hipError_t launch_energy_rows(int nrows, const int32_t *rn, const int32_t *rn2, const double *E, double *HT,
                               hipStream_t st);
-hipError_t launch_projection(int M, const int64_t *row_off, const int64_t *row_cnt, PairList pl,
-                             const double *hv, const double *ca, int Sa, const double *cb, int Sb,
-                             int nrows, const int32_t *rn, const int32_t *rn2, double *Y, double *Yo,
-                             double *HT, double *O, hipStream_t st);
-hipError_t launch_bucket(PairList pl, int64_t n, const int32_t *pqidx, int n_o, int n_slot, int M,
-                         int32_t *key, int64_t *count, int64_t *start, int64_t *cursor, int64_t *sorted,
-                         int64_t *tmp, int64_t *d0, hipStream_t st);
-hipError_t launch_gamma(int W, PairList pl, const int64_t *start, const int64_t *count,
-                        const int64_t *sorted, const int64_t *d0, int M0, const int32_t *slotP, const int32_t *slotQ,
-                        const GammaList &gl, const uint64_t *da, const int8_t *spa, const int8_t *spb, const double *ca,
-                        int Sa, const double *cb, int Sb, bool tri, double *At, hipStream_t st);
+hipError_t launch_target_sums(int W, const TgtInts &I, int n_o, const std::vector<PairJob> &h, const PairJob *jobs,
+                              hipStream_t st);
 hipError_t launch_relayout(const double *ttcc, const double *tctc, int n_o, int n_cont, const int32_t *slotPJ,
                            const int32_t *slotQJ, int nJ, const int32_t *slotPK, const int32_t *slotQK, int nK,
                            int ja0, int nca, int jb0, int ncb, double *B, hipStream_t st, const PackedCC *pk);
@@ -95,12 +84,11 @@ hipError_t launch_expand_f64_batched(const GemmTask *tasks, int ntask, int64_t t
                                      hipStream_t st);
 hipError_t launch_l2_batched(int W, const L2Task *tasks, int ntask, int64_t total, int grid, hipStream_t st);
 hipError_t launch_class4_batched(const C4Task *tasks, int ntask, int64_t total, int grid, hipStream_t st);
-hipError_t launch_mirror(double *H, int64_t ld, int D, int C, hipStream_t st);
+hipError_t launch_mirror(double *H, int64_t ld, int D, int C, double *diag, hipStream_t st);
 hipError_t launch_scatter_pairs(const int32_t *px, const int32_t *py, const double *v, int64_t n, int transpose,
                                 double *out, int64_t ldo, hipStream_t st);
 hipError_t launch_pair_census(const int8_t *deg, const uint64_t *label, int64_t n, unsigned long long *out,
                               hipStream_t st);
-hipError_t launch_diag(const double *H, int64_t ld, int D, double *out, hipStream_t st);
 hipError_t launch_gather_elements(const double *H, int64_t ldh, const int64_t *rows, const int64_t *cols, int64_t n,
                                   double *out, hipStream_t st);
 hipError_t launch_get_block(const double *H, int64_t ldh, int64_t row0, int nrows, int64_t col0, int ncols, int mode,
@@ -379,6 +367,11 @@ struct cch_ctx {
     double *d_R = nullptr;
     int64_t ldr = 0;
     std::vector<PairPlan> pp;
+    // tables for the launches that take all of a build's scans or symmetry pairs
+    ScanJob *d_tt_scans = nullptr, *d_lt_scans = nullptr;
+    PairJob *d_jobs = nullptr;
+    std::vector<PairJob> h_jobs;
+    int max_dets = 0;
     std::vector<LtPlan> lt;
     hipEvent_t ev[8] = {};
     hipEvent_t mv0 = nullptr, mv1 = nullptr, rr0 = nullptr, rr1 = nullptr;
@@ -931,7 +924,7 @@ static cch_status alloc_pairs(cch_ctx *c, DevPairs &p, int mode, const uint64_t 
     TRY(dalloc(c, &p.row_cnt, nA));
     int64_t *d_total = nullptr;
     TRY(dalloc(c, &d_total, 1));
-    HIPCK(c, launch_scan(mode, c->W, A, nA, B, nB, 2 * c->n_o, nullptr, p.row_cnt, PairList{}, c->stream));
+    HIPCK(c, launch_scan(mode, c->W, ScanJob{A, B, nA, nB, nullptr, p.row_cnt}, 2 * c->n_o, c->stream));
     HIPCK(c, launch_exclusive_scan(p.row_cnt, p.row_off, nA, d_total, c->stream));
     int64_t total = 0;
     HIPCK(c, hipMemcpyAsync(&total, d_total, 8, hipMemcpyDeviceToHost, c->stream));
@@ -950,6 +943,80 @@ static cch_status upload(cch_ctx *c, T **d, const std::vector<T> &h)
 {
     TRY(dalloc(c, d, h.size()));
     if (!h.empty()) HIPCK(c, hipMemcpy(*d, h.data(), h.size() * sizeof(T), hipMemcpyHostToDevice));
+    return CCH_OK;
+}
+
+// The tables of scans and of symmetry pairs that a build's launches read. They
+// hold addresses and sizes of the plan's buffers, some hundred bytes a pair, and
+// are no part of a caller's memory budget.
+template <class T>
+static cch_status table(cch_ctx *c, T **d, const std::vector<T> &h)
+{
+    if (h.empty()) return CCH_OK;
+    void *q = nullptr;
+    if (hipMalloc(&q, sizeof(T) * h.size()) != hipSuccess) return fail(c, CCH_E_OOM, "job tables");
+    c->allocs.push_back(q);
+    *d = (T *)q;
+    HIPCK(c, hipMemcpy(q, h.data(), sizeof(T) * h.size(), hipMemcpyHostToDevice));
+    return CCH_OK;
+}
+
+static cch_status job_tables(cch_ctx *c)
+{
+    std::vector<ScanJob> tt, lt;
+    c->h_jobs.clear();
+    c->max_dets = 0;
+    for (auto &p : c->pp) {
+        const SymInfo &sa = c->syms[p.a], &sb = c->syms[p.b];
+        c->max_dets = std::max(c->max_dets, sa.M);
+        tt.push_back(ScanJob{sa.d_dets, sb.d_dets, sa.M, sb.M, p.pr.row_off, p.pr.row_cnt, p.pr.pl, p.d_count, p.d_cursor,
+                             p.d_d0, p.n_slot + 1, sa.M});
+        PairJob j{};
+        j.da = sa.d_dets;
+        j.db = sb.d_dets;
+        j.spa = sa.d_cspin;
+        j.spb = sb.d_cspin;
+        j.ca = sa.d_ci;
+        j.cb = sb.d_ci;
+        j.Ma = sa.M;
+        j.Sa = sa.S;
+        j.Sb = sb.S;
+        j.tri = p.a == p.b;
+        j.nrows = p.nrows;
+        j.M0 = sa.irrep == sb.irrep ? sa.M : 0;
+        j.n = p.pr.n;
+        j.row_off = p.pr.row_off;
+        j.row_cnt = p.pr.row_cnt;
+        j.pl = p.pr.pl;
+        j.hv = p.d_hv;
+        j.Y = p.d_Y;
+        j.Yo = p.d_Yo;
+        j.HT = p.d_HT;
+        j.O = p.d_O;
+        j.rn = p.d_rn;
+        j.rn2 = p.d_rn2;
+        j.pqidx = p.d_pqidx;
+        j.slotP = p.d_slotP;
+        j.slotQ = p.d_slotQ;
+        j.n_slot = p.n_slot;
+        j.key = p.d_key;
+        j.count = p.d_count;
+        j.start = p.d_start;
+        j.cursor = p.d_cursor;
+        j.sorted = p.d_sorted;
+        j.tmp = p.d_tmp;
+        j.d0 = p.d_d0;
+        j.gl = GammaList{p.form, p.form == GAM_PLAIN ? p.n_slot : p.nF, p.d_k1, p.d_k2};
+        j.At = p.d_At;
+        c->h_jobs.push_back(j);
+    }
+    for (auto &L : c->lt) {
+        const SymInfo &s = c->syms[L.sym];
+        lt.push_back(ScanJob{c->d_l2, s.d_dets, c->n_l2, s.M, L.pr.row_off, L.pr.row_cnt, L.pr.pl});
+    }
+    TRY(table(c, &c->d_tt_scans, tt));
+    TRY(table(c, &c->d_lt_scans, lt));
+    TRY(table(c, &c->d_jobs, c->h_jobs));
     return CCH_OK;
 }
 
@@ -1173,6 +1240,7 @@ cch_status cch_plan(cch_ctx *c, const cch_plan_opts *opts)
             c->b_shared = true;
         }
     }
+    TRY(job_tables(c));
     c->planned = true;
     return CCH_OK;
 }
@@ -1292,52 +1360,28 @@ static hipError_t relayout_f64(cch_ctx *c, const PairPlan &p, int j0, int j1, hi
                            sa.ja0 + j0, j1 - j0, sb.ja0, sb.nc, p.d_B, st, c->packed ? &pk : nullptr);
 }
 
-// phases 0-2: scans, target elements and densities, relayout; every symmetry
-// pair (and L2-target group) writes only its own buffers, so with `fan` they
-// run on the auxiliary streams side by side
+// phases 0-2: scans, target elements and densities (a launch per stage for all
+// symmetry pairs: ten of them had 110 launches at D = 8000, 0.27 of 1.29 ms, and
+// sixteen small instances 1.9 of 6.5 ms), then the relayouts; every pair writes
+// only its own buffers, so with `fan` these run on the auxiliary streams side by
+// side
 static cch_status enqueue_pre(cch_ctx *c, hipStream_t st, bool ev, bool fan, bool lt_scans = true)
 {
     const TgtInts I{c->d_h, c->d_tttt, c->n_o, c->n_orb, c->e_core};
     const Fan f{c, st, fan && c->have_aux};
     EVREC(0);
-    HIPCK(c, f.begin());
-    int w = 0;
-    for (auto &p : c->pp) {
-        SymInfo &sa = c->syms[p.a], &sb = c->syms[p.b];
-        HIPCK(c, launch_scan(SCAN_TT, c->W, sa.d_dets, sa.M, sb.d_dets, sb.M, 2 * c->n_o, p.pr.row_off,
-                             p.pr.row_cnt, p.pr.pl, f(w++)));
-    }
-    for (auto &L : c->lt) {
-        if (!lt_scans) break;
-        SymInfo &s = c->syms[L.sym];
-        HIPCK(c, launch_scan(SCAN_LT, c->W, c->d_l2, c->n_l2, s.d_dets, s.M, 2 * c->n_o, L.pr.row_off,
-                             L.pr.row_cnt, L.pr.pl, f(w++)));
-    }
-    HIPCK(c, f.end());
+    HIPCK(c, launch_scans(SCAN_TT, c->W, c->d_tt_scans, (int)c->pp.size(), c->max_dets, 2 * c->n_o, st));
+    if (lt_scans)
+        HIPCK(c, launch_scans(SCAN_LT, c->W, c->d_lt_scans, (int)c->lt.size(), c->n_l2, 2 * c->n_o, st));
     EVREC(1);
-    HIPCK(c, f.begin());
-    w = 0;
-    for (auto &p : c->pp) {
-        SymInfo &sa = c->syms[p.a], &sb = c->syms[p.b];
-        const hipStream_t s = f(w++);
-        HIPCK(c, launch_pair_values(c->W, I, sa.d_dets, sb.d_dets, p.pr.pl, p.pr.n, p.d_hv, s));
-        HIPCK(c, launch_projection(sa.M, p.pr.row_off, p.pr.row_cnt, p.pr.pl, p.d_hv, sa.d_ci, sa.S, sb.d_ci, sb.S,
-                                   p.nrows, p.d_rn, p.d_rn2, p.d_Y, p.d_Yo, p.d_HT, p.d_O, s));
-        if (c->energy_mode)
-            HIPCK(c, launch_energy_rows(p.nrows, p.d_rn, p.d_rn2, p.a == p.b ? c->d_tgtE + sa.e_off : nullptr,
-                                        p.d_HT, s));
-        HIPCK(c, launch_bucket(p.pr.pl, p.pr.n, p.d_pqidx, c->n_o, p.n_slot, sa.M, p.d_key, p.d_count, p.d_start,
-                               p.d_cursor, p.d_sorted, p.d_tmp, p.d_d0, s));
-        const int M0 = (sa.irrep == sb.irrep) ? sa.M : 0;
-        const GammaList gl{p.form, p.form == GAM_PLAIN ? p.n_slot : p.nF, p.d_k1, p.d_k2};
-        HIPCK(c, launch_gamma(c->W, p.pr.pl, p.d_start, p.d_count, p.d_sorted, p.d_d0, M0, p.d_slotP, p.d_slotQ,
-                              gl, sa.d_dets, sa.d_cspin, sb.d_cspin, sa.d_ci, sa.S, sb.d_ci, sb.S, p.a == p.b,
-                              p.d_At, s));
-    }
-    HIPCK(c, f.end());
+    HIPCK(c, launch_target_sums(c->W, I, c->n_o, c->h_jobs, c->d_jobs, st));
+    if (c->energy_mode)
+        for (auto &p : c->pp)
+            HIPCK(c, launch_energy_rows(p.nrows, p.d_rn, p.d_rn2,
+                                        p.a == p.b ? c->d_tgtE + c->syms[p.a].e_off : nullptr, p.d_HT, st));
+    int w = 0;
     EVREC(2);
     HIPCK(c, f.begin());
-    w = 0;
     for (auto &p : c->pp) {
         SymInfo &sa = c->syms[p.a], &sb = c->syms[p.b];
         if (sa.nc == 0 || sb.nc == 0) continue;
@@ -1431,8 +1475,7 @@ static cch_status enqueue_post(cch_ctx *c, hipStream_t st)
 {
     if (c->sparse) {
         // upper triangle of the continuum block, its diagonal, and the transpose of class 4
-        HIPCK(c, launch_mirror(c->d_H, c->ld, (int)c->Dc, (int)c->Dc, st));
-        HIPCK(c, launch_diag(c->d_H, c->ld, (int)c->Dc, c->d_diag, st));
+        HIPCK(c, launch_mirror(c->d_H, c->ld, (int)c->Dc, (int)c->Dc, c->d_diag, st));
         HIPCK(c, launch_transpose_c4(c->d_H, c->ld, (int)c->Dc, c->n_l2, c->d_R, c->ldr, st));
         return CCH_OK;
     }
@@ -1441,8 +1484,7 @@ static cch_status enqueue_post(cch_ctx *c, hipStream_t st)
                                      c->d_csf_coef, c->d_H, c->ld, st));
     // the L2 block kernel writes both triangles (not over CSFs, whose gather
     // writes the lower one)
-    HIPCK(c, launch_mirror(c->d_H, c->ld, (int)c->D, (int)(c->l2csf ? c->D : c->Dc), st));
-    HIPCK(c, launch_diag(c->d_H, c->ld, (int)c->D, c->d_diag, st));
+    HIPCK(c, launch_mirror(c->d_H, c->ld, (int)c->D, (int)(c->l2csf ? c->D : c->Dc), c->d_diag, st));
     return CCH_OK;
 }
 
@@ -1474,11 +1516,7 @@ cch_status cch_build(cch_ctx *c)
         TRY(enqueue_l2(c, sl));
         HIPCK(c, hipEventRecord(c->l2_ev[1], sl));
         HIPCK(c, hipEventRecord(c->c4_ev[0], s4));
-        for (auto &L : c->lt) {
-            SymInfo &s = c->syms[L.sym];
-            HIPCK(c, launch_scan(SCAN_LT, c->W, c->d_l2, c->n_l2, s.d_dets, s.M, 2 * c->n_o, L.pr.row_off,
-                                 L.pr.row_cnt, L.pr.pl, s4));
-        }
+        HIPCK(c, launch_scans(SCAN_LT, c->W, c->d_lt_scans, (int)c->lt.size(), c->n_l2, 2 * c->n_o, s4));
         TRY(enqueue_class4(c, s4, false));
         HIPCK(c, hipEventRecord(c->c4_ev[1], s4));
         TRY(enqueue_pre(c, st, ev, true, false));
@@ -1644,7 +1682,7 @@ cch_status cch_work_detail(cch_ctx *c, double *out, int32_t n)
         if (e == hipSuccess) e = galloc((void **)&ro, 8 * (size_t)c->n_l2);
         if (e == hipSuccess) e = galloc((void **)&tot, 8);
         if (e == hipSuccess)
-            e = launch_scan(SCAN_LL, c->W, c->d_l2, c->n_l2, c->d_l2, c->n_l2, 2 * c->n_o, nullptr, rc, PairList{},
+            e = launch_scan(SCAN_LL, c->W, ScanJob{c->d_l2, c->d_l2, c->n_l2, c->n_l2, nullptr, rc}, 2 * c->n_o,
                             c->stream);
         if (e == hipSuccess) e = launch_exclusive_scan(rc, ro, c->n_l2, tot, c->stream);
         if (e == hipSuccess) e = hipMemcpyAsync(&h, tot, 8, hipMemcpyDeviceToHost, c->stream);
@@ -2257,7 +2295,7 @@ cch_status cch_get_labels(cch_ctx *c, int32_t which, int32_t sym_a, int32_t sym_
     hipError_t e = galloc((void **)&P.row_off, 8 * (size_t)nA);
     if (e == hipSuccess) e = galloc((void **)&P.row_cnt, 8 * (size_t)nA);
     if (e == hipSuccess) e = galloc((void **)&d_total, 8);
-    if (e == hipSuccess) e = launch_scan(mode, c->W, A, nA, B, nB, 2 * c->n_o, nullptr, P.row_cnt, PairList{}, c->stream);
+    if (e == hipSuccess) e = launch_scan(mode, c->W, ScanJob{A, B, nA, nB, nullptr, P.row_cnt}, 2 * c->n_o, c->stream);
     if (e == hipSuccess) e = launch_exclusive_scan(P.row_cnt, P.row_off, nA, d_total, c->stream);
     int64_t total = 0;
     if (e == hipSuccess) e = hipMemcpyAsync(&total, d_total, 8, hipMemcpyDeviceToHost, c->stream);
@@ -2267,7 +2305,7 @@ cch_status cch_get_labels(cch_ctx *c, int32_t which, int32_t sym_a, int32_t sym_
     if (e == hipSuccess) e = galloc((void **)&P.pl.deg, (size_t)total);
     if (e == hipSuccess) e = galloc((void **)&P.pl.phase, (size_t)total);
     if (e == hipSuccess) e = galloc((void **)&P.pl.label, 8 * (size_t)total);
-    if (e == hipSuccess) e = launch_scan(mode, c->W, A, nA, B, nB, 2 * c->n_o, P.row_off, P.row_cnt, P.pl, c->stream);
+    if (e == hipSuccess) e = launch_scan(mode, c->W, ScanJob{A, B, nA, nB, P.row_off, P.row_cnt, P.pl}, 2 * c->n_o, c->stream);
     const int64_t m = std::min(total, cap);
     if (e == hipSuccess && m > 0) {
         if (x) e = hipMemcpyAsync(x, P.pl.x, 4 * m, hipMemcpyDeviceToHost, c->stream);

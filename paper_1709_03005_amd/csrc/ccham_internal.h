@@ -339,6 +339,20 @@ struct PairList {
 
 enum ScanMode { SCAN_TT = 0, SCAN_LL = 1, SCAN_LT = 2 };
 
+// one excitation scan: bras A against kets B; emits from row_off[x], or counts
+// into row_cnt (row_off = nullptr). An emitting scan may also clear words that
+// later kernels of the stream count in: zero0 and zero1 (nz each), ones (no words
+// set to -1)
+struct ScanJob {
+    const uint64_t *A, *B;
+    int nA, nB;
+    const int64_t *row_off;
+    int64_t *row_cnt;
+    PairList out;
+    int64_t *zero0, *zero1, *ones;
+    int nz, no;
+};
+
 // the symmetry-packed two-continuum integrals, for one relayout launch: record
 // of the target pair (P, Q) at rec[P * n_o + Q]; inside it, the (tt|cc) rows
 // of this launch start at boffJ (row length ncb), the (tc|tc) block of the
@@ -355,6 +369,26 @@ enum GammaMode { GAM_PLAIN = 0, GAM_RECT = 1, GAM_SQUARE = 2 };
 struct GammaList {
     int mode, n;
     const int32_t *k1, *k2;
+};
+
+// the target-space sums of one symmetry pair (k_target.hip): every kernel of a
+// build takes all pairs in one launch, pair blockIdx.y of a table on the device
+struct PairJob {
+    const uint64_t *da, *db;     // determinants of the two symmetries
+    const int8_t *spa, *spb;     // continuum spins per determinant or nullptr
+    const double *ca, *cb;       // [Ma][Sa], [Mb][Sb]
+    int Ma, Sa, Sb, tri, nrows;  // tri: a symmetry with itself, states n' <= n
+    int M0;                      // Ma if the symmetries share an irrep, else 0
+    int64_t n;                   // connected pairs
+    const int64_t *row_off, *row_cnt;
+    PairList pl;
+    double *hv, *Y, *Yo, *HT, *O;
+    const int32_t *rn, *rn2, *pqidx, *slotP, *slotQ;
+    int n_slot;
+    int32_t *key;
+    int64_t *count, *start, *cursor, *sorted, *tmp, *d0;
+    GammaList gl;
+    double *At;
 };
 
 // work vectors of the Householder tridiagonalisation (length n each): x = the
@@ -478,9 +512,8 @@ struct DavSel {
 };
 
 struct GemmDesc;
-hipError_t launch_scan(int mode, int W, const uint64_t *A, int nA, const uint64_t *B, int nB,
-                       int top, const int64_t *row_off, int64_t *row_cnt, PairList out,
-                       hipStream_t st);
+hipError_t launch_scan(int mode, int W, const ScanJob &one, int top, hipStream_t st);
+hipError_t launch_scans(int mode, int W, const ScanJob *jobs, int njob, int max_rows, int top, hipStream_t st);
 hipError_t launch_exclusive_scan(const int64_t *in, int64_t *out, int n, int64_t *total,
                                  hipStream_t st);
 hipError_t launch_symv(const double *H, int64_t ld, int D, int C, const double *V, int64_t ldv, int b, double *W,

@@ -1,6 +1,6 @@
 // Matrix bookkeeping kernels: mirror of the lower triangle (the matrix is
 // real symmetric and only the lower triangle is evaluated, Sec. 2.2),
-// diagonal extraction, and fills that replace memsets on the stream.
+// with the diagonal's extraction, and fills that replace memsets on the stream.
 #include <algorithm>
 
 #include "ccham_internal.h"
@@ -10,10 +10,17 @@ namespace cch {
 // H[c][r] = H[r][c] for r > c and c < C, over the 64 x 64 tiles of the lower
 // triangle with a column before C; tiles go through LDS so both reads and
 // writes are coalesced. (The L2 block, behind the C continuum columns, is
-// written to both triangles by its own kernel.)
-__global__ __launch_bounds__(256) void k_mirror(double *__restrict__ H, int64_t ld, int D, int C)
+// written to both triangles by its own kernel.) The workgroups past the tiles copy
+// the diagonal, which the mirror does not touch.
+__global__ __launch_bounds__(256) void k_mirror(double *__restrict__ H, int64_t ld, int D, int C, int64_t tiles,
+                                                double *__restrict__ diag)
 {
     __shared__ double tile[64][65];
+    if ((int64_t)blockIdx.x >= tiles) {
+        const int i = (int)(blockIdx.x - tiles) * 256 + (int)threadIdx.x;
+        if (i < D) diag[i] = H[(int64_t)i * ld + i];
+        return;
+    }
     // tile columns 0 .. tc-1; rows of tiles first by their triangle, then full
     const int64_t tc = (C + 63) / 64, b = blockIdx.x, ntri = tc * (tc + 1) / 2;
     int64_t ti, tj;
@@ -42,25 +49,12 @@ __global__ __launch_bounds__(256) void k_mirror(double *__restrict__ H, int64_t 
     }
 }
 
-// C = D: the whole matrix
-hipError_t launch_mirror(double *H, int64_t ld, int D, int C, hipStream_t st)
-{
-    if (D <= 0 || C <= 0) return hipSuccess;
-    const int64_t T = (D + 63) / 64, tc = (C + 63) / 64;
-    hipLaunchKernelGGL(k_mirror, dim3((unsigned)(tc * (tc + 1) / 2 + (T - tc) * tc)), dim3(256), 0, st, H, ld, D, C);
-    return hipGetLastError();
-}
-
-__global__ void k_diag(const double *__restrict__ H, int64_t ld, int D, double *__restrict__ out)
-{
-    const int i = blockIdx.x * blockDim.x + threadIdx.x;
-    if (i < D) out[i] = H[(int64_t)i * ld + i];
-}
-
-hipError_t launch_diag(const double *H, int64_t ld, int D, double *out, hipStream_t st)
+// C = D: the whole matrix; diag[i] = H[i][i], i < D
+hipError_t launch_mirror(double *H, int64_t ld, int D, int C, double *diag, hipStream_t st)
 {
     if (D <= 0) return hipSuccess;
-    hipLaunchKernelGGL(k_diag, dim3((D + 255) / 256), dim3(256), 0, st, H, ld, D, out);
+    const int64_t T = (D + 63) / 64, tc = (std::max(C, 0) + 63) / 64, tiles = tc * (tc + 1) / 2 + (T - tc) * tc;
+    hipLaunchKernelGGL(k_mirror, dim3((unsigned)(tiles + (D + 255) / 256)), dim3(256), 0, st, H, ld, D, C, tiles, diag);
     return hipGetLastError();
 }
 

@@ -19,11 +19,17 @@ namespace cch {
 constexpr int SCAN_THREADS = 256, SCAN_WAVES = SCAN_THREADS / 64;
 
 template <int W, int MODE, bool EMIT>
-__global__ __launch_bounds__(SCAN_THREADS) void k_scan(const uint64_t *__restrict__ A, int nA,
-                                                       const uint64_t *__restrict__ B, int nB,
-                                                       int top, const int64_t *__restrict__ row_off,
-                                                       int64_t *__restrict__ row_cnt, PairList out)
+__global__ __launch_bounds__(SCAN_THREADS) void k_scan(ScanJob one, const ScanJob *__restrict__ many, int top)
 {
+    const ScanJob J = many ? many[blockIdx.y] : one;
+    const uint64_t *A = J.A, *B = J.B;
+    const int nA = J.nA, nB = J.nB;
+    const PairList out = J.out;
+    if (EMIT) {
+        for (int i = blockIdx.x * SCAN_THREADS + threadIdx.x; i < J.nz; i += gridDim.x * SCAN_THREADS)
+            J.zero0[i] = J.zero1[i] = 0;
+        for (int i = blockIdx.x * SCAN_THREADS + threadIdx.x; i < J.no; i += gridDim.x * SCAN_THREADS) J.ones[i] = -1;
+    }
     __shared__ int32_t found[SCAN_WAVES][128];   // connected kets: fewer than 64 and one step's
     const int lane = threadIdx.x & 63, wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int x = blockIdx.x * SCAN_WAVES + wv;
@@ -33,7 +39,7 @@ __global__ __launch_bounds__(SCAN_THREADS) void k_scan(const uint64_t *__restric
 #pragma unroll
     for (int w = 0; w < W; ++w) a[w] = A[(size_t)x * W + w];
     const int ylim = (MODE == SCAN_LL) ? x + 1 : nB;
-    int64_t at = EMIT ? row_off[x] : 0;
+    int64_t at = EMIT ? J.row_off[x] : 0;
     int n = 0;   // listed
     // kets are read two steps ahead
     uint64_t b0[W], b1[W];
@@ -99,77 +105,105 @@ __global__ __launch_bounds__(SCAN_THREADS) void k_scan(const uint64_t *__restric
             wave_order();
         }
     }
-    if (!EMIT && lane == 0) row_cnt[x] = at;
-}
-
-template <int W, int MODE>
-static hipError_t scan_w(const uint64_t *A, int nA, const uint64_t *B, int nB, int top,
-                         const int64_t *row_off, int64_t *row_cnt, PairList out, hipStream_t st)
-{
-    if (nA <= 0) return hipSuccess;
-    const dim3 g((nA + SCAN_WAVES - 1) / SCAN_WAVES);
-    if (row_off)
-        hipLaunchKernelGGL((k_scan<W, MODE, true>), g, dim3(SCAN_THREADS), 0, st, A, nA, B,
-                           nB, top, row_off, row_cnt, out);
-    else
-        hipLaunchKernelGGL((k_scan<W, MODE, false>), g, dim3(SCAN_THREADS), 0, st, A, nA, B,
-                           nB, top, row_off, row_cnt, out);
-    return hipGetLastError();
+    if (!EMIT && lane == 0) J.row_cnt[x] = at;
 }
 
 template <int MODE>
-static hipError_t scan_mode(int W, const uint64_t *A, int nA, const uint64_t *B, int nB, int top,
-                            const int64_t *row_off, int64_t *row_cnt, PairList out, hipStream_t st)
+static hipError_t scan_mode(int W, const ScanJob &one, const ScanJob *many, int njob, int rows, bool emit, int top,
+                            hipStream_t st)
 {
+    const dim3 g((rows + SCAN_WAVES - 1) / SCAN_WAVES, njob), b(SCAN_THREADS);
+#define SCAN_CASE(W_)                                                                                \
+    case W_:                                                                                         \
+        if (emit) hipLaunchKernelGGL((k_scan<W_, MODE, true>), g, b, 0, st, one, many, top);         \
+        else hipLaunchKernelGGL((k_scan<W_, MODE, false>), g, b, 0, st, one, many, top);             \
+        return hipGetLastError();
     switch (W) {
-    case 1: return scan_w<1, MODE>(A, nA, B, nB, top, row_off, row_cnt, out, st);
-    case 2: return scan_w<2, MODE>(A, nA, B, nB, top, row_off, row_cnt, out, st);
-    case 3: return scan_w<3, MODE>(A, nA, B, nB, top, row_off, row_cnt, out, st);
-    case 4: return scan_w<4, MODE>(A, nA, B, nB, top, row_off, row_cnt, out, st);
+        SCAN_CASE(1)
+        SCAN_CASE(2)
+        SCAN_CASE(3)
+        SCAN_CASE(4)
+    }
+#undef SCAN_CASE
+    return hipErrorInvalidValue;
+}
+
+static hipError_t scan_any(int mode, int W, const ScanJob &one, const ScanJob *many, int njob, int rows, bool emit,
+                           int top, hipStream_t st)
+{
+    if (rows <= 0 || njob <= 0) return hipSuccess;
+    switch (mode) {
+    case SCAN_TT: return scan_mode<SCAN_TT>(W, one, many, njob, rows, emit, top, st);
+    case SCAN_LL: return scan_mode<SCAN_LL>(W, one, many, njob, rows, emit, top, st);
+    case SCAN_LT: return scan_mode<SCAN_LT>(W, one, many, njob, rows, emit, top, st);
     }
     return hipErrorInvalidValue;
 }
 
 // mode SCAN_TT/SCAN_LL/SCAN_LT; row_off == nullptr: count pass into row_cnt,
 // else emit pass writing pairs from row_off[x].
-hipError_t launch_scan(int mode, int W, const uint64_t *A, int nA, const uint64_t *B, int nB, int top,
-                       const int64_t *row_off, int64_t *row_cnt, PairList out, hipStream_t st)
+hipError_t launch_scan(int mode, int W, const ScanJob &one, int top, hipStream_t st)
 {
-    switch (mode) {
-    case SCAN_TT: return scan_mode<SCAN_TT>(W, A, nA, B, nB, top, row_off, row_cnt, out, st);
-    case SCAN_LL: return scan_mode<SCAN_LL>(W, A, nA, B, nB, top, row_off, row_cnt, out, st);
-    case SCAN_LT: return scan_mode<SCAN_LT>(W, A, nA, B, nB, top, row_off, row_cnt, out, st);
-    }
-    return hipErrorInvalidValue;
+    return scan_any(mode, W, one, nullptr, 1, one.nA, one.row_off != nullptr, top, st);
+}
+
+// emit passes of a table of scans on the device, the longest of max_rows rows
+hipError_t launch_scans(int mode, int W, const ScanJob *jobs, int njob, int max_rows, int top, hipStream_t st)
+{
+    return scan_any(mode, W, ScanJob{}, jobs, njob, max_rows, true, top, st);
 }
 
 // ---------------------------------------------------------------------------
 // exclusive prefix sum of int64 counts, one workgroup (n up to a few 1e5)
 // ---------------------------------------------------------------------------
-__global__ __launch_bounds__(1024) void k_exscan(const int64_t *__restrict__ in, int64_t *__restrict__ out,
-                                                 int n, int64_t *__restrict__ total)
+__device__ __forceinline__ void exscan_block(const int64_t *__restrict__ in, int64_t *__restrict__ out, int n,
+                                             int64_t *__restrict__ total)
 {
-    __shared__ int64_t buf[1024];
-    __shared__ int64_t carry;
-    if (threadIdx.x == 0) carry = 0;
-    __syncthreads();
+    __shared__ int64_t wave[16];
+    const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
+    int64_t carry = 0;
     for (int b0 = 0; b0 < n; b0 += 1024) {
         const int i = b0 + threadIdx.x;
         const int64_t v = i < n ? in[i] : 0;
-        buf[threadIdx.x] = v;
-        __syncthreads();
-        for (int o = 1; o < 1024; o <<= 1) {
-            int64_t t = threadIdx.x >= o ? buf[threadIdx.x - o] : 0;
-            __syncthreads();
-            buf[threadIdx.x] += t;
-            __syncthreads();
+        int64_t s = v;   // inclusive over the wave
+#pragma unroll
+        for (int o = 1; o < 64; o <<= 1) {
+            const int64_t t = __shfl_up(s, o, 64);
+            if (lane >= o) s += t;
         }
-        if (i < n) out[i] = carry + buf[threadIdx.x] - v;
+        __syncthreads();   // the sums of the chunk before have been read
+        if (lane == 63) wave[wv] = s;
         __syncthreads();
-        if (threadIdx.x == 0) carry += buf[1023];
-        __syncthreads();
+        int64_t before = 0, all = 0;
+#pragma unroll
+        for (int k = 0; k < 16; ++k) {
+            before += k < wv ? wave[k] : 0;
+            all += wave[k];
+        }
+        if (i < n) out[i] = carry + before + s - v;
+        carry += all;
     }
     if (threadIdx.x == 0 && total) *total = carry;
+}
+
+__global__ __launch_bounds__(1024) void k_exscan(const int64_t *__restrict__ in, int64_t *__restrict__ out, int n,
+                                                 int64_t *__restrict__ total)
+{
+    exscan_block(in, out, n, total);
+}
+
+// first entries of the label buckets, a symmetry pair a workgroup
+__global__ __launch_bounds__(1024) void k_slot_start(const PairJob *__restrict__ jobs)
+{
+    const PairJob &J = jobs[blockIdx.x];
+    exscan_block(J.count, J.start, J.n_slot, nullptr);
+}
+
+hipError_t launch_slot_start(const PairJob *jobs, int njob, hipStream_t st)
+{
+    if (njob <= 0) return hipSuccess;
+    hipLaunchKernelGGL(k_slot_start, dim3(njob), dim3(1024), 0, st, jobs);
+    return hipGetLastError();
 }
 
 hipError_t launch_exclusive_scan(const int64_t *in, int64_t *out, int n, int64_t *total, hipStream_t st)

@@ -7,50 +7,43 @@
 //     labels (P Q | j j') and (P j' | j Q): spin-summed and alpha-resolved
 //     transition densities Gamma_{nn',PQ} = sum_mm' c_imn c_i'm'n' <m|E_PQ|m'>,
 //     accumulated per label from the pairs bucketed by label (deterministic).
+#include <algorithm>
+#include <vector>
+
 #include "ccham_internal.h"
 
 namespace cch {
 
-// ---------------------------------------------------------------------------
-// H_T values of the connected pairs
+// H_T values of the connected pairs, and their buckets by integral label (P, Q):
+// key = slot of a degree-1 pair, counted; degree-0 pairs are recorded per bra row;
+// degree 2 has no density term. (Counters and records were cleared by the scan.)
 // ---------------------------------------------------------------------------
 template <int W>
-__global__ __launch_bounds__(256) void k_pair_values(TgtInts I, const uint64_t *__restrict__ da,
-                                                     const uint64_t *__restrict__ db, PairList pl,
-                                                     int64_t n, double *__restrict__ hv)
+__global__ __launch_bounds__(256) void k_pair_values(TgtInts I, int n_o, const PairJob *__restrict__ jobs)
 {
+    const PairJob &J = jobs[blockIdx.y];
     const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= n) return;
-    const int deg = pl.deg[i];
-    const uint64_t lab = pl.label[i];
+    if (i >= J.n) return;
+    const int deg = J.pl.deg[i], x = J.pl.x[i], y = J.pl.y[i];
+    const uint64_t lab = J.pl.label[i];
     int h[2] = {lab_field(lab, 1), lab_field(lab, 3)};
     int p[2] = {lab_field(lab, 0), lab_field(lab, 2)};
+    int k = -1;
+    if (deg == 1) k = J.pqidx[(p[0] >> 1) * n_o + (h[0] >> 1)];
+    else if (deg == 0) J.d0[x] = i;   // distinct determinants: at most one per bra row
+    J.key[i] = k;
+    if (k >= 0) atomicAdd((unsigned long long *)&J.count[k], 1ull);
     uint64_t A[W], B[W];
     int dm = 0;   // alpha electrons of the bra minus those of the ket
 #pragma unroll
     for (int w = 0; w < W; ++w) {
-        A[w] = da[(size_t)pl.x[i] * W + w];
-        B[w] = db[(size_t)pl.y[i] * W + w];
+        A[w] = J.da[(size_t)x * W + w];
+        B[w] = J.db[(size_t)y * W + w];
         dm += __popcll(A[w] & 0x5555555555555555ull) - __popcll(B[w] & 0x5555555555555555ull);
     }
     // target determinants of different M_S (given with continuum electrons of
     // different spin): the spin-free H_T has no element between them
-    hv[i] = dm ? 0.0 : sc_value<W>(I, A, B, deg, h, p, pl.phase[i]);
-}
-
-hipError_t launch_pair_values(int W, TgtInts I, const uint64_t *da, const uint64_t *db, PairList pl,
-                              int64_t n, double *hv, hipStream_t st)
-{
-    if (n <= 0) return hipSuccess;
-    const dim3 g((unsigned)((n + 255) / 256)), b(256);
-    switch (W) {
-    case 1: hipLaunchKernelGGL((k_pair_values<1>), g, b, 0, st, I, da, db, pl, n, hv); break;
-    case 2: hipLaunchKernelGGL((k_pair_values<2>), g, b, 0, st, I, da, db, pl, n, hv); break;
-    case 3: hipLaunchKernelGGL((k_pair_values<3>), g, b, 0, st, I, da, db, pl, n, hv); break;
-    case 4: hipLaunchKernelGGL((k_pair_values<4>), g, b, 0, st, I, da, db, pl, n, hv); break;
-    default: return hipErrorInvalidValue;
-    }
-    return hipGetLastError();
+    J.hv[i] = dm ? 0.0 : sc_value<W>(I, A, B, deg, h, p, J.pl.phase[i]);
 }
 
 // ---------------------------------------------------------------------------
@@ -68,19 +61,22 @@ hipError_t launch_pair_values(int W, TgtInts I, const uint64_t *da, const uint64
 // ---------------------------------------------------------------------------
 constexpr int SP_B = 8, SP_W = 8;
 
-__global__ __launch_bounds__(64 * SP_W) void k_spmm_rows(int M, const int64_t *__restrict__ row_off,
-                                                   const int64_t *__restrict__ row_cnt, PairList pl,
-                                                   const double *__restrict__ hv,
-                                                   const double *__restrict__ cb, int Sb, int lg_states,
-                                                   double *__restrict__ Y, double *__restrict__ Yo)
+__global__ __launch_bounds__(64 * SP_W) void k_spmm_rows(const PairJob *__restrict__ jobs)
 {
+    const PairJob &J = jobs[blockIdx.y];
+    if ((int)blockIdx.x >= J.Ma) return;
+    const PairList pl = J.pl;
+    const double *hv = J.hv, *cb = J.cb;
+    const int Sb = J.Sb;
+    int lg_states = 0;   // state lanes: the power of two >= Sb, at most 64
+    while ((1 << lg_states) < Sb && lg_states < 6) ++lg_states;
     __shared__ double red[2][SP_W][64];
     const int m = blockIdx.x;
     const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
     const int ns = 1 << lg_states;              // state lanes (power of two, <= 64)
     const int lg_g = 6 - lg_states;             // pair groups: 1 << lg_g
     const int nl = lane & (ns - 1), g = lane >> lg_states;
-    const int64_t p0 = row_off[m], np = row_cnt[m];
+    const int64_t p0 = J.row_off[m], np = J.row_cnt[m];
     // (the flag of a degree-0 pair in the sign bit of its row; a lane past the
     // row's end holds the row's first pair with value 0)
     auto pair = [&](int64_t q, int32_t &y, double &h) {
@@ -129,21 +125,19 @@ __global__ __launch_bounds__(64 * SP_W) void k_spmm_rows(int M, const int64_t *_
             double s = 0.0;
 #pragma unroll
             for (int z = 0; z < SP_W; ++z) s += red[wv][z][lane];
-            (wv ? Yo : Y)[(size_t)m * Sb + n] = s;
+            (wv ? J.Yo : J.Y)[(size_t)m * Sb + n] = s;
         }
     }
 }
 
 // HT[r] = sum_m ca[m][na[r]] Y[m][nb[r]],  O[r] likewise with Yo.
-__global__ __launch_bounds__(256) void k_project(int M, const double *__restrict__ ca, int Sa,
-                                                 const double *__restrict__ Y,
-                                                 const double *__restrict__ Yo, int Sb,
-                                                 const int32_t *__restrict__ rn,
-                                                 const int32_t *__restrict__ rn2,
-                                                 double *__restrict__ HT, double *__restrict__ O)
+__global__ __launch_bounds__(256) void k_project(const PairJob *__restrict__ jobs)
 {
-    const int r = blockIdx.x;
-    const int n = rn[r], n2 = rn2[r];
+    const PairJob &J = jobs[blockIdx.y];
+    const int r = blockIdx.x, M = J.Ma, Sa = J.Sa, Sb = J.Sb;
+    if (r >= J.nrows) return;
+    const double *ca = J.ca, *Y = J.Y, *Yo = J.Yo;
+    const int n = J.rn[r], n2 = J.rn2[r];
     double a = 0.0, b = 0.0;
     for (int m = threadIdx.x; m < M; m += 256) {
         const double c = ca[(size_t)m * Sa + n];
@@ -162,8 +156,8 @@ __global__ __launch_bounds__(256) void k_project(int M, const double *__restrict
         __syncthreads();
     }
     if (threadIdx.x == 0) {
-        HT[r] = ra[0];
-        O[r] = rb[0];
+        J.HT[r] = ra[0];
+        J.O[r] = rb[0];
     }
 }
 
@@ -186,56 +180,19 @@ hipError_t launch_energy_rows(int nrows, const int32_t *rn, const int32_t *rn2, 
     return hipGetLastError();
 }
 
-hipError_t launch_projection(int M, const int64_t *row_off, const int64_t *row_cnt, PairList pl,
-                             const double *hv, const double *ca, int Sa, const double *cb, int Sb,
-                             int nrows, const int32_t *rn, const int32_t *rn2, double *Y, double *Yo,
-                             double *HT, double *O, hipStream_t st)
-{
-    if (M > 0) {
-        int lg = 0;   // state lanes: the power of two >= Sb, at most 64
-        while ((1 << lg) < Sb && lg < 6) ++lg;
-        hipLaunchKernelGGL(k_spmm_rows, dim3(M), dim3(64 * SP_W), 0, st, M, row_off, row_cnt, pl,
-                           hv, cb, Sb, lg, Y, Yo);
-    }
-    hipLaunchKernelGGL(k_project, dim3(nrows), dim3(256), 0, st, M, ca, Sa, Y, Yo, Sb, rn, rn2, HT, O);
-    return hipGetLastError();
-}
-
 // ---------------------------------------------------------------------------
-// bucketing of pairs by integral label (P, Q): key = slot of a degree-1
-// pair; degree-0 pairs are recorded per bra row; degree 2 has no density
-// term. Counting sort with a per-bucket ordering by pair index so the
-// accumulation order is fixed.
+// bucketing of pairs by integral label: counting sort with a per-bucket ordering
+// by pair index so the accumulation order is fixed.
 // ---------------------------------------------------------------------------
-__global__ void k_slot_count(PairList pl, int64_t n, const int32_t *__restrict__ pqidx, int n_o,
-                             int32_t *__restrict__ key, int64_t *__restrict__ count,
-                             int64_t *__restrict__ d0)
+__global__ void k_slot_scatter(const PairJob *__restrict__ jobs)
 {
+    const PairJob &J = jobs[blockIdx.y];
     const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= n) return;
-    const int d = pl.deg[i];
-    int k = -1;
-    if (d == 1) {
-        const uint64_t lab = pl.label[i];
-        const int P = lab_field(lab, 0) >> 1, Q = lab_field(lab, 1) >> 1;
-        k = pqidx[P * n_o + Q];
-    } else if (d == 0) {
-        d0[pl.x[i]] = i;     // distinct determinants: at most one per bra row
-    }
-    key[i] = k;
-    if (k >= 0) atomicAdd((unsigned long long *)&count[k], 1ull);
-}
-
-__global__ void k_slot_scatter(int64_t n, const int32_t *__restrict__ key,
-                               const int64_t *__restrict__ start, int64_t *__restrict__ cursor,
-                               int64_t *__restrict__ sorted)
-{
-    const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= n) return;
-    const int k = key[i];
+    if (i >= J.n) return;
+    const int k = J.key[i];
     if (k < 0) return;
-    const int64_t pos = start[k] + (int64_t)atomicAdd((unsigned long long *)&cursor[k], 1ull);
-    sorted[pos] = i;
+    const int64_t pos = J.start[k] + (int64_t)atomicAdd((unsigned long long *)&J.cursor[k], 1ull);
+    J.sorted[pos] = i;
 }
 
 // sort inside each bucket (values are distinct pair indices), one workgroup
@@ -245,11 +202,12 @@ __global__ void k_slot_scatter(int64_t n, const int32_t *__restrict__ key,
 // of the other run's elements below it (binary search). O(n log^2 n) per
 // bucket; the result is the ascending order.
 constexpr int BS_CHUNK = 512;
-__global__ __launch_bounds__(256) void k_bucket_sort(const int64_t *__restrict__ start,
-                                                     const int64_t *__restrict__ count,
-                                                     int64_t *__restrict__ sorted,
-                                                     int64_t *__restrict__ tmp)
+__global__ __launch_bounds__(256) void k_bucket_sort(const PairJob *__restrict__ jobs)
 {
+    const PairJob &J = jobs[blockIdx.y];
+    if ((int)blockIdx.x >= J.n_slot) return;
+    const int64_t *start = J.start, *count = J.count;
+    int64_t *sorted = J.sorted, *tmp = J.tmp;
     __shared__ int64_t buf[BS_CHUNK];
     const int k = blockIdx.x;
     const int64_t s0 = start[k], n = count[k];
@@ -307,26 +265,6 @@ __global__ __launch_bounds__(256) void k_bucket_sort(const int64_t *__restrict__
     }
 }
 
-hipError_t launch_bucket(PairList pl, int64_t n, const int32_t *pqidx, int n_o, int n_slot, int M,
-                         int32_t *key, int64_t *count, int64_t *start, int64_t *cursor,
-                         int64_t *sorted, int64_t *tmp, int64_t *d0, hipStream_t st)
-{
-    hipError_t e;
-    if ((e = launch_fill_i64(count, 0, n_slot + 1, st)) != hipSuccess) return e;
-    if ((e = launch_fill_i64(cursor, 0, n_slot + 1, st)) != hipSuccess) return e;
-    if ((e = launch_fill_i64(d0, -1, M, st)) != hipSuccess) return e;
-    if (n > 0) {
-        const dim3 g((unsigned)((n + 255) / 256));
-        hipLaunchKernelGGL(k_slot_count, g, dim3(256), 0, st, pl, n, pqidx, n_o, key, count, d0);
-        if ((e = launch_exclusive_scan(count, start, n_slot, nullptr, st)) != hipSuccess) return e;
-        hipLaunchKernelGGL(k_slot_scatter, g, dim3(256), 0, st, n, key, start, cursor, sorted);
-        hipLaunchKernelGGL(k_bucket_sort, dim3(n_slot), dim3(256), 0, st, start, count, sorted, tmp);
-    } else {
-        if ((e = launch_exclusive_scan(count, start, n_slot, nullptr, st)) != hipSuccess) return e;
-    }
-    return hipGetLastError();
-}
-
 // ---------------------------------------------------------------------------
 // Gamma: one workgroup per label slot (P, Q), or in the folded layouts per pair
 // of slots (P, Q), (Q, P). Per slot,
@@ -361,31 +299,28 @@ constexpr int GAM_U = 4;        // instructions' operands loaded together
 typedef double gam4 __attribute__((ext_vector_type(4)));
 
 template <int W, int NB>
-__global__ __launch_bounds__(64 * GAM_W) void k_gamma(PairList pl, const int64_t *__restrict__ start,
-                                                      const int64_t *__restrict__ count,
-                                                      const int64_t *__restrict__ sorted,
-                                                      const int64_t *__restrict__ d0, int M0,
-                                                      const int32_t *__restrict__ slotP,
-                                                      const int32_t *__restrict__ slotQ, GammaList gl,
-                                                      const uint64_t *__restrict__ da,
-                                                      const int8_t *__restrict__ spa,
-                                                      const int8_t *__restrict__ spb,
-                                                      const double *__restrict__ ca, int Sa,
-                                                      const double *__restrict__ cb, int Sb, int tri, int nrows,
-                                                      double *__restrict__ At)
+__global__ __launch_bounds__(64 * GAM_W) void k_gamma(const PairJob *__restrict__ jobs, int groups)
 {
+    const PairJob &J_ = jobs[blockIdx.z / groups];
+    const GammaList gl = J_.gl;
+    const int Sa = J_.Sa, Sb = J_.Sb, tri = J_.tri, nrows = J_.nrows, M0 = J_.M0;
+    const PairList pl = J_.pl;
+    const int64_t *sorted = J_.sorted, *d0 = J_.d0;
+    const uint64_t *da = J_.da;
+    const int8_t *spa = J_.spa, *spb = J_.spb;
+    double *At = J_.At;
     __shared__ double red[GAM_W][NB * 256];
     const int t0 = gl.n - 1 - (int)blockIdx.x;
-    const int na0 = (int)blockIdx.y * 16, nb0 = (int)blockIdx.z * 16 * NB;
-    if (tri && nb0 > na0 + 15) return;   // rows n >= n' only
+    const int na0 = (int)blockIdx.y * 16, nb0 = (int)blockIdx.z % groups * 16 * NB;
+    if (t0 < 0 || na0 >= Sa || nb0 >= Sb || (tri && nb0 > na0 + 15)) return;   // tri: rows n >= n' only
     const int nbt = min(NB, (min(Sb, tri ? na0 + 16 : Sb) - nb0 + 15) / 16);   // ket tiles with an output
     const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
     const int lo = lane & 15, hi = lane >> 4;
     const int ks[2] = {gl.k1 ? gl.k1[t0] : t0, gl.k2 ? gl.k2[t0] : -1};
-    const double *ca_l = ca + min(na0 + lo, Sa - 1);
+    const double *ca_l = J_.ca + min(na0 + lo, Sa - 1);
     const double *cb_l[NB];
 #pragma unroll
-    for (int b = 0; b < NB; ++b) cb_l[b] = cb + min(nb0 + 16 * b + lo, Sb - 1);
+    for (int b = 0; b < NB; ++b) cb_l[b] = J_.cb + min(nb0 + 16 * b + lo, Sb - 1);
     gam4 J[NB], K[2][NB];
 #pragma unroll
     for (int b = 0; b < NB; ++b) J[b] = K[0][b] = K[1][b] = (gam4){0.0, 0.0, 0.0, 0.0};
@@ -394,8 +329,8 @@ __global__ __launch_bounds__(64 * GAM_W) void k_gamma(PairList pl, const int64_t
     for (int half = 0; half < 2; ++half) {
         const int k = ks[half];
         if (k < 0) continue;
-        const int P = slotP[k], Q = slotQ[k];
-        const int64_t s1 = start[k], n1 = count[k];
+        const int P = J_.slotP[k], Q = J_.slotQ[k];
+        const int64_t s1 = J_.start[k], n1 = J_.count[k];
         const int64_t ntot = n1 + (P == Q ? M0 : 0);
         waves = max(waves, (int)min<int64_t>(GAM_W, (ntot + 63) / 64));
         // entry e: its CI rows and weights (whole numbers from -1 to 2, two apart
@@ -512,32 +447,62 @@ __global__ __launch_bounds__(64 * GAM_W) void k_gamma(PairList pl, const int64_t
     }
 }
 
-// rows r = (n, n'): every pair of states, or with tri (a symmetry with itself)
-// those with n' <= n; n' runs fastest
-hipError_t launch_gamma(int W, PairList pl, const int64_t *start, const int64_t *count,
-                        const int64_t *sorted, const int64_t *d0, int M0, const int32_t *slotP, const int32_t *slotQ,
-                        const GammaList &gl, const uint64_t *da, const int8_t *spa, const int8_t *spb, const double *ca,
-                        int Sa, const double *cb, int Sb, bool tri, double *At, hipStream_t st)
+// rows r = (n, n') of Gamma: every pair of states, or with tri (a symmetry with
+// itself) those with n' <= n; n' runs fastest
+
+hipError_t launch_slot_start(const PairJob *jobs, int njob, hipStream_t st);   // k_scan.hip
+
+// every symmetry pair's target elements, projections, label buckets and densities;
+// h: the table's copy on the host (its sizes), jobs: the table. One launch a stage:
+// a pair's own launches, eleven each, cost more than their work below some
+// thousand determinants.
+hipError_t launch_target_sums(int W, const TgtInts &I, int n_o, const std::vector<PairJob> &h, const PairJob *jobs,
+                              hipStream_t st)
 {
-    const int nrows = tri ? Sa * (Sa + 1) / 2 : Sa * Sb;
-    if (gl.n <= 0 || nrows <= 0) return hipSuccess;
-    const int NB = Sb > 16 ? 2 : 1, groups = (Sb + 16 * NB - 1) / (16 * NB);
-    const dim3 g(gl.n, (Sa + 15) / 16, groups), b(64 * GAM_W);
-#define GAMMA(W_, NB_)                                                                                              \
-    case 8 * W_ + NB_:                                                                                              \
-        hipLaunchKernelGGL((k_gamma<W_, NB_>), g, b, 0, st, pl, start, count, sorted, d0, M0, slotP, slotQ, gl, da, \
-                           spa, spb, ca, Sa, cb, Sb, (int)tri, nrows, At);                                          \
-        break;
-#define GAMMA_W(W_) GAMMA(W_, 1) GAMMA(W_, 2)
-    switch (8 * W + NB) {
-        GAMMA_W(1)
-        GAMMA_W(2)
-        GAMMA_W(3)
-        GAMMA_W(4)
-    default: return hipErrorInvalidValue;
+    const unsigned nj = (unsigned)h.size();
+    if (nj == 0) return hipSuccess;
+    int64_t n = 0;
+    int M = 0, nrows = 0, slots = 0, gl = 0, Sa = 0, Sb = 0;
+    for (const PairJob &p : h) {
+        n = std::max(n, p.n);
+        M = std::max(M, p.Ma);
+        nrows = std::max(nrows, p.nrows);
+        slots = std::max(slots, p.n_slot);
+        gl = std::max(gl, p.gl.n);
+        Sa = std::max(Sa, p.Sa);
+        Sb = std::max(Sb, p.Sb);
     }
-#undef GAMMA_W
+    const dim3 gp((unsigned)((n + 255) / 256), nj), b(256);
+    if (n > 0) {
+        switch (W) {
+        case 1: hipLaunchKernelGGL((k_pair_values<1>), gp, b, 0, st, I, n_o, jobs); break;
+        case 2: hipLaunchKernelGGL((k_pair_values<2>), gp, b, 0, st, I, n_o, jobs); break;
+        case 3: hipLaunchKernelGGL((k_pair_values<3>), gp, b, 0, st, I, n_o, jobs); break;
+        case 4: hipLaunchKernelGGL((k_pair_values<4>), gp, b, 0, st, I, n_o, jobs); break;
+        default: return hipErrorInvalidValue;
+        }
+    }
+    if (M > 0) hipLaunchKernelGGL(k_spmm_rows, dim3(M, nj), dim3(64 * SP_W), 0, st, jobs);
+    if (nrows > 0) hipLaunchKernelGGL(k_project, dim3(nrows, nj), b, 0, st, jobs);
+    if (slots > 0) {
+        const hipError_t e = launch_slot_start(jobs, (int)nj, st);
+        if (e != hipSuccess) return e;
+        if (n > 0) {
+            hipLaunchKernelGGL(k_slot_scatter, gp, b, 0, st, jobs);
+            hipLaunchKernelGGL(k_bucket_sort, dim3(slots, nj), b, 0, st, jobs);
+        }
+    }
+    if (gl > 0 && nrows > 0) {
+        const int NB = Sb > 16 ? 2 : 1, groups = (Sb + 16 * NB - 1) / (16 * NB);
+        const dim3 g(gl, (Sa + 15) / 16, groups * nj), t(64 * GAM_W);
+#define GAMMA(W_, NB_) \
+    case 8 * W_ + NB_: hipLaunchKernelGGL((k_gamma<W_, NB_>), g, t, 0, st, jobs, groups); break;
+        switch (8 * W + NB) {
+            GAMMA(1, 1) GAMMA(1, 2) GAMMA(2, 1) GAMMA(2, 2) GAMMA(3, 1) GAMMA(3, 2) GAMMA(4, 1) GAMMA(4, 2)
+        default: return hipErrorInvalidValue;
+        }
 #undef GAMMA
+    }
     return hipGetLastError();
 }
 
