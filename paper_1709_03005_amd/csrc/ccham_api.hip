@@ -72,9 +72,10 @@ hipError_t launch_l2csf_gather(const double *Hd, int64_t ldd, int Dc, int ncsf, 
                                const int32_t *det, const double *coef, double *H, int64_t ld, hipStream_t st);
 struct GemmTask {
     ExpandOp op;
-    int tiles_m, tiles_n;
+    int height, tiles_m, tiles_n;
     int64_t first;
 };
+int expand_task_height(int nrows, int bm);
 struct L2Task {
     L2Args a;
     int64_t first;
@@ -2729,13 +2730,15 @@ cch_status cch_batch_create(cch_batch **out, cch_ctx *const *ctxs, int32_t n, in
         for (auto &p : c->pp) {
             SymInfo &sa = c->syms[p.a], &sb = c->syms[p.b];
             if (sa.nc == 0 || sb.nc == 0 || p.nrows == 0) continue;
-            GemmTask g{expand_op(c, p, 0, sa.nc), 0, 0, 0};
-            g.tiles_m = (p.nrows + 31) / 32;
+            GemmTask g{expand_op(c, p, 0, sa.nc), 0, 0, 0, 0};
+            g.height = expand_task_height(p.nrows, 32);
+            g.tiles_m = (p.nrows + g.height - 1) / g.height;
             g.tiles_n = expand_cols(g.op);
             g.first = t32;
             t32 += (int64_t)g.tiles_m * g.tiles_n;
             g32.push_back(g);
-            g.tiles_m = (p.nrows + 63) / 64;
+            g.height = expand_task_height(p.nrows, 64);
+            g.tiles_m = (p.nrows + g.height - 1) / g.height;
             g.first = t64;
             t64 += (int64_t)g.tiles_m * g.tiles_n;
             g64.push_back(g);
