@@ -830,56 +830,72 @@ __device__ __forceinline__ double pch_wmax(double v)
     return pch_rl(s, 63);
 }
 
-__global__ __launch_bounds__(256) void k_pchol(const double *__restrict__ G, int ldg, int b,
-                                               const double *__restrict__ S, int lds, int m,
-                                               const double *__restrict__ ref, int ref_stride, double rel,
-                                               double *__restrict__ Cout, int ldc, int32_t *__restrict__ rank_out)
+// One workgroup, and latency is all of it: the columns of the pivoted Cholesky
+// step and of the inverse stay in the registers of wave 0 (NB >= b of them, so a
+// pivot costs its maximum, root and quotient and no LDS round trips), and the
+// products with S are spread over all waves. b = 10, m = 80:
+// 18 -> 13 us; with the columns in LDS a pivot took its reads one after the other.
+constexpr int PCH_T = 512;
+
+template <int NB>
+__global__ __launch_bounds__(PCH_T) void k_pchol(const double *__restrict__ G, int ldg, int b, unsigned inv_b,
+                                                 const double *__restrict__ S, int lds, int m,
+                                                 const double *__restrict__ ref, int ref_stride, double rel,
+                                                 double *__restrict__ Cout, int ldc, int32_t *__restrict__ rank_out)
 {
-    __shared__ double A[PCH_MAX][PCH_MAX + 1];    // lane l of wave 0 owns column l; column PCH_MAX is padding
-    __shared__ double Ss[PCH_M][PCH_MAX + 1];
-    __shared__ double Rq[PCH_MAX][PCH_MAX + 1];   // row i of R by original column
-    __shared__ double R[PCH_MAX][PCH_MAX + 1];    // R in pivot order
-    __shared__ double Ri[PCH_MAX][PCH_MAX + 1];   // its inverse
-    __shared__ double Bq[PCH_MAX][PCH_MAX + 1];   // B by original column
-    __shared__ double rdg[PCH_MAX];               // 1 / R[i][i]
-    __shared__ int piv[PCH_MAX];
+    __shared__ double A[NB][NB + 1];
+    __shared__ double Ss[PCH_M][NB + 1];
+    __shared__ double Rq[NB][NB + 1];   // row i of R by original column
+    __shared__ double R[NB][NB + 1];    // R in pivot order
+    __shared__ double Bq[NB][NB + 1];   // B by original column
     __shared__ int rank_sh;
     const int t = threadIdx.x;
-    for (int e = t; e < m * b; e += 256) Ss[e / b][e % b] = S[(int64_t)(e / b) * lds + e % b];
-    for (int e = t; e < b * b; e += 256) {
-        const int i = e / b, j = e % b;
-        A[i][j] = 0.5 * (G[(int64_t)i * ldg + j] + G[(int64_t)j * ldg + i]);
+    // e / b for e < 2^12 and b <= 32: inv_b = ceil(2^20 / b)
+    const auto div_b = [&](int e) { return (int)(((unsigned)e * inv_b) >> 20); };
+#pragma unroll 4
+    for (int e = t; e < m * b; e += PCH_T) {
+        const int i = div_b(e), j = e - i * b;
+        Ss[i][j] = S[(int64_t)i * lds + j];
     }
-    for (int e = t; e < PCH_MAX * PCH_MAX; e += 256) {
-        Rq[e / PCH_MAX][e % PCH_MAX] = 0.0;
-        Bq[e / PCH_MAX][e % PCH_MAX] = 0.0;
+    for (int e = t; e < NB * NB; e += PCH_T) {
+        const int i = e / NB, j = e % NB;
+        A[i][j] = i < b && j < b ? 0.5 * (G[(int64_t)i * ldg + j] + G[(int64_t)j * ldg + i]) : 0.0;
+        R[i][j] = 0.0;
+        Rq[i][j] = 0.0;
+        Bq[i][j] = 0.0;
     }
     __syncthreads();
-    // A -= S^T S in four interleaved partial sums, combined in a fixed order:
-    // the same operations for (i, j) and (j, i), so A stays exactly symmetric
-    for (int e = t; e < b * b; e += 256) {
-        const int i = e / b, j = e % b;
-        double s4[4] = {0.0, 0.0, 0.0, 0.0};
-        int q = 0;
-        for (; q + 3 < m; q += 4)
-#pragma unroll
-            for (int u = 0; u < 4; ++u) s4[u] = fma(Ss[q + u][i], Ss[q + u][j], s4[u]);
-        for (; q < m; ++q) s4[0] = fma(Ss[q][i], Ss[q][j], s4[0]);
-        A[i][j] -= (s4[0] + s4[1]) + (s4[2] + s4[3]);
+    // A -= S^T S in four interleaved partial sums, a lane each, combined in a fixed
+    // order: the same operations for (i, j) and (j, i), so A stays exactly symmetric
+    for (int e = t >> 2; e < b * b; e += PCH_T / 4) {
+        const int i = div_b(e), j = e - i * b, u = t & 3;
+        double s = 0.0;
+        const int m4 = m & ~3;
+#pragma unroll 4
+        for (int q = u; q < m4; q += 4) s = fma(Ss[q][i], Ss[q][j], s);
+        if (u == 0)
+            for (int q = m4; q < m; ++q) s = fma(Ss[q][i], Ss[q][j], s);
+        s += __shfl_xor(s, 1, 4);
+        s += __shfl_xor(s, 2, 4);
+        if (u == 0) A[i][j] -= s;
     }
     __syncthreads();
     if (t < 64) {
-        // pivoted Cholesky in wave 0 alone (no barrier inside). Every value that
-        // another lane reads (key through DPP, the R row through lane reads) is
-        // formed by selects with the whole wave active; only stores are masked.
+        // pivoted Cholesky in wave 0 alone (no barrier inside): lane l holds column l.
+        // Every value that another lane reads (key through DPP, the R row through
+        // lane reads) is formed by selects with the whole wave active; only stores
+        // are masked. Rows and columns already used are updated too, as nothing
+        // reads them again.
         const bool mine = t < b;
-        const int tc = mine ? t : PCH_MAX;   // own column, or the padding column
-        const double refd = mine ? rel * rel * (ref ? ref[(int64_t)t * ref_stride] : A[t][t]) : 0.0;
+        double a[NB];
+#pragma unroll
+        for (int q = 0; q < NB; ++q) a[q] = mine ? A[q][t & (NB - 1)] : 0.0;
+        double d = mine ? A[t & (NB - 1)][t & (NB - 1)] : 0.0;
+        const double refd = mine ? rel * rel * (ref ? ref[(int64_t)t * ref_stride] : d) : 0.0;
         bool used = !mine;
-        int r = b;
+        int r = b, my = -1;   // my: the step at which column l was the pivot
         for (int i = 0; i < b; ++i) {
             // pivot: the largest admissible remaining diagonal (ties: lowest column)
-            const double d = A[mine ? t : 0][mine ? t : 0];
             const bool cand = !used && d > refd && d > 0.0;
             const double key = cand ? d : 0.0;
             const double mx = pch_wmax(key);
@@ -887,66 +903,54 @@ __global__ __launch_bounds__(256) void k_pchol(const double *__restrict__ G, int
                 r = i;
                 break;
             }
-            const int p = __ffsll((unsigned long long)__ballot(key == mx)) - 1;
+            const int p = __builtin_amdgcn_readfirstlane(__ffsll((unsigned long long)__ballot(key == mx)) - 1);
             const double rp = sqrt(mx);
-            const double quo = A[p][tc] / rp;
+            double ap = 0.0;
+#pragma unroll
+            for (int q = 0; q < NB; ++q) ap = q == p ? a[q] : ap;
+            const double quo = ap / rp;
             const double rl = used ? 0.0 : (t == p ? rp : quo);
-            used = used || t == p;
+            if (t == p) {
+                used = true;
+                my = i;
+            }
             if (mine) Rq[i][t] = rl;
-            if (t == 0) piv[i] = p;
-            // Schur complement on the columns still free: lane l updates its
-            // column, four rows loaded before any is stored
-            const unsigned long long freem = __ballot(!used);
-            int q = 0;
-            for (; q + 3 < b; q += 4) {
-                double a4[4], r4[4];
+            // Schur complement: lane l updates its column
 #pragma unroll
-                for (int u = 0; u < 4; ++u) {
-                    a4[u] = A[q + u][tc];
-                    r4[u] = pch_rl(rl, q + u);
-                }
-#pragma unroll
-                for (int u = 0; u < 4; ++u) {
-                    const bool upd = !used && ((freem >> (q + u)) & 1ull);
-                    A[q + u][tc] = upd ? fma(-r4[u], rl, a4[u]) : a4[u];
-                }
-            }
-            for (; q < b; ++q) {
-                const double a1 = A[q][tc], r1 = pch_rl(rl, q);
-                const bool upd = !used && ((freem >> q) & 1ull);
-                A[q][tc] = upd ? fma(-r1, rl, a1) : a1;
-            }
+            for (int q = 0; q < NB; ++q) a[q] = fma(-pch_rl(rl, q), rl, a[q]);
+            d = fma(-rl, rl, d);
         }
+        // R in pivot order, column by column, and its inverse: column c in lane c by
+        // back substitution, each solved entry taken off the rows above it
+        if (my >= 0)
+            for (int i = 0; i <= my; ++i) R[i][my] = Rq[i][t];
         if (t == 0) rank_sh = r;
-    }
-    __syncthreads();
-    const int r = rank_sh;
-    for (int e = t; e < r * r; e += 256) {
-        const int i = e / r, j = e % r;
-        R[i][j] = (j >= i) ? Rq[i][piv[j]] : 0.0;
-    }
-    if (t < r) rdg[t] = 1.0 / Rq[t][piv[t]];
-    __syncthreads();
-    // inverse of R, column c per thread (back substitution with the reciprocal
-    // diagonal)
-    if (t < r) {
-        const int c = t;
-        for (int i = c; i >= 0; --i) {
-            double s = (i == c) ? 1.0 : 0.0;
-            for (int j = i + 1; j <= c; ++j) s -= R[i][j] * Ri[j][c];
-            Ri[i][c] = s * rdg[i];
+        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
+        __builtin_amdgcn_wave_barrier();
+        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup");
+        const int tc = t & (NB - 1);
+        const double rd = tc < r ? 1.0 / R[tc][tc] : 0.0;
+        double x[NB];
+#pragma unroll
+        for (int i = 0; i < NB; ++i) x[i] = i == t ? 1.0 : 0.0;
+#pragma unroll
+        for (int j = NB - 1; j >= 0; --j) {
+            x[j] *= pch_rl(rd, j);
+#pragma unroll
+            for (int i = 0; i < j; ++i) x[i] = fma(-R[i][j], x[j], x[i]);
         }
-    }
-    __syncthreads();
-    // B[perm[j]][c] = (R^-1)[j][c]: upper triangular, only j <= c was formed
-    for (int e = t; e < r * r; e += 256) {
-        const int j = e / r, c = e % r;
-        Bq[piv[j]][c] = j <= c ? Ri[j][c] : 0.0;
+        // B[perm[j]][c] = (R^-1)[j][c]: upper triangular, rows and columns before the rank
+        const bool col = t < r;
+#pragma unroll
+        for (int j = 0; j < NB; ++j) {
+            const unsigned long long who = __ballot(my == j);
+            if (col && who) Bq[__ffsll(who) - 1][t] = j <= t ? x[j] : 0.0;
+        }
     }
     __syncthreads();
     // M = [-S B; B]
-    for (int e = t; e < (m + b) * b; e += 256) {
-        const int q = e / b, c = e % b;
+    for (int e = t; e < (m + b) * b; e += PCH_T) {
+        const int q = div_b(e), c = e - q * b;
         double v;
         if (q < m) {
             v = 0.0;
@@ -956,14 +960,21 @@ __global__ __launch_bounds__(256) void k_pchol(const double *__restrict__ G, int
         }
         Cout[(int64_t)q * ldc + c] = v;
     }
-    if (t == 0) *rank_out = r;
+    if (t == 0) *rank_out = rank_sh;
 }
 
 hipError_t launch_pchol(const double *G, int ldg, int b, const double *S, int lds, int m, const double *ref,
                         int ref_stride, double rel, double *C, int ldc, int32_t *rank, hipStream_t st)
 {
     if (b <= 0 || b > PCH_MAX || m < 0 || m > PCH_M || (m > 0 && S == nullptr)) return hipErrorInvalidValue;
-    hipLaunchKernelGGL(k_pchol, dim3(1), dim3(256), 0, st, G, ldg, b, S, lds, m, ref, ref_stride, rel, C, ldc, rank);
+    const unsigned inv_b = ((1u << 20) + b - 1) / b;
+    const auto go = [&](auto k) {
+        hipLaunchKernelGGL(k, dim3(1), dim3(PCH_T), 0, st, G, ldg, b, inv_b, S, lds, m, ref, ref_stride, rel, C, ldc,
+                           rank);
+    };
+    if (b <= 8) go(k_pchol<8>);
+    else if (b <= 16) go(k_pchol<16>);
+    else go(k_pchol<32>);
     return hipGetLastError();
 }
 
