@@ -1571,12 +1571,9 @@ cch_status cch_build(cch_ctx *c)
         hipStream_t s4 = c->aux[CCH_NPAIRS_ST], sl = c->aux[CCH_NPAIRS_ST + 1];
         HIPCK(c, hipStreamWaitEvent(s4, c->fork_ev, 0));
         HIPCK(c, hipStreamWaitEvent(sl, c->fork_ev, 0));
-        HIPCK(c, hipEventRecord(c->l2_ev[0], sl));
-        TRY(enqueue_l2(c, sl));
-        HIPCK(c, hipEventRecord(c->l2_ev[1], sl));
-        // so do the FP64 integral rows, which wait for nothing either: beside the
-        // scans and densities, which leave the memory idle (D = 8000:
-        // the build 0.89 -> 0.84 ms; D = 40000: 10.96 -> 10.53)
+        // the FP64 integral rows wait for nothing either: beside the scans and
+        // densities, which leave the memory idle (D = 8000: the build 0.89 -> 0.84 ms;
+        // D = 40000: 10.96 -> 10.53)
         const Fan f{c, st, c->opts.precision == CCH_PREC_FP64 && !c->b_shared};
         if (f.on) {
             HIPCK(c, f.begin());
@@ -1591,6 +1588,13 @@ cch_status cch_build(cch_ctx *c)
             EVREC(3);   // the products start here
         }
         c->rl_timed = f.on;
+        // the L2 block after them: once its workgroups fill the dispatcher, nothing
+        // queued on another stream starts, and the products wait for the integral
+        // rows (D = 40000 10.74 -> 10.43 ms, a build and solve at D = 60000 195 -> 189;
+        // behind class 4 as well it gains half of that)
+        HIPCK(c, hipEventRecord(c->l2_ev[0], sl));
+        TRY(enqueue_l2(c, sl));
+        HIPCK(c, hipEventRecord(c->l2_ev[1], sl));
         HIPCK(c, hipEventRecord(c->c4_ev[0], s4));
         HIPCK(c, launch_scans(SCAN_LT, c->W, c->d_lt_scans, (int)c->lt.size(), c->n_l2, 2 * c->n_o, s4));
         TRY(enqueue_class4(c, s4, false));
