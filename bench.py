@@ -47,7 +47,7 @@ FP64_VALU_PEAK_TFLOPS = 78.6
 # workload and kernel family, with the hash of the family's source text when
 # counted (the region of its file between two marker lines, or the whole
 # file): a family whose source has changed since reports null. The relayout
-# entry is the sum of its two launches (J and K layouts), the mat-vec entry the
+# entry is the sum of its launches, the mat-vec entry the
 # sum of the product and its reduction of partial sums.
 COUNTER_SCALE = {"FETCH_SIZE": 2.0, "WRITE_SIZE": 1.0}
 KERNEL_SOURCE = {
@@ -57,21 +57,26 @@ KERNEL_SOURCE = {
     "relayout": ("k_gemm.hip", "// K0: B[k][jj*ncb + jj']", "// K5: C = A * B"),
     "class4": ("k_class4.hip", None, None),
     "l2_block": ("k_l2.hip", "// Classes 2 and 8", "// L2 functions given as CSFs"),
-    "mirror": ("k_misc.hip", "// H[c][r] = H[r][c]", "__global__ void k_diag"),
+    "mirror": ("k_misc.hip", "// H[c][r] = H[r][c]", "// C = D: the whole matrix"),
     "rayleigh_ritz": ("k_rr.hip", None, None),
 }
 TRAFFIC = {
-    # (workload, family): (sha256 prefix of the family's source, FETCH_SIZE KiB, WRITE_SIZE KiB)
-    ("medium", "rayleigh_ritz"): ("ad413139aab2388c", 53.878, 25.493),
-    ("medium", "l2_block"): ("238d74161bdf3234", 22104.250, 98764.125),
-    # the product instances of one solve (49 of three vector groups, 7 of one,
-    # 2 of two, 1 of four) averaged per launch, plus the reduction
-    ("learned", "matvec"): ("7818879eb813e1ad", 7412237.1, 567456.0),
-    ("learned", "expansion_gemm"): ("7eeac111dbc075d6", 16520452.1, 1562812.5),
-    ("learned", "relayout"): ("29b301ee4afa7f1b", 2000324.2, 4000000.0),
-    ("learned", "class4"): ("1c100f7420acfa5b", 5756553.2, 10223622.8),
-    ("learned", "l2_block"): ("238d74161bdf3234", 1770334.4, 6273721.4),
-    ("learned", "mirror"): ("e5a76a20e4f84e29", 7038936.4, 14062968.8),
+    # (workload, family): (sha256 prefix of the family's source, FETCH_SIZE KiB, WRITE_SIZE KiB);
+    # the mat-vec averaged over the product instances of one solve, with the reduction
+    ("medium", "matvec"): ("0ff798e23148460a", 134499.3, 12866.3),
+    ("medium", "expansion_gemm"): ("1bc4e6a77a9184ed", 323349.0, 37510.5),
+    ("medium", "relayout"): ("7d0655f693706042", 347215.8, 509724.9),
+    ("medium", "class4"): ("d03cf0057bbc44d4", 66567.2, 120313.2),
+    ("medium", "l2_block"): ("d41318e67d054e01", 29924.1, 195977.4),
+    ("medium", "mirror"): ("c3a15eb9e31d99ef", 77236.8, 152429.7),
+    ("medium", "rayleigh_ritz"): ("ce8076ced68b2de3", 61.7, 25.5),
+    ("learned", "matvec"): ("0ff798e23148460a", 7353071.0, 451424.6),
+    ("learned", "expansion_gemm"): ("1bc4e6a77a9184ed", 8340469.9, 1626163.7),
+    ("learned", "relayout"): ("7d0655f693706042", 779360.8, 1666132.5),
+    ("learned", "class4"): ("d03cf0057bbc44d4", 3973416.2, 6250000.0),
+    ("learned", "l2_block"): ("d41318e67d054e01", 2000317.8, 12502374.4),
+    ("learned", "mirror"): ("c3a15eb9e31d99ef", 3912629.6, 7813125.0),
+    ("learned", "rayleigh_ritz"): ("ce8076ced68b2de3", 70.3, 42.6),
 }
 
 
@@ -559,16 +564,17 @@ def main():
                                 "TFLOP/s", 1e12, note="2 x rows x cols x K per symmetry pair, FP64 MFMA"),
         "class4": entry("mfma", work["class4_flops"], phase_ms["class4"], FP64_MFMA_PEAK_TFLOPS, "TFLOP/s", 1e12,
                         note="2 S n_c flops per term of a connected L2 x target pair (Eq. 5), FP64 MFMA "
-                             "(16 states x 16 continuum orbitals per tile); phase time includes its L2 x "
-                             "target scan"),
-        "densities": entry("alu", work["density_flops"], phase_ms["target_densities"], FP64_VALU_PEAK_TFLOPS,
+                             "(quads of states against gathered integral rows); phase time includes its "
+                             "L2 x target scan"),
+        "densities": entry("mfma", work["density_flops"], phase_ms["target_densities"], FP64_MFMA_PEAK_TFLOPS,
                            "TFLOP/s", 1e12,
                            note="transition densities of Eq. 8 (one multiply-add per (n, n') row per density "
                                 "update); the phase also holds the target pair values, the projection and "
-                                "the bucket sort, so this is a lower bound of the density kernel's rate"),
-        "l2_block": entry("hbm", 8.0 * work["l2_lower_elements"], phase_ms["l2_block"], HBM_PEAK_GBS, "GB/s",
-                          1e9, note="8 B written per lower-triangle L2 element"),
-        "relayout": entry("hbm", work["relayout_bytes"], phase_ms["relayout"], HBM_PEAK_GBS, "GB/s", 1e9),
+                                "the bucket sort, so this is a lower bound of the density kernel's rate, FP64 MFMA"),
+        "l2_block": entry("hbm", 16.0 * work["l2_lower_elements"], phase_ms["l2_block"], HBM_PEAK_GBS, "GB/s",
+                          1e9, note="16 B written per lower-triangle L2 element (both triangles)"),
+        "relayout": entry("hbm", work["relayout_bytes"], phase_ms["relayout"], HBM_PEAK_GBS, "GB/s", 1e9,
+                          note="FP64 builds run it beside the scans and densities and share the device with them"),
         "mirror": entry("hbm", work["mirror_bytes"], phase_ms["mirror_diag"], HBM_PEAK_GBS, "GB/s", 1e9,
                         note="16 B per element above the diagonal; phase includes the diagonal copy"),
     }
