@@ -493,7 +493,9 @@ cch_status cch_eig_all(cch_ctx *ctx, const double *A, int64_t lda, int32_t n, do
  * queued work on the context's stream), and per-phase times (phases[8],
  * NULL allowed): 0 excitation scans, 1 target elements + densities,
  * 2 integral relayout, 3 expansion GEMM, 4 class 4, 5 classes 2/8,
- * 6 mirror + diagonal, 7 reserved (0). Synchronous. */
+ * 6 mirror + diagonal, 7 reserved (0). From D = 4096 on phases 4 and 5, and 2
+ * in an FP64 build, run beside the others and are timed on their own streams.
+ * Synchronous. */
 cch_status cch_build_time(cch_ctx *ctx, float *total_ms, float *phases);
 
 /* Work counts of the planned build, for throughput and roofline figures:
