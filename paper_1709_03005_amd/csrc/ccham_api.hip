@@ -2178,7 +2178,10 @@ cch_status cch_eig_all(cch_ctx *c, const double *A, int64_t lda, int32_t n, doub
     std::vector<double> hd((size_t)n), he((size_t)std::max(n - 1, 1));
     EGK(hipMemcpyAsync(hd.data(), tv.d, 8 * (size_t)n, hipMemcpyDeviceToHost, st));
     if (n > 1) EGK(hipMemcpyAsync(he.data(), tv.e, 8 * (size_t)(n - 1), hipMemcpyDeviceToHost, st));
+    unsigned long long amax = 0;
+    EGK(hipMemcpyAsync(&amax, tv.amax, 8, hipMemcpyDeviceToHost, st));
     EGK(hipStreamSynchronize(st));
+    const int shift = trd_shift(amax);   // T, and all up to w at the end, are scaled by 2^-shift
     for (int i = 0; i < n; ++i)
         if (!std::isfinite(hd[i]) || (i < n - 1 && !std::isfinite(he[i]))) {
             evclean();
@@ -2306,6 +2309,10 @@ cch_status cch_eig_all(cch_ctx *c, const double *A, int64_t lda, int32_t n, doub
         }
     }
     EGK(hipEventRecord(e3, st));
+    if (shift != 0) {
+        for (double &x : hw) x = std::ldexp(x, shift);
+        EGK(hipMemcpyAsync(w_d, hw.data(), 8 * (size_t)n, hipMemcpyHostToDevice, st));
+    }
     EGK(hipMemcpyAsync(w, w_d, 8 * (size_t)n, dev ? hipMemcpyDeviceToDevice : hipMemcpyDeviceToHost, st));
     EGK(hipStreamSynchronize(st));
     if (info) {

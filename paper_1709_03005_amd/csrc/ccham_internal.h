@@ -391,12 +391,22 @@ struct PairJob {
     double *At;
 };
 
+// the power of two that the Householder tridiagonalisation takes out of a matrix
+// whose largest |entry| has the bits amax: none for entries between 2^-96 and 2^97
+// or a non-finite matrix, else the one that brings the largest entry to [1, 2)
+// (subnormal ones: to 2^-51 or more)
+__host__ __device__ inline int trd_shift(unsigned long long amax)
+{
+    const int ex = (int)(amax >> 52);
+    const bool fits = (ex >= 1023 - 96 && ex <= 1023 + 96) || ex == 2047 || amax == 0;
+    return fits ? 0 : ex - 1023;
+}
+
 // work vectors of the Householder tridiagonalisation (length n each): x = the
 // current column after the panel's corrections times a power of two (two
 // buffers, by column parity), y = A_0 x as the row pass leaves it; the diagonal
 // d, the off-diagonal e and the reflector scalars tau of T; amax: the largest
-// |entry| of the matrix (its bits), whose exponent is that power of two's.
-// x0, x1: 16-byte aligned
+// |entry| of the matrix before trd_shift (its bits). x0, x1: 16-byte aligned
 struct TrdVec {
     double *x0, *x1, *y;
     double *d, *e, *tau;

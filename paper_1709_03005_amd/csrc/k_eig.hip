@@ -192,11 +192,16 @@ hipError_t launch_eig_gemm(int M, int N, int K, double alpha, const double *A, i
 // partial sums of its predecessor (sigma = |x|^2 over the part to annihilate,
 // and the panel's vectors times x) every workgroup forms the reflector j and z
 // alike, p . v = tau (v . A_0 v - 2 sum_k (v_k . v)(w_k . v)) follows without a
-// further pass over the rows (x . A_0 x is cubic in the matrix: x is stored
-// times the power of two that brings the largest entry to [1, 2), which leaves v
-// and tau as they are, so that the range of the entries stays that of their
-// squares), and the workgroup finishes v_j, p and w_j for its
+// further pass over the rows, and the workgroup finishes v_j, p and w_j for its
 // rows, corrects column j + 1 and stores the partial sums for the next one.
+// The range: sigma is quadratic in x and x . A_0 x cubic in the matrix. A whose
+// largest entry lies outside [2^-96, 2^97) is first scaled by a power of two
+// (trd_shift), and x is stored times 2^TRD_XS, which leaves v and tau as they
+// are. sigma then stays below 2^870 and x . A_0 x below 2^980 (entries grow to n
+// times the largest one, n < 2^16), and of a sigma from TRD_SIG_MIN = 2^-900 on
+// neither loses a bit to underflow (the terms of x . A_0 x are 2^-996 then, their
+// rounding 2^-1075). A smaller sigma, entries below 2^-770, counts as zero: a
+// reflector formed from squares that have lost their bits would not be orthogonal.
 // For trailing blocks of at least TRD_TILE_MIN rows the product reads only the
 // lower triangle, in tiles, whose row and column sums the column kernel adds.
 // panel buffers (ldp doubles a row): PV rows 2k, 2k + 1 = v_k, w_k; PW rows
@@ -244,6 +249,8 @@ __device__ __forceinline__ double quad_sum(double x)   // over lanes 4 a .. 4 a 
 // three launches a column took 8.0 and 9.1 us for this part, and 4.8 us more
 // for the tile sums; a column with its product 8.7 instead of 12.3 us at
 // n = 301 and 30 instead of 42 at n = 8000 to 3072
+constexpr int TRD_XS = 320;                // x is stored times 2^TRD_XS
+constexpr double TRD_SIG_MIN = 0x1p-900;   // a smaller |x|^2 counts as zero
 constexpr int TRD_CT = 4 * TRD_CR;         // threads of the column kernel
 constexpr int TRD_CW = TRD_CT / 64;
 constexpr int TRD_LS = 2 * TRD_NB + 8;     // LDS row stride of the panel rows (two rows apart: other banks)
@@ -265,9 +272,8 @@ __global__ __launch_bounds__(TRD_CT) void k_trd_col(double *__restrict__ A, int6
     const int r = c + (int)blockIdx.x * TRD_CR + rl, rr = min(r, n - 1);
     const bool in = r < n;
     const int j = c - 1, np = fin ? i - 1 : i;   // pairs of the panel already stored
-    // the power of two that x is stored with, and its reciprocal (normal numbers both)
-    const uint64_t ex = min(max((uint64_t)(*V.amax >> 52), (uint64_t)1), (uint64_t)2045);
-    const double fx = __builtin_bit_cast(double, (2046 - ex) << 52), fxi = __builtin_bit_cast(double, ex << 52);
+    const double fx = __builtin_bit_cast(double, (uint64_t)(1023 + TRD_XS) << 52);
+    const double fxi = __builtin_bit_cast(double, (uint64_t)(1023 - TRD_XS) << 52);
     const double *xj = (j & 1) ? V.x1 : V.x0;
     // item b <= rt of a row's tile sums is rowp[b][r], item b > rt colp[b - 1][r]
     auto tile_sum = [&](int b, int rt, int row) -> double {
@@ -335,7 +341,7 @@ __global__ __launch_bounds__(TRD_CT) void k_trd_col(double *__restrict__ A, int6
         for (int k = 0; k < TRD_CW; ++k) xax += r2[k];
         // (the root and the two quotients to about one ulp: short chains)
         double tau = 0.0, beta = alpha, scale = 0.0;
-        if (sig > 0.0) {
+        if (sig >= TRD_SIG_MIN) {
             const double h = fma(alpha, alpha, sig);
             beta = -copysign(h * rr_rsqrt(h), alpha);
             tau = fma(-alpha, rr_recip(beta), 1.0);   // (beta - alpha) / beta
@@ -609,7 +615,8 @@ hipError_t launch_trd_panel(double *A, int64_t lda, int n, int j0, int nbp, cons
     return hipGetLastError();
 }
 
-// W = (W + W^T) / 2 in place (the operation is defined on a symmetric matrix);
+// W = (W + W^T) / 2 in place (the operation is defined on a symmetric matrix), then
+// scaled by the power of two of trd_shift;
 // the rows' pad columns n .. ld - 1 become 0; amax: the largest |entry| as bits
 // (zeroed by k_word_zero). A workgroup takes the 32 x 32 tiles (rt, ct) and
 // (ct, rt), ct <= rt, through LDS, so that both are read and written by rows:
@@ -647,6 +654,17 @@ __global__ __launch_bounds__(256) void k_symmetrize(double *__restrict__ W, int6
     if ((t & 63) == 0 && m > __hip_atomic_load(amax, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) atomicMax(amax, m);
 }
 
+// W times 2^-trd_shift(amax): nothing to do, and nothing read, for entries of an
+// ordinary size
+__global__ __launch_bounds__(256) void k_scale_pow2(double *__restrict__ W, int64_t len,
+                                                    const unsigned long long *__restrict__ amax)
+{
+    const int sh = trd_shift(*amax);
+    if (sh == 0) return;
+    for (int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x; i < len; i += (int64_t)gridDim.x * 256)
+        W[i] = ldexp(W[i], -sh);
+}
+
 __global__ void k_word_zero(unsigned long long *__restrict__ w) { *w = 0; }
 
 hipError_t launch_symmetrize(double *W, int64_t ld, int n, unsigned long long *amax, hipStream_t st)
@@ -655,6 +673,9 @@ hipError_t launch_symmetrize(double *W, int64_t ld, int n, unsigned long long *a
     const unsigned T = (unsigned)((n + SYM_T - 1) / SYM_T);
     hipLaunchKernelGGL(k_word_zero, dim3(1), dim3(1), 0, st, amax);
     hipLaunchKernelGGL(k_symmetrize, dim3(T, T), dim3(256), 0, st, W, ld, n, amax);
+    const int64_t len = (int64_t)n * ld;
+    hipLaunchKernelGGL(k_scale_pow2, dim3((unsigned)std::min<int64_t>((len + 255) / 256, 2048)), dim3(256), 0, st, W, len,
+                       amax);
     return hipGetLastError();
 }
 

@@ -265,11 +265,14 @@ __device__ __forceinline__ void rr_house(RRShared &sh, int n, int tid, int wv)
             const double alpha = rr_pick(x0, x1, k + 1);
             const double h = fma(alpha, alpha, sig);
             const double bt = -copysign(h * rr_rsqrt(h), alpha);
-            const double tau = sig == 0.0 ? 0.0 : fma(-alpha, rr_recip(bt), 1.0);   // (beta - alpha) / beta
-            const double inv = sig == 0.0 ? 0.0 : rr_recip(alpha - bt);
+            // (a sigma whose squares have lost bits to underflow gives no orthogonal
+            // reflector: entries below 2^-500 of the largest one count as zero)
+            const bool none = sig < 0x1p-1000;
+            const double tau = none ? 0.0 : fma(-alpha, rr_recip(bt), 1.0);   // (beta - alpha) / beta
+            const double inv = none ? 0.0 : rr_recip(alpha - bt);
             if (lane == 0) {
                 sh.tau[k] = tau;
-                sh.e[k] = sig == 0.0 ? alpha : bt;
+                sh.e[k] = none ? alpha : bt;
                 sh.hinv[k] = inv;
             }
             A[k][lane] = x0;
