@@ -79,15 +79,15 @@ hipError_t launch_l2_csr_fill(const double *H, int64_t ld, int Dc, int nl2, cons
 }
 
 // VT[i][q] = V[q][i] (0 for q >= b), i < n, q < 2 LPR: the vectors of one row
-// side by side for the gathers of the sparse product
+// side by side for the gathers of the sparse product; record n is zero
 template <int LPR>
 __global__ __launch_bounds__(256) void k_vt(const double *__restrict__ V, int64_t ldv, int n, int b,
                                             double *__restrict__ VT)
 {
     const int i = blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= n) return;
+    if (i > n) return;
 #pragma unroll
-    for (int q = 0; q < 2 * LPR; ++q) VT[(int64_t)i * (2 * LPR) + q] = q < b ? V[(int64_t)q * ldv + i] : 0.0;
+    for (int q = 0; q < 2 * LPR; ++q) VT[(int64_t)i * (2 * LPR) + q] = i < n && q < b ? V[(int64_t)q * ldv + i] : 0.0;
 }
 
 // W[q][Dc + r] (+)= sum over the non-zeros (j, v) of L2 row r of v VT[j][q]
@@ -132,11 +132,12 @@ __global__ __launch_bounds__(256) void k_l2_spmm(const int64_t *__restrict__ off
     double aa[U], ab[U];
     __shared__ SpEntry ring[4][CH];
     SpEntry *mine = ring[threadIdx.x >> 6];   // this wave's batch
-    auto load = [&](int64_t e) {   // past the end: column 0 with the value 0
+    auto load = [&](int64_t e) {   // past the end: the zero record with the value 0 (a
+                                   // column's would spread what is not finite in it)
 #pragma unroll
         for (int k = 0; k < C; ++k) {
             const bool in = e + 64 * k + lane < e1;
-            c1[k] = in ? col[e + 64 * k + lane] : 0;
+            c1[k] = in ? col[e + 64 * k + lane] : nl2;
             v1[k] = in ? val[e + 64 * k + lane] : 0.0;
         }
     };
@@ -195,7 +196,7 @@ template <int LPR>
 static void spmm_launch(const int64_t *off, const int32_t *col, const double *val, int Dc, int nl2, const double *V,
                         int64_t ldv, int b, double *W, int64_t ldw, double *VT, hipStream_t st)
 {
-    hipLaunchKernelGGL((k_vt<LPR>), dim3((nl2 + 255) / 256), dim3(256), 0, st, V + Dc, ldv, nl2, b, VT);
+    hipLaunchKernelGGL((k_vt<LPR>), dim3(nl2 / 256 + 1), dim3(256), 0, st, V + Dc, ldv, nl2, b, VT);
     hipLaunchKernelGGL((k_l2_spmm<LPR>), dim3((nl2 + 3) / 4), dim3(256), 0, st, off, col, val, Dc, nl2, VT, b, W, ldw,
                        Dc > 0 ? 1 : 0);
 }
@@ -204,7 +205,8 @@ static void spmm_launch(const int64_t *off, const int32_t *col, const double *va
 int64_t l2csr_scratch(int D, int Dc)
 {
     // the continuum part's sums (a multiple of 16 doubles), then the transposed block
-    return symv_scratch_doubles(D, Dc) + (int64_t)16 * D;
+    // with its zero record
+    return symv_scratch_doubles(D, Dc) + (int64_t)16 * (D + 1);
 }
 
 // P: rows 0..D-1, columns < Dc (leading dimension ldp)
