@@ -192,8 +192,10 @@ cch_status cch_set_orbitals(cch_ctx *ctx, int32_t n_o, const uint8_t *tgt_irrep,
  *   tttc [n_o][n_o][n_o][n_cont]   (pq|r j)
  *   ttcc [n_o][n_o][n_cont][n_cont] (pq|j j')
  *   tctc [n_o][n_cont][n_o][n_cont] (p j|q j')
- * with the permutational symmetries of real orbitals: the FP64 build reads one
- * of the equal values (pq|jj') = (qp|jj') = (pq|j'j) and (pj|qj') = (qj'|pj).
+ * The FP64 build reads one of the values that real orbitals make equal,
+ * (pq|jj') = (qp|jj') = (pq|j'j) and (pj|qj') = (qj'|pj), where they all agree
+ * to 2^-49 of their size (checked by cch_plan), and else every value as given,
+ * as the other precisions do.
  * e_core is added to every diagonal element. Requires cch_set_orbitals. */
 cch_status cch_set_integrals(cch_ctx *ctx, const double *h, const double *tttt,
                              const double *tttc, const double *ttcc, const double *tctc,
@@ -502,7 +504,8 @@ cch_status cch_build_time(cch_ctx *ctx, float *total_ms, float *phases);
  * out[0] lower-triangle elements computed (D(D+1)/2 when stored dense; with
  * CCH_PLAN_SPARSE_L2 the dense parts plus the L2 block's structural non-zeros
  * of the lower triangle), out[1] expansion GEMM flops (2 * rows * cols * K
- * summed over symmetry pairs, each distinct integral once in FP64), out[2] connected target pairs, out[3]
+ * summed over symmetry pairs; in FP64 each distinct integral once, where
+ * cch_plan found the symmetries of real orbitals), out[2] connected target pairs, out[3]
  * connected L2 x target pairs, out[4] relayout bytes moved (read + write),
  * out[5] class-4 outputs, out[6] L2 lower-triangle elements computed (all of
  * them dense, the structural non-zeros sparse), out[7] number of symmetry

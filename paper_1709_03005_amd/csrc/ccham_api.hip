@@ -29,6 +29,7 @@ hipError_t launch_relayout(const double *ttcc, const double *tctc, int n_o, int 
 hipError_t launch_relayout_sq(const double *ttcc, const double *tctc, int n_o, int n_cont, const int32_t *fP,
                               const int32_t *fQ, int nF, int n_off, int ja0, int nc, int j0, int j1, double *B,
                               hipStream_t st, const PackedCC *pk);
+hipError_t launch_cc_sym(const CcBlocks &B, const double *ttcc, const double *tctc, int32_t *flag, hipStream_t st);
 struct ExpandEpi {
     double *H;
     int64_t ld;
@@ -201,7 +202,7 @@ struct PairPlan {
     DevPairs pr;
     int n_slot = 0, nrows = 0;
     int32_t *d_slotP = nullptr, *d_slotQ = nullptr, *d_pqidx = nullptr, *d_rn = nullptr, *d_rn2 = nullptr;
-    // FP64 expansion, each distinct integral once: nF pairs P >= Q of slots
+    // FP64 expansion of integrals with their symmetries, each distinct one once: nF pairs P >= Q of slots
     // (n_off with P > Q first), as slot indices and as orbitals; rect pairs also
     // list the exchange rows P Q, Q P alternating
     GammaMode form = GAM_PLAIN;
@@ -1061,6 +1062,35 @@ static cch_status job_tables(cch_ctx *c)
     return CCH_OK;
 }
 
+// whether the two-continuum integrals have the symmetries of real orbitals
+// (launch_cc_sym), so that the FP64 expansion may multiply each distinct one once
+static cch_status integrals_fold(cch_ctx *c, bool *fold)
+{
+    *fold = true;
+    if (c->n_cont == 0) return CCH_OK;
+    CcBlocks B{};
+    B.n_o = c->n_o;
+    B.n_cont = c->n_cont;
+    B.n_irrep = c->packed ? c->n_irrep : 1;
+    B.n[0] = c->n_cont;
+    if (c->packed) {
+        B.rec = c->d_pk_rec;
+        for (int a = 0; a < c->n_irrep; ++a) B.n[a] = c->n_c[a];
+        for (int x = 0; x < c->n_irrep; ++x)
+            for (int a = 0; a < c->n_irrep; ++a) B.blk[x][a] = c->pk_blk[(size_t)x * c->n_irrep + a];
+        for (int p = 0; p < c->n_o; ++p) B.irrep[p] = c->tgt_irrep[p];
+    }
+    int32_t *d = nullptr, differ = 0;
+    if (c->scratch.take((void **)&d, 4) != hipSuccess) return fail(c, CCH_E_OOM, "integral check");
+    hipError_t e = launch_cc_sym(B, c->d_ttcc, c->d_tctc, d, c->stream);
+    if (e == hipSuccess) e = hipMemcpyAsync(&differ, d, 4, hipMemcpyDeviceToHost, c->stream);
+    if (e == hipSuccess) e = hipStreamSynchronize(c->stream);
+    c->scratch.give(d);
+    if (e != hipSuccess) return fail(c, CCH_E_HIP, "integral check: %s", hipGetErrorString(e));
+    *fold = differ == 0;
+    return CCH_OK;
+}
+
 cch_status cch_plan(cch_ctx *c, const cch_plan_opts *opts)
 {
     if (!c) return CCH_E_INVALID_ARG;
@@ -1111,6 +1141,8 @@ cch_status cch_plan(cch_ctx *c, const cch_plan_opts *opts)
         return fail(c, CCH_E_STATE, "L2 functions given as CSFs need the dense L2 block (no CCH_PLAN_SPARSE_L2)");
     // dense: D x D; sparse L2 block: d_H keeps only the continuum columns
     c->ld = c->sparse ? std::max<int64_t>(32, (c->Dc + 31) / 32 * 32) : (c->D + 31) / 32 * 32;
+    bool fold = false;
+    if (c->opts.precision == CCH_PREC_FP64) TRY(integrals_fold(c, &fold));
     // symmetry pairs a >= b
     int64_t maxB = 0;
     for (int a = 0; a < (int)c->syms.size(); ++a) {
@@ -1138,7 +1170,7 @@ cch_status cch_plan(cch_ctx *c, const cch_plan_opts *opts)
                     rn2.push_back(n2);
                 }
             p.nrows = (int)rn.size();
-            if (c->opts.precision == CCH_PREC_FP64) {
+            if (fold) {
                 p.form = sa.ja0 == sb.ja0 && sa.nc == sb.nc ? GAM_SQUARE : GAM_RECT;
                 std::vector<int32_t> k1, k2, fP, fQ, xP, xQ;
                 for (int diag = 0; diag < 2; ++diag)   // the pairs P = Q last
@@ -1388,17 +1420,19 @@ static PackedCC packed_cc(const cch_ctx *c, const PairPlan &p, int j0)
     return pk;
 }
 
-// the integral rows of a pair's FP64 product for the continuum rows j0..j1-1
-static hipError_t relayout_f64(cch_ctx *c, const PairPlan &p, int j0, int j1, hipStream_t st)
+// the integral rows of a pair's product for the continuum rows j0..j1-1
+static hipError_t relayout_rows(cch_ctx *c, const PairPlan &p, int j0, int j1, hipStream_t st)
 {
     const SymInfo &sa = c->syms[p.a], &sb = c->syms[p.b];
-    const bool sq = p.form == GAM_SQUARE;
+    const bool sq = p.form == GAM_SQUARE, plain = p.form == GAM_PLAIN;
     const PackedCC pk = packed_cc(c, p, sq ? 0 : j0);
     if (sq)
         return launch_relayout_sq(c->d_ttcc, c->d_tctc, c->n_o, c->n_cont, p.d_fP, p.d_fQ, p.nF, p.n_off, sa.ja0,
                                   sa.nc, j0, j1, p.d_B, st, c->packed ? &pk : nullptr);
-    return launch_relayout(c->d_ttcc, c->d_tctc, c->n_o, c->n_cont, p.d_fP, p.d_fQ, p.nF, p.d_xP, p.d_xQ, 2 * p.n_off,
-                           sa.ja0 + j0, j1 - j0, sb.ja0, sb.nc, p.d_B, st, c->packed ? &pk : nullptr);
+    return launch_relayout(c->d_ttcc, c->d_tctc, c->n_o, c->n_cont, plain ? p.d_slotP : p.d_fP,
+                           plain ? p.d_slotQ : p.d_fQ, plain ? p.n_slot : p.nF, plain ? p.d_slotP : p.d_xP,
+                           plain ? p.d_slotQ : p.d_xQ, plain ? p.n_slot : 2 * p.n_off, sa.ja0 + j0, j1 - j0, sb.ja0,
+                           sb.nc, p.d_B, st, c->packed ? &pk : nullptr);
 }
 
 // every pair's integral rows (and, at reduced precision, the operands made from
@@ -1411,14 +1445,7 @@ static cch_status enqueue_relayouts(cch_ctx *c, const Fan &f)
         if (sa.nc == 0 || sb.nc == 0) continue;
         if (c->b_shared) continue;   // one shared buffer: rows are laid out pass by pass in phase 3
         const hipStream_t s = f(w++);
-        if (p.form != GAM_PLAIN) {
-            HIPCK(c, relayout_f64(c, p, 0, sa.nc, s));
-            continue;
-        }
-        const PackedCC pk = packed_cc(c, p, 0);
-        HIPCK(c, launch_relayout(c->d_ttcc, c->d_tctc, c->n_o, c->n_cont, p.d_slotP, p.d_slotQ, p.n_slot, p.d_slotP,
-                                 p.d_slotQ, p.n_slot, sa.ja0, sa.nc, sb.ja0, sb.nc, p.d_B, s,
-                                 c->packed ? &pk : nullptr));
+        HIPCK(c, relayout_rows(c, p, 0, sa.nc, s));
         const int K = 2 * p.n_slot, N = sa.nc * sb.nc;
         if (c->opts.precision == CCH_PREC_FP32) {
             HIPCK(c, launch_to_f32(p.d_At, p.d_At32, (int64_t)K * p.nrows, s));
@@ -1494,7 +1521,7 @@ static cch_status enqueue_gemm(cch_ctx *c, hipStream_t st, bool fan)
             // the product's columns (j, j') of those rows; each output keeps its sum over K
             for (int j0 = 0; j0 < sa.nc; j0 += p.jj_chunk) {
                 const int j1 = std::min(j0 + p.jj_chunk, sa.nc);
-                HIPCK(c, relayout_f64(c, p, j0, j1, st));
+                HIPCK(c, relayout_rows(c, p, j0, j1, st));
                 HIPCK(c, launch_expand_f64(expand_op(c, p, j0, j1), st));
             }
         }

@@ -363,6 +363,18 @@ struct PackedCC {
     int jr0, nca_full;
 };
 
+// the layout of the two-continuum integrals, for a pass over all of them: packed
+// (rec: record of the pair (P, Q); blk[x][a]: the block of rows of irrep a in a
+// record whose target orbitals' irreps differ by x; n[a] continuum orbitals) or
+// dense (rec = nullptr: one block of n[0] = n_cont orbitals, n_irrep = 1)
+struct CcBlocks {
+    const int64_t *rec;
+    int64_t blk[8][8];
+    int32_t n[8];
+    uint8_t irrep[32 * CCH_MAXW];
+    int n_irrep, n_o, n_cont;
+};
+
 // the slots (or pairs of slots) a density launch forms, and how it lays the
 // rows out for the expansion product (k_target.hip); k1 = nullptr: slot t
 enum GammaMode { GAM_PLAIN = 0, GAM_RECT = 1, GAM_SQUARE = 2 };
