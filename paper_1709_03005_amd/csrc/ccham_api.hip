@@ -1497,7 +1497,7 @@ static cch_status enqueue_gemm(cch_ctx *c, hipStream_t st, bool fan)
         // all in one launch: a pair's product alone has fewer workgroups than the
         // chip has compute units (at D = 8000 ten products of 100 to 176, 0.26 ms
         // on four streams, 0.13 in one launch)
-        HIPCK(c, launch_expand_f64_batched(c->d_mm, c->mm_n, c->mm_tiles, c->mm_bm, INT32_MAX, st));
+        HIPCK(c, launch_expand_f64_batched(c->d_mm, c->mm_n, c->mm_tiles, c->mm_bm, 1 << 20, st));
         return CCH_OK;
     }
     const Fan f{c, st, fan && c->have_aux && !c->b_shared};

@@ -339,6 +339,9 @@ struct PairList {
 
 enum ScanMode { SCAN_TT = 0, SCAN_LL = 1, SCAN_LT = 2 };
 
+// workgroups of a launch along y or z at most
+constexpr int GRID_YZ = 65535;
+
 // one excitation scan: bras A against kets B; emits from row_off[x], or counts
 // into row_cnt (row_off = nullptr). An emitting scan may also clear words that
 // later kernels of the stream count in: zero0 and zero1 (nz each), ones (no words

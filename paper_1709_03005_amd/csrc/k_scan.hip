@@ -150,7 +150,10 @@ hipError_t launch_scan(int mode, int W, const ScanJob &one, int top, hipStream_t
 // emit passes of a table of scans on the device, the longest of max_rows rows
 hipError_t launch_scans(int mode, int W, const ScanJob *jobs, int njob, int max_rows, int top, hipStream_t st)
 {
-    return scan_any(mode, W, ScanJob{}, jobs, njob, max_rows, true, top, st);
+    hipError_t e = hipSuccess;
+    for (int j0 = 0; j0 < njob && e == hipSuccess; j0 += GRID_YZ)
+        e = scan_any(mode, W, ScanJob{}, jobs + j0, min(GRID_YZ, njob - j0), max_rows, true, top, st);
+    return e;
 }
 
 // ---------------------------------------------------------------------------

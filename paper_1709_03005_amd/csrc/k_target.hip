@@ -447,30 +447,22 @@ __global__ __launch_bounds__(64 * GAM_W) void k_gamma(const PairJob *__restrict_
     }
 }
 
-// rows r = (n, n') of Gamma: every pair of states, or with tri (a symmetry with
-// itself) those with n' <= n; n' runs fastest
-
 hipError_t launch_slot_start(const PairJob *jobs, int njob, hipStream_t st);   // k_scan.hip
 
-// every symmetry pair's target elements, projections, label buckets and densities;
-// h: the table's copy on the host (its sizes), jobs: the table. One launch a stage:
-// a pair's own launches, eleven each, cost more than their work below some
-// thousand determinants.
-hipError_t launch_target_sums(int W, const TgtInts &I, int n_o, const std::vector<PairJob> &h, const PairJob *jobs,
-                              hipStream_t st)
+// the stages for the symmetry pairs h[0 .. nj - 1] of the table jobs
+static hipError_t target_sums(int W, const TgtInts &I, int n_o, const PairJob *h, const PairJob *jobs, unsigned nj,
+                              int NB, int groups, hipStream_t st)
 {
-    const unsigned nj = (unsigned)h.size();
-    if (nj == 0) return hipSuccess;
     int64_t n = 0;
-    int M = 0, nrows = 0, slots = 0, gl = 0, Sa = 0, Sb = 0;
-    for (const PairJob &p : h) {
+    int M = 0, nrows = 0, slots = 0, gl = 0, Sa = 0;
+    for (unsigned i = 0; i < nj; ++i) {
+        const PairJob &p = h[i];
         n = std::max(n, p.n);
         M = std::max(M, p.Ma);
         nrows = std::max(nrows, p.nrows);
         slots = std::max(slots, p.n_slot);
         gl = std::max(gl, p.gl.n);
         Sa = std::max(Sa, p.Sa);
-        Sb = std::max(Sb, p.Sb);
     }
     const dim3 gp((unsigned)((n + 255) / 256), nj), b(256);
     if (n > 0) {
@@ -493,7 +485,6 @@ hipError_t launch_target_sums(int W, const TgtInts &I, int n_o, const std::vecto
         }
     }
     if (gl > 0 && nrows > 0) {
-        const int NB = Sb > 16 ? 2 : 1, groups = (Sb + 16 * NB - 1) / (16 * NB);
         const dim3 g(gl, (Sa + 15) / 16, groups * nj), t(64 * GAM_W);
 #define GAMMA(W_, NB_) \
     case 8 * W_ + NB_: hipLaunchKernelGGL((k_gamma<W_, NB_>), g, t, 0, st, jobs, groups); break;
@@ -504,6 +495,24 @@ hipError_t launch_target_sums(int W, const TgtInts &I, int n_o, const std::vecto
 #undef GAMMA
     }
     return hipGetLastError();
+}
+
+// every symmetry pair's target elements, projections, label buckets and densities;
+// h: the table's copy on the host (its sizes), jobs: the table. One launch a stage
+// for as many pairs as a grid holds (k_gamma has up to eight workgroups a pair
+// along z): a pair's own launches, eleven each, cost more than their work below
+// some thousand determinants.
+hipError_t launch_target_sums(int W, const TgtInts &I, int n_o, const std::vector<PairJob> &h, const PairJob *jobs,
+                              hipStream_t st)
+{
+    int Sb = 1;
+    for (const PairJob &p : h) Sb = std::max(Sb, p.Sb);
+    const int NB = Sb > 16 ? 2 : 1, groups = (Sb + 16 * NB - 1) / (16 * NB);
+    const size_t most = (size_t)(GRID_YZ / groups);
+    hipError_t e = hipSuccess;
+    for (size_t j0 = 0; j0 < h.size() && e == hipSuccess; j0 += most)
+        e = target_sums(W, I, n_o, h.data() + j0, jobs + j0, (unsigned)std::min(most, h.size() - j0), NB, groups, st);
+    return e;
 }
 
 }  // namespace cch
