@@ -620,7 +620,7 @@ cch_status cch_set_integrals(cch_ctx *c, const double *h, const double *tttt, co
     if (!std::isfinite(e_core)) return fail(c, CCH_E_INPUT, "e_core is not finite");
     const size_t no = c->n_o, nc = c->n_cont, norb = c->n_orb;
     const size_t nh = norb * norb, n4 = no * no * no * no, n3c = no * no * no * nc, n2c = no * no * nc * nc;
-    TRY(dalloc(c, &c->d_h, nh));
+    TRY(dalloc(c, &c->d_h, nh + 1));   // (a word for cch_plan behind it)
     TRY(dalloc(c, &c->d_tttt, n4));
     TRY(dalloc(c, &c->d_tttc, n3c));
     TRY(dalloc(c, &c->d_ttcc, n2c));
@@ -664,7 +664,7 @@ cch_status cch_set_integrals_packed(cch_ctx *c, const double *h, const double *t
     const size_t npk = (size_t)rec[(size_t)no * no];
     const size_t nc = c->n_cont, norb = c->n_orb;
     const size_t nh = norb * norb, n4 = (size_t)no * no * no * no, n3c = (size_t)no * no * no * nc;
-    TRY(dalloc(c, &c->d_h, nh));
+    TRY(dalloc(c, &c->d_h, nh + 1));   // (a word for cch_plan behind it)
     TRY(dalloc(c, &c->d_tttt, n4));
     TRY(dalloc(c, &c->d_tttc, n3c));
     TRY(dalloc(c, &c->d_ttcc, npk));
@@ -1071,22 +1071,18 @@ static cch_status integrals_fold(cch_ctx *c, bool *fold)
     CcBlocks B{};
     B.n_o = c->n_o;
     B.n_cont = c->n_cont;
-    B.n_irrep = c->packed ? c->n_irrep : 1;
-    B.n[0] = c->n_cont;
-    if (c->packed) {
-        B.rec = c->d_pk_rec;
-        for (int a = 0; a < c->n_irrep; ++a) B.n[a] = c->n_c[a];
-        for (int x = 0; x < c->n_irrep; ++x)
-            for (int a = 0; a < c->n_irrep; ++a) B.blk[x][a] = c->pk_blk[(size_t)x * c->n_irrep + a];
-        for (int p = 0; p < c->n_o; ++p) B.irrep[p] = c->tgt_irrep[p];
+    B.n_irrep = c->n_irrep;
+    for (int a = 0; a < c->n_irrep; ++a) {
+        B.n[a] = c->n_c[a];
+        B.start[a] = c->cont_start[a];
+        for (int x = 0; x < c->n_irrep && c->packed; ++x) B.blk[x][a] = c->pk_blk[(size_t)x * c->n_irrep + a];
     }
-    int32_t *d = nullptr, differ = 0;
-    if (c->scratch.take((void **)&d, 4) != hipSuccess) return fail(c, CCH_E_OOM, "integral check");
-    hipError_t e = launch_cc_sym(B, c->d_ttcc, c->d_tctc, d, c->stream);
-    if (e == hipSuccess) e = hipMemcpyAsync(&differ, d, 4, hipMemcpyDeviceToHost, c->stream);
-    if (e == hipSuccess) e = hipStreamSynchronize(c->stream);
-    c->scratch.give(d);
-    if (e != hipSuccess) return fail(c, CCH_E_HIP, "integral check: %s", hipGetErrorString(e));
+    for (int p = 0; p < c->n_o; ++p) B.irrep[p] = c->tgt_irrep[p];
+    if (c->packed) B.rec = c->d_pk_rec;
+    int32_t *d = reinterpret_cast<int32_t *>(c->d_h + (size_t)c->n_orb * c->n_orb), differ = 0;   // the word behind h
+    HIPCK(c, launch_cc_sym(B, c->d_ttcc, c->d_tctc, d, c->stream));
+    HIPCK(c, hipMemcpyAsync(&differ, d, 4, hipMemcpyDeviceToHost, c->stream));
+    HIPCK(c, hipStreamSynchronize(c->stream));
     *fold = differ == 0;
     return CCH_OK;
 }

@@ -366,14 +366,14 @@ struct PackedCC {
     int jr0, nca_full;
 };
 
-// the layout of the two-continuum integrals, for a pass over all of them: packed
-// (rec: record of the pair (P, Q); blk[x][a]: the block of rows of irrep a in a
-// record whose target orbitals' irreps differ by x; n[a] continuum orbitals) or
-// dense (rec = nullptr: one block of n[0] = n_cont orbitals, n_irrep = 1)
+// the blocks of the two-continuum integrals that symmetry allows, for a pass over
+// them: n[a] continuum orbitals of irrep a from start[a] on; packed layout: record
+// of the pair (P, Q) at rec[P * n_o + Q], the block of rows of irrep a at blk[x][a]
+// of it where the target orbitals' irreps differ by x; dense layout: rec = nullptr
 struct CcBlocks {
     const int64_t *rec;
     int64_t blk[8][8];
-    int32_t n[8];
+    int32_t n[8], start[8];
     uint8_t irrep[32 * CCH_MAXW];
     int n_irrep, n_o, n_cont;
 };

@@ -247,8 +247,8 @@ hipError_t launch_relayout_sq(const double *ttcc, const double *tctc, int n_o, i
 // transformation leave when multiplied in another order), or are not finite, set
 // *flag; the expansion then reads every value as given. A workgroup takes a pair
 // P >= Q and the tiles (j, j') and (j', j) of the blocks of the irreps (a, b) and
-// (b, a); the dense layout is one block over all continuum orbitals. Once per
-// plan, bound by reading both arrays.
+// (b, a) that symmetry allows, the values that a build reads. Once per plan, bound
+// by reading them.
 // ---------------------------------------------------------------------------
 __device__ __forceinline__ bool cc_differ(double a, double b)
 {
@@ -265,13 +265,15 @@ __global__ __launch_bounds__(256) void k_cc_sym(CcBlocks B, const double *__rest
     const int Q = (int)blockIdx.z - P * (P + 1) / 2;
     const int r0 = blockIdx.x * 32, c0 = blockIdx.y * 32;
     const int tx = threadIdx.x & 31, ty = threadIdx.x >> 5;
-    const int x = B.rec ? B.irrep[P] ^ B.irrep[Q] : 0;
-    // (P Q | j j') and (P j | Q j'), j of irrep a
+    const int x = B.irrep[P] ^ B.irrep[Q];
+    // (P Q | j j') and (P j | Q j'), j of irrep a, j' of irrep a ^ x
     auto coul = [&](int p, int q, int a) -> const double * {
-        return ttcc + (B.rec ? B.rec[(size_t)p * B.n_o + q] + B.blk[x][a] : ((int64_t)p * B.n_o + q) * B.n_cont * B.n_cont);
+        if (B.rec) return ttcc + B.rec[(size_t)p * B.n_o + q] + B.blk[x][a];
+        return ttcc + (((int64_t)p * B.n_o + q) * B.n_cont + B.start[a]) * B.n_cont + B.start[a ^ x];
     };
     auto exch = [&](int p, int q, int a) -> const double * {
-        return tctc + (B.rec ? B.rec[(size_t)p * B.n_o + q] + B.blk[x][a] : ((int64_t)p * B.n_cont * B.n_o + q) * B.n_cont);
+        if (B.rec) return tctc + B.rec[(size_t)p * B.n_o + q] + B.blk[x][a];
+        return tctc + (((int64_t)p * B.n_cont + B.start[a]) * B.n_o + q) * B.n_cont + B.start[a ^ x];
     };
     bool bad = false;
     for (int a = 0; a < B.n_irrep; ++a) {
