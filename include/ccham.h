@@ -30,8 +30,10 @@
  * which case it is a device pointer on the context's device. Device work is
  * ordered on the context's HIP stream; cch_sync() waits for it.
  * One context must not be used from two threads at once. A context keeps the
- * work space of its calls (at most 1/64 of the device's memory while idle;
- * none under cch_plan_opts.max_device_bytes) until cch_destroy.
+ * work space of its calls for the next ones, until cch_destroy: idle, that of all
+ * contexts of a device holds at most 1/64 of its memory (none of a context
+ * under cch_plan_opts.max_device_bytes), and it is freed when any allocation of
+ * this library on the device would fail without it.
  */
 #ifndef CCHAM_H
 #define CCHAM_H

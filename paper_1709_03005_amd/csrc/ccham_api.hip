@@ -16,6 +16,7 @@
 
 #include "../../include/ccham.h"
 #include "ccham_internal.h"
+#include "work_space.h"
 
 namespace cch {
 // launchers defined in the kernel files
@@ -239,68 +240,23 @@ struct LtPlan {
 
 }  // namespace
 
-// Work space of a context's calls (solver bases, mat-vec partials, staging of
-// host arrays), kept between calls: a hipFree waits for the whole device and
-// unmaps, and with several large contexts resident a product of 1 ms spent 11
-// ms on it (D = 24011; a solve at D = 8000 2.5 of its 14.5 ms). take() reuses
-// an idle block of at most twice the size, else allocates; give() keeps idle
-// blocks while they hold at most `keep` bytes in all and frees the largest
-// ones beyond that. The blocks belong to one context, whose calls run one at
-// a time and queue their kernels on one stream, so a reused block's earlier
-// work is ordered before its next.
-struct Scratch {
-    struct Block {
-        void *p;
-        size_t bytes;
-        bool used;
-    };
-    std::vector<Block> blocks;
-    size_t keep = 0;
-    void drop_idle(size_t most)
+namespace cch {
+struct HipDev {
+    using Err = hipError_t;
+    static hipError_t alloc(void **p, size_t bytes)
     {
-        size_t idle = 0;
-        for (auto &b : blocks) idle += b.used ? 0 : b.bytes;
-        while (idle > most) {
-            size_t at = blocks.size();
-            for (size_t i = 0; i < blocks.size(); ++i)
-                if (!blocks[i].used && (at == blocks.size() || blocks[i].bytes > blocks[at].bytes)) at = i;
-            idle -= blocks[at].bytes;
-            (void)hipFree(blocks[at].p);
-            blocks.erase(blocks.begin() + (std::ptrdiff_t)at);
-        }
+        *p = nullptr;
+        const hipError_t e = hipMalloc(p, bytes);
+        if (e != hipSuccess) (void)hipGetLastError();
+        return e;
     }
-    hipError_t take(void **p, size_t bytes)
-    {
-        bytes = (std::max<size_t>(bytes, 1) + 255) / 256 * 256;
-        Block *best = nullptr;
-        for (auto &b : blocks)
-            if (!b.used && b.bytes >= bytes && b.bytes / 2 <= bytes && (!best || b.bytes < best->bytes)) best = &b;
-        if (best) {
-            best->used = true;
-            *p = best->p;
-            return hipSuccess;
-        }
-        blocks.reserve(blocks.size() + 1);
-        void *q = nullptr;
-        hipError_t e = hipMalloc(&q, bytes);
-        if (e != hipSuccess) {   // the idle blocks may hold what is missing
-            drop_idle(0);
-            (void)hipGetLastError();
-            e = hipMalloc(&q, bytes);
-        }
-        if (e != hipSuccess) return e;
-        blocks.push_back({q, bytes, true});
-        *p = q;
-        return hipSuccess;
-    }
-    void give(void *p)
-    {
-        if (!p) return;
-        for (auto &b : blocks)
-            if (b.p == p) b.used = false;
-        drop_idle(keep);
-    }
+    static void release(void *p) { (void)hipFree(p); }
 };
+typedef WorkSpace<HipDev> Scratch;
+
+// every device allocation that is not a context's work space
+hipError_t dev_malloc(int device, void **p, size_t bytes) { return Scratch::alloc(device, p, bytes); }
+}  // namespace cch
 
 constexpr int CCH_NAUX = 6;   // auxiliary streams of a build: 4 for the symmetry pairs, class 4, L2 block
 constexpr int CCH_NPAIRS_ST = 4;
@@ -424,7 +380,7 @@ static cch_status dalloc(cch_ctx *c, T **p, size_t n)
     if (c->opts.max_device_bytes > 0 && c->bytes + (int64_t)bytes > c->opts.max_device_bytes)
         return fail(c, CCH_E_OOM, "device budget of %lld bytes exceeded", (long long)c->opts.max_device_bytes);
     void *q = nullptr;
-    hipError_t e = hipMalloc(&q, bytes);
+    hipError_t e = dev_malloc(c->device, &q, bytes);
     if (e != hipSuccess) return fail(c, CCH_E_OOM, "hipMalloc(%zu): %s", bytes, hipGetErrorString(e));
     c->allocs.push_back(q);
     c->bytes += (int64_t)bytes;
@@ -520,9 +476,9 @@ cch_status cch_create(cch_ctx **out, int32_t device, void *hip_stream)
         aux_ok = timing_event(&c->c4_ev[i]) == hipSuccess && timing_event(&c->l2_ev[i]) == hipSuccess &&
                  timing_event(&c->rl_ev[i]) == hipSuccess;
     {
-        // idle work space kept by one context: 1/64 of the device (4.5 GB of 288)
+        // idle work space kept by the contexts of a device: 1/64 of it (4.5 GB of 288)
         size_t free_b = 0, total_b = 0;
-        if (hipMemGetInfo(&free_b, &total_b) == hipSuccess) c->scratch.keep = total_b / 64;
+        c->scratch.open(device, hipMemGetInfo(&free_b, &total_b) == hipSuccess ? total_b / 64 : 0);
     }
     c->have_aux = aux_ok;   // without them every phase runs on the context stream
     c->opts.precision = CCH_PREC_FP64;
@@ -536,7 +492,7 @@ cch_status cch_destroy(cch_ctx *c)
     (void)hipSetDevice(c->device);
     (void)hipStreamSynchronize(c->stream);
     for (void *p : c->allocs) (void)hipFree(p);
-    for (auto &b : c->scratch.blocks) (void)hipFree(b.p);
+    c->scratch.close();
     if (c->pinned) (void)hipHostFree(c->pinned);
     if (!c->csr.planned) {
         (void)hipFree(c->csr.off);
@@ -972,7 +928,7 @@ static cch_status table(cch_ctx *c, T **d, const std::vector<T> &h)
 {
     if (h.empty()) return CCH_OK;
     void *q = nullptr;
-    if (hipMalloc(&q, sizeof(T) * h.size()) != hipSuccess) return fail(c, CCH_E_OOM, "job tables");
+    if (dev_malloc(c->device, &q, sizeof(T) * h.size()) != hipSuccess) return fail(c, CCH_E_OOM, "job tables");
     c->allocs.push_back(q);
     *d = (T *)q;
     HIPCK(c, hipMemcpy(q, h.data(), sizeof(T) * h.size(), hipMemcpyHostToDevice));
@@ -1102,10 +1058,8 @@ cch_status cch_plan(cch_ctx *c, const cch_plan_opts *opts)
         if (opts->max_device_bytes < 0) return fail(c, CCH_E_INVALID_ARG, "negative memory budget");
         if (opts->flags & ~CCH_PLAN_SPARSE_L2) return fail(c, CCH_E_INVALID_ARG, "unknown plan flags %d", opts->flags);
         c->opts = *opts;
-        if (opts->max_device_bytes > 0) {   // a caller who budgets memory gets it back after each call
-            c->scratch.keep = 0;
-            c->scratch.drop_idle(0);
-        }
+        if (opts->max_device_bytes > 0) c->scratch.open(c->device, 0);   // a caller who budgets memory gets it back
+                                                                         // after each call
     }
     HIPCK(c, hipSetDevice(c->device));
     // rows
@@ -1723,7 +1677,7 @@ cch_status cch_target_hamiltonian(cch_ctx *c, int32_t sym_a, int32_t sym_b, doub
     int64_t ldo = ld;
     if (!dev) {
         ldo = mb;
-        if (hipMalloc((void **)&d, 8 * (size_t)std::max(1, ma) * std::max(1, mb)) != hipSuccess)
+        if (dev_malloc(c->device, (void **)&d, 8 * (size_t)std::max(1, ma) * std::max(1, mb)) != hipSuccess)
             return fail(c, CCH_E_OOM, "target Hamiltonian staging");
     }
     hipError_t e = hipSuccess;
@@ -1752,7 +1706,7 @@ cch_status cch_work_detail(cch_ctx *c, double *out, int32_t n)
     std::vector<void *> tmp;
     auto cleanup = [&]() { for (void *p : tmp) (void)hipFree(p); };
     auto galloc = [&](void **p, size_t bytes) -> hipError_t {
-        hipError_t e = hipMalloc(p, bytes ? bytes : 8);
+        hipError_t e = dev_malloc(c->device, p, bytes ? bytes : 8);
         if (e == hipSuccess) tmp.push_back(*p);
         return e;
     };
@@ -1833,7 +1787,7 @@ cch_status cch_get_matrix(cch_ctx *c, double *out, int64_t ld, int32_t flags)
         // caller's device array, or through a staging block for host output)
         const SparseMat S = sparse_mat(c);
         double *stage = nullptr;
-        if (!to_dev && hipMalloc((void **)&stage, 8 * (size_t)rows_per * D) != hipSuccess)
+        if (!to_dev && dev_malloc(c->device, (void **)&stage, 8 * (size_t)rows_per * D) != hipSuccess)
             return fail(c, CCH_E_OOM, "read-out staging block");
         hipError_t e = hipSuccess;
         for (int64_t r0 = 0; r0 < D && e == hipSuccess; r0 += rows_per) {
@@ -1941,8 +1895,8 @@ cch_status cch_get_elements(cch_ctx *c, int64_t n, const int64_t *rows, const in
                         (long long)hr[i], (long long)hc[i], (long long)c->D);
     int64_t *d_idx = nullptr;
     double *d_out = nullptr;
-    hipError_t e = hipMalloc((void **)&d_idx, 16 * (size_t)n);
-    if (e == hipSuccess) e = hipMalloc((void **)&d_out, 8 * (size_t)n);
+    hipError_t e = dev_malloc(c->device, (void **)&d_idx, 16 * (size_t)n);
+    if (e == hipSuccess) e = dev_malloc(c->device, (void **)&d_out, 8 * (size_t)n);
     if (e == hipSuccess) e = hipMemcpyAsync(d_idx, hr.data(), 8 * (size_t)n, hipMemcpyHostToDevice, c->stream);
     if (e == hipSuccess) e = hipMemcpyAsync(d_idx + n, hc.data(), 8 * (size_t)n, hipMemcpyHostToDevice, c->stream);
     if (e == hipSuccess)
@@ -2026,7 +1980,7 @@ cch_status cch_get_block(cch_ctx *c, int32_t cls, int32_t sym_a, int32_t sym_b, 
         const SparseMat S = sparse_mat(c);
         const int64_t rows_per = std::max<int64_t>(1, (int64_t(1) << 30) / (8 * nc));
         double *stage = nullptr;
-        if (!(flags & CCH_MEM_DEVICE) && hipMalloc((void **)&stage, 8 * (size_t)rows_per * nc) != hipSuccess)
+        if (!(flags & CCH_MEM_DEVICE) && dev_malloc(c->device, (void **)&stage, 8 * (size_t)rows_per * nc) != hipSuccess)
             return fail(c, CCH_E_OOM, "block staging");
         hipError_t e = hipSuccess;
         for (int64_t i0 = 0; i0 < nr && e == hipSuccess; i0 += rows_per) {
@@ -2052,7 +2006,7 @@ cch_status cch_get_block(cch_ctx *c, int32_t cls, int32_t sym_a, int32_t sym_b, 
         return CCH_OK;
     }
     double *tmp = nullptr;
-    if (hipMalloc((void **)&tmp, 8 * (size_t)nr * nc) != hipSuccess) return fail(c, CCH_E_OOM, "block staging");
+    if (dev_malloc(c->device, (void **)&tmp, 8 * (size_t)nr * nc) != hipSuccess) return fail(c, CCH_E_OOM, "block staging");
     hipError_t e = launch_get_block(c->d_H, c->ld, r0, (int)nr, c0, (int)nc, mode, nca, ncb, tmp, nc, c->stream);
     if (e == hipSuccess) e = hipMemcpy2DAsync(out, ld * 8, tmp, nc * 8, nc * 8, nr, hipMemcpyDeviceToHost, c->stream);
     if (e == hipSuccess) e = hipStreamSynchronize(c->stream);
@@ -2395,7 +2349,7 @@ cch_status cch_get_labels(cch_ctx *c, int32_t which, int32_t sym_a, int32_t sym_
     // temporary buffers, freed at the end of the call
     std::vector<void *> tmp;
     auto galloc = [&](void **p, size_t bytes) -> hipError_t {
-        hipError_t e = hipMalloc(p, bytes ? bytes : 8);
+        hipError_t e = dev_malloc(c->device, p, bytes ? bytes : 8);
         if (e == hipSuccess) tmp.push_back(*p);
         return e;
     };
@@ -2503,10 +2457,10 @@ cch_status cch_mlp_create(cch_mlp **out, int32_t device, void *hip_stream, uint6
     m->device = device;
     m->st = (hipStream_t)hip_stream;
     const int P = mlp_num_params();
-    bool ok = hipMalloc(&m->w, 4 * (size_t)P) == hipSuccess && hipMalloc(&m->m, 4 * (size_t)P) == hipSuccess &&
-              hipMalloc(&m->v, 4 * (size_t)P) == hipSuccess && hipMalloc(&m->grad, 4 * (size_t)P) == hipSuccess &&
-              hipMalloc(&m->w2, 2 * 128 * 128) == hipSuccess && hipMalloc(&m->w2t, 2 * 128 * 128) == hipSuccess &&
-              hipMalloc(&m->loss, 8) == hipSuccess;
+    const auto get = [&](auto **p, size_t bytes) { return dev_malloc(device, (void **)p, bytes) == hipSuccess; };
+    bool ok = get(&m->w, 4 * (size_t)P) && get(&m->m, 4 * (size_t)P) && get(&m->v, 4 * (size_t)P) &&
+              get(&m->grad, 4 * (size_t)P) && get(&m->w2, 2 * 128 * 128) && get(&m->w2t, 2 * 128 * 128) &&
+              get(&m->loss, 8);
     if (!ok) {
         cch_mlp_destroy(m);
         return mfail(nullptr, CCH_E_OOM, "MLP buffers");
@@ -2562,8 +2516,9 @@ static cch_status mlp_rows(cch_mlp *m, int64_t n, const float *X, const float *t
     if (!(flags & CCH_MEM_DEVICE) && n > m->cap) {
         for (float *p : {m->xin, m->tin, m->ein, m->win}) if (p) (void)hipFree(p);
         m->xin = m->tin = m->ein = m->win = nullptr;
-        if (hipMalloc(&m->xin, 16 * (size_t)n) != hipSuccess || hipMalloc(&m->tin, 4 * (size_t)n) != hipSuccess ||
-            hipMalloc(&m->ein, 4 * (size_t)n) != hipSuccess || hipMalloc(&m->win, 4 * (size_t)n) != hipSuccess)
+        const auto get = [&](float **p, size_t bytes) { return dev_malloc(m->device, (void **)p, bytes) == hipSuccess; };
+        if (!get(&m->xin, 16 * (size_t)n) || !get(&m->tin, 4 * (size_t)n) || !get(&m->ein, 4 * (size_t)n) ||
+            !get(&m->win, 4 * (size_t)n))
             return mfail(m, CCH_E_OOM, "row buffers");
         m->cap = n;
     }
@@ -2587,8 +2542,8 @@ static cch_status mlp_part(cch_mlp *m, int64_t n)
         if (m->lpart) (void)hipFree(m->lpart);
         m->part = nullptr;
         m->lpart = nullptr;
-        if (hipMalloc(&m->part, 4 * (size_t)blocks * mlp_num_params()) != hipSuccess ||
-            hipMalloc(&m->lpart, 8 * (size_t)blocks) != hipSuccess)
+        if (dev_malloc(m->device, (void **)&m->part, 4 * (size_t)blocks * mlp_num_params()) != hipSuccess ||
+            dev_malloc(m->device, (void **)&m->lpart, 8 * (size_t)blocks) != hipSuccess)
             return mfail(m, CCH_E_OOM, "gradient partials");
         m->part_blocks = blocks;
     }
@@ -2605,7 +2560,7 @@ cch_status cch_mlp_forward(cch_mlp *m, const float *X, int64_t n, float *g, int3
     if (!(flags & CCH_MEM_DEVICE)) {
         if (m->gout) (void)hipFree(m->gout);
         m->gout = nullptr;
-        if (hipMalloc(&m->gout, 4 * (size_t)n) != hipSuccess) return mfail(m, CCH_E_OOM, "output buffer");
+        if (dev_malloc(m->device, (void **)&m->gout, 4 * (size_t)n) != hipSuccess) return mfail(m, CCH_E_OOM, "output buffer");
         dg = m->gout;
     }
     MCK(m, launch_mlp_forward(m->w, m->w2, m->w2t, dX, n, dg, m->st));
@@ -2661,9 +2616,9 @@ cch_status cch_mlp_features(cch_ctx *c, double theta, float *X, int32_t flags)
     double *rho = nullptr, *th = nullptr;
     float *dX = X;
     int32_t *sel = nullptr;
-    bool ok = hipMalloc(&rho, 8 * (size_t)D) == hipSuccess && hipMalloc(&th, 8) == hipSuccess &&
-              hipMalloc(&sel, 4) == hipSuccess;
-    if (ok && !(flags & CCH_MEM_DEVICE)) ok = hipMalloc(&dX, 16 * (size_t)D) == hipSuccess;
+    bool ok = dev_malloc(c->device, (void **)&rho, 8 * (size_t)D) == hipSuccess &&
+              dev_malloc(c->device, (void **)&th, 8) == hipSuccess && dev_malloc(c->device, (void **)&sel, 4) == hipSuccess;
+    if (ok && !(flags & CCH_MEM_DEVICE)) ok = dev_malloc(c->device, (void **)&dX, 16 * (size_t)D) == hipSuccess;
     const int32_t zero = 0;
     hipError_t e = ok ? hipSuccess : hipErrorOutOfMemory;
     if (e == hipSuccess) e = hipMemcpy(th, &theta, 8, hipMemcpyHostToDevice);
@@ -2744,7 +2699,7 @@ template <class T>
 static cch_status bupload(cch_batch *b, T **d, const std::vector<T> &h)
 {
     void *p = nullptr;
-    BCK(b, hipMalloc(&p, sizeof(T) * (h.empty() ? 1 : h.size())));
+    BCK(b, dev_malloc(b->device, (void **)&p, sizeof(T) * (h.empty() ? 1 : h.size())));
     b->allocs.push_back(p);
     if (!h.empty()) BCK(b, hipMemcpy(p, h.data(), sizeof(T) * h.size(), hipMemcpyHostToDevice));
     *d = (T *)p;
@@ -3076,10 +3031,10 @@ static cch_status ensure_l2csr(cch_ctx *c, hipStream_t st)
 {
     if (c->csr.gen == c->build_gen) return CCH_OK;
     const int nl2 = c->n_l2r, Dc = (int)c->Dc;
-    if (!c->csr.off && hipMalloc((void **)&c->csr.off, 8 * ((size_t)nl2 + 1)) != hipSuccess)
+    if (!c->csr.off && dev_malloc(c->device, (void **)&c->csr.off, 8 * ((size_t)nl2 + 1)) != hipSuccess)
         return fail(c, CCH_E_OOM, "L2 row offsets");
     int64_t *cnt = nullptr;
-    if (hipMalloc((void **)&cnt, 8 * (size_t)nl2) != hipSuccess) return fail(c, CCH_E_OOM, "L2 row counts");
+    if (dev_malloc(c->device, (void **)&cnt, 8 * (size_t)nl2) != hipSuccess) return fail(c, CCH_E_OOM, "L2 row counts");
     int64_t nnz = 0;
     hipError_t e = launch_l2_csr_count(c->d_H, c->ld, Dc, nl2, cnt, st);
     if (e == hipSuccess) e = launch_exclusive_scan(cnt, c->csr.off, nl2, c->csr.off + nl2, st);
@@ -3093,8 +3048,8 @@ static cch_status ensure_l2csr(cch_ctx *c, hipStream_t st)
         c->csr.col = nullptr;
         c->csr.val = nullptr;
         c->csr.cap = 0;
-        if (hipMalloc((void **)&c->csr.col, 4 * (size_t)std::max<int64_t>(nnz, 1)) != hipSuccess ||
-            hipMalloc((void **)&c->csr.val, 8 * (size_t)std::max<int64_t>(nnz, 1)) != hipSuccess)
+        if (dev_malloc(c->device, (void **)&c->csr.col, 4 * (size_t)std::max<int64_t>(nnz, 1)) != hipSuccess ||
+            dev_malloc(c->device, (void **)&c->csr.val, 8 * (size_t)std::max<int64_t>(nnz, 1)) != hipSuccess)
             return fail(c, CCH_E_OOM, "L2 CSR of %lld non-zeros", (long long)nnz);
         c->csr.cap = nnz;
     }

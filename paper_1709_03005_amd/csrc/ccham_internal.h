@@ -537,6 +537,9 @@ struct DavSel {
 };
 
 struct GemmDesc;
+// device memory that is no context's work space; idle work space on the device
+// makes room for it
+__attribute__((visibility("hidden"))) hipError_t dev_malloc(int device, void **p, size_t bytes);
 hipError_t launch_scan(int mode, int W, const ScanJob &one, int top, hipStream_t st);
 hipError_t launch_scans(int mode, int W, const ScanJob *jobs, int njob, int max_rows, int top, hipStream_t st);
 hipError_t launch_exclusive_scan(const int64_t *in, int64_t *out, int n, int64_t *total,

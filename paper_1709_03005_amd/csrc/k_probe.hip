@@ -6,6 +6,7 @@
 #include <hip/hip_runtime.h>
 
 #include "../../include/ccham.h"
+#include "ccham_internal.h"
 
 namespace {
 
@@ -57,7 +58,7 @@ extern "C" cch_status cch_probe_fp64(int32_t device, void *hip_stream, double *r
     double *out = nullptr;
     hipEvent_t e0 = nullptr, e1 = nullptr;
     cch_status rc = CCH_OK;
-    if (hipMalloc((void **)&out, sizeof(double) * PROBE_WG * 256) != hipSuccess) return CCH_E_OOM;
+    if (cch::dev_malloc(device, (void **)&out, sizeof(double) * PROBE_WG * 256) != hipSuccess) return CCH_E_OOM;
     if (hipEventCreate(&e0) != hipSuccess || hipEventCreate(&e1) != hipSuccess) rc = CCH_E_HIP;
     for (int mode = 0; mode < 3 && rc == CCH_OK; ++mode) {
         float best = 0.0f;

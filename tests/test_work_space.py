@@ -1,0 +1,148 @@
+"""The work space that contexts keep between calls (csrc/work_space.h), compiled
+for the host against a device of 1000 bytes a unit that counts what it holds:
+blocks are reused; an allocation that fails, of the same context or of another,
+frees every idle block of its device and no other; all contexts of a device
+together keep a bounded amount; a context under a memory budget keeps nothing
+and leaves the others' alone; several threads; nothing is left at the end."""
+import os
+import subprocess
+
+import pytest
+
+HERE = os.path.dirname(os.path.abspath(__file__))
+CSRC = os.path.join(os.path.dirname(HERE), "paper_1709_03005_amd", "csrc")
+
+SRC = r"""
+#include <atomic>
+#include <cstdio>
+#include <cstdlib>
+#include <map>
+#include <thread>
+#include "work_space.h"
+
+constexpr size_t U = 256;   // the blocks' granularity
+struct Dev {
+    using Err = int;
+    static std::map<void *, std::pair<int, size_t>> &live() { static std::map<void *, std::pair<int, size_t>> m; return m; }
+    static std::mutex &lock() { static std::mutex m; return m; }
+    static int current;
+    static size_t cap;
+    static size_t used(int d)
+    {
+        size_t n = 0;
+        for (auto &kv : live()) n += kv.second.first == d ? kv.second.second : 0;
+        return n;
+    }
+    static int alloc(void **p, size_t bytes)
+    {
+        std::lock_guard<std::mutex> g(lock());
+        *p = nullptr;
+        if (used(current) + bytes > cap) return 2;
+        *p = malloc(1);
+        live()[*p] = {current, bytes};
+        return 0;
+    }
+    static void release(void *p)
+    {
+        std::lock_guard<std::mutex> g(lock());
+        if (!live().erase(p)) { printf("released twice\n"); exit(1); }
+        free(p);
+    }
+};
+int Dev::current = 0;
+size_t Dev::cap = 100 * U;
+typedef cch::WorkSpace<Dev> WS;
+#define CHECK(x) do { if (!(x)) { printf("line %d: %s\n", __LINE__, #x); exit(1); } } while (0)
+
+int main()
+{
+    void *p, *q, *r;
+    {   // reuse, by size: at most twice as large
+        WS a;
+        a.open(0, 50 * U);
+        CHECK(a.take(&p, 10 * U - 3) == 0);
+        a.give(p);
+        CHECK(a.take(&q, 5 * U) == 0 && q == p);
+        CHECK(a.take(&r, 5 * U) == 0 && r != p);
+        a.give(q);
+        CHECK(a.take(&p, 4 * U) == 0 && p != q);
+        a.give(p);
+        a.give(r);
+        CHECK(Dev::used(0) == 19 * U);
+    }
+    CHECK(Dev::live().empty());
+    {   // idle blocks make room, whoever asks; another device's stay
+        WS a, b, c;
+        a.open(0, 90 * U);
+        b.open(0, 90 * U);
+        Dev::current = 1;
+        c.open(1, 90 * U);
+        CHECK(c.take(&p, 30 * U) == 0);
+        c.give(p);
+        Dev::current = 0;
+        CHECK(a.take(&p, 40 * U) == 0 && a.take(&q, 20 * U) == 0);
+        a.give(p);
+        CHECK(WS::alloc(0, &r, 60 * U) == 0);           // no work space of anybody's
+        CHECK(Dev::used(0) == 80 * U && Dev::used(1) == 30 * U);
+        CHECK(WS::alloc(0, &p, 30 * U) == 2);           // (20 in use, 60 allocated)
+        Dev::release(r);
+        a.give(q);
+        CHECK(b.take(&p, 95 * U) == 0);                 // another context's work space
+        CHECK(Dev::used(0) == 95 * U);
+        b.give(p);
+        CHECK(Dev::used(0) == 0 && Dev::used(1) == 30 * U);   // more than is kept
+    }
+    CHECK(Dev::live().empty());
+    {   // the bound is the device's, not a context's; a budgeted one keeps nothing
+        WS a, b, c;
+        a.open(0, 40 * U);
+        b.open(0, 40 * U);
+        CHECK(a.take(&p, 30 * U) == 0);
+        a.give(p);
+        CHECK(b.take(&p, 25 * U) == 0 && b.take(&q, 5 * U) == 0);
+        b.give(p);
+        CHECK(Dev::used(0) == 30 * U);                  // a's 30 went
+        c.open(0, 40 * U);
+        CHECK(c.take(&r, 8 * U) == 0);
+        c.open(0, 0);
+        c.give(r);
+        CHECK(Dev::used(0) == 30 * U);
+        b.give(q);
+        CHECK(Dev::used(0) == 30 * U);
+    }
+    CHECK(Dev::live().empty());
+    {   // threads, a context each, more than fits at once
+        Dev::cap = 300 * U;
+        std::atomic<int> bad{0};
+        std::vector<std::thread> ts;
+        for (int t = 0; t < 6; ++t)
+            ts.emplace_back([&, t] {
+                WS w;
+                w.open(0, 60 * U);
+                for (int i = 0; i < 3000; ++i) {
+                    void *x = nullptr, *y = nullptr, *z = nullptr;
+                    if (w.take(&x, (1 + (i * 7 + t) % 20) * U) || w.take(&y, (1 + i % 10) * U)) ++bad;
+                    if (i % 16 == 0 && WS::alloc(0, &z, 10 * U)) ++bad;
+                    w.give(x);
+                    w.give(y);
+                    if (z) Dev::release(z);
+                }
+            });
+        for (auto &t : ts) t.join();
+        CHECK(bad == 0);
+    }
+    CHECK(Dev::live().empty());
+    printf("ok\n");
+    return 0;
+}
+"""
+
+
+@pytest.mark.parametrize("flags", [[], ["-fsanitize=thread"]], ids=["plain", "threads"])
+def test_work_space(tmp_path, flags):
+    src, exe = tmp_path / "w.cpp", tmp_path / "w"
+    src.write_text(SRC)
+    subprocess.run(["g++", "-std=c++17", "-O1", "-g", "-Wall", "-pthread", *flags, "-I", CSRC, str(src), "-o", str(exe)],
+                   check=True, timeout=120)
+    r = subprocess.run([str(exe)], capture_output=True, text=True, timeout=120)
+    assert r.returncode == 0 and r.stdout.strip() == "ok", r.stdout + r.stderr
