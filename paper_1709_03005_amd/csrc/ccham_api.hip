@@ -1870,7 +1870,8 @@ cch_status cch_apply(cch_ctx *c, const double *V, int64_t ldv, int32_t b, double
                       : launch_matvec(c->d_H, c->ld, (int)D, dV, lv, b, dW, lw, Wp, c->stream);
     if (e == hipSuccess && !dev)
         e = hipMemcpy2DAsync(W, 8 * ldw, dW, 8 * D, 8 * D, b, hipMemcpyDeviceToHost, c->stream);
-    if (e == hipSuccess) e = hipStreamSynchronize(c->stream);
+    const hipError_t es = hipStreamSynchronize(c->stream);   // (after a failure too: what was queued reads the blocks)
+    if (e == hipSuccess) e = es;
     c->scratch.give(Wp);
     if (!dev) {
         c->scratch.give(dV);
@@ -2026,8 +2027,9 @@ cch_status cch_subspace_eig(cch_ctx *c, const double *G, int32_t ldg, int32_t m,
     hipStream_t st = c->stream;
     const bool dev = flags & CCH_MEM_DEVICE;
     double *dG = nullptr, *dT = nullptr, *dY = nullptr;
-    int32_t *dF = nullptr;
+    int32_t *dF = nullptr, hf = 0;
     auto cleanup = [&]() {
+        (void)hipStreamSynchronize(st);   // (after a failure: what was queued reads the blocks and writes hf)
         if (!dev) {
             c->scratch.give(dG);
             c->scratch.give(dT);
@@ -2057,7 +2059,6 @@ cch_status cch_subspace_eig(cch_ctx *c, const double *G, int32_t ldg, int32_t m,
     ECK(hipMemsetAsync(dF, 0, 4, st));
     if (method == CCH_EIG_JACOBI) ECK(launch_jacobi_eig(dG, ldg, m, dT, dY, ldy, st));
     else ECK(launch_rr_eig(dG, ldg, m, dT, dY, ldy, dF, st));
-    int32_t hf = 0;
     ECK(hipMemcpyAsync(&hf, dF, 4, hipMemcpyDeviceToHost, st));
     if (!dev) {
         ECK(hipMemcpyAsync(theta, dT, 8 * (size_t)m, hipMemcpyDeviceToHost, st));
@@ -2090,7 +2091,12 @@ cch_status cch_eig_all(cch_ctx *c, const double *A, int64_t lda, int32_t n, doub
     const int64_t ld = ((int64_t)n + 31) / 32 * 32;
     const int NB = 128;   // reflectors per block of the back-transformation (at most 128: launch_larft)
     std::vector<void *> tmp;
-    auto cleanup = [&]() { for (void *p : tmp) c->scratch.give(p); };
+    auto cleanup = [&]() {
+        // after a failure: what was queued uses the blocks, this call's host arrays
+        // and the caller's
+        (void)hipStreamSynchronize(st);
+        for (void *p : tmp) c->scratch.give(p);
+    };
     auto al = [&](void **p, size_t bytes) -> bool {
         if (c->scratch.take(p, bytes ? bytes : 8) != hipSuccess) return false;
         tmp.push_back(*p);
@@ -3101,7 +3107,12 @@ cch_status cch_davidson(cch_ctx *c, const cch_dav_opts *o, double *evals, double
     const int64_t ldv = ((int64_t)D + 31) / 32 * 32;
     const int BMAX = 32;                       // block columns (<= 2k <= 32)
     std::vector<void *> tmp;
-    auto cleanup = [&]() { for (void *p : tmp) c->scratch.give(p); };
+    auto cleanup = [&]() {
+        // after a failure: what was queued uses the blocks, this call's host arrays
+        // and the caller's
+        (void)hipStreamSynchronize(st);
+        for (void *p : tmp) c->scratch.give(p);
+    };
     auto A = [&](void **p, size_t bytes) -> bool {
         if (c->scratch.take(p, bytes ? bytes : 8) != hipSuccess) return false;
         tmp.push_back(*p);
