@@ -243,10 +243,11 @@ struct LtPlan {
 namespace cch {
 struct HipDev {
     using Err = hipError_t;
-    static hipError_t alloc(void **p, size_t bytes)
+    static hipError_t alloc(int device, void **p, size_t bytes)
     {
         *p = nullptr;
-        const hipError_t e = hipMalloc(p, bytes);
+        hipError_t e = hipSetDevice(device);
+        if (e == hipSuccess) e = hipMalloc(p, bytes);
         if (e != hipSuccess) (void)hipGetLastError();
         return e;
     }
@@ -1853,6 +1854,7 @@ cch_status cch_apply(cch_ctx *c, const double *V, int64_t ldv, int32_t b, double
     if (!c->built) return fail(c, CCH_E_STATE, "build first");
     const int64_t D = c->D;
     if (b == 0 || D == 0) return CCH_OK;
+    HIPCK(c, hipSetDevice(c->device));
     if (ldv < D || ldw < D) return fail(c, CCH_E_INVALID_ARG, "leading dimensions %lld, %lld below D = %lld",
                                         (long long)ldv, (long long)ldw, (long long)D);
     const bool dev = flags & CCH_MEM_DEVICE;

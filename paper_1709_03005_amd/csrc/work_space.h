@@ -13,8 +13,8 @@
 // again. One lock over all work spaces of the process covers this; it is taken a
 // few times a call.
 //
-// Dev: an error type Err (Err(0): success), static Err alloc(void **, size_t) and
-// static void release(void *), on the current device.
+// Dev: an error type Err (Err(0): success), static Err alloc(int device, void **,
+// size_t), on that device whichever is current, and static void release(void *).
 #pragma once
 #include <algorithm>
 #include <cstddef>
@@ -127,7 +127,7 @@ private:
 
     static Err alloc_locked(int device, void **p, size_t bytes)
     {
-        const Err e = Dev::alloc(p, bytes);
+        const Err e = Dev::alloc(device, p, bytes);
         if (e == Err(0)) return e;
         bool freed = false;
         for (WorkSpace *w : all().spaces)
@@ -136,7 +136,7 @@ private:
                     w->drop(b);
                     freed = true;
                 }
-        return freed ? Dev::alloc(p, bytes) : e;
+        return freed ? Dev::alloc(device, p, bytes) : e;
     }
 
     // frees idle blocks until what is kept is within the bounds

@@ -25,7 +25,6 @@ struct Dev {
     using Err = int;
     static std::map<void *, std::pair<int, size_t>> &live() { static std::map<void *, std::pair<int, size_t>> m; return m; }
     static std::mutex &lock() { static std::mutex m; return m; }
-    static int current;
     static size_t cap;
     static size_t used(int d)
     {
@@ -33,13 +32,13 @@ struct Dev {
         for (auto &kv : live()) n += kv.second.first == d ? kv.second.second : 0;
         return n;
     }
-    static int alloc(void **p, size_t bytes)
+    static int alloc(int device, void **p, size_t bytes)
     {
         std::lock_guard<std::mutex> g(lock());
         *p = nullptr;
-        if (used(current) + bytes > cap) return 2;
+        if (used(device) + bytes > cap) return 2;
         *p = malloc(1);
-        live()[*p] = {current, bytes};
+        live()[*p] = {device, bytes};
         return 0;
     }
     static void release(void *p)
@@ -49,7 +48,6 @@ struct Dev {
         free(p);
     }
 };
-int Dev::current = 0;
 size_t Dev::cap = 100 * U;
 typedef cch::WorkSpace<Dev> WS;
 #define CHECK(x) do { if (!(x)) { printf("line %d: %s\n", __LINE__, #x); exit(1); } } while (0)
@@ -75,11 +73,9 @@ int main()
         WS a, b, c;
         a.open(0, 90 * U);
         b.open(0, 90 * U);
-        Dev::current = 1;
         c.open(1, 90 * U);
         CHECK(c.take(&p, 30 * U) == 0);
         c.give(p);
-        Dev::current = 0;
         CHECK(a.take(&p, 40 * U) == 0 && a.take(&q, 20 * U) == 0);
         a.give(p);
         CHECK(WS::alloc(0, &r, 60 * U) == 0);           // no work space of anybody's
