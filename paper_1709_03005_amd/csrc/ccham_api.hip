@@ -921,28 +921,32 @@ static cch_status upload(cch_ctx *c, T **d, const std::vector<T> &h)
     return CCH_OK;
 }
 
-// The tables of scans and of symmetry pairs that a build's launches read. They
-// hold addresses and sizes of the plan's buffers, some hundred bytes a pair, and
-// are no part of a caller's memory budget.
-template <class T>
-static cch_status table(cch_ctx *c, T **d, const std::vector<T> &h)
+static ExpandOp expand_op(cch_ctx *c, const PairPlan &p, int j0, int j1);
+
+// The tables of scans and of symmetry pairs that a build's launches read: the
+// buffers (some hundred bytes a pair), before what is left of a budget goes to the
+// integral rows, and their contents, once every buffer of the plan has its place.
+static cch_status alloc_job_tables(cch_ctx *c)
 {
-    if (h.empty()) return CCH_OK;
-    void *q = nullptr;
-    if (dev_malloc(c->device, &q, sizeof(T) * h.size()) != hipSuccess) return fail(c, CCH_E_OOM, "job tables");
-    c->allocs.push_back(q);
-    *d = (T *)q;
-    HIPCK(c, hipMemcpy(q, h.data(), sizeof(T) * h.size(), hipMemcpyHostToDevice));
+    TRY(dalloc(c, &c->d_tt_scans, c->pp.size()));
+    TRY(dalloc(c, &c->d_lt_scans, c->lt.size()));
+    TRY(dalloc(c, &c->d_jobs, c->pp.size()));
     return CCH_OK;
 }
 
-static ExpandOp expand_op(cch_ctx *c, const PairPlan &p, int j0, int j1);
+template <class T>
+static cch_status fill_table(cch_ctx *c, T *d, const std::vector<T> &h)
+{
+    if (!h.empty()) HIPCK(c, hipMemcpy(d, h.data(), sizeof(T) * h.size(), hipMemcpyHostToDevice));
+    return CCH_OK;
+}
 
-static cch_status job_tables(cch_ctx *c)
+static cch_status fill_job_tables(cch_ctx *c)
 {
     // the FP64 products of several pairs that each have their own integral rows and
     // fewer tiles than four a compute unit (more fill the chip by themselves, with
-    // the registers of one form of tile instead of all)
+    // the registers of one form of tile instead of all); a launch each, with the same
+    // bits, where a budget has no room for their table
     std::vector<GemmTask> mm;
     int64_t most = 0;
     c->mm_tiles = 0;
@@ -960,8 +964,13 @@ static cch_status job_tables(cch_ctx *c)
             most = std::max(most, (int64_t)g.tiles_m * g.tiles_n);
             mm.push_back(g);
         }
-    c->mm_n = mm.size() > 1 && most < 1024 ? (int)mm.size() : 0;
-    if (c->mm_n) TRY(table(c, &c->d_mm, mm));
+    const int64_t budget = c->opts.max_device_bytes;
+    const bool room = budget == 0 || c->bytes + (int64_t)(sizeof(GemmTask) * mm.size()) <= budget;
+    c->mm_n = mm.size() > 1 && most < 1024 && room ? (int)mm.size() : 0;
+    if (c->mm_n) {
+        TRY(dalloc(c, &c->d_mm, mm.size()));
+        TRY(fill_table(c, c->d_mm, mm));
+    }
     std::vector<ScanJob> tt, lt;
     c->h_jobs.clear();
     c->max_dets = 0;
@@ -1013,9 +1022,9 @@ static cch_status job_tables(cch_ctx *c)
         const SymInfo &s = c->syms[L.sym];
         lt.push_back(ScanJob{c->d_l2, s.d_dets, c->n_l2, s.M, L.pr.row_off, L.pr.row_cnt, L.pr.pl});
     }
-    TRY(table(c, &c->d_tt_scans, tt));
-    TRY(table(c, &c->d_lt_scans, lt));
-    TRY(table(c, &c->d_jobs, c->h_jobs));
+    TRY(fill_table(c, c->d_tt_scans, tt));
+    TRY(fill_table(c, c->d_lt_scans, lt));
+    TRY(fill_table(c, c->d_jobs, c->h_jobs));
     return CCH_OK;
 }
 
@@ -1235,6 +1244,7 @@ cch_status cch_plan(cch_ctx *c, const cch_plan_opts *opts)
         c->csr.nnz = c->csr.cap = nnz;
         c->csr.planned = true;
     }
+    TRY(alloc_job_tables(c));
     if (c->opts.precision == CCH_PREC_FP64) {
         const int64_t budget = c->opts.max_device_bytes;
         if (budget == 0 || c->bytes + 8 * maxB <= budget) {
@@ -1264,7 +1274,7 @@ cch_status cch_plan(cch_ctx *c, const cch_plan_opts *opts)
             c->b_shared = true;
         }
     }
-    TRY(job_tables(c));
+    TRY(fill_job_tables(c));
     c->planned = true;
     return CCH_OK;
 }
