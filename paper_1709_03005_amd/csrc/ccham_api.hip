@@ -31,24 +31,6 @@ hipError_t launch_relayout_sq(const double *ttcc, const double *tctc, int n_o, i
                               const int32_t *fQ, int nF, int n_off, int ja0, int nc, int j0, int j1, double *B,
                               hipStream_t st, const PackedCC *pk);
 hipError_t launch_cc_sym(const CcBlocks &B, const double *ttcc, const double *tctc, int32_t *flag, hipStream_t st);
-struct ExpandEpi {
-    double *H;
-    int64_t ld;
-    int64_t row0a, row0b;
-    int nca, ncb;
-    int ja0, jb0;
-    const int32_t *rn, *rn2;
-    const double *HT, *O;
-    const double *h;
-    int n_o, n_orb;
-};
-struct ExpandOp {
-    const double *At, *B;
-    int nrows, KS, KA;
-    int sq, j0, j1;
-    int N;
-    ExpandEpi ep;
-};
 hipError_t launch_expand_f64(const ExpandOp &op, hipStream_t st);
 int expand_cols(const ExpandOp &op);
 hipError_t launch_to_f32(const double *x, float *y, int64_t n, hipStream_t st);
@@ -60,28 +42,10 @@ hipError_t launch_expand_bf16split(const __bf16 *SA, const __bf16 *SB, const dou
                                    int s, int nrows, int N, int ldk, const ExpandEpi &ep, hipStream_t st);
 hipError_t launch_class4(const Class4Args &a, int n_l2, hipStream_t st);
 int c4_items(int S, int nc, int n_l2);
-struct L2Args {
-    const uint64_t *dets;
-    int n_l2;
-    TgtInts I;
-    double *H;
-    int64_t ld;
-    int64_t row0;
-    int both;
-};
 hipError_t launch_l2_block(int W, const L2Args &a, hipStream_t st);
 hipError_t launch_l2csf_gather(const double *Hd, int64_t ldd, int Dc, int ncsf, const int32_t *start,
                                const int32_t *det, const double *coef, double *H, int64_t ld, hipStream_t st);
-struct GemmTask {
-    ExpandOp op;
-    int height, tiles_m, tiles_n;
-    int64_t first;
-};
 int expand_task_height(int nrows, int bm);
-struct L2Task {
-    L2Args a;
-    int64_t first;
-};
 int64_t l2_tiles(int n_l2);
 hipError_t launch_expand_f64_batched(const GemmTask *tasks, int ntask, int64_t total, int bm, int grid,
                                      hipStream_t st);

@@ -476,9 +476,6 @@ inline size_t trd_panel_layout(int n, int64_t ldp, double *base, TrdPanel *P)
     return at;
 }
 
-// a matrix whose L2 block (classes 2 and 8) is held as CSR: P[r][c] for
-// c < Dc (every row), R[r][c - Dc] for r < Dc <= c, and the L2 block's rows
-// as CSR (columns relative to Dc, ascending)
 // class 4 of one target symmetry (k_class4.hip)
 struct Class4Args {
     const uint64_t *tdets;   // target dets of the symmetry [M][W]
@@ -513,6 +510,56 @@ struct C4Task {
     int64_t first;   // first global work item of this block
 };
 
+// where the expansion product's results go, and what is added to them
+struct ExpandEpi {
+    double *H;            // contracted matrix, row-major
+    int64_t ld;
+    int64_t row0a, row0b; // first row of symmetry a / b
+    int nca, ncb;         // continuum orbitals of a / b
+    int ja0, jb0;         // first global continuum index of a / b
+    const int32_t *rn, *rn2;
+    const double *HT, *O; // per GEMM row
+    const double *h;      // one-electron matrix [n_orb][n_orb]
+    int n_o, n_orb;
+};
+
+// one product: rect, N = (rows j of the pass) x ncb columns, KA = 0; or square,
+// columns j >= j' of j0 <= j < j1
+struct ExpandOp {
+    const double *At, *B;
+    int nrows, KS, KA;
+    int sq, j0, j1;
+    int N;                // columns of B (the leading dimension)
+    ExpandEpi ep;
+};
+
+// one product of a persistent launch (k_gemm.hip): tiles [first, first + tiles_m *
+// tiles_n) of the list, `height` rows each
+struct GemmTask {
+    ExpandOp op;
+    int height, tiles_m, tiles_n;
+    int64_t first;
+};
+
+// the dense L2 block, classes 2 and 8 (k_l2.hip)
+struct L2Args {
+    const uint64_t *dets;   // [n_l2][W]
+    int n_l2;
+    TgtInts I;
+    double *H;
+    int64_t ld;
+    int64_t row0;           // first L2 row / column of the matrix
+    int both;               // write the upper triangle as well
+};
+
+struct L2Task {   // one instance of a persistent launch
+    L2Args a;
+    int64_t first;   // first global tile of this instance
+};
+
+// a matrix whose L2 block (classes 2 and 8) is held as CSR: P[r][c] for
+// c < Dc (every row), R[r][c - Dc] for r < Dc <= c, and the L2 block's rows
+// as CSR (columns relative to Dc, ascending)
 struct SparseMat {
     const double *P;
     int64_t ldp;
@@ -536,7 +583,6 @@ struct DavSel {
     int32_t e[32];
 };
 
-struct GemmDesc;
 // device memory that is no context's work space; idle work space on the device
 // makes room for it
 __attribute__((visibility("hidden"))) hipError_t dev_malloc(int device, void **p, size_t bytes);

@@ -336,27 +336,6 @@ hipError_t launch_cc_sym(const CcBlocks &B, const double *ttcc, const double *tc
 // (k < KS) and of the antisymmetric one (KS <= k < KS + KA) go to two sets of
 // accumulators.
 // ---------------------------------------------------------------------------
-struct ExpandEpi {
-    double *H;            // contracted matrix, row-major
-    int64_t ld;
-    int64_t row0a, row0b; // first row of symmetry a / b
-    int nca, ncb;         // continuum orbitals of a / b
-    int ja0, jb0;         // first global continuum index of a / b
-    const int32_t *rn, *rn2;
-    const double *HT, *O; // per GEMM row
-    const double *h;      // one-electron matrix [n_orb][n_orb]
-    int n_o, n_orb;
-};
-
-// one product: rect, N = (rows j of the pass) x ncb columns, KA = 0; or square,
-// columns j >= j' of j0 <= j < j1
-struct ExpandOp {
-    const double *At, *B;
-    int nrows, KS, KA;
-    int sq, j0, j1;
-    int N;                // columns of B (the leading dimension)
-    ExpandEpi ep;
-};
 
 constexpr int GBN = 128, GBK = 16, GBJ = 8;
 
@@ -571,11 +550,6 @@ hipError_t launch_expand_f64(const ExpandOp &op, hipStream_t st)
 // tile. Two waves a SIMD at BM = 64, where the compiler's own choice of registers
 // left one. Sixteen instances of 500 to 6000 rows: the build 4.56 -> 4.45 ms.
 // ---------------------------------------------------------------------------
-struct GemmTask {
-    ExpandOp op;
-    int height, tiles_m, tiles_n;
-    int64_t first;
-};
 
 // height of a task's tiles in the persistent form with tiles of at most bm rows:
 // as many workgroups as the whole list has, so only the padding counts

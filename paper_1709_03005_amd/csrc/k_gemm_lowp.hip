@@ -21,18 +21,6 @@
 
 namespace cch {
 
-struct ExpandEpi {
-    double *H;
-    int64_t ld;
-    int64_t row0a, row0b;
-    int nca, ncb;
-    int ja0, jb0;
-    const int32_t *rn, *rn2;
-    const double *HT, *O;
-    const double *h;
-    int n_o, n_orb;
-};
-
 typedef float fx4 __attribute__((ext_vector_type(4)));
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 

@@ -21,16 +21,6 @@
 
 namespace cch {
 
-struct L2Args {
-    const uint64_t *dets;   // [n_l2][W]
-    int n_l2;
-    TgtInts I;
-    double *H;
-    int64_t ld;
-    int64_t row0;           // first L2 row / column of the matrix
-    int both;               // write the upper triangle as well
-};
-
 // tiles of TR rows x 64 columns (TR divides 64) in the rows before tile row i
 template <int TR>
 __host__ __device__ __forceinline__ int64_t l2_tiles_before(int64_t i)
@@ -207,18 +197,14 @@ hipError_t launch_l2csf_gather(const double *Hd, int64_t ldd, int Dc, int ncsf, 
     return hipGetLastError();
 }
 
-// persistent form over many instances with the same word count
-struct L2Task {
-    L2Args a;
-    int64_t first;   // first global tile of this instance
-};
-
+// tiles of an instance in the persistent form
 int64_t l2_tiles(int n_l2)
 {
     const int64_t T = (n_l2 + 63) / 64;
     return T * (T + 1) / 2;
 }
 
+// persistent form over many instances with the same word count
 template <int W>
 __global__ __launch_bounds__(256) void k_l2_batched(const L2Task *__restrict__ tasks, int ntask, int64_t total)
 {
