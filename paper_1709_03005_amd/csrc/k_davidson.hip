@@ -794,40 +794,19 @@ hipError_t launch_jacobi_correct(const double *R, int64_t ld, int D, const doubl
 // ---------------------------------------------------------------------------
 constexpr int PCH_MAX = 32, PCH_M = 96;
 
-struct PchI2 {
-    int x, y;
-};
-
-template <int CTRL, int ROW_MASK, int BANK_MASK>
-__device__ __forceinline__ double pch_dpp(double v)
-{
-    PchI2 a = __builtin_bit_cast(PchI2, v);
-    a.x = __builtin_amdgcn_update_dpp(0, a.x, CTRL, ROW_MASK, BANK_MASK, true);
-    a.y = __builtin_amdgcn_update_dpp(0, a.y, CTRL, ROW_MASK, BANK_MASK, true);
-    return __builtin_bit_cast(double, a);
-}
-
-__device__ __forceinline__ double pch_rl(double v, int lane)
-{
-    PchI2 a = __builtin_bit_cast(PchI2, v);
-    a.x = __builtin_amdgcn_readlane(a.x, lane);
-    a.y = __builtin_amdgcn_readlane(a.y, lane);
-    return __builtin_bit_cast(double, a);
-}
-
 // maximum over the 64 lanes of values >= 0 (lanes without a DPP source read
 // 0): within rows of 16 by row shifts, then across rows by row broadcasts;
 // the result collects in lane 63 and is read from there
 __device__ __forceinline__ double pch_wmax(double v)
 {
-    double s = fmax(v, pch_dpp<0x111, 0xf, 0xf>(v));
-    s = fmax(s, pch_dpp<0x112, 0xf, 0xf>(v));
-    s = fmax(s, pch_dpp<0x113, 0xf, 0xf>(v));
-    s = fmax(s, pch_dpp<0x114, 0xf, 0xe>(s));
-    s = fmax(s, pch_dpp<0x118, 0xf, 0xc>(s));
-    s = fmax(s, pch_dpp<0x142, 0xa, 0xf>(s));
-    s = fmax(s, pch_dpp<0x143, 0xc, 0xf>(s));
-    return pch_rl(s, 63);
+    double s = fmax(v, rr_dpp<0x111, 0xf, 0xf>(v));
+    s = fmax(s, rr_dpp<0x112, 0xf, 0xf>(v));
+    s = fmax(s, rr_dpp<0x113, 0xf, 0xf>(v));
+    s = fmax(s, rr_dpp<0x114, 0xf, 0xe>(s));
+    s = fmax(s, rr_dpp<0x118, 0xf, 0xc>(s));
+    s = fmax(s, rr_dpp<0x142, 0xa, 0xf>(s));
+    s = fmax(s, rr_dpp<0x143, 0xc, 0xf>(s));
+    return rr_rl(s, 63);
 }
 
 // One workgroup, and latency is all of it: the columns of the pivoted Cholesky
@@ -917,7 +896,7 @@ __global__ __launch_bounds__(PCH_T) void k_pchol(const double *__restrict__ G, i
             if (mine) Rq[i][t] = rl;
             // Schur complement: lane l updates its column
 #pragma unroll
-            for (int q = 0; q < NB; ++q) a[q] = fma(-pch_rl(rl, q), rl, a[q]);
+            for (int q = 0; q < NB; ++q) a[q] = fma(-rr_rl(rl, q), rl, a[q]);
             d = fma(-rl, rl, d);
         }
         // R in pivot order, column by column, and its inverse: column c in lane c by
@@ -935,7 +914,7 @@ __global__ __launch_bounds__(PCH_T) void k_pchol(const double *__restrict__ G, i
         for (int i = 0; i < NB; ++i) x[i] = i == t ? 1.0 : 0.0;
 #pragma unroll
         for (int j = NB - 1; j >= 0; --j) {
-            x[j] *= pch_rl(rd, j);
+            x[j] *= rr_rl(rd, j);
 #pragma unroll
             for (int i = 0; i < j; ++i) x[i] = fma(-R[i][j], x[j], x[i]);
         }

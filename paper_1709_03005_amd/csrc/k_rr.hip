@@ -83,11 +83,6 @@ __device__ __forceinline__ double rr_block_max(double v, double *red)
     return s;
 }
 
-// ---------------------------------------------------------------------------
-// Cyclic Jacobi, parallel (round-robin tournament) ordering: m/2 disjoint
-// rotations per round, m-1 rounds per sweep; a rotation is skipped when
-// |a_pq| <= 1e-16 sqrt(|a_pp a_qq|), and the sweeps stop after one with no
-// rotation. Reads G itself (unscaled) and writes theta and Y.
 // a value every lane holds alike (read from LDS), as a wave-uniform scalar
 __device__ __forceinline__ double rr_uni(double v)
 {
@@ -97,6 +92,11 @@ __device__ __forceinline__ double rr_uni(double v)
     return __builtin_bit_cast(double, a);
 }
 
+// ---------------------------------------------------------------------------
+// Cyclic Jacobi, parallel (round-robin tournament) ordering: m/2 disjoint
+// rotations per round, m-1 rounds per sweep; a rotation is skipped when
+// |a_pq| <= 1e-16 sqrt(|a_pp a_qq|), and the sweeps stop after one with no
+// rotation. Reads G itself (unscaled) and writes theta and Y.
 // ---------------------------------------------------------------------------
 __device__ void rr_jacobi(RRShared &sh, const double *__restrict__ G, int ldg, int m, double *__restrict__ theta,
                           double *__restrict__ Y, int ldy, int max_sweeps)

@@ -14,6 +14,7 @@
 
 namespace cch {
 
+// ---------------------------------------------------------------------------
 // H_T values of the connected pairs, and their buckets by integral label (P, Q):
 // key = slot of a degree-1 pair, counted; degree-0 pairs are recorded per bra row;
 // degree 2 has no density term. (Counters and records were cleared by the scan.)
