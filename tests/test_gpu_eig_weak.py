@@ -72,3 +72,15 @@ def test_rayleigh_ritz(n, row, s):
         th, Y, nf = ctx.subspace_eig(M)
     _check(M, th, Y.T, 1e-13)
     assert nf == 0
+
+
+@pytest.mark.parametrize("n", [33, 64, 150])
+def test_graded_over_150_decades(n):
+    # every column is weaker than the one before it, down through the window
+    import paper_1709_03005_amd as cc
+    s = np.logspace(0, -150, n)
+    M = np.random.default_rng(n).standard_normal((n, n))
+    M = (M + M.T) * s[:, None] * s[None, :]
+    with cc.Context(0) as ctx:
+        w, V, _ = ctx.eig_all(M)
+    _check(M, w, V, 1e-12 * max(1.0, n / 100))
