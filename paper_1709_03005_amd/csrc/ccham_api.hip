@@ -885,6 +885,25 @@ static cch_status upload(cch_ctx *c, T **d, const std::vector<T> &h)
     return CCH_OK;
 }
 
+// the index lists of a symmetry pair, in one buffer and one copy (each list's own
+// allocation and copy, up to eleven a pair, took a third of a plan)
+struct IndexLists {
+    std::vector<int32_t> all;
+    std::vector<std::pair<int32_t **, size_t>> where;   // pointer, first entry
+    void add(int32_t **d, const std::vector<int32_t> &h)
+    {
+        where.push_back({d, all.size()});
+        all.insert(all.end(), h.begin(), h.end());
+    }
+    cch_status upload_all(cch_ctx *c)
+    {
+        int32_t *d = nullptr;
+        TRY(upload(c, &d, all));
+        for (auto &w : where) *w.first = d + w.second;
+        return CCH_OK;
+    }
+};
+
 static ExpandOp expand_op(cch_ctx *c, const PairPlan &p, int j0, int j1);
 
 // The tables of scans and of symmetry pairs that a build's launches read: the
@@ -1077,6 +1096,7 @@ cch_status cch_plan(cch_ctx *c, const cch_plan_opts *opts)
             SymInfo &sa = c->syms[a], &sb = c->syms[b];
             TRY(alloc_pairs(c, p.pr, SCAN_TT, sa.d_dets, sa.M, sb.d_dets, sb.M));
             // label slots (P, Q) allowed by symmetry
+            IndexLists lists;
             const int want = sa.irrep ^ sb.irrep;
             std::vector<int32_t> sP, sQ, pq((size_t)c->n_o * c->n_o, -1);
             for (int P = 0; P < c->n_o; ++P)
@@ -1114,20 +1134,21 @@ cch_status cch_plan(cch_ctx *c, const cch_plan_opts *opts)
                 // two symmetries of one irrep share their continuum range and have
                 // slots P = Q; a rect pair (different irreps) has none
                 if (p.form == GAM_RECT && p.nF != p.n_off) return fail(c, CCH_E_STATE, "symmetry pair (%d, %d)", a, b);
-                TRY(upload(c, &p.d_k1, k1));
-                TRY(upload(c, &p.d_k2, k2));
-                TRY(upload(c, &p.d_fP, fP));
-                TRY(upload(c, &p.d_fQ, fQ));
+                lists.add(&p.d_k1, k1);
+                lists.add(&p.d_k2, k2);
+                lists.add(&p.d_fP, fP);
+                lists.add(&p.d_fQ, fQ);
                 if (p.form == GAM_RECT) {
-                    TRY(upload(c, &p.d_xP, xP));
-                    TRY(upload(c, &p.d_xQ, xQ));
+                    lists.add(&p.d_xP, xP);
+                    lists.add(&p.d_xQ, xQ);
                 }
             }
-            TRY(upload(c, &p.d_slotP, sP));
-            TRY(upload(c, &p.d_slotQ, sQ));
-            TRY(upload(c, &p.d_pqidx, pq));
-            TRY(upload(c, &p.d_rn, rn));
-            TRY(upload(c, &p.d_rn2, rn2));
+            lists.add(&p.d_slotP, sP);
+            lists.add(&p.d_slotQ, sQ);
+            lists.add(&p.d_pqidx, pq);
+            lists.add(&p.d_rn, rn);
+            lists.add(&p.d_rn2, rn2);
+            TRY(lists.upload_all(c));
             TRY(dalloc(c, &p.d_hv, p.pr.n));
             TRY(dalloc(c, &p.d_Y, (size_t)sa.M * sb.S));
             TRY(dalloc(c, &p.d_Yo, (size_t)sa.M * sb.S));
