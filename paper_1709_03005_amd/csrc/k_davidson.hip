@@ -112,11 +112,12 @@ __global__ __launch_bounds__(256) void k_matvec_mfma(const double *__restrict__ 
 // bytes. The V columns of the row product are fixed over an item: registers up
 // to three groups, LDS for four.
 //
-// Bound by HBM: at D = 60000 one launch takes 2.33 / 2.7 / 3.2 ms for 4 / 10 /
-// 16 vectors (6.2 / 5.3 / 4.5 TB/s of its 14.4 GB; a read-only sweep reaches 6.0).
-// The form before staged 64 x 64 tiles for all eight waves in LDS behind two
-// barriers each: 3.0 / 3.6 / 4.5 ms, two tiles in flight per compute unit but
-// every wave waiting for the tile's slowest load.
+// Up to four vectors bound by HBM, beyond that by reads and matrix instructions
+// together: at D = 60000 one launch takes 2.5 / 2.75 / 3.0 / 3.3 ms for 4 / 8 / 12 /
+// 16 vectors (5.8 / 5.2 / 4.8 / 4.4 TB/s of its 14.4 GB; a read-only sweep reaches
+// 6.0). The form before staged 64 x 64 tiles for all eight waves in LDS behind two
+// barriers each: 3.0 / 3.6 / 4.5 ms for 4 / 10 / 16 vectors, two tiles in flight per
+// compute unit but every wave waiting for the tile's slowest load.
 // ---------------------------------------------------------------------------
 constexpr int SV_CW = 512, SV_WC = 64, SV_BR = 16;   // strip, columns per wave, rows per block
 constexpr int SV_TS = 34;            // LDS row stride of a turned 16 x 32 half block (16-byte slots: conflict-free)

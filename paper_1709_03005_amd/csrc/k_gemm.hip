@@ -32,6 +32,85 @@
 namespace cch {
 
 // ---------------------------------------------------------------------------
+// Do the two-continuum integrals have the symmetries that the folded product
+// reads one value for, (PQ|jj') = (QP|jj') = (PQ|j'j) and (Pj|Qj') = (Qj'|Pj)?
+// Values that differ by more than 2^-49 of the larger (what the factors of a
+// transformation leave when multiplied in another order), or are not finite, set
+// *flag; the expansion then reads every value as given. A workgroup takes a pair
+// P >= Q and the tiles (j, j') and (j', j) of the blocks of the irreps (a, b) and
+// (b, a) that symmetry allows, the values that a build reads. Once per plan, bound
+// by reading them.
+// ---------------------------------------------------------------------------
+__device__ __forceinline__ bool cc_differ(double a, double b)
+{
+    return !(fabs(a - b) <= 0x1p-49 * fmax(fabs(a), fabs(b)));
+}
+
+__global__ __launch_bounds__(256) void k_cc_sym(CcBlocks B, const double *__restrict__ ttcc,
+                                                const double *__restrict__ tctc, int32_t *__restrict__ flag)
+{
+    __shared__ double tb[32][33], tf[32][33], te[32][33];
+    int P = (int)((sqrt(8.0 * blockIdx.z + 1.0) - 1.0) * 0.5);
+    while ((P + 1) * (P + 2) / 2 <= (int)blockIdx.z) ++P;
+    while (P * (P + 1) / 2 > (int)blockIdx.z) --P;
+    const int Q = (int)blockIdx.z - P * (P + 1) / 2;
+    const int r0 = blockIdx.x * 32, c0 = blockIdx.y * 32;
+    const int tx = threadIdx.x & 31, ty = threadIdx.x >> 5;
+    const int x = B.irrep[P] ^ B.irrep[Q];
+    // (P Q | j j') and (P j | Q j'), j of irrep a, j' of irrep a ^ x
+    auto coul = [&](int p, int q, int a) -> const double * {
+        if (B.rec) return ttcc + B.rec[(size_t)p * B.n_o + q] + B.blk[x][a];
+        return ttcc + (((int64_t)p * B.n_o + q) * B.n_cont + B.start[a]) * B.n_cont + B.start[a ^ x];
+    };
+    auto exch = [&](int p, int q, int a) -> const double * {
+        if (B.rec) return tctc + B.rec[(size_t)p * B.n_o + q] + B.blk[x][a];
+        return tctc + (((int64_t)p * B.n_cont + B.start[a]) * B.n_o + q) * B.n_cont + B.start[a ^ x];
+    };
+    bool bad = false;
+    for (int a = 0; a < B.n_irrep; ++a) {
+        const int b = a ^ x, na = B.n[a], nb = B.n[b];
+        if (b < a || (b == a && c0 > r0) || r0 >= na || c0 >= nb) continue;   // (the whole workgroup)
+        const int64_t lc = B.rec ? nb : B.n_cont, lct = B.rec ? na : B.n_cont;   // row lengths of the two blocks
+        const int64_t le = B.rec ? nb : (int64_t)B.n_o * B.n_cont, let = B.rec ? na : le;
+        const double *A1 = coul(P, Q, a), *A2 = coul(P, Q, b), *C1 = coul(Q, P, a), *C2 = coul(Q, P, b);
+        const double *E1 = exch(P, Q, a), *E2 = exch(P, Q, b), *F1 = exch(Q, P, b), *F2 = exch(Q, P, a);
+        __syncthreads();
+        for (int r = ty; r < 32; r += 8) {   // row c0 + r, column r0 + tx of the blocks (b, a)
+            const int j = c0 + r, k = r0 + tx;
+            const bool in = j < nb && k < na;
+            const int64_t oc = j * lct + k, oe = j * let + k;
+            tb[r][tx] = in ? A2[oc] : 0.0;
+            tf[r][tx] = in ? F1[oe] : 0.0;
+            te[r][tx] = in ? E2[oe] : 0.0;
+            if (in) bad |= cc_differ(tb[r][tx], C2[oc]);
+        }
+        __syncthreads();
+        for (int r = ty; r < 32; r += 8) {   // row r0 + r, column c0 + tx of the blocks (a, b)
+            const int j = r0 + r, k = c0 + tx;
+            if (j >= na || k >= nb) continue;
+            const double v = A1[j * lc + k];
+            bad |= cc_differ(v, C1[j * lc + k]) || cc_differ(v, tb[tx][r]);
+            bad |= cc_differ(E1[j * le + k], tf[tx][r]) || cc_differ(F2[j * le + k], te[tx][r]);
+        }
+    }
+    if (__any(bad) && (threadIdx.x & 63) == 0) *flag = 1;
+}
+
+__global__ void k_flag_zero(int32_t *__restrict__ flag) { *flag = 0; }
+
+// *flag = 1 if the integrals lack a symmetry, else 0
+hipError_t launch_cc_sym(const CcBlocks &B, const double *ttcc, const double *tctc, int32_t *flag, hipStream_t st)
+{
+    hipLaunchKernelGGL(k_flag_zero, dim3(1), dim3(1), 0, st, flag);
+    int most = 0;
+    for (int a = 0; a < B.n_irrep; ++a) most = std::max(most, B.n[a]);
+    const int T = (most + 31) / 32;
+    if (T > 0)
+        hipLaunchKernelGGL(k_cc_sym, dim3(T, T, B.n_o * (B.n_o + 1) / 2), dim3(256), 0, st, B, ttcc, tctc, flag);
+    return hipGetLastError();
+}
+
+// ---------------------------------------------------------------------------
 // K0: B[k][jj*ncb + jj'] for one symmetry pair (plain and rect forms).
 //   k <  nJ: (P Q | J J')    = ttcc[P][Q][J][J']       (row copy)
 //   k >= nJ: -(P J' | J Q)   = -tctc[P][J'][Q][J]     (tile transpose)
@@ -237,85 +316,6 @@ hipError_t launch_relayout_sq(const double *ttcc, const double *tctc, int n_o, i
     else
         hipLaunchKernelGGL(k_relayout_sq<false>, g, dim3(256), 0, st, ttcc, tctc, PackedCC{}, n_o, n_cont, fP, fQ, nF,
                            n_off, ja0, nc, j0, j1, B);
-    return hipGetLastError();
-}
-
-// ---------------------------------------------------------------------------
-// Do the two-continuum integrals have the symmetries that the folded product
-// reads one value for, (PQ|jj') = (QP|jj') = (PQ|j'j) and (Pj|Qj') = (Qj'|Pj)?
-// Values that differ by more than 2^-49 of the larger (what the factors of a
-// transformation leave when multiplied in another order), or are not finite, set
-// *flag; the expansion then reads every value as given. A workgroup takes a pair
-// P >= Q and the tiles (j, j') and (j', j) of the blocks of the irreps (a, b) and
-// (b, a) that symmetry allows, the values that a build reads. Once per plan, bound
-// by reading them.
-// ---------------------------------------------------------------------------
-__device__ __forceinline__ bool cc_differ(double a, double b)
-{
-    return !(fabs(a - b) <= 0x1p-49 * fmax(fabs(a), fabs(b)));
-}
-
-__global__ __launch_bounds__(256) void k_cc_sym(CcBlocks B, const double *__restrict__ ttcc,
-                                                const double *__restrict__ tctc, int32_t *__restrict__ flag)
-{
-    __shared__ double tb[32][33], tf[32][33], te[32][33];
-    int P = (int)((sqrt(8.0 * blockIdx.z + 1.0) - 1.0) * 0.5);
-    while ((P + 1) * (P + 2) / 2 <= (int)blockIdx.z) ++P;
-    while (P * (P + 1) / 2 > (int)blockIdx.z) --P;
-    const int Q = (int)blockIdx.z - P * (P + 1) / 2;
-    const int r0 = blockIdx.x * 32, c0 = blockIdx.y * 32;
-    const int tx = threadIdx.x & 31, ty = threadIdx.x >> 5;
-    const int x = B.irrep[P] ^ B.irrep[Q];
-    // (P Q | j j') and (P j | Q j'), j of irrep a, j' of irrep a ^ x
-    auto coul = [&](int p, int q, int a) -> const double * {
-        if (B.rec) return ttcc + B.rec[(size_t)p * B.n_o + q] + B.blk[x][a];
-        return ttcc + (((int64_t)p * B.n_o + q) * B.n_cont + B.start[a]) * B.n_cont + B.start[a ^ x];
-    };
-    auto exch = [&](int p, int q, int a) -> const double * {
-        if (B.rec) return tctc + B.rec[(size_t)p * B.n_o + q] + B.blk[x][a];
-        return tctc + (((int64_t)p * B.n_cont + B.start[a]) * B.n_o + q) * B.n_cont + B.start[a ^ x];
-    };
-    bool bad = false;
-    for (int a = 0; a < B.n_irrep; ++a) {
-        const int b = a ^ x, na = B.n[a], nb = B.n[b];
-        if (b < a || (b == a && c0 > r0) || r0 >= na || c0 >= nb) continue;   // (the whole workgroup)
-        const int64_t lc = B.rec ? nb : B.n_cont, lct = B.rec ? na : B.n_cont;   // row lengths of the two blocks
-        const int64_t le = B.rec ? nb : (int64_t)B.n_o * B.n_cont, let = B.rec ? na : le;
-        const double *A1 = coul(P, Q, a), *A2 = coul(P, Q, b), *C1 = coul(Q, P, a), *C2 = coul(Q, P, b);
-        const double *E1 = exch(P, Q, a), *E2 = exch(P, Q, b), *F1 = exch(Q, P, b), *F2 = exch(Q, P, a);
-        __syncthreads();
-        for (int r = ty; r < 32; r += 8) {   // row c0 + r, column r0 + tx of the blocks (b, a)
-            const int j = c0 + r, k = r0 + tx;
-            const bool in = j < nb && k < na;
-            const int64_t oc = j * lct + k, oe = j * let + k;
-            tb[r][tx] = in ? A2[oc] : 0.0;
-            tf[r][tx] = in ? F1[oe] : 0.0;
-            te[r][tx] = in ? E2[oe] : 0.0;
-            if (in) bad |= cc_differ(tb[r][tx], C2[oc]);
-        }
-        __syncthreads();
-        for (int r = ty; r < 32; r += 8) {   // row r0 + r, column c0 + tx of the blocks (a, b)
-            const int j = r0 + r, k = c0 + tx;
-            if (j >= na || k >= nb) continue;
-            const double v = A1[j * lc + k];
-            bad |= cc_differ(v, C1[j * lc + k]) || cc_differ(v, tb[tx][r]);
-            bad |= cc_differ(E1[j * le + k], tf[tx][r]) || cc_differ(F2[j * le + k], te[tx][r]);
-        }
-    }
-    if (__any(bad) && (threadIdx.x & 63) == 0) *flag = 1;
-}
-
-__global__ void k_flag_zero(int32_t *__restrict__ flag) { *flag = 0; }
-
-// *flag = 1 if the integrals lack a symmetry, else 0
-hipError_t launch_cc_sym(const CcBlocks &B, const double *ttcc, const double *tctc, int32_t *flag, hipStream_t st)
-{
-    hipLaunchKernelGGL(k_flag_zero, dim3(1), dim3(1), 0, st, flag);
-    int most = 0;
-    for (int a = 0; a < B.n_irrep; ++a) most = std::max(most, B.n[a]);
-    const int T = (most + 31) / 32;
-    if (T > 0)
-        hipLaunchKernelGGL(k_cc_sym, dim3(T, T, B.n_o * (B.n_o + 1) / 2), dim3(256), 0, st, B, ttcc, tctc, flag);
     return hipGetLastError();
 }
 

@@ -193,8 +193,8 @@ __global__ __launch_bounds__(256) void k_slice_rows(const double *__restrict__ A
 // A workgroup takes 64 columns, once for their largest entries and once for the
 // slices. In the second pass a thread slices 16 k of its column; the 64 x 64 tile
 // of each slice is turned in LDS, so that B is read by rows and each slice is
-// written 128 bytes of a column at a time. Bound by memory (B twice, the slices
-// once): 1600 x 90000 in three slices in SLC_MS, 3.9 ms with one entry in flight
+// written 128 bytes of a column at a time. Moves B twice and the slices once:
+// 1600 x 90000 in three slices (3.2 GB) in 1.35 ms, 3.9 ms with one entry in flight
 // per thread and the tiles as floats in LDS.
 constexpr int SC_K = 64, SC_LD = SC_K + 8;   // tile depth; LDS row stride (16-byte rows, other banks)
 

@@ -11,10 +11,12 @@
 // like work -- in one pass over the tile half of the waves had at least one
 // connected lane, and the other 63 waited for its integrals -- and the tile
 // is written from LDS to both triangles, so no later pass reads the L2 block
-// back. Bound by the HBM write of the two triangles, 16 B per pair: 40000
-// functions, both triangles in 7.6 ms beside class 4, where the one-pass form
-// took 6.9 ms for the lower one and the mirror 3.0 ms for the rest; 2997
-// functions 0.058 ms instead of 0.320 + 0.03.
+// back. 40000 functions, both triangles (12.8 GB) in 5.1 ms alone, where the
+// writes by themselves would take 2.0: a tile's scan, evaluation and writes follow
+// one another, and three workgroups (43 KB of LDS each) a compute unit hide part
+// of that. Beside class 4 the one-pass form took 6.9 ms for the lower triangle
+// and the mirror 3.0 ms for the rest, this one 7.6 in all; 2997 functions 0.06 ms
+// instead of 0.320 + 0.03.
 #include <algorithm>
 
 #include "ccham_internal.h"
