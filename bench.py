@@ -63,20 +63,20 @@ KERNEL_SOURCE = {
 TRAFFIC = {
     # (workload, family): (sha256 prefix of the family's source, FETCH_SIZE KiB, WRITE_SIZE KiB);
     # the mat-vec averaged over the product instances of one solve, with the reduction
-    ("medium", "matvec"): ("0ff798e23148460a", 134499.3, 12866.3),
-    ("medium", "expansion_gemm"): ("1bc4e6a77a9184ed", 323349.0, 37510.5),
-    ("medium", "relayout"): ("7d0655f693706042", 347215.8, 509724.9),
-    ("medium", "class4"): ("d03cf0057bbc44d4", 66567.2, 120313.2),
-    ("medium", "l2_block"): ("d41318e67d054e01", 29924.1, 195977.4),
-    ("medium", "mirror"): ("c3a15eb9e31d99ef", 77236.8, 152429.7),
-    ("medium", "rayleigh_ritz"): ("ce8076ced68b2de3", 61.7, 25.5),
-    ("learned", "matvec"): ("0ff798e23148460a", 7353071.0, 451424.6),
-    ("learned", "expansion_gemm"): ("1bc4e6a77a9184ed", 8340469.9, 1626163.7),
-    ("learned", "relayout"): ("7d0655f693706042", 779360.8, 1666132.5),
-    ("learned", "class4"): ("d03cf0057bbc44d4", 3973416.2, 6250000.0),
-    ("learned", "l2_block"): ("d41318e67d054e01", 2000317.8, 12502374.4),
-    ("learned", "mirror"): ("c3a15eb9e31d99ef", 3912629.6, 7813125.0),
-    ("learned", "rayleigh_ritz"): ("ce8076ced68b2de3", 70.3, 42.6),
+    ("medium", "matvec"): ("0e4e45b3c971d9e6", 134499.2, 12864.8),
+    ("medium", "expansion_gemm"): ("682294ea08cfcb76", 323326.1, 37531.5),
+    ("medium", "relayout"): ("7d0655f693706042", 347202.0, 509723.4),
+    ("medium", "class4"): ("d03cf0057bbc44d4", 66577.8, 120320.4),
+    ("medium", "l2_block"): ("1f20de9f49ce44d8", 29922.9, 195898.4),
+    ("medium", "mirror"): ("c3a15eb9e31d99ef", 77236.9, 152429.7),
+    ("medium", "rayleigh_ritz"): ("ea28b9652dce02d3", 61.6, 25.5),
+    ("learned", "matvec"): ("0e4e45b3c971d9e6", 7353082.2, 451423.5),
+    ("learned", "expansion_gemm"): ("682294ea08cfcb76", 7960265.3, 1625333.8),
+    ("learned", "relayout"): ("7d0655f693706042", 779366.6, 1666129.4),
+    ("learned", "class4"): ("d03cf0057bbc44d4", 3970972.6, 6250000.0),
+    ("learned", "l2_block"): ("1f20de9f49ce44d8", 1998929.4, 12502381.2),
+    ("learned", "mirror"): ("c3a15eb9e31d99ef", 3912628.7, 7813125.0),
+    ("learned", "rayleigh_ritz"): ("ea28b9652dce02d3", 70.2, 42.6),
 }
 
 
