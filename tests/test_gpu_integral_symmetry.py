@@ -70,3 +70,22 @@ def test_one_value_off_is_found(which, j, k, P, Q, packed):
         if packed:
             y = synth.pack_integrals(y)
         assert (_flops(y) == plain) == found, err
+
+
+def test_batch_of_both_layouts():
+    import paper_1709_03005_amd as cc
+    a, b = copy.deepcopy(_instance(2)), _instance(4, 20)
+    a.ttcc = a.ttcc * np.random.default_rng(3).uniform(0.5, 1.5, a.ttcc.shape)
+    single = []
+    for inst in (a, b):
+        with cc.from_instance(inst) as ctx:
+            ctx.build()
+            single.append(ctx.get_matrix())
+    with cc.from_instance(a) as x, cc.from_instance(b) as y:
+        batch = cc.Batch([x, y])
+        for _ in range(2):
+            batch.build()
+            x.sync()
+            assert np.array_equal(x.get_matrix(), single[0])
+            assert np.array_equal(y.get_matrix(), single[1])
+        batch.close()
