@@ -2025,8 +2025,8 @@ cch_status cch_subspace_eig(cch_ctx *c, const double *G, int32_t ldg, int32_t m,
     const bool dev = flags & CCH_MEM_DEVICE;
     double *dG = nullptr, *dT = nullptr, *dY = nullptr;
     int32_t *dF = nullptr, hf = 0;
-    auto cleanup = [&]() {
-        (void)hipStreamSynchronize(st);   // (after a failure: what was queued reads the blocks and writes hf)
+    auto cleanup = [&](bool failed = true) {
+        if (failed) (void)hipStreamSynchronize(st);   // what was queued reads the blocks and writes hf
         if (!dev) {
             c->scratch.give(dG);
             c->scratch.give(dT);
@@ -2063,7 +2063,7 @@ cch_status cch_subspace_eig(cch_ctx *c, const double *G, int32_t ldg, int32_t m,
     }
     ECK(hipStreamSynchronize(st));
 #undef ECK
-    cleanup();
+    cleanup(false);
     if (fallback) *fallback = hf;
     return CCH_OK;
 }
@@ -2088,10 +2088,9 @@ cch_status cch_eig_all(cch_ctx *c, const double *A, int64_t lda, int32_t n, doub
     const int64_t ld = ((int64_t)n + 31) / 32 * 32;
     const int NB = 128;   // reflectors per block of the back-transformation (at most 128: launch_larft)
     std::vector<void *> tmp;
-    auto cleanup = [&]() {
-        // after a failure: what was queued uses the blocks, this call's host arrays
-        // and the caller's
-        (void)hipStreamSynchronize(st);
+    auto cleanup = [&](bool failed = true) {
+        // what was queued uses the blocks, this call's host arrays and the caller's
+        if (failed) (void)hipStreamSynchronize(st);
         for (void *p : tmp) c->scratch.give(p);
     };
     auto al = [&](void **p, size_t bytes) -> bool {
@@ -2318,7 +2317,7 @@ cch_status cch_eig_all(cch_ctx *c, const double *A, int64_t lda, int32_t n, doub
     }
 #undef EGK
     evclean();
-    cleanup();
+    cleanup(false);
     return CCH_OK;
 }
 
@@ -3104,10 +3103,9 @@ cch_status cch_davidson(cch_ctx *c, const cch_dav_opts *o, double *evals, double
     const int64_t ldv = ((int64_t)D + 31) / 32 * 32;
     const int BMAX = 32;                       // block columns (<= 2k <= 32)
     std::vector<void *> tmp;
-    auto cleanup = [&]() {
-        // after a failure: what was queued uses the blocks, this call's host arrays
-        // and the caller's
-        (void)hipStreamSynchronize(st);
+    auto cleanup = [&](bool failed = true) {
+        // what was queued uses the blocks, this call's host arrays and the caller's
+        if (failed) (void)hipStreamSynchronize(st);
         for (void *p : tmp) c->scratch.give(p);
     };
     auto A = [&](void **p, size_t bytes) -> bool {
@@ -3407,7 +3405,7 @@ cch_status cch_davidson(cch_ctx *c, const cch_dav_opts *o, double *evals, double
         }
     }
     DCK(hipStreamSynchronize(st));
-    cleanup();
+    cleanup(false);
     if (info) {
         info->iterations = iters;
         info->matvecs = matvecs;

@@ -51,6 +51,7 @@ public:
         const std::lock_guard<std::mutex> lock(all().m);
         for (auto &b : blocks_) Dev::release(b.p);
         blocks_.clear();
+        idle_ = 0;
         auto &s = all().spaces;
         s.erase(std::remove(s.begin(), s.end(), this), s.end());
         open_ = false;
@@ -65,6 +66,7 @@ public:
             if (!b.used && b.bytes >= bytes && b.bytes / 2 <= bytes && (!best || b.bytes < best->bytes)) best = &b;
         if (best) {
             best->used = true;
+            idle_ -= best->bytes;
             *p = best->p;
             return Err(0);
         }
@@ -78,7 +80,10 @@ public:
         if (!p) return;
         const std::lock_guard<std::mutex> lock(all().m);
         for (auto &b : blocks_)
-            if (b.p == p) b.used = false;
+            if (b.p == p && b.used) {
+                b.used = false;
+                idle_ += b.bytes;
+            }
         trim();
     }
 
@@ -106,12 +111,6 @@ private:
         return *a;
     }
 
-    size_t idle() const
-    {
-        size_t n = 0;
-        for (auto &b : blocks_) n += b.used ? 0 : b.bytes;
-        return n;
-    }
     Block *largest()
     {
         Block *at = nullptr;
@@ -122,6 +121,7 @@ private:
     void drop(Block *b)
     {
         Dev::release(b->p);
+        idle_ -= b->bytes;
         blocks_.erase(blocks_.begin() + (b - blocks_.data()));
     }
 
@@ -148,20 +148,20 @@ private:
         }
         for (;;) {
             size_t total = 0;
+            for (WorkSpace *w : all().spaces) total += w->device_ == device_ ? w->idle_ : 0;
+            if (total <= keep_) return;
             WorkSpace *from = nullptr;
-            for (WorkSpace *w : all().spaces) {
-                if (w->device_ != device_ || w->idle() == 0) continue;
-                total += w->idle();
-                if (!from || w->largest()->bytes > from->largest()->bytes) from = w;
-            }
-            if (!from || total <= keep_) return;
+            for (WorkSpace *w : all().spaces)
+                if (w->device_ == device_ && w->idle_ > 0 &&
+                    (!from || w->largest()->bytes > from->largest()->bytes))
+                    from = w;
             from->drop(from->largest());
         }
     }
 
     std::vector<Block> blocks_;
     int device_ = 0;
-    size_t keep_ = 0;
+    size_t keep_ = 0, idle_ = 0;   // idle_: bytes of the blocks not in use
     bool open_ = false;
 };
 
