@@ -141,4 +141,6 @@ def test_work_space(tmp_path, flags):
     subprocess.run(["g++", "-std=c++17", "-O1", "-g", "-Wall", "-pthread", *flags, "-I", CSRC, str(src), "-o", str(exe)],
                    check=True, timeout=120)
     r = subprocess.run([str(exe)], capture_output=True, text=True, timeout=120)
+    if "FATAL: ThreadSanitizer" in r.stderr:   # (an address layout that it does not know)
+        pytest.skip(r.stderr.strip().splitlines()[0])
     assert r.returncode == 0 and r.stdout.strip() == "ok", r.stdout + r.stderr
