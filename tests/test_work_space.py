@@ -1,5 +1,5 @@
 """The work space that contexts keep between calls (csrc/work_space.h), compiled
-for the host against a device of 1000 bytes a unit that counts what it holds:
+for the host against a device that counts what it holds:
 blocks are reused; an allocation that fails, of the same context or of another,
 frees every idle block of its device and no other; all contexts of a device
 together keep a bounded amount; a context under a memory budget keeps nothing
